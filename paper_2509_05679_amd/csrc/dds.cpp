@@ -134,9 +134,10 @@ struct Module {
   size_t err_bytes = 0;
   char* err = nullptr;
   UpdateDesc* descs_dev = nullptr;
-  int* map_update_dev = nullptr;
+  int* map_update_dev = nullptr;  // 1024-element blocks of every weight copy
+  int* map_range_dev = nullptr;   // ranges of the update kernel (exact-mean path)
   int* map_stash_dev = nullptr;
-  int blocks_update = 0, blocks_stash = 0;
+  int blocks_update = 0, blocks_stash = 0, ranges_update = 0;
   int out_tensor = -1;
   long long canon_params = 0;
   hipStream_t stream = nullptr;
@@ -637,14 +638,17 @@ int layout(dds_ctx& c, Arena& A) {
       m.err = A.take(m.err_bytes * m.err_depth);
     }
     // descriptor tables
-    int nb_u = 0, nb_s = 0;
+    int nb_u = 0, nb_s = 0, nb_r = 0;
     for (ParamLayer& L : m.layers) {
+      nb_r += (int)((L.n + update_elems(L.nsplit) - 1) / update_elems(L.nsplit));
       nb_u += (int)((L.n + 1023) / 1024);
       if (L.need_stash) nb_s += L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64);  // 64 x 64 tiles per tap
     }
     if (c.gossip) m.cons_dev = (double*)A.take(sizeof(double) * 2 * (nb_u > 0 ? nb_u : 1) * c.W);
     m.blocks_update = nb_u;  // per weight copy; the tables list copy 0 first, then copy 1, ...
     m.blocks_stash = nb_s;
+    m.ranges_update = c.gossip ? 0 : nb_r;
+    m.map_range_dev = (int*)A.take(sizeof(int) * 2 * (m.ranges_update > 0 ? m.ranges_update : 1));
     m.descs_dev = (UpdateDesc*)A.take(sizeof(UpdateDesc) * m.layers.size() * c.copies);
     m.map_update_dev = (int*)A.take(sizeof(int) * 2 * (nb_u > 0 ? nb_u : 1) * c.copies);
     m.map_stash_dev = (int*)A.take(sizeof(int) * 2 * (nb_s > 0 ? nb_s : 1) * c.copies);
@@ -1005,7 +1009,7 @@ int upload_tables(dds_ctx& c) {
     // one descriptor per (weight copy, layer); copy r sums only its own data-group's splits
     const size_t nl = m.layers.size();
     std::vector<UpdateDesc> descs(nl * c.copies);
-    std::vector<int> mu, ms;
+    std::vector<int> mu, ms, mr;
     for (int r = 0; r < c.copies; ++r)
     for (size_t li = 0; li < nl; ++li) {
       const ParamLayer& L = m.layers[li];
@@ -1024,11 +1028,14 @@ int upload_tables(dds_ctx& c) {
       d.nsplit = q;
       d.Cout = L.Cout; d.RS = L.RS; d.Cinpad = L.Cinpad; d.Cin = L.Cin; d.Coutpad = L.Coutpad;
       for (int b = 0; b < (int)((L.n + 1023) / 1024); ++b) { mu.push_back(di); mu.push_back(b); }
+      if (!c.gossip)
+        for (long long e = 0; e < L.n; e += update_elems(L.nsplit)) { mr.push_back(di); mr.push_back((int)(e / 32)); }
       if (L.need_stash)
         for (int b = 0; b < L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64); ++b) { ms.push_back(di); ms.push_back(b); }
     }
     if (!descs.empty()) HIP_TRY(hipMemcpy(m.descs_dev, descs.data(), sizeof(UpdateDesc) * descs.size(), hipMemcpyHostToDevice));
     if (!mu.empty()) HIP_TRY(hipMemcpy(m.map_update_dev, mu.data(), sizeof(int) * mu.size(), hipMemcpyHostToDevice));
+    if (!mr.empty()) HIP_TRY(hipMemcpy(m.map_range_dev, mr.data(), sizeof(int) * mr.size(), hipMemcpyHostToDevice));
     if (!ms.empty()) HIP_TRY(hipMemcpy(m.map_stash_dev, ms.data(), sizeof(int) * ms.size(), hipMemcpyHostToDevice));
     m.map_update_host.assign(mu.begin(), mu.begin() + 2 * m.blocks_update);
   }
@@ -1363,7 +1370,7 @@ int dds_step(dds_ctx* c, const float* const* x, const int32_t* const* y, float l
     if (sc.b >= 0) {
       run_backward(*c, m, sc, s);
       if (!c->gossip) {
-        launch_update(c->dt, m.descs_dev, m.map_update_dev, m.blocks_update, c->W, step, c->mu, s);
+        launch_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, c->W, step, c->mu, s);
       } else {
         // u_r = w_r - lr * direction_r from every data-group's own splits, then the mixing step, in one kernel
         launch_gossip_update(c->dt, m.descs_dev, m.map_update_dev, m.blocks_update, c->P_dev, c->W, m.n_master, step,

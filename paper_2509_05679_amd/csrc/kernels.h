@@ -158,11 +158,14 @@ void launch_gap_bwd(int dt, const void* dy, const void* x, void* dx, int N, int 
 // logits fp32 [W*B][ldl]; dlogits dtype T [W*B][ldg] (may be null); loss [W] (may be null)
 void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void* dlogits, float* loss,
                        int W, int B, int classes, int ldl, int ldg, hipStream_t s);
-// descs: device array of UpdateDesc; block_map: device array of (descriptor, block)
-// pairs, one per workgroup of 1024 elements.
-// update: g = (1/W) sum over splits, momentum, SGD on the fp32 master, recast into `work`.
-void launch_update(int dt, const UpdateDesc* descs_dev, const int* block_map_dev, int total_blocks, int W,
+// Elements of a parameter block that one workgroup of the update kernel owns: the fewer, the more splits have to be
+// summed for each, so that a launch always has thousands of partial rows in flight (see update_kernel).
+__host__ __device__ inline int update_elems(int nsplit) { return nsplit >= 256 ? 32 : nsplit >= 64 ? 64 : 256; }
+// update: g = (1/W) sum over splits, momentum, SGD on the fp32 master, recast into `work`. range_map: device array of
+// (descriptor, first element / 32) pairs, one per workgroup of update_elems(nsplit) elements.
+void launch_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev, int total_ranges, int W,
                    float lr, float mu, hipStream_t s);
+// The other kernels' block_map: device array of (descriptor, block) pairs, one per 1024 elements.
 // General mixing matrix (W weight copies, rep_stride elements apart; a descriptor's nsplit = splits per data-group):
 // u_r = w_r - lr*direction_r from data-group r's own splits, then w_s = sum_r P[s][r] u_r into master
 // and `work`. descs / block_map / total_blocks: the entries of data-group 0. P: device, W x W row-major.

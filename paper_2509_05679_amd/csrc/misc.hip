@@ -232,42 +232,49 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* logits, co
 }
 
 // ------------------------------------------------------------------ update
-// block_map[2*e] = descriptor index, block_map[2*e+1] = 1024-element block within the
-// descriptor; four workgroups share an entry, 256 consecutive elements each. Lane l of every
-// wave owns elements 4l..4l+3 of the workgroup's range; wave w sums the splits w, w+4, w+8, ...
-// (eight row reads in flight, each a fully coalesced 1 KiB), in a fixed order: eight interleaved
-// running sums, a fixed tree over them, then a fixed tree over the four waves through LDS. The
-// result is bit-reproducible for a given split count. g = sum/W; v = mu*v + g; w -= lr*v (or lr*g).
-template <typename T>
-__global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, const int* block_map, float invW, float lr, float mu) {
-  const UpdateDesc d = descs[block_map[2 * (blockIdx.x >> 2)]];
-  const long long blk0 = (long long)block_map[2 * (blockIdx.x >> 2) + 1] * 1024 + (blockIdx.x & 3) * 256;
+// One workgroup owns E consecutive elements of one parameter block (map entry: descriptor, first element / 32) and all of
+// its nsplit partial rows. A row of the workgroup's range is read by E / 4 lanes, 16 bytes each, so the 256 threads
+// read R = 1024 / E rows at a time, eight such reads in flight per thread; row-lane r sums the splits r, r + R, ...
+// HBM-bound when enough of them are in flight: 4 bytes per partial value. E falls with the split count
+// (update_elems): a 16-channel layer has 1024 splits of 2320 values, and with 256-element ranges its ten workgroups
+// walked 256 rows one after another: 94 us for the update of the single-module ResNet-20 step (57 MB of partial
+// sums), 53 us per module of ResNet-56. 32-element ranges spread the same bytes over 73 workgroups of 32 row-lanes:
+// 33 and 19 us.
+// Order of the sum (bit-reproducible for a given split count): eight interleaved running sums, a fixed tree over
+// them, a tree over the row-lanes of a wave, a fixed tree over the four waves through LDS.
+// g = sum/W; v = mu*v + g; w -= lr*v (or lr*g).
+__device__ __forceinline__ void add4(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
+
+template <typename T, int E>
+__device__ __forceinline__ void update_range(const UpdateDesc& d, long long first, float invW, float lr, float mu, float4 (*red)[64]) {
+  constexpr int LPR = E / 4;      // lanes per row
+  constexpr int R = 256 / LPR;    // row-lanes of the workgroup
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const long long base = blk0 + lane * 4;
-  __shared__ float4 red[3][64];
+  const int r0 = threadIdx.x / LPR;
+  const long long base = first + (threadIdx.x % LPR) * 4;
   float4 a[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
   if (base < d.n) {  // rows are pstride = n rounded up to 4 floats long: the vector read stays inside the row
     const float* src = d.partial + base;
-    for (int j = wave; j < d.nsplit; j += 32) {
+    for (int j = r0; j < d.nsplit; j += 8 * R) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int jj = j + 4 * u;
-        if (jj < d.nsplit) {
-          const float4 t = *(const float4*)(src + (size_t)jj * d.pstride);
-          a[u].x += t.x; a[u].y += t.y; a[u].z += t.z; a[u].w += t.w;
-        }
+        const int jj = j + R * u;
+        if (jj < d.nsplit) add4(a[u], *(const float4*)(src + (size_t)jj * d.pstride));
       }
     }
   }
 #pragma unroll
   for (int w = 4; w > 0; w >>= 1)
 #pragma unroll
-    for (int u = 0; u < w; ++u) { a[u].x += a[u + w].x; a[u].y += a[u + w].y; a[u].z += a[u + w].z; a[u].w += a[u + w].w; }
-  if (wave > 0) red[wave - 1][lane] = a[0];
+    for (int u = 0; u < w; ++u) add4(a[u], a[u + w]);
+#pragma unroll
+  for (int o = 32; o >= LPR; o >>= 1)
+    add4(a[0], make_float4(__shfl_xor(a[0].x, o, 64), __shfl_xor(a[0].y, o, 64), __shfl_xor(a[0].z, o, 64), __shfl_xor(a[0].w, o, 64)));
+  if (wave > 0 && lane < LPR) red[wave - 1][lane] = a[0];
   __syncthreads();
-  if (wave > 0 || base >= d.n) return;
+  if (wave > 0 || lane >= LPR || base >= d.n) return;
   {
     const float4 r1 = red[0][lane], r2 = red[1][lane], r3 = red[2][lane];
     a[0].x = (a[0].x + r1.x) + (r2.x + r3.x); a[0].y = (a[0].y + r1.y) + (r2.y + r3.y);
@@ -306,6 +313,18 @@ __global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, co
         else ((float*)d.work)[i] = w;
       }
     }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, const int* block_map, float invW, float lr, float mu) {
+  __shared__ float4 red[3][64];
+  const UpdateDesc d = descs[block_map[2 * blockIdx.x]];
+  const long long first = (long long)block_map[2 * blockIdx.x + 1] * 32;
+  switch (update_elems(d.nsplit)) {
+    case 32: update_range<T, 32>(d, first, invW, lr, mu, red); break;
+    case 64: update_range<T, 64>(d, first, invW, lr, mu, red); break;
+    default: update_range<T, 256>(d, first, invW, lr, mu, red); break;
   }
 }
 
@@ -533,7 +552,7 @@ void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void*
 void launch_update(int dt, const UpdateDesc* descs, const int* block_map, int total_blocks, int W, float lr, float mu,
                    hipStream_t s) {
   if (total_blocks <= 0) return;
-  DDS_DISPATCH(dt, update_kernel, <<<4 * total_blocks, 256, 0, s>>>(descs, block_map, 1.f / (float)W, lr, mu));
+  DDS_DISPATCH(dt, update_kernel, <<<total_blocks, 256, 0, s>>>(descs, block_map, 1.f / (float)W, lr, mu));
 }
 
 void launch_recast(int dt, const UpdateDesc* descs, const int* block_map, int total_blocks, hipStream_t s) {
