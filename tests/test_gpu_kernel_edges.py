@@ -3,7 +3,7 @@
 Tolerances: the ones of tests/parity.py (tiny = toy networks, where fp32 rounding is all there is)."""
 import pytest
 
-from dds_inputs.configs import tiny_resnet
+from dds_inputs.configs import Workload, tiny_resnet
 from test_gpu_parity import _compare
 
 pytestmark = pytest.mark.gpu
@@ -14,3 +14,12 @@ def test_update_ranges_by_split_count(W, B):
     # 16-channel layers at 16 x 16 pixels have one split per image: 63 / 64 / 255 / 256 of them lie on both sides of the
     # lines between 256-, 64- and 32-element ranges
     _compare(tiny_resnet(K=1, W=W, B=B, hw=16, c=16, precision="bf16"), seed=20, T=2)
+
+
+@pytest.mark.parametrize("c,hw,B", [(4, 2, 3), (20, 6, 2), (1028, 2, 2)])
+def test_global_average_pool_chunk_and_pixel_remainders(c, hw, B):
+    # channel chunks that do not divide the workgroup, fewer pixels than pixel lanes, more than 256 chunks
+    ops = [{"op": "conv", "cin": 3, "cout": c, "k": 1, "stride": 1, "pad": 0}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
+    _compare(Workload(name=f"gap_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
+                      precision="f32", lr=0.05, momentum=0.0, steps=2), seed=21, T=2, every_step=True, tiny=True)
