@@ -135,7 +135,7 @@ struct Module {
   char* err = nullptr;
   UpdateDesc* descs_dev = nullptr;
   int* map_update_dev = nullptr;  // 1024-element blocks of every weight copy
-  int* map_range_dev = nullptr;   // ranges of the update kernel (exact-mean path)
+  int* map_range_dev = nullptr;   // element ranges of the update kernels (weight copy 0)
   int* map_stash_dev = nullptr;
   int blocks_update = 0, blocks_stash = 0, ranges_update = 0;
   int out_tensor = -1;
@@ -549,6 +549,9 @@ int plan_module(const dds_spec& sp, int k0, int K, int N, int dt, const Tensor* 
   return DDS_OK;
 }
 
+// elements of a layer that one workgroup of the update kernel owns
+int range_elems(const dds_ctx& c, const ParamLayer& L) { return c.gossip ? gossip_elems(L.nsplit / c.copies) : update_elems(L.nsplit); }
+
 int layout(dds_ctx& c, Arena& A) {
   const int es = dtype_size(c.dt);
   for (int k0 = 0; k0 < c.K; ++k0) {
@@ -640,14 +643,14 @@ int layout(dds_ctx& c, Arena& A) {
     // descriptor tables
     int nb_u = 0, nb_s = 0, nb_r = 0;
     for (ParamLayer& L : m.layers) {
-      nb_r += (int)((L.n + update_elems(L.nsplit) - 1) / update_elems(L.nsplit));
+      nb_r += (int)((L.n + range_elems(c, L) - 1) / range_elems(c, L));
       nb_u += (int)((L.n + 1023) / 1024);
       if (L.need_stash) nb_s += L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64);  // 64 x 64 tiles per tap
     }
     if (c.gossip) m.cons_dev = (double*)A.take(sizeof(double) * 2 * (nb_u > 0 ? nb_u : 1) * c.W);
     m.blocks_update = nb_u;  // per weight copy; the tables list copy 0 first, then copy 1, ...
     m.blocks_stash = nb_s;
-    m.ranges_update = c.gossip ? 0 : nb_r;
+    m.ranges_update = nb_r;
     m.map_range_dev = (int*)A.take(sizeof(int) * 2 * (m.ranges_update > 0 ? m.ranges_update : 1));
     m.descs_dev = (UpdateDesc*)A.take(sizeof(UpdateDesc) * m.layers.size() * c.copies);
     m.map_update_dev = (int*)A.take(sizeof(int) * 2 * (nb_u > 0 ? nb_u : 1) * c.copies);
@@ -1028,8 +1031,8 @@ int upload_tables(dds_ctx& c) {
       d.nsplit = q;
       d.Cout = L.Cout; d.RS = L.RS; d.Cinpad = L.Cinpad; d.Cin = L.Cin; d.Coutpad = L.Coutpad;
       for (int b = 0; b < (int)((L.n + 1023) / 1024); ++b) { mu.push_back(di); mu.push_back(b); }
-      if (!c.gossip)
-        for (long long e = 0; e < L.n; e += update_elems(L.nsplit)) { mr.push_back(di); mr.push_back((int)(e / 32)); }
+      if (r == 0)
+        for (long long e = 0; e < L.n; e += range_elems(c, L)) { mr.push_back(di); mr.push_back((int)(e / 32)); }
       if (L.need_stash)
         for (int b = 0; b < L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64); ++b) { ms.push_back(di); ms.push_back(b); }
     }
@@ -1373,7 +1376,7 @@ int dds_step(dds_ctx* c, const float* const* x, const int32_t* const* y, float l
         launch_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, c->W, step, c->mu, s);
       } else {
         // u_r = w_r - lr * direction_r from every data-group's own splits, then the mixing step, in one kernel
-        launch_gossip_update(c->dt, m.descs_dev, m.map_update_dev, m.blocks_update, c->P_dev, c->W, m.n_master, step,
+        launch_gossip_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, c->P_dev, c->W, m.n_master, step,
                              c->mu, s);
       }
       launch_stash(c->dt, m.descs_dev, m.map_stash_dev, m.blocks_stash * c->copies, sc.snap_write, s);

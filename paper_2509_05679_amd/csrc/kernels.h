@@ -168,8 +168,10 @@ void launch_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev
 // The other kernels' block_map: device array of (descriptor, block) pairs, one per 1024 elements.
 // General mixing matrix (W weight copies, rep_stride elements apart; a descriptor's nsplit = splits per data-group):
 // u_r = w_r - lr*direction_r from data-group r's own splits, then w_s = sum_r P[s][r] u_r into master
-// and `work`. descs / block_map / total_blocks: the entries of data-group 0. P: device, W x W row-major.
-void launch_gossip_update(int dt, const UpdateDesc* descs_dev, const int* block_map_dev, int total_blocks,
+// and `work`. descs / range_map: the entries of data-group 0, one per workgroup of gossip_elems(nsplit) elements.
+// P: device, W x W row-major.
+__host__ __device__ inline int gossip_elems(int nsplit) { return nsplit >= 32 ? 32 : nsplit >= 8 ? 64 : 256; }
+void launch_gossip_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev, int total_ranges,
                           const float* P_dev, int W, long long rep_stride, float lr, float mu, hipStream_t s);
 // Squared distances to the data-group mean: out[(2*b + part) * W + s] for workgroup b of the
 // update block map of data-group 0 (1024 elements of one layer each); part 0 = weight, 1 = bias; fp64.

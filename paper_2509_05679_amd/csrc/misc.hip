@@ -361,30 +361,49 @@ __global__ __launch_bounds__(256) void recast_kernel(const UpdateDesc* descs, co
 }
 
 // Update (a)/(b) of Section 3.3 with a general mixing matrix P, for all W data-groups at once:
-//   g_r = sum of data-group r's q splits (in order), v_r = mu*v_r + g_r, u_r = w_r - lr*v_r (or lr*g_r),
+//   g_r = sum of data-group r's q splits (fixed order), v_r = mu*v_r + g_r, u_r = w_r - lr*v_r (or lr*g_r),
 //   w_s = sum_r P[s][r] * u_r (r ascending, fp32), written to the fp32 master and the compute-precision copy.
-// descs / block_map: data-group 0's entries (its `partial` points at split 0 of all W*q splits); data-group
-// r's master / momentum / work lie r*rep_stride elements further. One thread owns four consecutive
-// elements in all W copies, so the update is in place. Every layer's arrays are allocated in whole
-// multiples of 64 elements and split rows in multiples of 4, so the four-wide accesses of the last
-// thread of a layer stay inside that layer's padding.
-template <typename T>
-__global__ __launch_bounds__(256) void gossip_update_kernel(const UpdateDesc* descs, const int* block_map, const float* P,
-                                                            int W, long long rep_stride, float lr, float mu) {
-  const UpdateDesc d = descs[block_map[2 * blockIdx.x]];
-  const long long base = (long long)block_map[2 * blockIdx.x + 1] * 1024 + threadIdx.x * 4;
-  if (base >= d.n) return;
+// descs / range_map: data-group 0's entries (its `partial` points at split 0 of all W*q splits); data-group
+// r's master / momentum / work lie r*rep_stride elements further.
+// A workgroup owns E elements in all W copies, so the update is in place. Its four waves take the data-groups
+// r = wave, wave + 4, ...: a partial row of the range is read by E / 4 lanes, the wave's 256 / E row-lanes take every
+// (256 / E)-th split with eight reads in flight each, and u_r goes to LDS; after one barrier all threads share the W * E
+// mixed values. HBM-bound; E falls with the split count for the reason given at update_kernel. (One thread per four
+// elements that walked all W * q rows itself took 78 us per module of the ResNet-18 shapes with W = 4, this 50; an
+// eight-module ResNet-56 on a ring of eight groups went from 2.38 to 1.85 ms per iteration.)
+// Every layer's arrays are allocated in whole multiples of 64 elements and split rows in multiples of 4, so the
+// four-wide accesses of the last thread of a layer stay inside that layer's padding.
+template <typename T, int E>
+__device__ __forceinline__ void gossip_range(const UpdateDesc& d, long long first, const float* P, int W, long long rep_stride,
+                                             float lr, float mu, float4* u) {
+  constexpr int LPR = E / 4, RL = 64 / LPR;  // lanes per row, row-lanes of a wave
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int q = d.nsplit;  // splits per data-group of this layer
-  float4 u[32];
+  const int rl = lane / LPR, l = lane % LPR;
+  const long long base = first + l * 4;
+  for (int r = wave; r < W; r += 4) {
+    float4 a[8];
 #pragma unroll
-  for (int r = 0; r < 32; ++r) {
-    if (r >= W) continue;
-    const float* src = d.partial + (size_t)r * q * d.pstride + base;
-    float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = 0; j < q; ++j) {
-      const float4 t = *(const float4*)(src + (size_t)j * d.pstride);
-      g.x += t.x; g.y += t.y; g.z += t.z; g.w += t.w;
+    for (int k = 0; k < 8; ++k) a[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (base < d.n) {
+      const float* src = d.partial + (size_t)r * q * d.pstride + base;
+      for (int j = rl; j < q; j += 8 * RL) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int jj = j + RL * k;
+          if (jj < q) add4(a[k], *(const float4*)(src + (size_t)jj * d.pstride));
+        }
+      }
     }
+#pragma unroll
+    for (int w = 4; w > 0; w >>= 1)
+#pragma unroll
+      for (int k = 0; k < w; ++k) add4(a[k], a[k + w]);
+#pragma unroll
+    for (int o = 32; o >= LPR; o >>= 1)
+      add4(a[0], make_float4(__shfl_xor(a[0].x, o, 64), __shfl_xor(a[0].y, o, 64), __shfl_xor(a[0].z, o, 64), __shfl_xor(a[0].w, o, 64)));
+    if (rl != 0 || base >= d.n) continue;
+    float4 g = a[0];
     if (d.momentum) {
       float4* vp = (float4*)(d.momentum + (long long)r * rep_stride + base);
       float4 v = *vp;
@@ -393,27 +412,43 @@ __global__ __launch_bounds__(256) void gossip_update_kernel(const UpdateDesc* de
       g = v;
     }
     const float4 w = *(const float4*)(d.master + (long long)r * rep_stride + base);
-    u[r] = make_float4(w.x - lr * g.x, w.y - lr * g.y, w.z - lr * g.z, w.w - lr * g.w);
+    u[r * LPR + l] = make_float4(w.x - lr * g.x, w.y - lr * g.y, w.z - lr * g.z, w.w - lr * g.w);
   }
-  for (int s = 0; s < W; ++s) {
+  __syncthreads();
+  for (int i = threadIdx.x; i < W * LPR; i += 256) {
+    const int s = i / LPR, ll = i % LPR;
+    const long long b = first + ll * 4;
+    if (b >= d.n) continue;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int r = 0; r < 32; ++r) {
-      if (r >= W) continue;
+    for (int r = 0; r < W; ++r) {
       const float c = P[s * W + r];
-      a.x = fmaf(c, u[r].x, a.x); a.y = fmaf(c, u[r].y, a.y); a.z = fmaf(c, u[r].z, a.z); a.w = fmaf(c, u[r].w, a.w);
+      const float4 t = u[r * LPR + ll];
+      a.x = fmaf(c, t.x, a.x); a.y = fmaf(c, t.y, a.y); a.z = fmaf(c, t.z, a.z); a.w = fmaf(c, t.w, a.w);
     }
-    *(float4*)(d.master + (long long)s * rep_stride + base) = a;
+    *(float4*)(d.master + (long long)s * rep_stride + b) = a;
     if (d.work) {
       if (sizeof(T) == 2) {
         uint2 o;
         o.x = (uint32_t)f2bf(a.x) | ((uint32_t)f2bf(a.y) << 16);
         o.y = (uint32_t)f2bf(a.z) | ((uint32_t)f2bf(a.w) << 16);
-        *(uint2*)((char*)d.work + ((long long)s * rep_stride + base) * 2) = o;
+        *(uint2*)((char*)d.work + ((long long)s * rep_stride + b) * 2) = o;
       } else {
-        *(float4*)((char*)d.work + ((long long)s * rep_stride + base) * 4) = a;
+        *(float4*)((char*)d.work + ((long long)s * rep_stride + b) * 4) = a;
       }
     }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void gossip_update_kernel(const UpdateDesc* descs, const int* range_map, const float* P,
+                                                            int W, long long rep_stride, float lr, float mu) {
+  extern __shared__ float4 u[];  // [W][E / 4], E <= 256
+  const UpdateDesc d = descs[range_map[2 * blockIdx.x]];
+  const long long first = (long long)range_map[2 * blockIdx.x + 1] * 32;
+  switch (gossip_elems(d.nsplit)) {
+    case 32: gossip_range<T, 32>(d, first, P, W, rep_stride, lr, mu, u); break;
+    case 64: gossip_range<T, 64>(d, first, P, W, rep_stride, lr, mu, u); break;
+    default: gossip_range<T, 256>(d, first, P, W, rep_stride, lr, mu, u); break;
   }
 }
 
@@ -584,10 +619,11 @@ void launch_stash(int dt, const UpdateDesc* descs, const int* block_map, int tot
   DDS_DISPATCH(dt, stash_kernel, <<<total_blocks, 256, 0, s>>>(descs, block_map, slot));
 }
 
-void launch_gossip_update(int dt, const UpdateDesc* descs, const int* block_map, int total_blocks, const float* P, int W,
+void launch_gossip_update(int dt, const UpdateDesc* descs, const int* range_map, int total_ranges, const float* P, int W,
                           long long rep_stride, float lr, float mu, hipStream_t s) {
-  if (total_blocks <= 0) return;
-  DDS_DISPATCH(dt, gossip_update_kernel, <<<total_blocks, 256, 0, s>>>(descs, block_map, P, W, rep_stride, lr, mu));
+  if (total_ranges <= 0) return;
+  DDS_DISPATCH(dt, gossip_update_kernel,
+               <<<total_ranges, 256, (size_t)W * 1024, s>>>(descs, range_map, P, W, rep_stride, lr, mu));
 }
 
 void launch_consensus(const UpdateDesc* descs, const int* block_map, int total_blocks, int W, long long rep_stride,

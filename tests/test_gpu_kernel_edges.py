@@ -3,7 +3,7 @@
 Tolerances: the ones of tests/parity.py (tiny = toy networks, where fp32 rounding is all there is)."""
 import pytest
 
-from dds_inputs.configs import Workload, tiny_resnet
+from dds_inputs.configs import Workload, ring_mixing, tiny_resnet
 from test_gpu_parity import _compare
 
 pytestmark = pytest.mark.gpu
@@ -23,3 +23,10 @@ def test_global_average_pool_chunk_and_pixel_remainders(c, hw, B):
            {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
     _compare(Workload(name=f"gap_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
                       precision="f32", lr=0.05, momentum=0.0, steps=2), seed=21, T=2, every_step=True, tiny=True)
+
+
+@pytest.mark.parametrize("W,B", [(2, 7), (3, 8), (2, 31), (5, 32)])
+def test_mixing_update_ranges_by_split_count(W, B):
+    # 7 / 8 / 31 / 32 splits per data-group: both sides of the lines between 256-, 64- and 32-element ranges
+    from test_gpu_gossip import _compare as compare_gossip
+    compare_gossip(tiny_resnet(K=2, W=W, B=B, hw=16, c=16, precision="bf16"), seed=22, T=4, mixing=ring_mixing(W, 0.3))
