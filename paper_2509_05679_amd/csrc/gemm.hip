@@ -1484,6 +1484,7 @@ int launch_conv_one(const ConvParams& p, hipStream_t s);
 
 template <typename T>
 int launch_conv_t(const ConvParams& p, hipStream_t s) {
+  if (launch_linear(sizeof(T) == 4 ? DT_F32 : DT_BF16, p, s)) return 0;
   if (p.nrep > 1 && (p.Nimg % p.nrep != 0 || !replicas_tile_aligned(p))) {
     int family = 1;  // one launch per data-group
     for (int r = 0; r < p.nrep; ++r) family &= launch_conv_one<T>(replica_slice<T>(p, r), s);
@@ -1495,6 +1496,7 @@ int launch_conv_t(const ConvParams& p, hipStream_t s) {
 template <typename T>
 int launch_conv_one(const ConvParams& p, hipStream_t s) {
   constexpr int BKB = 64;
+  if (p.nrep <= 1 && launch_linear(sizeof(T) == 4 ? DT_F32 : DT_BF16, p, s)) return 0;  // a data-group's slice
   if (sizeof(T) == 2 && launch_conv_narrow(p, s)) return 1;
   if (launch_dma<T>(p, s)) return 1;
   // dgrad of a stride-2 convolution: workgroups per parity class (class (0,0) is the largest)

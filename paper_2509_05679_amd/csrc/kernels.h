@@ -134,6 +134,8 @@ struct UpdateDesc {
 // Both return the kernel family that took the launch: 0 = generic implicit GEMM (register-staged),
 // 1 = the asynchronous global->LDS kernels (conv3x3_dma_kernel / wgrad_dma_kernel).
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
+// plain products of few rows (linear.hip); false: not taken, nothing launched
+bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
 int launch_wgrad(int dt, const WgradParams& p, hipStream_t s);

@@ -30,3 +30,26 @@ def test_mixing_update_ranges_by_split_count(W, B):
     # 7 / 8 / 31 / 32 splits per data-group: both sides of the lines between 256-, 64- and 32-element ranges
     from test_gpu_gossip import _compare as compare_gossip
     compare_gossip(tiny_resnet(K=2, W=W, B=B, hw=16, c=16, precision="bf16"), seed=22, T=4, mixing=ring_mixing(W, 0.3))
+
+
+def _two_linear(precision, feat, hidden, W, B):
+    ops = [{"op": "linear", "cin": feat, "cout": hidden}, {"op": "relu"}, {"op": "linear", "cin": hidden, "cout": 10},
+           {"op": "softmax_ce"}]
+    return Workload(name=f"linear_{feat}_{hidden}", ops=ops, bounds=[0, 2, 4], K=2, W=W, B=B, in_shape=(feat, 1, 1),
+                    classes=10, precision=precision, lr=0.05, momentum=0.0, steps=4)
+
+
+@pytest.mark.parametrize("precision,feat,hidden,W,B", [
+    ("f32", 12, 8, 1, 1), ("f32", 124, 36, 2, 17), ("f32", 132, 128, 3, 16), ("f32", 1500, 130, 2, 9),
+    ("bf16", 24, 16, 1, 15), ("bf16", 248, 136, 2, 31), ("bf16", 264, 40, 2, 33)])
+def test_linear_layers_of_few_rows(precision, feat, hidden, W, B):
+    # reductions on both sides of eight 64-byte k-steps and with a ragged last one, rows and columns off the
+    # 16-element grid, hidden widths beyond one 128-column workgroup
+    wl = _two_linear(precision, feat, hidden, W, B)
+    _compare(wl, seed=23, T=4, every_step=precision == "f32", tiny=precision == "f32")
+
+
+@pytest.mark.parametrize("B", [16, 5])
+def test_linear_layers_with_weights_per_data_group(B):
+    from test_gpu_gossip import _compare as compare_gossip
+    compare_gossip(_two_linear("f32", 40, 24, 3, B), seed=24, T=4, mixing=ring_mixing(3, 0.3))
