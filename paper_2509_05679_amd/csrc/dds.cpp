@@ -122,7 +122,7 @@ struct Module {
   float* snap_master = nullptr;  // [R][copies][n_master] fp32 parameters as the forward of that slot saw them
   char* snap_work = nullptr;     // the same for the compute-precision copy (bf16 path)
   double* bn_scratch = nullptr;  // per-split sums of the batch-normalisation kernels (largest node of the module)
-  double* bn_totals = nullptr;   // dbeta / dgamma per data-group and channel of the node being back-propagated
+  float* bn_coef = nullptr;      // per-channel factors of the node being streamed
   long long n_master = 0;  // floats per weight copy
   float* master = nullptr;    // [copies][n_master]
   float* momentum = nullptr;  // [copies][n_master]
@@ -570,7 +570,7 @@ int layout(dds_ctx& c, Arena& A) {
     }
     // batch normalisation: what the backward of a mini-batch needs from its forward (mean, rstd, gamma
     // per data-group and channel) lives in the ring slot too; the row splits are fixed here
-    size_t bn_scratch_bytes = 0, bn_totals_bytes = 0;
+    size_t bn_scratch_bytes = 0, bn_coef_bytes = 0;
     for (Node& nd : m.nodes) {
       if (nd.kind != N_BN) continue;
       const Tensor& tb = m.tensors[nd.out];
@@ -586,14 +586,14 @@ int layout(dds_ctx& c, Arena& A) {
       nd.bn_rows_per_split = (rows_per_rep + ns - 1) / ns;
       nd.bn_nsplit = (int)((rows_per_rep + nd.bn_rows_per_split - 1) / nd.bn_rows_per_split);
       const size_t sb = (size_t)c.W * nd.bn_nsplit * tb.Cpad * 2 * sizeof(double);
-      const size_t tb_bytes = (size_t)c.W * tb.Cpad * 2 * sizeof(double);
+      const size_t cb = (size_t)c.W * kBnCoefRows * tb.Cpad * sizeof(float);
       bn_scratch_bytes = sb > bn_scratch_bytes ? sb : bn_scratch_bytes;
-      bn_totals_bytes = tb_bytes > bn_totals_bytes ? tb_bytes : bn_totals_bytes;
+      bn_coef_bytes = cb > bn_coef_bytes ? cb : bn_coef_bytes;
     }
     m.slot_bytes = off;
     m.ring = A.take(m.slot_bytes * m.R);
     if (m.recompute) m.area = A.take(aoff);
-    if (bn_scratch_bytes) { m.bn_scratch = (double*)A.take(bn_scratch_bytes); m.bn_totals = (double*)A.take(bn_totals_bytes); }
+    if (bn_scratch_bytes) { m.bn_scratch = (double*)A.take(bn_scratch_bytes); m.bn_coef = (float*)A.take(bn_coef_bytes); }
     for (Tensor& t : m.tensors)
       if (t.kind == T_TEMP) t.temp = A.take(t.bytes);
     for (GradBuf& g : m.grads) g.ptr = A.take(g.bytes);
@@ -808,7 +808,7 @@ BnParams bn_params(dds_ctx& c, Module& m, const Node& nd, int slot, const float*
   p.gstride = L.Cinpad;
   p.stats = (float*)(m.recompute ? m.area + nd.stats_off : m.ring + (size_t)slot * m.slot_bytes + nd.stats_off);
   p.scratch = m.bn_scratch;
-  p.totals = m.bn_totals;
+  p.coef = m.bn_coef;
   p.partial = L.partial;
   p.pstride = L.pstride;
   p.W = c.W;

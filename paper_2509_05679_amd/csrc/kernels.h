@@ -87,6 +87,7 @@ struct WgradParams {
 // Training-mode batch normalisation of a [W * rows_per_rep][ld] tensor, statistics per data-group.
 //   forward : y = relu?( alpha * (gamma * (x - mean) * rstd + beta) + res ), stats <- mean, rstd, gamma
 //   backward: dgamma / dbeta partial rows (one per (data-group, split)), dx from dy, x and the saved stats
+constexpr int kBnCoefRows = 5;
 struct BnParams {
   const void* x;      // input of the normalisation (the convolution output), dtype T
   void* y;            // forward output, dtype T
@@ -100,7 +101,7 @@ struct BnParams {
   int gstride;
   float* stats;       // [W][3][ld]: mean, rstd, gamma of this mini-batch
   double* scratch;    // [W][nsplit][ld][2] per-split sums (forward: x, x^2; backward: g, g * xhat)
-  double* totals;     // backward: [W][ld][2] dbeta, dgamma per data-group
+  float* coef;        // [W][kBnCoefRows][ld] per-channel factors of the streaming kernel that follows
   float* partial;     // backward: [W][pstride] parameter-gradient rows, one per data-group
   long long pstride;
   int W, C, ld, nsplit;

@@ -16,11 +16,18 @@ namespace {
 struct bf16_t { uint16_t v; };
 
 __device__ __forceinline__ float bf2f(uint16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// two floats -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  f32x2_t v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+// 0x00010001 where both halves of a packed bf16 pair are > 0, 0 / 1 per half otherwise
+__device__ __forceinline__ uint32_t positive_pair(uint32_t w) {
+  typedef short s16x2_t __attribute__((ext_vector_type(2)));
+  const s16x2_t one = {1, 1}, zero = {0, 0};
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_elementwise_min(__builtin_bit_cast(s16x2_t, w), one), zero));
 }
 
 // Eight consecutive channels of one row. Channel strides are multiples of 8 (bf16) or 4 (fp32):
@@ -44,16 +51,26 @@ __device__ __forceinline__ void load8(const void* base, size_t elem, bool full, 
   }
 }
 
+// Stores eight channels and returns their sign byte (bit i = stored value i > 0).
 template <typename T>
-__device__ __forceinline__ void store8(void* base, size_t elem, bool full, const float (&f)[8]) {
+__device__ __forceinline__ uint32_t store8(void* base, size_t elem, bool full, const float (&f)[8]) {
   if (sizeof(T) == 2) {
     uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f2bf(f[2 * i]) | ((uint32_t)f2bf(f[2 * i + 1]) << 16);
+    for (int i = 0; i < 4; ++i) w[i] = pack_bf16(f[2 * i], f[2 * i + 1]);
     *(uint4*)((char*)base + elem * 2) = make_uint4(w[0], w[1], w[2], w[3]);
+    // pair i's low half belongs to bit 2 i, its high half (bit 16) to bit 2 i + 1
+    uint32_t t = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t |= positive_pair(w[i]) << (2 * i);
+    return (t | (t >> 15)) & 0xffu;
   } else {
     *(float4*)((char*)base + elem * 4) = make_float4(f[0], f[1], f[2], f[3]);
     if (full) *(float4*)((char*)base + elem * 4 + 16) = make_float4(f[4], f[5], f[6], f[7]);
+    uint32_t t = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t |= (f[i] > 0.f ? 1u : 0u) << i;
+    return t;
   }
 }
 
@@ -79,6 +96,14 @@ __device__ __forceinline__ Lane make_lane(const BnParams& p) {
   l.row_lo = (long long)rep * p.rows_per_rep + lo;
   l.row_hi = (long long)rep * p.rows_per_rep + hi;
   return l;
+}
+
+// this thread's eight entries of a per-channel table row (16-byte aligned, ld is a multiple of 4)
+__device__ __forceinline__ void load_coef(const float* row, const Lane& l, float (&f)[8]) {
+  const int c0 = l.active ? l.c0 : 0;
+  const float4 a = *(const float4*)(row + c0);
+  const float4 b = *(const float4*)(row + (l.full ? c0 + 4 : c0));
+  f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
 }
 
 // Second half of the workgroup reduction. red[v * 256 + thread] holds quantity v (0-7: first sum of the
@@ -133,24 +158,25 @@ __global__ __launch_bounds__(256) void bn_fwd_stats_kernel(BnParams p) {
 
 // grid (ceil(ld / 16), W), 256 threads = 16 split lanes x 16 channels: folds the nsplit partial sums of a
 // channel (lane j takes splits j, j+16, ...; the sixteen lanes are combined in a fixed order) once per
-// data-group, so that the streaming kernels read finished per-channel values.
-// Forward (sum x, sum x^2): mean, rstd (and the gamma in use) into `stats`. Backward (sum g, sum g*xhat):
-// dbeta, dgamma totals in fp64 into totals[(rep * ld + c) * 2 + {0, 1}] for the streaming kernel, and in fp32
-// into row `rep` of the parameter-gradient partials (dgamma[c] at c * gstride, dbeta[c] at C * gstride + c: the
-// layout of a 1x1 "convolution" with one input channel, so that the update kernels treat gamma / beta like
-// any other layer with one split per data-group).
+// data-group and leaves the per-channel factors of the streaming kernel in coef[rep][.][ld], so that each of its
+// threads starts with a few 16-byte loads instead of dozens of scalar ones.
+// Forward (sum x, sum x^2): mean, rstd (and the gamma in use) into `stats`; coef rows: scale, shift. Backward (sum g,
+// sum g*xhat): dbeta, dgamma in fp32 into row `rep` of the parameter-gradient partials (dgamma[c] at c * gstride,
+// dbeta[c] at C * gstride + c: the layout of a 1x1 "convolution" with one input channel, so that the update kernels
+// treat gamma / beta like any other layer with one split per data-group); coef rows: mean, rstd, and k0, k1, k2 of
+// dx = k0 * dy - k1 - xhat * k2. Channels past C (row padding) get zeros.
 template <bool BWD>
 __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p) {
   const int rep = blockIdx.y, lane4 = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + (threadIdx.x & 15);
-  const bool live = BWD ? c < p.C : c < p.ld;
+  const bool live = c < p.ld;
   double a = 0.0, b = 0.0;
   if (live) {
 #pragma unroll 8
     for (int sp = lane4; sp < p.nsplit; sp += 16) {
-      const double* in = p.scratch + (((size_t)rep * p.nsplit + sp) * p.ld + c) * 2;
-      a += in[0];
-      b += in[1];
+      const double2 in = *(const double2*)(p.scratch + (((size_t)rep * p.nsplit + sp) * p.ld + c) * 2);
+      a += in.x;
+      b += in.y;
     }
   }
   __shared__ double red[2][16][16];
@@ -161,83 +187,81 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p) {
   const int ch = threadIdx.x & 15;
   a = b = 0.0;
   for (int j = 0; j < 16; ++j) { a += red[0][j][ch]; b += red[1][j][ch]; }
+  const double m = (double)p.rows_per_rep;
+  const bool real = c < p.C;
+  float* st = p.stats + (size_t)rep * 3 * p.ld;
+  float* coef = p.coef + (size_t)rep * kBnCoefRows * p.ld + c;
   if (BWD) {
-    double* out = p.totals + ((size_t)rep * p.ld + c) * 2;
-    out[0] = a;  // dbeta
-    out[1] = b;  // dgamma
-    float* row = p.partial + (size_t)rep * p.pstride;
-    row[(size_t)c * p.gstride] = (float)b;
-    row[(size_t)p.C * p.gstride + c] = (float)a;
+    const float mean = st[c], rstd = st[p.ld + c], gr = st[2 * p.ld + c] * rstd;  // gamma * rstd
+    if (real) {
+      float* row = p.partial + (size_t)rep * p.pstride;
+      row[(size_t)c * p.gstride] = (float)b;
+      row[(size_t)p.C * p.gstride + c] = (float)a;
+    }
+    // dx = gr * (alpha*dy - db/m - xhat*dg/m), db and dg already carry alpha
+    coef[0] = real ? mean : 0.f;
+    coef[p.ld] = real ? rstd : 0.f;
+    coef[2 * p.ld] = real ? gr * p.alpha : 0.f;
+    coef[3 * p.ld] = real ? gr * (float)(a / m) : 0.f;
+    coef[4 * p.ld] = real ? gr * (float)(b / m) : 0.f;
   } else {
-    const double m = (double)p.rows_per_rep;
     const double mean = a / m;
     double var = b / m - mean * mean;
     var = var > 0.0 ? var : 0.0;
-    float* st = p.stats + (size_t)rep * 3 * p.ld;
-    st[c] = (float)mean;
-    st[p.ld + c] = (float)(1.0 / sqrt(var + (double)p.eps));
-    st[2 * p.ld + c] = c < p.C ? p.gamma[(size_t)rep * p.rep_stride + (size_t)c * p.gstride] : 0.f;
+    const float meanf = (float)mean, rstd = (float)(1.0 / sqrt(var + (double)p.eps));
+    const float g = real ? p.gamma[(size_t)rep * p.rep_stride + (size_t)c * p.gstride] : 0.f;
+    const float beta = real ? p.beta[(size_t)rep * p.rep_stride + c] : 0.f;
+    st[c] = meanf;
+    st[p.ld + c] = rstd;
+    st[2 * p.ld + c] = g;
+    coef[0] = p.alpha * g * rstd;
+    coef[p.ld] = p.alpha * (beta - meanf * g * rstd);
   }
 }
 
-// grid (nsplit, W): same row partition as the statistics kernel; streams its rows.
+// grid (nsplit, W): same row partition as the statistics kernel; streams its rows. HBM-bound (reads x and the residual,
+// writes y and 1/16 of it in sign bits); the rows of a trip are requested before anything is computed, the first ones
+// before the per-channel factors, and stores and sign bits are packed conversions. Average over the ResNet-18 shapes at
+// 4 x 128 (33 MB tensors): 16 us, 5.2 TB/s; with 32 scalar loads of statistics in front of the first row and
+// conversions in integer arithmetic it was 30 us (backward: 15.5 against 25 us).
 template <typename T>
 __global__ __launch_bounds__(256) void bn_fwd_apply_kernel(BnParams p) {
   const Lane l = make_lane(p);
   if (!l.active) return;
-  const int rep = blockIdx.y;
-  const float* beta = p.beta + (size_t)rep * p.rep_stride;
-  const float* st = p.stats + (size_t)rep * 3 * p.ld;
+  const float* coef = p.coef + (size_t)blockIdx.y * kBnCoefRows * p.ld;
   float scale[8], shift[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    scale[i] = shift[i] = 0.f;
-    const int c = l.c0 + i;
-    if (c >= p.C) continue;
-    const float mean = st[c], rstd = st[p.ld + c], g = st[2 * p.ld + c];
-    scale[i] = p.alpha * g * rstd;
-    shift[i] = p.alpha * (beta[c] - mean * g * rstd);
-  }
-  auto finish_row = [&](long long r, float (&f)[8], const float (&q)[8]) {
-    const size_t e = (size_t)r * p.ld + l.c0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float v = fmaf(f[i], scale[i], shift[i]);
-      if (p.res) v += q[i];
-      if (p.relu) v = v > 0.f ? v : 0.f;
-      f[i] = v;
-    }
-    store8<T>(p.y, e, l.full, f);
-    if (p.bits_out) {
-      // the sign of the stored (rounded) value, as the convolution epilogues define the plane
-      uint32_t bits = 0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float stored = sizeof(T) == 2 ? bf2f(f2bf(f[i])) : f[i];
-        bits |= (stored > 0.f ? 1u : 0u) << i;
-      }
-      ((uint8_t*)p.bits_out)[(size_t)r * (p.ld / 8) + l.tg] = (uint8_t)bits;
-    }
-  };
-  // four rows per trip: all loads of the trip are issued before the first row is finished
-  long long r = l.row_lo + l.tr;
-  for (; r + 3 * l.rpp < l.row_hi; r += 4 * l.rpp) {
-    float f[4][8], q[4][8];
+  auto load_rows = [&](long long r, float (&f)[4][8], float (&q)[4][8]) {  // rows past the end read the last one again
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const size_t e = (size_t)(r + u * l.rpp) * p.ld + l.c0;
-      load8<T>(p.x, e, l.full, f[u]);
-      if (p.res) load8<T>(p.res, e, l.full, q[u]);
+      const long long ru = r + u * l.rpp < l.row_hi ? r + u * l.rpp : l.row_hi - 1;
+      load8<T>(p.x, (size_t)ru * p.ld + l.c0, l.full, f[u]);
+      if (p.res) load8<T>(p.res, (size_t)ru * p.ld + l.c0, l.full, q[u]);
     }
+  };
+  float f[4][8], q[4][8];
+  long long r = l.row_lo + l.tr;
+  load_rows(r, f, q);
+  load_coef(coef, l, scale);
+  load_coef(coef + p.ld, l, shift);
+  for (;;) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) finish_row(r + u * l.rpp, f[u], q[u]);
-  }
-  for (; r < l.row_hi; r += l.rpp) {
-    float f[8], q[8];
-    const size_t e = (size_t)r * p.ld + l.c0;
-    load8<T>(p.x, e, l.full, f);
-    if (p.res) load8<T>(p.res, e, l.full, q);
-    finish_row(r, f, q);
+    for (int u = 0; u < 4; ++u) {
+      const long long ru = r + u * l.rpp;
+      if (ru >= l.row_hi) break;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        float v = fmaf(f[u][i], scale[i], shift[i]);
+        if (p.res) v += q[u][i];
+        if (p.relu) v = v > 0.f ? v : 0.f;
+        f[u][i] = v;
+      }
+      const uint32_t bits = store8<T>(p.y, (size_t)ru * p.ld + l.c0, l.full, f[u]);
+      // the sign of the stored (rounded) value, as the convolution epilogues define the plane
+      if (p.bits_out) ((uint8_t*)p.bits_out)[(size_t)ru * (p.ld / 8) + l.tg] = (uint8_t)bits;
+    }
+    r += 4 * l.rpp;
+    if (r >= l.row_hi) break;
+    load_rows(r, f, q);
   }
 }
 
@@ -251,12 +275,8 @@ __global__ __launch_bounds__(256) void bn_bwd_stats_kernel(BnParams p) {
   const int rep = blockIdx.y;
   const float* st = p.stats + (size_t)rep * 3 * p.ld;
   float mean[8], rstd[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int c = l.c0 + i;
-    mean[i] = l.active && c < p.ld ? st[c] : 0.f;
-    rstd[i] = l.active && c < p.ld ? st[p.ld + c] : 0.f;
-  }
+  load_coef(st, l, mean);
+  load_coef(st + p.ld, l, rstd);
   double s[8], ss[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) s[i] = ss[i] = 0.0;
@@ -299,56 +319,44 @@ __global__ __launch_bounds__(256) void bn_bwd_stats_kernel(BnParams p) {
   fold_rows(red, cg, l.rpp, p.ld, (double)p.alpha, p.scratch + ((size_t)rep * gridDim.x + blockIdx.x) * p.ld * 2);
 }
 
-// grid (nsplit, W): streams dx from dy, x, the saved statistics and the finished dgamma / dbeta totals.
+// grid (nsplit, W): streams dx from dy, x and the per-channel factors, laid out as the forward streaming kernel.
 template <typename T>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(BnParams p) {
   const Lane l = make_lane(p);
   if (!l.active) return;
-  const int rep = blockIdx.y;
-  const float* st = p.stats + (size_t)rep * 3 * p.ld;
+  const float* coef = p.coef + (size_t)blockIdx.y * kBnCoefRows * p.ld;
   float mean[8], rstd[8], k0[8], k1[8], k2[8];
-  const double m = (double)p.rows_per_rep;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int c = l.c0 + i;
-    mean[i] = rstd[i] = k0[i] = k1[i] = k2[i] = 0.f;
-    if (c >= p.C) continue;
-    const double* tot = p.totals + ((size_t)rep * p.ld + c) * 2;
-    const double db = tot[0], dg = tot[1];
-    mean[i] = st[c];
-    rstd[i] = st[p.ld + c];
-    const float gr = st[2 * p.ld + c] * rstd[i];  // gamma * rstd
-    // dx = gr * (alpha*dy - db/m - xhat*dg/m), db and dg already carry alpha
-    k0[i] = gr * p.alpha;
-    k1[i] = gr * (float)(db / m);
-    k2[i] = gr * (float)(dg / m);
-  }
-  auto finish_row = [&](long long r, float (&f)[8], const float (&g)[8]) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float xh = (f[i] - mean[i]) * rstd[i];
-      f[i] = k0[i] * g[i] - k1[i] - xh * k2[i];
-    }
-    store8<T>(p.dx, (size_t)r * p.ld + l.c0, l.full, f);
-  };
-  long long r = l.row_lo + l.tr;
-  for (; r + 3 * l.rpp < l.row_hi; r += 4 * l.rpp) {
-    float f[4][8], g[4][8];
+  auto load_rows = [&](long long r, float (&f)[4][8], float (&g)[4][8]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const size_t e = (size_t)(r + u * l.rpp) * p.ld + l.c0;
-      load8<T>(p.x, e, l.full, f[u]);
-      load8<T>(p.dy, e, l.full, g[u]);
+      const long long ru = r + u * l.rpp < l.row_hi ? r + u * l.rpp : l.row_hi - 1;
+      load8<T>(p.x, (size_t)ru * p.ld + l.c0, l.full, f[u]);
+      load8<T>(p.dy, (size_t)ru * p.ld + l.c0, l.full, g[u]);
     }
+  };
+  float f[4][8], g[4][8];
+  long long r = l.row_lo + l.tr;
+  load_rows(r, f, g);
+  load_coef(coef, l, mean);
+  load_coef(coef + p.ld, l, rstd);
+  load_coef(coef + 2 * p.ld, l, k0);
+  load_coef(coef + 3 * p.ld, l, k1);
+  load_coef(coef + 4 * p.ld, l, k2);
+  for (;;) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) finish_row(r + u * l.rpp, f[u], g[u]);
-  }
-  for (; r < l.row_hi; r += l.rpp) {
-    float f[8], g[8];
-    const size_t e = (size_t)r * p.ld + l.c0;
-    load8<T>(p.x, e, l.full, f);
-    load8<T>(p.dy, e, l.full, g);
-    finish_row(r, f, g);
+    for (int u = 0; u < 4; ++u) {
+      const long long ru = r + u * l.rpp;
+      if (ru >= l.row_hi) break;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float xh = (f[u][i] - mean[i]) * rstd[i];
+        f[u][i] = k0[i] * g[u][i] - k1[i] - xh * k2[i];
+      }
+      (void)store8<T>(p.dx, (size_t)ru * p.ld + l.c0, l.full, f[u]);
+    }
+    r += 4 * l.rpp;
+    if (r >= l.row_hi) break;
+    load_rows(r, f, g);
   }
 }
 

@@ -53,3 +53,13 @@ def test_linear_layers_of_few_rows(precision, feat, hidden, W, B):
 def test_linear_layers_with_weights_per_data_group(B):
     from test_gpu_gossip import _compare as compare_gossip
     compare_gossip(_two_linear("f32", 40, 24, 3, B), seed=24, T=4, mixing=ring_mixing(3, 0.3))
+
+
+@pytest.mark.parametrize("c,hw,B", [(8, 1, 3), (16, 3, 5), (264, 5, 7), (12, 4, 33)])
+def test_batch_norm_row_remainders(c, hw, B):
+    # fewer rows than one pass of the workgroup, rows that do not fill the four-row trips, several splits
+    from test_gpu_batchnorm import _compare as compare_bn
+    ops = [{"op": "conv", "cin": 3, "cout": c, "k": 1, "stride": 1, "pad": 0}, {"op": "bn", "c": c, "eps": 1e-5},
+           {"op": "relu"}, {"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
+    compare_bn(Workload(name=f"bn_rows_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
+                        precision="f32", lr=0.05, momentum=0.0, steps=2), seed=25, T=2, every_step=True, tiny=True)
