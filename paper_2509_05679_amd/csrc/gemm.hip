@@ -551,26 +551,14 @@ __global__ __launch_bounds__(256, 2) void conv_gemm_kernel(ConvParams p_, int ti
   }
 }
 
-// ------------------------------------------------------------------ tile geometry of the 3x3 stride-1 kernels
-// A workgroup owns a TH x TW rectangle of one image (or IMGS whole small images) and stages the
-// input patch of that rectangle including its one-pixel halo in LDS.
-struct HaloGeom {
-  int tw_log, th_log;      // log2 of the tile width / height in pixels
-  int tiles_w, tiles_h;    // tiles per image
-  int imgs;                // images per tile
-  int PW, PP;              // patch row pitch (TW+2) and pixels per image patch ((TH+2)*(TW+2))
-  int patch_pix;           // imgs * PP
-  int patch_bytes;         // patch_pix * 144 rounded to 256
-  int flip;                // dgrad: tap (r,s) reads the patch at (2-r, 2-s)
-  int tpi_log, tilesw_log; // log2 of the tiles per image and per image row (both powers of two)
-  uint32_t mPP, mPW;       // ceil(2^32 / PP), ceil(2^32 / PW): floor(i / d) == __umulhi(i, m) for i, d < 2^16
-};
-
 // ------------------------------------------------------------------ 3x3 stride-1 forward / dgrad, asynchronous LDS fills
-// The workgroup owns BM output pixels and BN output channels. Per 64-byte channel chunk the
-// input patch with its halo is staged in LDS ONCE and all nine taps read their MFMA operands
-// from it at shifted rows, so activations cross the L2 about 1.3x instead of 9x; zero padding
-// is materialised in the patch, not tested in the inner loop. Every operand byte travels global -> LDS
+// The workgroup owns BM consecutive pixels of the flattened (image, row, column) index and BN output channels. In that
+// index the nine taps of a pixel are the pixels at distance -W-1 .. W+1, so the input patch of a tile is BM + 2W + 2
+// consecutive pixels whatever the image size: its copies are contiguous, need no table and no division, and no tile
+// holds padding (a rectangle of 8 x 32 pixels plus halo is 340 rows and fits few image sizes; four 8 x 8 images with
+// their halos are 400 rows against 274). Taps that leave the image read a block of zeros instead: one lane mask per
+// image edge and fragment, combined on the scalar unit. Per KB-byte channel chunk the patch is staged in LDS ONCE and
+// all nine taps read their MFMA operands from it at shifted rows. Every operand byte travels global -> LDS
 // with global_load_lds_dwordx4 (no staging registers, lane L of a wave fills bytes
 // [16L, 16L+16) of a 1 KiB LDS block), issued two pipeline stages (tap, channel chunk)
 // ahead of its use: weight tiles rotate through three LDS slots and the next channel
@@ -578,14 +566,17 @@ struct HaloGeom {
 // compiler does not model these copies, so their completion is counted by hand: loads
 // retire in order, every stage issues a fixed number per lane, and each stage waits
 // until only the younger ones are outstanding, then crosses one workgroup barrier.
-// LDS rows are KB unpadded bytes; the 16-byte column c of a row lives at column c ^ f(row),
-// applied by choosing which global column a lane fetches. A 16-byte-per-lane LDS read is
+// LDS rows are KB unpadded bytes; the 16-byte column c of row r lives at column c ^ f(r), f(r) = (r * KB / 256) mod
+// (KB/16), applied by choosing which global column a lane fetches. A 16-byte-per-lane LDS read is
 // served 16 lanes per cycle from 64 four-byte banks, and the 16 lanes of one cycle are the
 // four-lane quads q = lane/4 of a 32-lane half whose index has even (or odd) bit parity:
-// {0,3,5,6} and {1,2,4,7} (measured). f is chosen so that each such set reads 16 different
-// 16-byte bank groups: weight rows (consecutive across lanes) use f = (row * KB / 256) mod
-// (KB/16); patch rows use bits of the patch coordinates (see patch_swizzle), and the pixels
-// of a 32-pixel fragment are dealt to lanes so that one cycle's lanes hold 16 consecutive ones.
+// {0,3,5,6} and {1,2,4,7} (measured). Any 16 consecutive rows hit 16 different 16-byte bank groups under f; the
+// pixels of a 32-pixel fragment are dealt to lanes so that one cycle's lanes hold 16 consecutive ones, and a lane
+// whose tap is outside the image reads the zero block at the bank group it would have used.
+// Bound by the matrix unit and by one barrier per stage. Measured against rectangular tiles with halos (only images
+// whose sides are powers of two; 8 x 32 pixels + halo), alone: 512 images of 32 x 32 x 64 58.9 -> 56.5 us, 128 -> 128
+// channels at 16 x 16 unchanged at 45 us (860 TFLOP/s); per 8 iterations ResNet-20 in one module 5.77 -> 5.55 ms,
+// ResNet-56 23.0 -> 22.5 ms, and 28 x 28 images, which ran on conv_gemm_kernel, 3.08 -> 2.72 ms.
 __device__ __forceinline__ void dma16(const void* gsrc, uint32_t lds_base_uniform) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_base_uniform) : "memory", "m0");
 }
@@ -597,15 +588,27 @@ __device__ __forceinline__ void dma16s(const void* gbase_uniform, uint32_t goff,
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// floor(n / d) == __umulhi(n, mul) >> shift for 0 <= n < 2^31: mul = floor(2^(31+l) / d) + 1 with 2^(l-1) < d <= 2^l
+// exceeds 2^(31+l) / d by at most 2^l / d, which the division of a 31-bit n never sees
+struct Divisor {
+  uint32_t mul;
+  int shift;
+};
+inline Divisor make_divisor(int d) {  // d >= 2
+  int l = 1;
+  while ((1ll << l) < d) ++l;
+  return Divisor{(uint32_t)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
+}
+
 struct DmaGeom {
-  HaloGeom h;
-  int patch_rows;   // patch pixels rounded up to 8 (one wave fill = 8 rows)
-  int tab_bytes;    // pixel-offset table, rounded to 1 KiB
-  int smem_bytes;   // dynamic LDS of the launch
+  int patch_rows;   // BM + 2W + 2 rounded up to whole wave fills
+  int out_bytes;    // bytes of LDS the epilogue may stage tiles in (everything below the dump block)
+  int dgrad;        // tap (r, s) reads the patch at distance (1-r, 1-s) instead of (r-1, s-1)
+  Divisor dW, dH;
 };
 
 template <typename T, int BM, int BN, int WM, int WN, int PS, int KB>
-__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) == 4 ? 2 : 1) void conv3x3_dma_kernel(ConvParams p_, DmaGeom dg) {
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) == 4 ? 2 : 1) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
   constexpr int NW = (BM / WM) * (BN / WN);  // waves per workgroup (each owns a WM x WN sub-tile)
@@ -613,104 +616,60 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   constexpr int CPR = KB / 16;         // 16-byte columns per row
   constexpr int WL = BN / FROWS / NW;   // weight fills per lane per stage
   constexpr int NKS = KB / 32;         // MFMA k-steps per stage
-  constexpr int FB = KB == 128 ? 3 : 2;   // swizzle bits = log2(CPR)
   constexpr int RPL = KB == 128 ? 1 : 2;  // log2(rows per 256 bytes of LDS)
   static_assert(KB == 64 || KB == 128, "row depth");
   static_assert(WL >= 1, "weight tile smaller than one fill per wave");
   constexpr int NI = WM / 32, NJ = WN / 32;
   static_assert(NW == 4 || NW == 8, "four or eight waves");
   extern __shared__ __align__(16) char smem[];
-  const HaloGeom& g = dg.h;
-  const int prow = dg.patch_rows;
+  const int prow = g.patch_rows;
   const int pbuf_bytes = prow * KB;
-  int* tab = (int*)smem;
-  char* pbuf = smem + dg.tab_bytes;
-  char* wring = pbuf + (PS > 0 ? 2 : 1) * pbuf_bytes;
+  const int wring_off = (PS > 0 ? 2 : 1) * pbuf_bytes;
   const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
-  const uint32_t lds_pbuf = lds0 + dg.tab_bytes;
-  const uint32_t lds_wring = lds_pbuf + (PS > 0 ? 2 : 1) * pbuf_bytes;
+  const uint32_t lds_dump = lds0 + g.out_bytes;   // 1 KiB that absorbs surplus fills
+  const int zero_off = g.out_bytes + 1024;        // 256 bytes of zeros
+  char* wring = smem + wring_off;
+  const uint32_t lds_wring = lds0 + wring_off;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: everything derived from it stays in SGPRs
   const int wave_m = wave % (BM / WM), wave_n = wave / (BM / WM);
-  const int grp = blockIdx.x >> g.tpi_log, tin = blockIdx.x - (grp << g.tpi_log);
-  const int th_idx = tin >> g.tilesw_log, tw_idx = tin - (th_idx << g.tilesw_log);
-  const int img0 = grp * g.imgs, h0 = th_idx << g.th_log, w0 = tw_idx << g.tw_log;
-  const int n0 = blockIdx.y * BN;
-  if (p.nrep > 1) {  // the launcher made sure that the images of a tile belong to one data-group
-    const int r = min(img0 / (p.Nimg / p.nrep), p.nrep - 1);
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  if (p.nrep > 1) {  // the launcher made sure that the pixels of a tile belong to one data-group
+    const int r = min(m0 / (p.M / p.nrep), p.nrep - 1);
     p.w = (const char*)p.w + (size_t)r * p.w_rep;
     if (p.bias) p.bias += (size_t)r * p.bias_rep;
   }
-  const int TWm = (1 << g.tw_log) - 1, THm = (1 << g.th_log) - 1;
   const int nchunks = (p.Cx * ES) / KB;
   const size_t pixbytes = (size_t)p.Cx * ES;
-  // Swizzle of the patch row at patch coordinates (xx, yy). One LDS cycle reads a 16-pixel
-  // run of the tile: 16 x 1, 8 x 2 or 4 x 4 pixels, shifted by the tap. The low RPL bits of x
-  // already spread a run over the rows of one 256-byte bank line; f takes the next bits of x
-  // that vary inside the run and fills up with low bits of y.
-  const int sw_nx = min(FB, max(0, g.tw_log - RPL));
-  const int sw_mx = (1 << sw_nx) - 1, sw_my = (1 << (FB - sw_nx)) - 1;
-  auto patch_swizzle = [&](int xx, int yy) { return ((xx >> RPL) & sw_mx) | ((yy & sw_my) << sw_nx); };
+  if (tid < 16) *(uint4*)(smem + zero_off + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
 
-  // pixel-offset table of the patch rows: pixel index in the gathered tensor, or -1 (zero row)
-  for (int row = tid; row < prow; row += 64 * NW) {
-    int v = -1;
-    if (row < g.patch_pix) {
-      const int im = (int)__umulhi((uint32_t)row, g.mPP), rem = row - im * g.PP;
-      const int yy = (int)__umulhi((uint32_t)rem, g.mPW), xx = rem - yy * g.PW;
-      const int gi = img0 + im, gh = h0 + yy - 1, gw = w0 + xx - 1;
-      if (gi < p.Nimg && (unsigned)gh < (unsigned)p.H && (unsigned)gw < (unsigned)p.W)
-        v = ((gi * p.H + gh) * p.W + gw) * CPR + patch_swizzle(xx, yy);
-    }
-    tab[row] = v;
-  }
-  __syncthreads();
-
-  // column swizzle of a weight row (rows are consecutive across lanes, fills start at multiples of FROWS rows)
-  auto swz = [](int r) { return (r >> RPL) & (CPR - 1); };
   const int l8 = lane / CPR;  // row inside a fill
   const int pcol = lane % CPR;
-  const char* zsrc = (const char*)p.zeros + pcol * 16;  // the zero block is at least one pixel row long
+  // global 16-byte column this lane fetches: (row / 2^RPL) mod CPR of a row whose fill index has the wave's parity
+  const uint32_t c16 = (uint32_t)((pcol ^ (((l8 + (wave & 1) * FROWS) >> RPL) & (CPR - 1))) * 16);
   const int pw_total = prow / FROWS;  // wave fills in a patch
-  const uint32_t lds_dump = lds_wring + 3 * (BN * KB);  // 1 KiB that absorbs surplus fills
-  // Source of this lane's 16 bytes in the j-th patch fill of this wave, for channel chunk 0.
-  // Rows outside the image and surplus fills read the zero block.
-  // (table entries are read in one batch and turned into addresses with selects: a branch per
-  // entry would serialise one LDS round trip per fill at the very start of the kernel)
-  constexpr int NPRO = (KB == 128 && PS == 0) ? 11 : 7;  // fills per wave that cover the largest patch (4 waves x NPRO x FROWS rows)
-  const char* pro_src[NPRO];
-  {
-    int offs[NPRO];
+  // Patch fills of this wave: byte offset from the patch's first row. Rows before the tensor's first or after its
+  // last pixel repeat that pixel (no tap inside an image reads them).
+  constexpr int NPRO = (KB == 128 && PS == 0) ? 11 : 7;  // fills per wave that cover the largest patch
+  const int first = m0 - p.W - 1;  // pixel of patch row 0
+  const char* pbase = (const char*)p.x + (long long)first * (long long)pixbytes;
+  uint32_t poff[NPRO];
 #pragma unroll
-    for (int j = 0; j < NPRO; ++j) {
-      const int wl = wave + NW * j;
-      offs[j] = tab[(wl < pw_total ? wl * FROWS : 0) + l8];  // pixel * CPR + f, or -1
-    }
-#pragma unroll
-    for (int j = 0; j < NPRO; ++j) {
-      const bool ok = wave + NW * j < pw_total && offs[j] >= 0;
-      const int o = ok ? offs[j] : 0;
-      const char* a = (const char*)p.x + (size_t)(o >> FB) * pixbytes + ((pcol ^ (o & (CPR - 1))) << 4);
-      pro_src[j] = ok ? a : zsrc;
-    }
+  for (int j = 0; j < NPRO; ++j) {
+    const int row = (wave + NW * j) * FROWS + l8;
+    poff[j] = (uint32_t)(min(max(row, -first), p.M - 1 - first)) * (uint32_t)pixbytes + c16;
   }
-  auto patch_src = [&](int j) -> const char* { return pro_src[j]; };
   auto patch_dst = [&](int j, int buf) {
     const int wl = wave + NW * j;
-    return wl < pw_total ? lds_pbuf + buf * pbuf_bytes + wl * 1024 : lds_dump;
+    return wl < pw_total ? lds0 + buf * pbuf_bytes + wl * 1024 : lds_dump;
   };
-  constexpr int NPF = 7 * PS;  // patch fills per wave and chunk issued inside the loop
-  const char* psrc[NPF > 0 ? NPF : 1];
-#pragma unroll
-  for (int j = 0; j < NPF; ++j) psrc[j] = patch_src(j);
   // weight rows: byte offset of this lane's 16 bytes inside the weight tensor at tap 0, chunk 0.
   // Rows past Nout repeat the last one: their output columns lie past ldy == Nout and are never stored.
   uint32_t wvo[WL];
 #pragma unroll
   for (int u = 0; u < WL; ++u) {
     const int gn = n0 + (wave + NW * u) * FROWS + l8;
-    const int c16 = (pcol ^ swz(l8 + (wave & 1) * FROWS)) * 16;
     wvo[u] = (uint32_t)(gn < p.Nout ? gn : p.Nout - 1) * (uint32_t)(9 * pixbytes) + c16;
   }
   auto fill_w = [&](int chunk, int tap, int slot) {
@@ -728,47 +687,46 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   if (p.maskbits) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int m = wave_m * WM + i * 32 + lpix;
-      const int x = m & TWm, y = (m >> g.tw_log) & THm, im = m >> (g.tw_log + g.th_log);
-      const int gi = img0 + im;
-      const size_t pix = ((size_t)gi * p.H + h0 + y) * p.W + w0 + x;
+      const int pix = m0 + wave_m * WM + i * 32 + lpix;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) mb[i][j] = load_bits32(p.maskbits, pix, p.ldy, n0 + wave_n * WN + 32 * j, gi < p.Nimg);
+      for (int j = 0; j < NJ; ++j) mb[i][j] = load_bits32(p.maskbits, (size_t)pix, p.ldy, n0 + wave_n * WN + 32 * j, pix < p.M);
     }
   }
 
   // prologue: whole first patch, then the weight tiles of stages 0 and 1. Issued before the rest of
-  // the set-up (fragment addresses, sign words, accumulators) so that it runs under the copies' latency.
+  // the set-up (fragment addresses, edge masks, accumulators) so that it runs under the copies' latency.
 #pragma unroll
   for (int j = 0; j < NPRO; ++j)
-    if (wave + NW * j < pw_total) dma16(pro_src[j], patch_dst(j, 0));
+    if (wave + NW * j < pw_total) dma16s(pbase, poff[j], patch_dst(j, 0));
   fill_w(0, 0, 0);
   fill_w(0, 1, 1);
 
   // fragment addressing
   const int half = lane >> 5;
-  // Patch operand: LDS byte offset of a fragment row = row * KB + (((2 ks + half) ^ f) << 4) with
-  // f = fx(x + tap_s) | fy(y + tap_r). Per lane and tap coordinate the swizzle bits are kept in
-  // registers (sx also carries half), so a stage needs one add, one xor-add and one xor per k-step.
-  int rowb[NI], sx[NI][3], sy[NI][3];
+  // Patch operand of tap (r, s): row * KB + ((half ^ f(row)) << 4), row = tile pixel + (W + 1) +- ((r-1) W + (s-1))
+  int rowb[NI];
+  // is the neighbour that tap row 0 / 2 and tap column 0 / 2 read inside the image
+  bool ok_r0[NI], ok_r2[NI], ok_s0[NI], ok_s2[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int m = wave_m * WM + i * 32 + lpix;
-    const int x = m & TWm, y = (m >> g.tw_log) & THm, im = m >> (g.tw_log + g.th_log);
-    rowb[i] = (im * g.PP + y * g.PW + x) * KB;
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      const int tt = g.flip ? 2 - t : t;
-      sx[i][t] = ((patch_swizzle(x + tt, 0)) ^ half) << 4;
-      sy[i][t] = patch_swizzle(0, y + tt) << 4;
-    }
+    rowb[i] = (m + p.W + 1) * KB + half * 16;
+    const uint32_t pix = (uint32_t)(m0 + m);
+    const int line = (int)(__umulhi(pix, g.dW.mul) >> g.dW.shift), w = (int)pix - line * p.W;
+    const int h = line - (int)(__umulhi((uint32_t)line, g.dH.mul) >> g.dH.shift) * p.H;
+    const bool up = h > 0, down = h < p.H - 1, left = w > 0, right = w < p.W - 1;
+    ok_r0[i] = g.dgrad ? down : up;
+    ok_r2[i] = g.dgrad ? up : down;
+    ok_s0[i] = g.dgrad ? right : left;
+    ok_s2[i] = g.dgrad ? left : right;
   }
+  const int tap_w = (g.dgrad ? -p.W : p.W) * KB, tap_1 = g.dgrad ? -KB : KB;
   int boff[NJ][NKS];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int n = wave_n * WN + j * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) boff[j][ks] = n * KB + (((2 * ks + half) ^ swz(n)) << 4);
+    for (int ks = 0; ks < NKS; ++ks) boff[j][ks] = n * KB + (((2 * ks + half) ^ ((n >> RPL) & (CPR - 1))) << 4);
   }
   f32x16_t acc[NJ][NI];
 #pragma unroll
@@ -778,18 +736,30 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
 
-  const int pbuf_off = dg.tab_bytes;
-  auto compute = [&](int chunk, int tap_r, int tap_s, int slot) {
-    const int tapoff = (g.flip ? 2 - tap_r : tap_r) * g.PW + (g.flip ? 2 - tap_s : tap_s);
-    const int sbase = pbuf_off + (PS > 0 ? (chunk & 1) * pbuf_bytes : 0) + tapoff * KB;  // wave-uniform
-    const char* wb = wring + slot * (BN * KB);
-    int a0[NI];
+  // LDS offsets of this lane's patch operands at the tap about to be multiplied. They are formed behind the MFMAs of
+  // the previous tap, before the barrier: after it only the LDS reads stand between a stage and its first MFMA.
+  int a0[NI];
+  auto address = [&](int chunk, int tap_r, int tap_s) {
+    const int tapoff = (tap_r - 1) * tap_w + (tap_s - 1) * tap_1;  // wave-uniform
+    const int pbuf = PS > 0 ? (chunk & 1) * pbuf_bytes : 0;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       int rb = rowb[i];
       asm volatile("" : "+v"(rb));  // keeps the nine taps' addresses from being precomputed (and spilled)
-      a0[i] = (sx[i][tap_s] ^ sy[i][tap_r]) + (rb + sbase);
+      const int t = rb + tapoff;    // row * KB + half * 16; f(row) = bits 8.. of it
+      const int a = (t ^ ((t >> 4) & ((CPR - 1) << 4))) + pbuf;
+      if (tap_r == 1 && tap_s == 1) {
+        a0[i] = a;
+      } else {
+        const bool okr = tap_r == 0 ? ok_r0[i] : tap_r == 2 ? ok_r2[i] : true;
+        const bool oks = tap_s == 0 ? ok_s0[i] : tap_s == 2 ? ok_s2[i] : true;
+        a0[i] = okr && oks ? a : ((a & 0xf0) | zero_off);
+      }
+      asm volatile("" : "+v"(a0[i]));
     }
+  };
+  auto compute = [&](int slot) {
+    const char* wb = wring + slot * (BN * KB);
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       uint4 a[NI], b[NJ];
@@ -819,10 +789,13 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
     if (PS > 0 && (TAP) < 7) {                                                                      \
       const int cn = chunk + 1 < nchunks ? chunk + 1 : chunk;                                       \
       _Pragma("unroll") for (int u = 0; u < PS; ++u)                                                \
-        dma16(psrc[((TAP) < 7 ? (TAP) : 0) * PS + u] + (size_t)cn * KB, patch_dst((TAP) * PS + u, (chunk + 1) & 1)); \
+        dma16s(pbase + (size_t)cn * KB, poff[((TAP) < 7 ? (TAP) : 0) * PS + u], patch_dst((TAP) * PS + u, (chunk + 1) & 1)); \
     }                                                                                               \
-    compute(chunk, (TAP) / 3, (TAP) % 3, (TAP) % 3);                                                \
+    compute((TAP) % 3);                                                                             \
+    address(chunk + ((TAP) == 8 ? 1 : 0), ((TAP) + 1) % 9 / 3, ((TAP) + 1) % 3);                    \
   }
+
+  address(0, 0, 0);
 
   for (int chunk = 0; chunk < nchunks; ++chunk) {
     DDS_STAGE(0) DDS_STAGE(1) DDS_STAGE(2) DDS_STAGE(3) DDS_STAGE(4) DDS_STAGE(5) DDS_STAGE(6) DDS_STAGE(7) DDS_STAGE(8)
@@ -837,7 +810,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   constexpr int RPF = 64 / NCOL;       // rows per wave fill
   constexpr int FPW = BM / RPF / NW;    // fills per wave
   int res_off = -1, mask_off = -1, nregions = 0;
-  const int ab_off = (int)(lds_dump - lds0);  // the dump block now holds alpha * bias of this tile's channels
+  const int ab_off = g.out_bytes;  // the dump block now holds alpha * bias of this tile's channels
   float* ab_lds = (float*)(smem + ab_off);
   wg_barrier();
   if (tid < BN) {
@@ -847,19 +820,16 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   if (p.res || p.mask) {
     int region = 0;
     auto stage_tile = [&](const void* src_tensor) -> int {
-      if ((region + 1) * BM * ROWB > dg.smem_bytes - 1024) return -1;
+      if ((region + 1) * BM * ROWB > g.out_bytes) return -1;
       const int rbase = region * BM * ROWB;
 #pragma unroll
       for (int u = 0; u < FPW; ++u) {
         const int f = wave + NW * u;
         const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
         const int gc = (slot ^ row) & (NCOL - 1);
-        const int x = row & TWm, y = (row >> g.tw_log) & THm, im = row >> (g.tw_log + g.th_log);
-        const int gi = img0 + im;
         const int n = n0 + gc * (16 / ES);
-        const bool ok = gi < p.Nimg && n < p.ldy;
-        const size_t pix = ((size_t)gi * p.H + h0 + y) * p.W + w0 + x;
-        const char* src = ok ? (const char*)src_tensor + (pix * p.ldy + n) * ES : (const char*)p.zeros;
+        const bool ok = m0 + row < p.M && n < p.ldy;
+        const char* src = ok ? (const char*)src_tensor + ((size_t)(m0 + row) * p.ldy + n) * ES : (const char*)p.zeros;
         dma16(src, lds0 + rbase + f * 1024);
       }
       ++region;
@@ -871,7 +841,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
     nregions = region;
   }
   // Output tile in LDS: the residual tile's bytes if there is one, else the next free region.
-  int out_off = res_off >= 0 ? res_off : ((nregions + 1) * BM * ROWB <= dg.smem_bytes - 1024 ? nregions * BM * ROWB : -1);
+  int out_off = res_off >= 0 ? res_off : ((nregions + 1) * BM * ROWB <= g.out_bytes ? nregions * BM * ROWB : -1);
   if (p.out_f32) out_off = -1;
   __syncthreads();  // also orders the plain LDS stores of alpha * bias
 
@@ -880,10 +850,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int m = wave_m * WM + i * 32 + lpix;
-    const int x = m & TWm, y = (m >> g.tw_log) & THm, im = m >> (g.tw_log + g.th_log);
-    const int gi = img0 + im;
-    const size_t pix = ((size_t)gi * p.H + h0 + y) * p.W + w0 + x;
-    epilogue_tile<T, NJ, NI>(p, acc, i, gi < p.Nimg, pix, nb, bias, (const char DDS_LDS_AS*)smem, res_off, mask_off, m, ROWB,
+    epilogue_tile<T, NJ, NI>(p, acc, i, m0 + m < p.M, (size_t)(m0 + m), nb, bias, (const char DDS_LDS_AS*)smem, res_off, mask_off, m, ROWB,
                              wave_n * WN + 4 * (lane >> 5), ab_off, mb[i], out_off);
   }
   if (out_off >= 0) {
@@ -894,12 +861,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
       const int f = wave + NW * u;
       const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
       const int gc = (slot ^ row) & (NCOL - 1);
-      const int x = row & TWm, y = (row >> g.tw_log) & THm, im = row >> (g.tw_log + g.th_log);
-      const int gi = img0 + im;
       const int n = n0 + gc * (16 / ES);
-      const size_t pix = ((size_t)gi * p.H + h0 + y) * p.W + w0 + x;
       const u32x4_t v = *(const u32x4_t DDS_LDS_AS*)((const char DDS_LDS_AS*)smem + out_off + f * 1024 + lane * 16);
-      if (gi < p.Nimg && n < p.ldy) *(u32x4_t*)((char*)p.y + (pix * p.ldy + n) * ES) = v;
+      if (m0 + row < p.M && n < p.ldy) *(u32x4_t*)((char*)p.y + ((size_t)(m0 + row) * p.ldy + n) * ES) = v;
     }
   }
 }
@@ -910,102 +874,67 @@ inline int ilog2_exact(int v) {
   return (1 << l) == v ? l : -1;
 }
 
-// Fills g and returns true when the 3x3 stride-1 tiling covers this problem.
-template <typename T>
-bool halo_geometry(const ConvParams& p, HaloGeom& g, int BM = 256, int chunk_bytes = 64) {
-  const int CK = chunk_bytes / (int)sizeof(T);
-  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.H != p.Ho || p.W != p.Wo) return false;
-  if (p.Cx % CK != 0 || p.out_f32) return false;
-  const int lw = ilog2_exact(p.W), lh = ilog2_exact(p.H);
-  if (lw < 1 || lh < 1 || p.W > 32) return false;
-  int TW = p.W, TH, imgs;
-  if (p.H * p.W >= BM) {
-    TH = BM / TW;
-    imgs = 1;
-    if (TH < 1 || TH > p.H || p.H % TH) return false;
-  } else {
-    TH = p.H;
-    imgs = BM / (p.H * p.W);
-  }
-  g.tw_log = ilog2_exact(TW);
-  g.th_log = ilog2_exact(TH);
-  g.tiles_w = p.W / TW;
-  g.tiles_h = p.H / TH;
-  g.imgs = imgs;
-  g.PW = TW + 2;
-  g.PP = (TH + 2) * (TW + 2);
-  g.patch_pix = imgs * g.PP;
-  g.patch_bytes = (g.patch_pix * 144 + 255) / 256 * 256;
-  g.flip = p.dgrad;
-  g.tilesw_log = ilog2_exact(g.tiles_w);
-  g.tpi_log = ilog2_exact(g.tiles_w * g.tiles_h);
-  if (g.tilesw_log < 0 || g.tpi_log < 0 || g.PP >= 65536 || g.patch_pix >= 65536) return false;
-  g.mPP = (uint32_t)(((1ull << 32) + g.PP - 1) / g.PP);
-  g.mPW = (uint32_t)(((1ull << 32) + g.PW - 1) / g.PW);
-  return true;
-}
-
 template <typename T, int BM, int BN, int WM, int WN, int PS, int KB>
-bool launch_dma_inst(const ConvParams& p, const HaloGeom& h, hipStream_t s) {
+bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   constexpr int FROWS = 1024 / KB;
   constexpr int NW = (BM / WM) * (BN / WN);
-  DmaGeom dg;
-  dg.h = h;
-  dg.patch_rows = (h.patch_pix + FROWS - 1) / FROWS * FROWS;
-  dg.tab_bytes = (dg.patch_rows * 4 + 1023) / 1024 * 1024;
-  const int fills_per_wave = (dg.patch_rows / FROWS + NW - 1) / NW;
   if (p.Cx * (int)sizeof(T) % KB != 0) return false;
   const int nchunks = p.Cx * (int)sizeof(T) / KB;
-  if (fills_per_wave > ((KB == 128 && PS == 0) ? 11 : 7)) return false;  // prologue sources kept per lane
+  DmaGeom g;
+  g.patch_rows = (BM + 2 * p.W + 2 + FROWS - 1) / FROWS * FROWS;
+  g.dgrad = p.dgrad;
+  g.dW = make_divisor(p.W);
+  g.dH = make_divisor(p.H);
+  const int fills_per_wave = (g.patch_rows / FROWS + NW - 1) / NW;
+  if (fills_per_wave > ((KB == 128 && PS == 0) ? 11 : 7)) return false;  // patch offsets kept per lane
   if (PS == 0 ? nchunks != 1 : (nchunks < 2 || 7 * PS < fills_per_wave)) return false;
-  const int smem = dg.tab_bytes + (PS > 0 ? 2 : 1) * dg.patch_rows * KB + 3 * BN * KB + 1024;
-  if (smem > 160 * 1024 || p.zeros == nullptr) return false;
-  // pad rows come from the zero block; pad weight rows repeat row Nout-1 (columns past ldy are not stored);
-  // per-lane weight offsets are 32-bit
-  if (p.Cx * (int)sizeof(T) + 256 > kZeroBytes || p.ldy != p.Nout) return false;
-  if ((long long)p.Nout * 9 * p.Cx * (long long)sizeof(T) >= (1ll << 31)) return false;
-  dg.smem_bytes = smem;
+  int operands = (PS > 0 ? 2 : 1) * g.patch_rows * KB + 3 * BN * KB;
+  constexpr int tile = BM * BN * (int)sizeof(T);  // the output tile is staged where the operands were, if two workgroups still fit a CU
+  if (operands < tile && tile <= 72 * 1024) operands = tile;
+  g.out_bytes = operands;
+  const int smem = operands + 1024 + 256;
+  if (smem > 160 * 1024) return false;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  const int groups = (p.Nimg + h.imgs - 1) / h.imgs;
-  dim3 grid(groups * h.tiles_w * h.tiles_h, (p.ldy + BN - 1) / BN);
-  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB><<<grid, 64 * NW, smem, s>>>(p, dg);
+  dim3 grid((p.M + BM - 1) / BM, (p.ldy + BN - 1) / BN);
+  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB><<<grid, 64 * NW, smem, s>>>(p, g);
   return true;
 }
 
 // Picks the tile for the asynchronous kernel; false if the problem is outside its range.
 // Channel chunks are 64 bytes deep: the LDS footprint lets two or three workgroups share a
 // CU and hide each other's prologue and epilogue, and with 16 rows per wave fill a patch of
-// up to 340 rows needs at most 6 fills per wave, so one slice per tap (PS = 1) is enough.
+// up to 448 rows needs at most 7 fills per wave, so one slice per tap (PS = 1) is enough.
 template <typename T>
 bool launch_dma(const ConvParams& p, hipStream_t s) {
-  HaloGeom h;
   constexpr int KB = 64;
+  if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.H != p.Ho || p.W != p.Wo || p.out_f32) return false;
+  if (p.H < 2 || p.W < 2 || p.zeros == nullptr) return false;  // dividing by one is beyond make_divisor
+  // pad weight rows repeat row Nout-1 (columns past ldy are not stored); per-lane patch and weight offsets are 32-bit
+  if (p.ldy != p.Nout) return false;
+  if ((long long)p.Nout * 9 * p.Cx * (long long)sizeof(T) >= (1ll << 31)) return false;
   const int rowbytes = p.Cx * (int)sizeof(T);
-  if (rowbytes % KB != 0) return false;
+  if (rowbytes % KB != 0 || rowbytes > (1 << 20)) return false;
   const int nchunks = rowbytes / KB;
   // 64 bf16 (32 fp32) channels in and at most 64 out: one 128-byte chunk, i.e. whole cache lines per patch row,
   // nine stages instead of eighteen and the whole patch requested in the prologue (62.0 -> 59.4 us at 32 x 32 x 64)
-  if (rowbytes == 128 && p.ldy <= 64 && halo_geometry<T>(p, h, 256, 128) &&
-      launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, h, s)) return true;
+  if (rowbytes == 128 && p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, s)) return true;
   if (nchunks == 1) {
-    if (!halo_geometry<T>(p, h, 256, KB)) return false;
-    if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, h, s);
-    return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, h, s);
+    if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
+    return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
   }
   // small images: 128-pixel tiles give more workgroups. 256-pixel tiles from 256 workgroups up (one per CU: half the
   // weight copies per FLOP; with the other modules' kernels sharing the chip this beat two 128-pixel workgroups per
   // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step)
   const long long tiles256 = (long long)((p.M + 255) / 256) * ((p.ldy + 127) / 128);
-  if (tiles256 >= 256 && halo_geometry<T>(p, h, 256, KB)) {
-    if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, h, s)) return true;
-    if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, h, s)) return true;
+  if (tiles256 >= 256) {
+    if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, s)) return true;
+    if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
   }
-  if (halo_geometry<T>(p, h, 128, KB) && launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, h, s)) return true;
-  return false;
+  return launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, s);
 }
 
 // ------------------------------------------------------------------ wgrad

@@ -63,3 +63,23 @@ def test_batch_norm_row_remainders(c, hw, B):
            {"op": "relu"}, {"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
     compare_bn(Workload(name=f"bn_rows_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
                         precision="f32", lr=0.05, momentum=0.0, steps=2), seed=25, T=2, every_step=True, tiny=True)
+
+
+def _conv_chain(precision, widths, h, w, W, B):
+    ops = []
+    for cin, cout in zip((3,) + widths[:-1], widths):
+        ops += [{"op": "conv", "cin": cin, "cout": cout, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}]
+    ops += [{"op": "gap"}, {"op": "linear", "cin": widths[-1], "cout": 10}, {"op": "softmax_ce"}]
+    return Workload(name=f"conv_chain_{h}x{w}", ops=ops, bounds=[0, len(ops)], K=1, W=W, B=B, in_shape=(3, h, w), classes=10,
+                    precision=precision, lr=0.05, momentum=0.0, steps=2)
+
+
+@pytest.mark.parametrize("precision,widths,h,w,W,B", [
+    ("bf16", (32, 32, 64), 2, 2, 1, 3), ("bf16", (64, 64, 128), 3, 5, 2, 9), ("bf16", (64, 128, 128), 9, 7, 3, 5),
+    ("bf16", (64, 64, 32), 4, 47, 1, 2), ("bf16", (64, 64, 32), 5, 48, 1, 2), ("bf16", (32, 64), 3, 95, 1, 2),
+    ("bf16", (32, 64), 3, 96, 1, 2), ("bf16", (64, 128), 2, 160, 1, 2), ("f32", (32, 32, 64), 13, 3, 2, 7),
+    ("f32", (16, 48, 32), 6, 10, 2, 3)])
+def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
+    # images whose rows and planes are no power of two, tiles that hold many images or end inside one, patches on both
+    # sides of the most rows a launch can fetch (W = 47 / 95 / 159)
+    _compare(_conv_chain(precision, widths, h, w, W, B), seed=26, T=2, every_step=precision == "f32", tiny=precision == "f32")
