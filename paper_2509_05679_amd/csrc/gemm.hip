@@ -1371,6 +1371,172 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   }
 }
 
+// ------------------------------------------------------------------ the same weight gradients for any image size (bf16)
+// wgrad_dma_kernel wants images whose sides are powers of two and data-groups of whole 128-pixel tiles. Everything
+// else 3x3 stride 1, 3x3 stride 2 or 1x1 stride 2 comes here. The pixels of a data-group are numbered with a row pitch of Wo + 1 and one
+// extra row above every image, so that each row's padding is the extra column before it and each image's the extra
+// row: a tile is 128 consecutive such positions, dY and X are copied with zeros at the extra ones, and the taps are
+// constant distances (-Q-1 .. Q+1, Q = Wo + 1) with nothing to test in the inner loop. Price: (Ho+1)(Wo+1) / (Ho Wo)
+// of the arithmetic (1.07 at 28 x 28) and two multiply-high divisions per copied row. Otherwise as above: a workgroup owns
+// 64(k) x 64(c) for all taps; S2: one sub-pixel of the input at a time, its taps R', S' in {-1, 0}.
+// Bound, as there, by the barrier and the LDS reads around a tile's MFMAs. 64 -> 64 channels at 14 x 14, 194 images, with
+// 196 workgroups of wgrad_gemm_kernel (operands transposed in registers) 62 us, here 12 us; 32 -> 64 at stride 2 from
+// 28 x 28 42 -> 16 us.
+struct WgradFlatGeom {
+  int cblocks;     // 64-channel blocks of the input tensor
+  int sub[4];      // S2: sub-pixel (dy * 2 + dx) served by blockIdx.y / cblocks
+  int rmap[2][2];  // S2: see WgradGeom
+  int Q;           // position pitch of an image row, Wo + 1
+  int imgs_rep;    // images per data-group
+  int rep_tiles;   // 128-position tiles per data-group
+  int patch_rows;  // 128 + 2Q + 2 (S2: 128 + Q + 1) rounded up to 8
+  Divisor dQ, dH;  // by Q and by Ho + 1
+};
+
+template <bool S2>
+__global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams p, WgradFlatGeom wg) {
+  constexpr int NWV = S2 ? 4 : 12;  // waves: four per tap group, each a 32(k) x 32(c) quarter; stride 1: one group per kernel row
+  constexpr int NT = S2 ? 4 : 3;    // taps accumulated by one wave
+  extern __shared__ __align__(16) char smem[];
+  const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int slot_bytes = 16384 + wg.patch_rows * 128;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = (wave >> 1) & 1;
+  const int tg = wave >> 2;
+  const int by = blockIdx.y, z = blockIdx.z;
+  const int k0 = blockIdx.x * 64;
+  const int sub = S2 ? wg.sub[by / wg.cblocks] : 0;
+  const int sdy = sub >> 1, sdx = sub & 1;
+  const int c0 = (S2 ? by % wg.cblocks : by) * 64;
+  const int q = p.nsplit / p.nrep;
+  const int zr = z / q, zj = z - zr * q;
+  const int tile0 = (int)(((long long)zj * wg.rep_tiles) / q);
+  const int ntiles = (int)(((long long)(zj + 1) * wg.rep_tiles) / q) - tile0;
+
+  const int l8 = lane >> 3;
+  const int c16 = ((lane & 7) ^ ((l8 & 3) << 1)) * 16;  // global 16-byte column for LDS slot lane&7 of a row with row&3 == l8&3
+  const char* zsrc = (const char*)p.zeros + c16;
+  const bool ycol_ok = k0 + (c16 >> 1) < p.ldy, xcol_ok = c0 + (c16 >> 1) < p.Cx;
+  const char* ybase = (const char*)p.dy + (size_t)k0 * 2 + c16;
+  const char* xbase = (const char*)p.x + (size_t)c0 * 2 + c16;
+  const uint32_t ybytes = (uint32_t)p.ldy * 2, xbytes = (uint32_t)p.Cx * 2;
+  const int img0 = zr * wg.imgs_rep;
+  // position in the data-group -> image of the group, row, column of the output grid; false on the extra rows and columns
+  auto locate = [&](int u, int& im, int& h, int& w) {
+    const uint32_t uu = (uint32_t)max(u, 0);
+    const int line = (int)(__umulhi(uu, wg.dQ.mul) >> wg.dQ.shift);
+    w = (int)uu - line * wg.Q;
+    im = (int)(__umulhi((uint32_t)line, wg.dH.mul) >> wg.dH.shift);
+    h = line - im * (p.Ho + 1) - 1;
+    return u >= 0 && w < p.Wo && h >= 0 && im < wg.imgs_rep;
+  };
+  auto fill_tile = [&](int t, int slot) {
+    if (t >= ntiles) return;
+    const int u0 = (tile0 + t) * 128;
+    const uint32_t base = lds_ring + slot * slot_bytes;
+    for (int f = wave; f < 16 + (wg.patch_rows >> 3); f += NWV) {  // 16 fills of dY rows, then the patch: eight rows each
+      int im, h, w;
+      const char* src = zsrc;
+      if (f < 16) {
+        const bool ok = locate(u0 + f * 8 + l8, im, h, w) && ycol_ok;
+        if (ok) src = ybase + (size_t)((uint32_t)(((img0 + im) * p.Ho + h) * p.Wo + w)) * ybytes;
+      } else {
+        bool ok = locate(u0 - wg.Q - 1 + (f - 16) * 8 + l8, im, h, w) && xcol_ok;
+        const int hi = S2 ? 2 * h + sdy : h, wi = S2 ? 2 * w + sdx : w;
+        if (S2) ok = ok && hi < p.H && wi < p.W;
+        if (ok) src = xbase + (size_t)((uint32_t)(((img0 + im) * p.H + hi) * p.W + wi)) * xbytes;
+      }
+      dma16(src, base + f * 1024);
+    }
+  };
+  fill_tile(0, 0);
+
+  // fragment addressing as in wgrad_dma_kernel; the patch row of tile position u at tap (R, S) is u + R Q + S
+  const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;
+  const int rsub = lq >> 2, seg = lq & 3;
+  const int a_c = 4 * wave_m + 2 * grp16 + (seg >> 1);
+  const int a_lane = (8 * khalf + rsub) * 128 + ((a_c ^ (rsub << 1)) << 4) + 8 * (seg & 1);
+  const int b_c = 4 * wave_n + 2 * grp16 + (seg >> 1);
+  int baddr[2][NT];
+  bool live[NT];
+  int tapreal[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int toff = S2 ? (t >> 1) * wg.Q + (t & 1) : tg * wg.Q + t;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int row = 8 * khalf + rsub + 4 * hh + toff;
+      baddr[hh][t] = 16384 + row * 128 + ((b_c ^ ((row & 3) << 1)) << 4) + 8 * (seg & 1);
+    }
+    if (S2) {
+      const int rr = wg.rmap[t >> 1][sdy], ss = wg.rmap[t & 1][sdx];
+      live[t] = rr >= 0 && ss >= 0;
+      tapreal[t] = rr * p.S + ss;
+    } else {
+      live[t] = true;
+      tapreal[t] = tg * 3 + t;
+    }
+  }
+  f32x16_t acc[NT], accb;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) accb[e] = 0.f;
+  const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+  const bool idle_wave = k0 + wave_m * 32 >= p.Mout || c0 + wave_n * 32 >= p.Cx;
+  const bool bias_wave = wave_n == 0 && by == 0 && tg == (S2 ? 0 : 1);
+
+  for (int t = 0; t < ntiles; ++t) {
+    wait_vm<0>();
+    wg_barrier();
+    fill_tile(t + 1, (t + 1) & 1);
+    if (idle_wave) continue;
+    const uint32_t base = lds_ring + (t & 1) * slot_bytes;
+    const uint32_t ybuf = base + a_lane;
+    uint32_t bp[2][NT];
+#pragma unroll
+    for (int tap = 0; tap < NT; ++tap) { bp[0][tap] = base + baddr[0][tap]; bp[1][tap] = base + baddr[1][tap]; }
+    uint4 af[2], bf[2][NT];
+    auto load_frags = [&](int ks, int set) {  // 16 positions; fragments of step ks + 1 are read while step ks is multiplied
+      const uint2 a0 = lds_tr16_at(ybuf + ks * 2048), a1 = lds_tr16_at(ybuf + ks * 2048 + 512);
+      af[set] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+#pragma unroll
+      for (int tap = 0; tap < NT; ++tap) {
+        const uint2 b0 = lds_tr16_at(bp[0][tap] + ks * 2048), b1 = lds_tr16_at(bp[1][tap] + ks * 2048);
+        bf[set][tap] = make_uint4(b0.x, b0.y, b1.x, b1.y);
+      }
+    };
+    load_frags(0, 0);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      if (ks + 1 < 8) load_frags(ks + 1, (ks + 1) & 1);
+#pragma unroll
+      for (int tap = 0; tap < NT; ++tap)
+        if (!S2 || live[tap]) mfma16B<bf16_t>(af[ks & 1], bf[ks & 1][tap], acc[tap]);
+      if (bias_wave) mfma16B<bf16_t>(af[ks & 1], ones, accb);  // bias gradient: column sums of dY
+    }
+  }
+  wait_vm<0>();
+
+  float* out = p.partial + (size_t)z * p.Pl;
+  const int cin = c0 + wave_n * 32 + (lane & 31);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int k = k0 + wave_m * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    if (k >= p.Mout) continue;
+    if (cin < p.Cx) {
+#pragma unroll
+      for (int tap = 0; tap < NT; ++tap)
+        if (live[tap]) out[(size_t)k * p.NK + tapreal[tap] * p.Cx + cin] = p.alpha * acc[tap][e];
+    }
+    if (bias_wave && (lane & 31) == 0) out[(size_t)p.Mout * p.NK + k] = p.alpha * accb[e];
+  }
+}
+
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // Problem of data-group r alone (see ConvParams::nrep): its images, outputs and weights.
@@ -1494,6 +1660,60 @@ bool wgrad_dma_eligible(const WgradParams& p, int* nsub_out, int* cblocks_out, i
   return true;
 }
 
+// Sub-pixels of a stride-2 layer in launch order and the real tap of (virtual tap, sub-pixel offset):
+// 3x3 pad 1: rows 2oy-1, 2oy, 2oy+1; 1x1 pad 0: row 2oy
+int wgrad_s2_taps(int R, int (&sub)[4], int (&rmap)[2][2]) {
+  if (R == 3) { rmap[0][0] = -1; rmap[0][1] = 0; rmap[1][0] = 1; rmap[1][1] = 2; }
+  else { rmap[0][0] = -1; rmap[0][1] = -1; rmap[1][0] = 0; rmap[1][1] = -1; }
+  int nsub = 0;
+  // heaviest sub-pixels first: (1,1) accumulates four taps, (0,0) one
+  for (int s = 3; s >= 0; --s) {
+    const int dy = s >> 1, dx = s & 1;
+    const bool any_r = rmap[0][dy] >= 0 || rmap[1][dy] >= 0, any_s = rmap[0][dx] >= 0 || rmap[1][dx] >= 0;
+    if (any_r && any_s) sub[nsub++] = s;
+  }
+  return nsub;
+}
+
+// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size; nsplit and the pointers are not looked at.
+bool wgrad_flat_geometry(const WgradParams& p, int W, WgradFlatGeom& wg, int& nsub) {
+  const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
+  const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
+                  p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2;
+  if ((!s1 && !s2) || W < 1 || p.Nimg % W != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return false;
+  if (p.zeros == nullptr) return false;
+  wg.cblocks = cdiv(p.Cx, 64);
+  wg.Q = p.Wo + 1;
+  wg.imgs_rep = p.Nimg / W;
+  const long long positions = (long long)wg.imgs_rep * (p.Ho + 1) * wg.Q;
+  if (positions + 128 + 2 * wg.Q >= (1ll << 31) || (long long)p.Nimg * p.H * p.W >= (1ll << 31)) return false;
+  wg.rep_tiles = (int)((positions + 127) / 128);
+  wg.patch_rows = (128 + (s2 ? wg.Q + 1 : 2 * wg.Q + 2) + 7) / 8 * 8;
+  if (2 * (16384 + wg.patch_rows * 128) > 160 * 1024) return false;  // rows of at most 180 (stride 2: 360) pixels
+  wg.dQ = make_divisor(wg.Q);
+  wg.dH = make_divisor(p.Ho + 1);
+  nsub = s2 ? wgrad_s2_taps(p.R, wg.sub, wg.rmap) : 1;
+  return true;
+}
+
+bool launch_wgrad_flat(const WgradParams& p, hipStream_t s) {
+  WgradFlatGeom wg{};
+  int nsub = 1;
+  if (p.nrep < 1 || p.nsplit % p.nrep != 0 || !wgrad_flat_geometry(p, p.nrep, wg, nsub)) return false;
+  if (p.nsplit / p.nrep > wg.rep_tiles) return false;  // no empty split
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)wgrad_flat_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)wgrad_flat_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    attr_set = true;
+  }
+  const int smem = 2 * (16384 + wg.patch_rows * 128);
+  dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
+  if (p.stride == 2) wgrad_flat_kernel<true><<<grid, 256, smem, s>>>(p, wg);
+  else wgrad_flat_kernel<false><<<grid, 768, smem, s>>>(p, wg);
+  return true;
+}
+
 bool launch_wgrad_dma(const WgradParams& p, hipStream_t s) {
   int nsub_e, cblocks, lw, th_log, tiles_h;
   if (!wgrad_dma_eligible(p, &nsub_e, &cblocks, &lw, &th_log, &tiles_h)) return false;
@@ -1503,18 +1723,7 @@ bool launch_wgrad_dma(const WgradParams& p, hipStream_t s) {
   wg.cblocks = cblocks;
   wg.xcd_remap = p.nsplit % 8 == 0 ? 1 : 0;
   int nsub = 1;
-  if (s2) {
-    // real tap for (virtual tap, sub-pixel offset): 3x3 pad 1: rows 2oy-1, 2oy, 2oy+1; 1x1 pad 0: row 2oy
-    if (p.R == 3) { wg.rmap[0][0] = -1; wg.rmap[0][1] = 0; wg.rmap[1][0] = 1; wg.rmap[1][1] = 2; }
-    else { wg.rmap[0][0] = -1; wg.rmap[0][1] = -1; wg.rmap[1][0] = 0; wg.rmap[1][1] = -1; }
-    nsub = 0;
-    // heaviest sub-pixels first: (1,1) accumulates four taps, (0,0) one
-    for (int sub = 3; sub >= 0; --sub) {
-      const int dy = sub >> 1, dx = sub & 1;
-      const bool any_r = wg.rmap[0][dy] >= 0 || wg.rmap[1][dy] >= 0, any_s = wg.rmap[0][dx] >= 0 || wg.rmap[1][dx] >= 0;
-      if (any_r && any_s) wg.sub[nsub++] = sub;
-    }
-  }
+  if (s2) nsub = wgrad_s2_taps(p.R, wg.sub, wg.rmap);
 #define DDS_WG_CASE(TWL, THL)                                                        \
   if (lw == TWL && th_log == THL) {                                                  \
     if (s2) launch_wgrad_dma_inst<TWL, THL, true>(p, wg, nsub, s);                   \
@@ -1530,7 +1739,7 @@ template <typename T>
 int launch_wgrad_t(const WgradParams& p, hipStream_t s) {
   constexpr int CE = 16 / sizeof(T);
   if (sizeof(T) == 2 && launch_wgrad_narrow(p, s)) return 1;
-  if (sizeof(T) == 2 && launch_wgrad_dma(p, s)) return 1;
+  if (sizeof(T) == 2 && (launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s))) return 1;
   if (p.Mout <= 64 && p.NK + CE <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
     wgrad_gemm_kernel<T, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
@@ -1569,10 +1778,12 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
     WgradParams probe = shape;
     probe.nsplit = W;
     probe.nrep = W;
-    int nsub = 0, cblocks = 0;
-    if (wgrad_dma_eligible(probe, &nsub, &cblocks)) {
+    WgradFlatGeom flat{};
+    int nsub = 0, cblocks = 0, rep_tiles = 0;
+    if (wgrad_dma_eligible(probe, &nsub, &cblocks)) rep_tiles = per_replica / 128;
+    else if (wgrad_flat_geometry(probe, W, flat, nsub)) { cblocks = flat.cblocks; rep_tiles = flat.rep_tiles; }
+    if (rep_tiles > 0) {
       const int blocks = cdiv(Mout, 64) * nsub * cblocks;
-      const int rep_tiles = per_replica / 128;
       // a stride-2 workgroup has four waves where a stride-1 one has twelve, and the four sub-pixels of a 3x3
       // kernel carry 4 : 2 : 2 : 1 taps: twice the workgroups (2.24 ms per ResNet-18 step; 2.26 with one or four times)
       if (shape.stride == 2) target_wgs *= 2;
@@ -1580,8 +1791,7 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
       if (q > rep_tiles) q = rep_tiles;
       if (q * W > 256) q = 256 / W;
       if (q < 1) q = 1;
-      probe.nsplit = W * q;
-      if (wgrad_dma_eligible(probe, &nsub, &cblocks)) return W * q;  // the launch will take the same decision
+      return W * q;  // the launch takes the same decision
     }
   }
   const int ce = dtype_ce(dt);

@@ -83,3 +83,21 @@ def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
     # images whose rows and planes are no power of two, tiles that hold many images or end inside one, patches on both
     # sides of the most rows a launch can fetch (W = 47 / 95 / 159)
     _compare(_conv_chain(precision, widths, h, w, W, B), seed=26, T=2, every_step=precision == "f32", tiny=precision == "f32")
+
+
+def _stride2_net(c1, c2, k, h, w, W, B):
+    ops = [{"op": "conv", "cin": 3, "cout": c1, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
+           {"op": "conv", "cin": c1, "cout": c2, "k": k, "stride": 2, "pad": k // 2}, {"op": "relu"},
+           {"op": "conv", "cin": c2, "cout": c2, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": c2, "cout": 10}, {"op": "softmax_ce"}]
+    return Workload(name=f"stride2_k{k}_{h}x{w}", ops=ops, bounds=[0, len(ops)], K=1, W=W, B=B, in_shape=(3, h, w), classes=10,
+                    precision="bf16", lr=0.05, momentum=0.0, steps=2)
+
+
+@pytest.mark.parametrize("c1,c2,k,h,w,W,B", [
+    (16, 32, 3, 7, 9, 2, 3), (24, 72, 3, 14, 13, 1, 9), (64, 64, 1, 11, 6, 3, 5), (64, 128, 3, 8, 8, 2, 9),
+    (32, 64, 3, 28, 30, 1, 3), (72, 136, 3, 3, 2, 2, 65), (8, 8, 1, 1, 5, 2, 30), (16, 16, 3, 2, 178, 1, 1)])
+def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
+    # odd sides, batches that are no whole 128-pixel tiles, channel counts off the 64-channel blocks, a single image
+    # row, data-groups of less than a tile, the longest rows
+    _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
