@@ -101,3 +101,10 @@ def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     # odd sides, batches that are no whole 128-pixel tiles, channel counts off the 64-channel blocks, a single image
     # row, data-groups of less than a tile, the longest rows
     _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
+
+
+@pytest.mark.parametrize("name,B,steps", [("paper_r20_S1K1", 194, 20), ("paper_r20_S1K1", 7, 40)])
+def test_single_module_beside_its_weight_gradients_is_bit_identical(name, B, steps):
+    # one module: weight gradients on a stream of their own, against everything on the caller's stream
+    from test_gpu_limits import test_run_ahead_across_iterations_is_bit_identical_to_serial_execution as compare
+    compare(name, B, steps)
