@@ -607,18 +607,21 @@ struct DmaGeom {
   Divisor dW, dH;
 };
 
-template <typename T, int BM, int BN, int WM, int WN, int PS, int KB>
+// RES (one channel chunk only): the weights of all nine taps are resident beside the patch, so everything is requested
+// at once and the taps run without a barrier between them.
+template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) == 4 ? 2 : 1) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
   constexpr int NW = (BM / WM) * (BN / WN);  // waves per workgroup (each owns a WM x WN sub-tile)
   constexpr int FROWS = 1024 / KB;     // LDS rows per wave fill (KB = bytes of channels per row: 64 or 128)
   constexpr int CPR = KB / 16;         // 16-byte columns per row
-  constexpr int WL = BN / FROWS / NW;   // weight fills per lane per stage
+  constexpr int RG = BN / FROWS;       // fills of a weight tile (one tap, one chunk)
+  constexpr int WL = RG >= NW ? RG / NW : 1;  // weight fills per lane per stage
   constexpr int NKS = KB / 32;         // MFMA k-steps per stage
   constexpr int RPL = KB == 128 ? 1 : 2;  // log2(rows per 256 bytes of LDS)
   static_assert(KB == 64 || KB == 128, "row depth");
-  static_assert(WL >= 1, "weight tile smaller than one fill per wave");
+  static_assert(RES ? PS == 0 && (RG >= NW || (RG % 2 == 0 && NW % RG == 0)) : RG >= NW, "fills of a weight tile per wave");
   constexpr int NI = WM / 32, NJ = WN / 32;
   static_assert(NW == 4 || NW == 8, "four or eight waves");
   extern __shared__ __align__(16) char smem[];
@@ -669,7 +672,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   uint32_t wvo[WL];
 #pragma unroll
   for (int u = 0; u < WL; ++u) {
-    const int gn = n0 + (wave + NW * u) * FROWS + l8;
+    const int gn = n0 + (wave % RG + NW * u) * FROWS + l8;
     wvo[u] = (uint32_t)(gn < p.Nout ? gn : p.Nout - 1) * (uint32_t)(9 * pixbytes) + c16;
   }
   auto fill_w = [&](int chunk, int tap, int slot) {
@@ -698,8 +701,19 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 #pragma unroll
   for (int j = 0; j < NPRO; ++j)
     if (wave + NW * j < pw_total) dma16s(pbase, poff[j], patch_dst(j, 0));
-  fill_w(0, 0, 0);
-  fill_w(0, 1, 1);
+  if (!RES) {
+    fill_w(0, 0, 0);
+    fill_w(0, 1, 1);
+  } else if (RG >= NW) {
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) fill_w(0, tap, tap);
+  } else {  // a tile is less than a fill per wave: the waves take the fills of consecutive taps
+#pragma unroll
+    for (int u = 0; u < (9 * RG + NW - 1) / NW; ++u) {
+      const int f = wave + NW * u;
+      if (f < 9 * RG) dma16s((const char*)p.w + (size_t)(f / RG) * pixbytes, wvo[0], lds_wring + f * 1024);
+    }
+  }
 
   // fragment addressing
   const int half = lane >> 5;
@@ -797,6 +811,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 
   address(0, 0, 0);
 
+  if (RES) {
+    wait_vm<0>();
+    wg_barrier();
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      compute(tap);
+      if (tap < 8) address(0, (tap + 1) / 3, (tap + 1) % 3);
+    }
+  } else
   for (int chunk = 0; chunk < nchunks; ++chunk) {
     DDS_STAGE(0) DDS_STAGE(1) DDS_STAGE(2) DDS_STAGE(3) DDS_STAGE(4) DDS_STAGE(5) DDS_STAGE(6) DDS_STAGE(7) DDS_STAGE(8)
   }
@@ -874,7 +897,7 @@ inline int ilog2_exact(int v) {
   return (1 << l) == v ? l : -1;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int PS, int KB>
+template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false>
 bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   constexpr int FROWS = 1024 / KB;
   constexpr int NW = (BM / WM) * (BN / WN);
@@ -888,7 +911,7 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   const int fills_per_wave = (g.patch_rows / FROWS + NW - 1) / NW;
   if (fills_per_wave > ((KB == 128 && PS == 0) ? 11 : 7)) return false;  // patch offsets kept per lane
   if (PS == 0 ? nchunks != 1 : (nchunks < 2 || 7 * PS < fills_per_wave)) return false;
-  int operands = (PS > 0 ? 2 : 1) * g.patch_rows * KB + 3 * BN * KB;
+  int operands = (PS > 0 ? 2 : 1) * g.patch_rows * KB + (RES ? 9 : 3) * BN * KB;
   constexpr int tile = BM * BN * (int)sizeof(T);  // the output tile is staged where the operands were, if two workgroups still fit a CU
   if (operands < tile && tile <= 72 * 1024) operands = tile;
   g.out_bytes = operands;
@@ -896,11 +919,11 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   if (smem > 160 * 1024) return false;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
   dim3 grid((p.M + BM - 1) / BM, (p.ldy + BN - 1) / BN);
-  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB><<<grid, 64 * NW, smem, s>>>(p, g);
+  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES><<<grid, 64 * NW, smem, s>>>(p, g);
   return true;
 }
 
@@ -919,9 +942,19 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
   const int rowbytes = p.Cx * (int)sizeof(T);
   if (rowbytes % KB != 0 || rowbytes > (1 << 20)) return false;
   const int nchunks = rowbytes / KB;
+  // At most 32 output channels of one chunk: 32-column tiles (a 64-column tile multiplies and stores half padding) of 128
+  // pixels with all weights resident, four workgroups a CU. 32 -> 32 channels at 16 x 16, bf16, alone: 256 images
+  // 21.5 -> 14.0 us, 194 images 9.8 -> 5.4 us (256-pixel tiles: 14.2 us and 776 workgroups 11.9 against 11.5 us).
+  if (p.ldy <= 32 && rowbytes == 128 && launch_dma_inst<T, 128, 32, 32, 32, 0, 128, true>(p, s)) return true;
+  if (p.ldy <= 32 && nchunks == 1 && launch_dma_inst<T, 128, 32, 32, 32, 0, KB, true>(p, s)) return true;
   // 64 bf16 (32 fp32) channels in and at most 64 out: one 128-byte chunk, i.e. whole cache lines per patch row,
-  // nine stages instead of eighteen and the whole patch requested in the prologue (62.0 -> 59.4 us at 32 x 32 x 64)
-  if (rowbytes == 128 && p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, s)) return true;
+  // nine stages instead of eighteen and the whole patch requested in the prologue (62.0 -> 59.4 us at 32 x 32 x 64).
+  // Resident weights take 74 KB, one workgroup per CU: for launches that give no CU a second one (64 -> 64 channels at
+  // 8 x 8, 194 images: 11.2 -> 5.5 us; with 776 workgroups 16.4 us against 10.5 us for the 256-pixel tiles).
+  if (rowbytes == 128 && p.ldy <= 64) {
+    if (p.M <= 64 * 256 && launch_dma_inst<T, 64, 64, 32, 32, 0, 128, true>(p, s)) return true;
+    if (launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, s)) return true;
+  }
   if (nchunks == 1) {
     if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
     return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
