@@ -588,6 +588,83 @@ __device__ __forceinline__ void dma16s(const void* gbase_uniform, uint32_t goff,
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// End of a workgroup of the asynchronous kernels: every copy has landed in this wave, acc holds its WM x WN tile.
+// The residual / mask tiles are staged in the first `room` bytes of LDS (the operand buffers are free now) so that the
+// epilogue pays one global round trip instead of one per 32-pixel column, and the output tile leaves from there in
+// whole rows. The 1 KiB behind them holds alpha * bias. pixel(row): output pixel of a tile row, -1 past the end.
+template <typename T, int BM, int BN, int WM, int WN, typename Pixel>
+__device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&acc)[WN / 32][WM / 32],
+                                         const uint32_t (&mb)[WM / 32][WN / 32], char* smem, int room, int n0, int wave,
+                                         int wave_m, int wave_n, int lane, int lpix, Pixel pixel) {
+  constexpr int ES = sizeof(T);
+  constexpr int NW = (BM / WM) * (BN / WN), NI = WM / 32, NJ = WN / 32;
+  constexpr int ROWB = BN * ES;        // bytes per tile row
+  constexpr int NCOL = ROWB / 16;      // 16-byte columns per row
+  constexpr int RPF = 64 / NCOL;       // rows per wave fill
+  constexpr int FPW = BM / RPF / NW;    // fills per wave
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  int res_off = -1, mask_off = -1, nregions = 0;
+  const int ab_off = room;
+  float* ab_lds = (float*)(smem + ab_off);
+  wg_barrier();
+  if ((int)threadIdx.x < BN) {
+    const int n = n0 + threadIdx.x;
+    ab_lds[threadIdx.x] = (p.bias != nullptr && n < p.Nout) ? p.alpha * p.bias[n] : 0.f;
+  }
+  if (p.res || p.mask) {
+    int region = 0;
+    auto stage_tile = [&](const void* src_tensor) -> int {
+      if ((region + 1) * BM * ROWB > room) return -1;
+      const int rbase = region * BM * ROWB;
+#pragma unroll
+      for (int u = 0; u < FPW; ++u) {
+        const int f = wave + NW * u;
+        const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
+        const int gc = (slot ^ row) & (NCOL - 1);
+        const int n = n0 + gc * (16 / ES);
+        const int pix = pixel(row);
+        const bool ok = pix >= 0 && n < p.ldy;
+        const char* src = ok ? (const char*)src_tensor + ((size_t)pix * p.ldy + n) * ES : (const char*)p.zeros;
+        dma16(src, lds0 + rbase + f * 1024);
+      }
+      ++region;
+      return rbase;
+    };
+    if (p.mask) mask_off = stage_tile(p.mask);
+    if (p.res) res_off = stage_tile(p.res);
+    wait_vm<0>();
+    nregions = region;
+  }
+  // Output tile in LDS: the residual tile's bytes if there is one, else the next free region.
+  int out_off = res_off >= 0 ? res_off : ((nregions + 1) * BM * ROWB <= room ? nregions * BM * ROWB : -1);
+  if (p.out_f32) out_off = -1;
+  __syncthreads();  // also orders the plain LDS stores of alpha * bias
+
+  const int nb = n0 + wave_n * WN + 4 * (lane >> 5);
+  float bias[NJ][4][4] = {};
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int m = wave_m * WM + i * 32 + lpix;
+    const int pix = pixel(m);
+    epilogue_tile<T, NJ, NI>(p, acc, i, pix >= 0, (size_t)max(pix, 0), nb, bias, (const char DDS_LDS_AS*)smem, res_off, mask_off, m, ROWB,
+                             wave_n * WN + 4 * (lane >> 5), ab_off, mb[i], out_off);
+  }
+  if (out_off >= 0) {
+    // write the tile out: a wave stores RPF whole tile rows per instruction, 16 bytes per lane
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < FPW; ++u) {
+      const int f = wave + NW * u;
+      const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
+      const int gc = (slot ^ row) & (NCOL - 1);
+      const int n = n0 + gc * (16 / ES);
+      const int pix = pixel(row);
+      const u32x4_t v = *(const u32x4_t DDS_LDS_AS*)((const char DDS_LDS_AS*)smem + out_off + f * 1024 + lane * 16);
+      if (pix >= 0 && n < p.ldy) *(u32x4_t*)((char*)p.y + ((size_t)pix * p.ldy + n) * ES) = v;
+    }
+  }
+}
+
 // floor(n / d) == __umulhi(n, mul) >> shift for 0 <= n < 2^31: mul = floor(2^(31+l) / d) + 1 with 2^(l-1) < d <= 2^l
 // exceeds 2^(31+l) / d by at most 2^l / d, which the division of a 31-bit n never sees
 struct Divisor {
@@ -826,69 +903,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 #undef DDS_STAGE
   wait_vm<0>();
 
-  // Stage the residual / mask tiles of this workgroup in LDS (the operand buffers are free
-  // now) so the epilogue pays one global round trip instead of one per 32-pixel column.
-  constexpr int ROWB = BN * ES;        // bytes per tile row
-  constexpr int NCOL = ROWB / 16;      // 16-byte columns per row
-  constexpr int RPF = 64 / NCOL;       // rows per wave fill
-  constexpr int FPW = BM / RPF / NW;    // fills per wave
-  int res_off = -1, mask_off = -1, nregions = 0;
-  const int ab_off = g.out_bytes;  // the dump block now holds alpha * bias of this tile's channels
-  float* ab_lds = (float*)(smem + ab_off);
-  wg_barrier();
-  if (tid < BN) {
-    const int n = n0 + tid;
-    ab_lds[tid] = (p.bias != nullptr && n < p.Nout) ? p.alpha * p.bias[n] : 0.f;
-  }
-  if (p.res || p.mask) {
-    int region = 0;
-    auto stage_tile = [&](const void* src_tensor) -> int {
-      if ((region + 1) * BM * ROWB > g.out_bytes) return -1;
-      const int rbase = region * BM * ROWB;
-#pragma unroll
-      for (int u = 0; u < FPW; ++u) {
-        const int f = wave + NW * u;
-        const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
-        const int gc = (slot ^ row) & (NCOL - 1);
-        const int n = n0 + gc * (16 / ES);
-        const bool ok = m0 + row < p.M && n < p.ldy;
-        const char* src = ok ? (const char*)src_tensor + ((size_t)(m0 + row) * p.ldy + n) * ES : (const char*)p.zeros;
-        dma16(src, lds0 + rbase + f * 1024);
-      }
-      ++region;
-      return rbase;
-    };
-    if (p.mask) mask_off = stage_tile(p.mask);
-    if (p.res) res_off = stage_tile(p.res);
-    wait_vm<0>();
-    nregions = region;
-  }
-  // Output tile in LDS: the residual tile's bytes if there is one, else the next free region.
-  int out_off = res_off >= 0 ? res_off : ((nregions + 1) * BM * ROWB <= g.out_bytes ? nregions * BM * ROWB : -1);
-  if (p.out_f32) out_off = -1;
-  __syncthreads();  // also orders the plain LDS stores of alpha * bias
-
-  const int nb = n0 + wave_n * WN + 4 * (lane >> 5);
-  float bias[NJ][4][4] = {};
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int m = wave_m * WM + i * 32 + lpix;
-    epilogue_tile<T, NJ, NI>(p, acc, i, m0 + m < p.M, (size_t)(m0 + m), nb, bias, (const char DDS_LDS_AS*)smem, res_off, mask_off, m, ROWB,
-                             wave_n * WN + 4 * (lane >> 5), ab_off, mb[i], out_off);
-  }
-  if (out_off >= 0) {
-    // write the tile out: a wave stores RPF whole tile rows per instruction, 16 bytes per lane
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < FPW; ++u) {
-      const int f = wave + NW * u;
-      const int row = f * RPF + lane / NCOL, slot = lane % NCOL;
-      const int gc = (slot ^ row) & (NCOL - 1);
-      const int n = n0 + gc * (16 / ES);
-      const u32x4_t v = *(const u32x4_t DDS_LDS_AS*)((const char DDS_LDS_AS*)smem + out_off + f * 1024 + lane * 16);
-      if (m0 + row < p.M && n < p.ldy) *(u32x4_t*)((char*)p.y + ((size_t)(m0 + row) * p.ldy + n) * ES) = v;
-    }
-  }
+  const auto pixel = [&](int row) { return m0 + row < p.M ? m0 + row : -1; };
+  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel);
 }
 
 inline int ilog2_exact(int v) {
@@ -968,6 +984,225 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
     if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
   }
   return launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, s);
+}
+
+// ------------------------------------------------------------------ any other convolution with whole 64-byte channel chunks
+// Strided, 1x1 and stride-2 input-gradient launches: the same implicit GEMM as conv_gemm_kernel, its operands copied
+// global -> LDS as in conv3x3_dma_kernel. A stage is one (tap, 64-byte channel chunk): BM gathered pixels (zeros where
+// the tap leaves the image) and BN weight rows, two stages ahead in three slots. Which pixel a tile row is, and where
+// its taps start, is worked out once per workgroup into a table in LDS.
+// S2 (dgrad of a stride-2 layer): output pixels are dealt to workgroups by parity class (h % 2, w % 2), blockIdx.x =
+// class * tiles_per_class + tile, the class with the most taps first; a class walks only the taps of its parity (4, 2, 2 and 1 of
+// nine), class (0, 0) also a folded 1x1 shortcut (x2, w2).
+// Bound by the copies and the barrier of short reductions. Alone against conv_gemm_kernel (operands staged through
+// registers, outputs stored 8 bytes at a time), ResNet-18 shapes, 512 images: input gradients of the stride-2 layers
+// 91 / 67 / 71 -> 54 / 42 / 46 us, their forward passes with the 1x1 shortcuts 50 / 40 / 58 -> 40 / 33 / 39 us.
+struct GatherGeom {
+  int tiles_per_class;
+  int out_bytes;  // bytes of LDS below the row table: operand slots, then the epilogue's tiles
+};
+
+template <typename T, int BM, int BN, int WM, int WN, bool S2>
+__global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, GatherGeom g) {
+  ConvParams p = p_;
+  constexpr int ES = sizeof(T);
+  constexpr int KB = 64, FROWS = 16, CPR = 4, NKS = 2;  // bytes of a row, rows of a 1 KiB fill, 16-byte columns, k-steps
+  constexpr int AP = BM / FROWS / 4;                     // fills per wave and stage: gathered rows ...
+  constexpr int RG = BN / FROWS, WL = RG >= 4 ? RG / 4 : 1;  // ... and weight rows (two waves copy the same ones if RG < 4)
+  constexpr int SLOT = (BM + BN) * KB;
+  constexpr int NI = WM / 32, NJ = WN / 32;
+  static_assert((BM / WM) * (BN / WN) == 4, "four waves");
+  static_assert(AP >= 1 && (RG >= 4 || RG == 2), "fills per wave");
+  extern __shared__ __align__(16) char smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  int* rowpix = (int*)(smem + g.out_bytes + 1024);  // output pixel of a tile row, -1 past the end
+  int2* rowsrc = (int2*)(rowpix + BM);               // pixel of x at tap offset (0, 0); its row << 16 | column, signed
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave % (BM / WM), wave_n = wave / (BM / WM);
+  const int cls = S2 ? 3 - (int)blockIdx.x / g.tiles_per_class : 0;
+  const int ch = cls >> 1, cw = cls & 1;
+  const int Hc = S2 ? (p.Ho - ch + 1) >> 1 : p.Ho, Wc = S2 ? (p.Wo - cw + 1) >> 1 : p.Wo;  // this class's output grid
+  const int Mc = p.Nimg * Hc * Wc;
+  const int m0 = (S2 ? (int)blockIdx.x - (3 - cls) * g.tiles_per_class : (int)blockIdx.x) * BM, n0 = blockIdx.y * BN;
+  if (m0 >= Mc) return;  // the classes of an odd-sized grid differ
+  if (p.nrep > 1) {  // the launcher made sure that a tile never straddles two data-groups
+    const int r = min(m0 / (Mc / p.nrep), p.nrep - 1);
+    p.w = (const char*)p.w + (size_t)r * p.w_rep;
+    if (p.bias) p.bias += (size_t)r * p.bias_rep;
+    if (p.w2) p.w2 = (const char*)p.w2 + (size_t)r * p.w2_rep;
+  }
+  if (tid < BM) {
+    const int m = min(m0 + tid, Mc - 1);
+    const int line = m / Wc, ow = m - line * Wc;
+    const int img = line / Hc, oh = line - img * Hc;
+    const int h = S2 ? oh : p.dgrad ? oh + p.pad : oh * p.stride - p.pad;
+    const int w = S2 ? ow : p.dgrad ? ow + p.pad : ow * p.stride - p.pad;
+    const int pix = S2 ? (img * p.Ho + 2 * oh + ch) * p.Wo + 2 * ow + cw : m;
+    rowpix[tid] = m0 + tid < Mc ? pix : -1;
+    rowsrc[tid] = make_int2((img * p.H + h) * p.W + w, (int)((uint32_t)h << 16 | (uint32_t)(w & 0xffff)));
+  }
+  __syncthreads();
+
+  const int l4 = lane >> 2;
+  const uint32_t c16 = (uint32_t)(((lane & 3) ^ ((l4 >> 2) & 3)) * 16);  // column c of row r lives at c ^ (r / 4) % 4
+  int a_pix[AP], a_h[AP], a_w[AP];
+#pragma unroll
+  for (int j = 0; j < AP; ++j) {
+    const int2 t = rowsrc[(wave + 4 * j) * FROWS + l4];
+    a_pix[j] = t.x;
+    a_h[j] = t.y >> 16;
+    a_w[j] = (int)(int16_t)(t.y & 0xffff);
+  }
+  const char* zsrc = (const char*)p.zeros + c16;
+  // weight rows past Nout repeat the last one: their columns are never stored
+  uint32_t wvo[WL], wvo2[S2 ? WL : 1];
+#pragma unroll
+  for (int u = 0; u < WL; ++u) {
+    const int n = min(n0 + (wave % RG + 4 * u) * FROWS + l4, p.Nout - 1);
+    wvo[u] = (uint32_t)n * (uint32_t)(p.Ktot * ES) + c16;
+    if (S2) wvo2[u] = (uint32_t)n * (uint32_t)(p.Cx2 * ES) + c16;
+  }
+  const int pixbytes = p.Cx * ES;
+  const int nchunks = pixbytes / KB;
+  // taps of this launch or class: r = r0, r0 + step, ...; likewise s
+  const int step = S2 ? 2 : 1;
+  const int r0 = S2 ? (ch + p.pad) & 1 : 0, s0 = S2 ? (cw + p.pad) & 1 : 0;
+  const int ntr = p.R > r0 ? (p.R - r0 + step - 1) / step : 0, nts = p.S > s0 ? (p.S - s0 + step - 1) / step : 0;
+  const int nk1 = ntr * nts * nchunks;  // stages of the layer itself; a folded shortcut's follow
+  const int nk = nk1 + (S2 && p.x2 != nullptr && cls == 0 ? p.Cx2 * ES / KB : 0);
+
+  int fr = r0, fs = s0, fc = 0;  // position of the next stage to be copied
+  auto fill = [&](int kt, int slot) {
+    const uint32_t base = lds0 + slot * SLOT;
+    if (S2 && kt >= nk1) {  // the shortcut reads the pixel itself from its own tensor
+      const int off = (kt - nk1) * KB;
+      const char* x = (const char*)p.x2 + off;
+#pragma unroll
+      for (int j = 0; j < AP; ++j)
+        dma16(x + (size_t)(uint32_t)a_pix[j] * (uint32_t)(p.Cx2 * ES) + c16, base + (wave + 4 * j) * 1024);
+#pragma unroll
+      for (int u = 0; u < WL; ++u)
+        dma16s((const char*)p.w2 + off, wvo2[u], base + BM * KB + (wave % RG + 4 * u) * 1024);
+      return;
+    }
+    // distance of the tap in x: forward (r, s), dgrad (-r, -s), S2 (ch + pad - r) / 2
+    const int dr = S2 ? (ch + p.pad - fr) / 2 : p.dgrad ? -fr : fr, ds = S2 ? (cw + p.pad - fs) / 2 : p.dgrad ? -fs : fs;
+    const int dp = dr * p.W + ds;
+    const char* x = (const char*)p.x + fc * KB;
+#pragma unroll
+    for (int j = 0; j < AP; ++j) {
+      const bool ok = (unsigned)(a_h[j] + dr) < (unsigned)p.H && (unsigned)(a_w[j] + ds) < (unsigned)p.W;
+      const char* src = x + (size_t)(uint32_t)(a_pix[j] + dp) * (uint32_t)pixbytes + c16;
+      dma16(ok ? src : zsrc, base + (wave + 4 * j) * 1024);
+    }
+    const char* w = (const char*)p.w + (size_t)(fr * p.S + fs) * pixbytes + fc * KB;
+#pragma unroll
+    for (int u = 0; u < WL; ++u) dma16s(w, wvo[u], base + BM * KB + (wave % RG + 4 * u) * 1024);
+    if (++fc == nchunks) {
+      fc = 0;
+      fs += step;
+      if (fs >= p.S) { fs = s0; fr += step; }
+    }
+  };
+  const int lq = (lane >> 2) & 7;
+  const int lpix = ((__builtin_popcount(lq) & 1) << 4) | ((lq >> 1) << 2) | (lane & 3);  // see conv3x3_dma_kernel
+  const int half = lane >> 5;
+  uint32_t mb[NI][NJ] = {};
+  if (p.maskbits) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int pix = rowpix[wave_m * WM + i * 32 + lpix];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) mb[i][j] = load_bits32(p.maskbits, (size_t)max(pix, 0), p.ldy, n0 + wave_n * WN + 32 * j, pix >= 0);
+    }
+  }
+  if (nk > 0) fill(0, 0);
+  if (nk > 1) fill(1, 1);
+  int aoff[NI], boff[NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int m = wave_m * WM + i * 32 + lpix;
+    aoff[i] = m * KB + ((half ^ ((m >> 2) & 3)) << 4);
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int n = wave_n * WN + j * 32 + (lane & 31);
+    boff[j] = BM * KB + n * KB + ((half ^ ((n >> 2) & 3)) << 4);
+  }
+  f32x16_t acc[NJ][NI];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
+
+  int cur = 0, nxt = 2;  // slots of this stage and of the one two ahead
+  for (int kt = 0; kt < nk; ++kt) {
+    if (kt + 1 < nk) wait_vm<AP + WL>();  // only the next stage's copies are younger
+    else wait_vm<0>();
+    wg_barrier();
+    if (kt + 2 < nk) fill(kt + 2, nxt);
+    const char* sb = smem + cur * SLOT;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      uint4 a[NI], b[NJ];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) a[i] = *(const uint4*)(sb + (aoff[i] ^ (ks << 5)));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) b[j] = *(const uint4*)(sb + (boff[j] ^ (ks << 5)));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) mfma16B<T>(b[j], a[i], acc[j][i]);
+    }
+    cur = cur == 2 ? 0 : cur + 1;
+    nxt = nxt == 2 ? 0 : nxt + 1;
+  }
+  wait_vm<0>();
+  const auto pixel = [&](int row) { return rowpix[row]; };
+  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel);
+}
+
+template <typename T, int BM, int BN, int WM, int WN, bool S2>
+bool launch_gather_inst(const ConvParams& p, hipStream_t s) {
+  GatherGeom g;
+  const int mc = S2 ? p.Nimg * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) : p.M;  // class (0, 0) is the largest
+  g.tiles_per_class = (mc + BM - 1) / BM;
+  constexpr int slots = 3 * (BM + BN) * 64, tile = BM * BN * (int)sizeof(T);
+  g.out_bytes = slots < tile && tile <= 72 * 1024 ? tile : slots;
+  const int smem = g.out_bytes + 1024 + BM * 12;
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)conv_gather_kernel<T, BM, BN, WM, WN, S2>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    attr_set = true;
+  }
+  dim3 grid((S2 ? 4 : 1) * g.tiles_per_class, (p.ldy + BN - 1) / BN);
+  conv_gather_kernel<T, BM, BN, WM, WN, S2><<<grid, 256, smem, s>>>(p, g);
+  return true;
+}
+
+template <typename T, bool S2>
+bool launch_gather_t(const ConvParams& p, hipStream_t s) {
+  if (p.ldy <= 32) return launch_gather_inst<T, 128, 32, 32, 32, S2>(p, s);
+  if (p.ldy <= 64) return launch_gather_inst<T, 128, 64, 64, 32, S2>(p, s);
+  return launch_gather_inst<T, 128, 128, 64, 64, S2>(p, s);
+}
+
+// False: not a launch of conv_gather_kernel, nothing launched.
+template <typename T>
+bool launch_gather(const ConvParams& p, hipStream_t s) {
+  constexpr int KE = 64 / (int)sizeof(T);
+  if (p.Cx % KE != 0 || p.ldy != p.Nout || p.zeros == nullptr || p.R < 1 || p.S < 1) return false;
+  if (p.Ktot != p.R * p.S * p.Cx || p.stride < 1 || p.stride > 2) return false;
+  // table entries hold a row and a column in 16 bits each; pixel numbers, weight offsets and bytes of a pixel are 32-bit
+  if (p.H > 30000 || p.W > 30000 || p.R > 1000 || p.S > 1000) return false;
+  if ((long long)p.Nimg * p.H * p.W >= (1ll << 30) || (long long)p.Nout * p.Ktot * (long long)sizeof(T) >= (1ll << 31)) return false;
+  if (!p.dgrad || p.stride == 1) return p.x2 == nullptr && launch_gather_t<T, false>(p, s);
+  if (p.x2 != nullptr && (p.Cx2 % KE != 0 || (long long)p.Nout * p.Cx2 * (long long)sizeof(T) >= (1ll << 31))) return false;
+  return launch_gather_t<T, true>(p, s);
 }
 
 // ------------------------------------------------------------------ wgrad
@@ -1626,7 +1861,7 @@ int launch_conv_one(const ConvParams& p, hipStream_t s) {
   constexpr int BKB = 64;
   if (p.nrep <= 1 && launch_linear(sizeof(T) == 4 ? DT_F32 : DT_BF16, p, s)) return 0;  // a data-group's slice
   if (sizeof(T) == 2 && launch_conv_narrow(p, s)) return 1;
-  if (launch_dma<T>(p, s)) return 1;
+  if (launch_dma<T>(p, s) || launch_gather<T>(p, s)) return 1;
   // dgrad of a stride-2 convolution: workgroups per parity class (class (0,0) is the largest)
   const bool s2 = p.dgrad && p.stride == 2 && p.Cx % (BKB / (int)sizeof(T)) == 0 &&
                   (p.x2 == nullptr || p.Cx2 % (BKB / (int)sizeof(T)) == 0);
