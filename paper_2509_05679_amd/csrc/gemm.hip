@@ -1209,12 +1209,6 @@ bool launch_gather(const ConvParams& p, hipStream_t s) {
 // 16-byte chunks loaded along the channel axis for CE consecutive pixels are
 // transposed in registers so that LDS rows run along the pixel (reduction) axis.
 template <typename T> __device__ __forceinline__ void transpose_chunks(const uint4* in, uint4* out);
-template <> __device__ __forceinline__ void transpose_chunks<float>(const uint4* in, uint4* out) {
-  out[0] = make_uint4(in[0].x, in[1].x, in[2].x, in[3].x);
-  out[1] = make_uint4(in[0].y, in[1].y, in[2].y, in[3].y);
-  out[2] = make_uint4(in[0].z, in[1].z, in[2].z, in[3].z);
-  out[3] = make_uint4(in[0].w, in[1].w, in[2].w, in[3].w);
-}
 __device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
 __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 template <> __device__ __forceinline__ void transpose_chunks<bf16_t>(const uint4* in, uint4* out) {
@@ -1229,7 +1223,6 @@ template <> __device__ __forceinline__ void transpose_chunks<bf16_t>(const uint4
   out[7] = make_uint4(pack_hi(in[0].w, in[1].w), pack_hi(in[2].w, in[3].w), pack_hi(in[4].w, in[5].w), pack_hi(in[6].w, in[7].w));
 }
 template <typename T> __device__ __forceinline__ uint4 one_chunk();
-template <> __device__ __forceinline__ uint4 one_chunk<float>() { return make_uint4(0x3f800000u, 0, 0, 0); }
 template <> __device__ __forceinline__ uint4 one_chunk<bf16_t>() { return make_uint4(0x3f80u, 0, 0, 0); }
 
 template <typename T, int BM, int BN, int WM, int WN>
@@ -1805,6 +1798,130 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
   }
 }
 
+// ------------------------------------------------------------------ wgrad, fp32
+// partial[z][m][n] = alpha * sum over the pixels of split z of dY[p][m] * X(p; n), n = (tap, c). v_mfma_f32_32x32x2_f32
+// takes one value of one pixel per lane, so both operands are used as they lie in memory: panels of 32 pixels x 32
+// channels, [pixel][128 bytes], copied global -> LDS (two slots), of which 32 consecutive lanes read 32 consecutive channels of a
+// pixel with no conflict and a constant offset per step. Lane l of wave w always copies pixel 8 w + l / 8 of a tile,
+// 16 bytes of one tap per panel: one image position per lane and tile, stepped without a division. Any kernel size,
+// stride, image size and batch; linear layers are the 1x1 case. The bias gradient is summed from the dY operand.
+// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers, the fp32
+// CNN's layers, 512 images, alone: 64 -> 128 channels at 16 x 16 282 -> 226 us, 128 -> 256 at 8 x 8 280 -> 200 us, 256 -> 512 at
+// 4 x 4 233 -> 184 us, the 3-channel stem 157 -> 63 us; the perceptron's 3072 -> 256 layer 11.5 -> 9.6 us.
+struct Wgrad32Geom {
+  int q, rep_tiles;       // splits and 32-pixel tiles per data-group
+  int sw, sh, si;         // 32 pixels = si images + sh rows + sw columns of the output grid
+};
+
+template <int BM, int BN>
+__global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad32Geom g) {
+  constexpr int AP = BM / 32, BP = BN / 32;           // panels
+  constexpr int NI = BM / 64, NJ = BN / 64;           // 32 x 32 blocks of a wave: a quarter of the tile
+  constexpr int SLOT = (AP + BP) * 4096;
+  __shared__ __align__(16) char smem[2 * SLOT];
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = wave >> 1;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, z = blockIdx.z;
+  const int zr = z / g.q, zj = z - zr * g.q;
+  const int rep_pix = p.P / p.nrep;
+  const int tile0 = (int)(((long long)zj * g.rep_tiles) / g.q);
+  const int ntiles = (int)(((long long)(zj + 1) * g.rep_tiles) / g.q) - tile0;
+  const int end = (zr + 1) * rep_pix;  // the group's last tile may be a partial one
+
+  const int l8 = lane >> 3, c4 = (lane & 7) * 4;  // pixel of a fill, first channel of this lane's 16 bytes
+  int pix = zr * rep_pix + tile0 * 32 + wave * 8 + l8;
+  int line = pix / p.Wo, ow = pix - line * p.Wo;
+  int img = line / p.Ho, oh = line - img * p.Ho;
+  bool n_ok[BP];
+  int n_r[BP], n_s[BP], n_off[BP];  // tap and element offset of this lane's columns in every panel
+#pragma unroll
+  for (int b = 0; b < BP; ++b) {
+    const int n = n0 + 32 * b + c4;
+    n_ok[b] = n < p.NK;
+    const int tap = (n_ok[b] ? n : 0) / p.Cx, c = (n_ok[b] ? n : 0) - tap * p.Cx;
+    n_r[b] = tap / p.S;
+    n_s[b] = tap - n_r[b] * p.S;
+    n_off[b] = (n_r[b] * p.W + n_s[b]) * p.Cx + c;
+  }
+  const float* zsrc = (const float*)p.zeros + c4;
+  int filled = 0;
+  auto fill = [&](int slot) {  // the next tile
+    if (filled++ >= ntiles) return;
+    const uint32_t base = lds0 + slot * SLOT + wave * 1024;
+    const bool live = pix < end;
+    const float* dy = (const float*)p.dy + (long long)pix * p.ldy + m0 + c4;
+#pragma unroll
+    for (int a = 0; a < AP; ++a) dma16(live && m0 + 32 * a + c4 < p.ldy ? dy + 32 * a : zsrc, base + a * 4096);
+    const int h = oh * p.stride - p.pad, w = ow * p.stride - p.pad;
+    const float* x = (const float*)p.x + ((long long)(img * p.H + h) * p.W + w) * p.Cx;
+#pragma unroll
+    for (int b = 0; b < BP; ++b) {
+      const bool ok = live && n_ok[b] && (unsigned)(h + n_r[b]) < (unsigned)p.H && (unsigned)(w + n_s[b]) < (unsigned)p.W;
+      dma16(ok ? x + n_off[b] : zsrc, base + (AP + b) * 4096);
+    }
+    pix += 32;
+    ow += g.sw;
+    if (ow >= p.Wo) { ow -= p.Wo; ++oh; }
+    oh += g.sh;
+    if (oh >= p.Ho) { oh -= p.Ho; ++img; }
+    img += g.si;
+  };
+  fill(0);
+
+  const int l32 = (lane >> 5) * 128 + (lane & 31) * 4;  // pixel lane / 32 of a pair, channel lane % 32
+  f32x16_t acc[NI][NJ];
+  float sumb[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    sumb[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  }
+  for (int t = 0; t < ntiles; ++t) {
+    wait_vm<0>();
+    wg_barrier();
+    fill((t + 1) & 1);
+    const char* sa = smem + (t & 1) * SLOT + wave_m * NI * 4096 + l32;
+    const char* sb = smem + (t & 1) * SLOT + (AP + wave_n * NJ) * 4096 + l32;
+#pragma unroll 4
+    for (int ks = 0; ks < 16; ++ks) {
+      float a[NI], b[NJ];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) a[i] = *(const float*)(sa + i * 4096 + ks * 256);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + ks * 256);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        sumb[i] += a[i];
+      }
+    }
+  }
+  wait_vm<0>();
+
+  float* out = p.partial + (size_t)z * p.Pl;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int mb = m0 + (wave_m * NI + i) * 32;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int n = n0 + (wave_n * NJ + j) * 32 + (lane & 31);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = mb + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (m < p.Mout && n < p.NK) out[(size_t)m * p.NK + n] = p.alpha * acc[i][j][e];
+      }
+    }
+    const float s = sumb[i] + __shfl_xor(sumb[i], 32, 64);
+    if (blockIdx.y == 0 && wave_n == 0 && lane < 32 && mb + lane < p.Mout) out[(size_t)p.Mout * p.NK + mb + lane] = p.alpha * s;
+  }
+}
+
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // Problem of data-group r alone (see ConvParams::nrep): its images, outputs and weights.
@@ -2003,20 +2120,38 @@ bool launch_wgrad_dma(const WgradParams& p, hipStream_t s) {
   return false;
 }
 
-template <typename T>
-int launch_wgrad_t(const WgradParams& p, hipStream_t s) {
-  constexpr int CE = 16 / sizeof(T);
-  if (sizeof(T) == 2 && launch_wgrad_narrow(p, s)) return 1;
-  if (sizeof(T) == 2 && (launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s))) return 1;
-  if (p.Mout <= 64 && p.NK + CE <= 128) {  // e.g. the stem: 3 input channels, 9 taps
+// Tile of an fp32 problem: 64 columns for narrow operands, else 128
+inline void wgrad_f32_tile(int Mout, int NK, int& BM, int& BN) {
+  BM = Mout <= 64 ? 64 : 128;
+  BN = Mout <= 64 && NK <= 64 ? 64 : 128;
+}
+
+void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
+  int BM, BN;
+  wgrad_f32_tile(p.Mout, p.NK, BM, BN);
+  Wgrad32Geom g;
+  g.q = p.nsplit / p.nrep;
+  g.rep_tiles = cdiv(p.P / p.nrep, 32);
+  g.sw = 32 % p.Wo;
+  g.sh = 32 / p.Wo % p.Ho;
+  g.si = 32 / p.Wo / p.Ho;
+  dim3 grid(cdiv(p.Mout, BM), cdiv(p.NK, BN), p.nsplit);
+  if (BM == 128) wgrad_f32_kernel<128, 128><<<grid, 256, 0, s>>>(p, g);
+  else if (BN == 128) wgrad_f32_kernel<64, 128><<<grid, 256, 0, s>>>(p, g);
+  else wgrad_f32_kernel<64, 64><<<grid, 256, 0, s>>>(p, g);
+}
+
+int launch_wgrad_bf16(const WgradParams& p, hipStream_t s) {
+  if (launch_wgrad_narrow(p, s) || launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s)) return 1;
+  if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
-    wgrad_gemm_kernel<T, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
+    wgrad_gemm_kernel<bf16_t, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
   } else if (p.Mout <= 64) {
-    dim3 grid(cdiv(p.Mout, 64), cdiv(p.NK + CE, 256), p.nsplit);
-    wgrad_gemm_kernel<T, 64, 256, 64, 64><<<grid, 256, 0, s>>>(p);
+    dim3 grid(cdiv(p.Mout, 64), cdiv(p.NK + 8, 256), p.nsplit);
+    wgrad_gemm_kernel<bf16_t, 64, 256, 64, 64><<<grid, 256, 0, s>>>(p);
   } else {
-    dim3 grid(cdiv(p.Mout, 128), cdiv(p.NK + CE, 128), p.nsplit);
-    wgrad_gemm_kernel<T, 128, 128, 64, 64><<<grid, 256, 0, s>>>(p);
+    dim3 grid(cdiv(p.Mout, 128), cdiv(p.NK + 8, 128), p.nsplit);
+    wgrad_gemm_kernel<bf16_t, 128, 128, 64, 64><<<grid, 256, 0, s>>>(p);
   }
   return 0;
 }
@@ -2028,7 +2163,9 @@ int launch_conv(int dt, const ConvParams& p, hipStream_t s) {
 }
 
 int launch_wgrad(int dt, const WgradParams& p, hipStream_t s) {
-  return dt == DT_F32 ? launch_wgrad_t<float>(p, s) : launch_wgrad_t<bf16_t>(p, s);
+  if (dt != DT_F32) return launch_wgrad_bf16(p, s);
+  launch_wgrad_f32(p, s);
+  return 1;
 }
 
 int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) {
@@ -2062,11 +2199,20 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
       return W * q;  // the launch takes the same decision
     }
   }
-  const int ce = dtype_ce(dt);
-  const int bke = 128 / dtype_size(dt);
-  int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + ce, 256) : cdiv(Mout, 128) * cdiv(NK + ce, 128);
-  int q = cdiv(1024, tiles * W);  // aim at ~1024 workgroups (512 and 256 measured slower on the fp32 CNN: 2.33-2.35 vs 2.25 ms)
-  int qmax = per_replica / (2 * bke);  // at least two k-tiles per split
+  if (dt == DT_F32) {
+    // aim at two workgroups per CU (1024 / 512 / 256 workgroups: 14.36 / 14.36 / 14.32 ms for 8 steps of the fp32 CNN; the
+    // fewer splits, the fewer partial sums to write and read), at least two 32-pixel tiles each
+    int BM, BN;
+    wgrad_f32_tile(Mout, NK, BM, BN);
+    int q = cdiv(512, cdiv(Mout, BM) * cdiv(NK, BN) * W);
+    const int qmax = cdiv(per_replica, 64);
+    if (q > qmax) q = qmax;
+    if (q * W > 256) q = 256 / W;
+    return W * (q < 1 ? 1 : q);
+  }
+  int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + 8, 256) : cdiv(Mout, 128) * cdiv(NK + 8, 128);
+  int q = cdiv(1024, tiles * W);
+  int qmax = per_replica / 128;  // at least two k-tiles per split
   if (qmax < 1) qmax = 1;
   if (q > qmax) q = qmax;
   if (q * W > 256) q = 256 / W;

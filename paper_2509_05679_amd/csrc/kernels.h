@@ -75,7 +75,7 @@ struct WgradParams {
   int R, S, stride, pad;
   int NK;           // R*S*Cx
   int P;            // Nimg*Ho*Wo
-  int pix_per_split; // generic kernel: pixels per split (P / nsplit, splits are equal)
+  int pix_per_split; // wgrad_gemm_kernel: pixels per split (P / nsplit, splits are equal)
   int nsplit;
   int nrep;          // data-groups: equal runs of consecutive images; nsplit is a multiple of it and no split
                      // holds pixels of two data-groups (the asynchronous kernel deals each group's 128-pixel
@@ -133,7 +133,7 @@ struct UpdateDesc {
 };
 
 // Both return the kernel family that took the launch: 0 = generic implicit GEMM (register-staged),
-// 1 = the asynchronous global->LDS kernels (conv3x3_dma_kernel / wgrad_dma_kernel).
+// 1 = the asynchronous global->LDS kernels (conv3x3_dma_kernel / wgrad_dma_kernel and their relatives).
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 // plain products of few rows (linear.hip); false: not taken, nothing launched
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);

@@ -85,13 +85,13 @@ def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
     _compare(_conv_chain(precision, widths, h, w, W, B), seed=26, T=2, every_step=precision == "f32", tiny=precision == "f32")
 
 
-def _stride2_net(c1, c2, k, h, w, W, B):
+def _stride2_net(c1, c2, k, h, w, W, B, precision="bf16"):
     ops = [{"op": "conv", "cin": 3, "cout": c1, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
            {"op": "conv", "cin": c1, "cout": c2, "k": k, "stride": 2, "pad": k // 2}, {"op": "relu"},
            {"op": "conv", "cin": c2, "cout": c2, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}, {"op": "gap"},
            {"op": "linear", "cin": c2, "cout": 10}, {"op": "softmax_ce"}]
     return Workload(name=f"stride2_k{k}_{h}x{w}", ops=ops, bounds=[0, len(ops)], K=1, W=W, B=B, in_shape=(3, h, w), classes=10,
-                    precision="bf16", lr=0.05, momentum=0.0, steps=2)
+                    precision=precision, lr=0.05, momentum=0.0, steps=2)
 
 
 @pytest.mark.parametrize("c1,c2,k,h,w,W,B", [
@@ -101,6 +101,14 @@ def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     # odd sides, batches that are no whole 128-pixel tiles, channel counts off the 64-channel blocks, a single image
     # row, data-groups of less than a tile, the longest rows
     _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
+
+
+@pytest.mark.parametrize("c1,c2,k,h,w,W,B", [
+    (16, 36, 3, 7, 9, 2, 3), (32, 64, 1, 8, 8, 2, 9), (68, 132, 3, 13, 14, 1, 3), (16, 16, 3, 2, 88, 1, 1),
+    (12, 16, 3, 1, 3, 3, 33)])
+def test_weight_gradients_of_any_image_size_fp32(c1, c2, k, h, w, W, B):
+    # channel counts off the 32-channel panels and 64-channel blocks, partial tiles, the longest rows
+    _compare(_stride2_net(c1, c2, k, h, w, W, B, "f32"), seed=28, T=2, every_step=True, tiny=True)
 
 
 @pytest.mark.parametrize("name,B,steps", [("paper_r20_S1K1", 194, 20), ("paper_r20_S1K1", 7, 40)])
