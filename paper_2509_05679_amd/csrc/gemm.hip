@@ -592,10 +592,11 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 // The residual / mask tiles are staged in the first `room` bytes of LDS (the operand buffers are free now) so that the
 // epilogue pays one global round trip instead of one per 32-pixel column, and the output tile leaves from there in
 // whole rows. The 1 KiB behind them holds alpha * bias. pixel(row): output pixel of a tile row, -1 past the end.
+// act (wave-uniform): false for waves beyond the tile's own, which only keep the barriers.
 template <typename T, int BM, int BN, int WM, int WN, typename Pixel>
 __device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&acc)[WN / 32][WM / 32],
                                          const uint32_t (&mb)[WM / 32][WN / 32], char* smem, int room, int n0, int wave,
-                                         int wave_m, int wave_n, int lane, int lpix, Pixel pixel) {
+                                         int wave_m, int wave_n, int lane, int lpix, Pixel pixel, bool act = true) {
   constexpr int ES = sizeof(T);
   constexpr int NW = (BM / WM) * (BN / WN), NI = WM / 32, NJ = WN / 32;
   constexpr int ROWB = BN * ES;        // bytes per tile row
@@ -616,6 +617,7 @@ __device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&a
     auto stage_tile = [&](const void* src_tensor) -> int {
       if ((region + 1) * BM * ROWB > room) return -1;
       const int rbase = region * BM * ROWB;
+      if (act)
 #pragma unroll
       for (int u = 0; u < FPW; ++u) {
         const int f = wave + NW * u;
@@ -642,6 +644,7 @@ __device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&a
 
   const int nb = n0 + wave_n * WN + 4 * (lane >> 5);
   float bias[NJ][4][4] = {};
+  if (act)
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int m = wave_m * WM + i * 32 + lpix;
@@ -652,6 +655,7 @@ __device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&a
   if (out_off >= 0) {
     // write the tile out: a wave stores RPF whole tile rows per instruction, 16 bytes per lane
     __syncthreads();
+    if (act)
 #pragma unroll
     for (int u = 0; u < FPW; ++u) {
       const int f = wave + NW * u;
@@ -663,6 +667,25 @@ __device__ __forceinline__ void tile_out(const ConvParams& p, const f32x16_t (&a
       if (pix >= 0 && n < p.ldy) *(u32x4_t*)((char*)p.y + ((size_t)pix * p.ldy + n) * ES) = v;
     }
   }
+}
+
+// The two halves of a workgroup's waves hold partial sums of the same tile: the second half's meet the first half's in
+// LDS (4 KiB per 32 x 32 block and wave, at the start of LDS) and end there.
+template <int NI, int NJ>
+__device__ __forceinline__ void add_halves(f32x16_t (&acc)[NJ][NI], char* smem, int khalf, int wave, int lane) {
+  __syncthreads();  // the operands have been read
+  f32x16_t* buf = (f32x16_t*)smem + (size_t)wave * NJ * NI * 64 + lane;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (khalf == 1) buf[(j * NI + i) * 64] = acc[j][i];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (khalf == 0) acc[j][i] += buf[(j * NI + i) * 64];
 }
 
 // floor(n / d) == __umulhi(n, mul) >> shift for 0 <= n < 2^31: mul = floor(2^(31+l) / d) + 1 with 2^(l-1) < d <= 2^l
@@ -686,8 +709,9 @@ struct DmaGeom {
 
 // RES (one channel chunk only): the weights of all nine taps are resident beside the patch, so everything is requested
 // at once and the taps run without a barrier between them.
-template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false>
-__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) == 4 ? 2 : 1) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
+// KS = 2: eight waves, each four of which have operand buffers of their own and walk half of the channel chunks.
+template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false, int KS = 1>
+__global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
   constexpr int NW = (BM / WM) * (BN / WN);  // waves per workgroup (each owns a WM x WN sub-tile)
@@ -700,7 +724,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   static_assert(KB == 64 || KB == 128, "row depth");
   static_assert(RES ? PS == 0 && (RG >= NW || (RG % 2 == 0 && NW % RG == 0)) : RG >= NW, "fills of a weight tile per wave");
   constexpr int NI = WM / 32, NJ = WN / 32;
-  static_assert(NW == 4 || NW == 8, "four or eight waves");
+  static_assert(NW == 4 && (KS == 1 || (KS == 2 && !RES)), "four waves per tile");
   extern __shared__ __align__(16) char smem[];
   const int prow = g.patch_rows;
   const int pbuf_bytes = prow * KB;
@@ -708,11 +732,12 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
   const uint32_t lds_dump = lds0 + g.out_bytes;   // 1 KiB that absorbs surplus fills
   const int zero_off = g.out_bytes + 1024;        // 256 bytes of zeros
-  char* wring = smem + wring_off;
-  const uint32_t lds_wring = lds0 + wring_off;
-
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: everything derived from it stays in SGPRs
+  const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: everything derived from it stays in SGPRs
+  const int wave = wave_wg & (NW - 1), khalf = wave_wg / NW;
+  const int buf0 = KS > 1 ? khalf * (wring_off + 3 * BN * KB) : 0;  // operand buffers of this half
+  char* wring = smem + buf0 + wring_off;
+  const uint32_t lds_pbuf = lds0 + buf0, lds_wring = lds_pbuf + wring_off;
   const int wave_m = wave % (BM / WM), wave_n = wave / (BM / WM);
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   if (p.nrep > 1) {  // the launcher made sure that the pixels of a tile belong to one data-group
@@ -720,8 +745,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
     p.w = (const char*)p.w + (size_t)r * p.w_rep;
     if (p.bias) p.bias += (size_t)r * p.bias_rep;
   }
-  const int nchunks = (p.Cx * ES) / KB;
+  const int nchunks = (p.Cx * ES) / KB / KS;  // channel chunks of this half
   const size_t pixbytes = (size_t)p.Cx * ES;
+  const size_t chunk0 = (size_t)khalf * nchunks * KB;
   if (tid < 16) *(uint4*)(smem + zero_off + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
 
   const int l8 = lane / CPR;  // row inside a fill
@@ -733,7 +759,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   // last pixel repeat that pixel (no tap inside an image reads them).
   constexpr int NPRO = (KB == 128 && PS == 0) ? 11 : 7;  // fills per wave that cover the largest patch
   const int first = m0 - p.W - 1;  // pixel of patch row 0
-  const char* pbase = (const char*)p.x + (long long)first * (long long)pixbytes;
+  const char* pbase = (const char*)p.x + (long long)first * (long long)pixbytes + chunk0;
   uint32_t poff[NPRO];
 #pragma unroll
   for (int j = 0; j < NPRO; ++j) {
@@ -742,7 +768,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   }
   auto patch_dst = [&](int j, int buf) {
     const int wl = wave + NW * j;
-    return wl < pw_total ? lds0 + buf * pbuf_bytes + wl * 1024 : lds_dump;
+    return wl < pw_total ? lds_pbuf + buf * pbuf_bytes + wl * 1024 : lds_dump;
   };
   // weight rows: byte offset of this lane's 16 bytes inside the weight tensor at tap 0, chunk 0.
   // Rows past Nout repeat the last one: their output columns lie past ldy == Nout and are never stored.
@@ -753,7 +779,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
     wvo[u] = (uint32_t)(gn < p.Nout ? gn : p.Nout - 1) * (uint32_t)(9 * pixbytes) + c16;
   }
   auto fill_w = [&](int chunk, int tap, int slot) {
-    const char* base = (const char*)p.w + (size_t)tap * pixbytes + (size_t)chunk * KB;  // wave-uniform
+    const char* base = (const char*)p.w + (size_t)tap * pixbytes + chunk0 + (size_t)chunk * KB;  // wave-uniform
 #pragma unroll
     for (int u = 0; u < WL; ++u) dma16s(base, wvo[u], lds_wring + slot * (BN * KB) + (wave + NW * u) * 1024);
   };
@@ -832,7 +858,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
   int a0[NI];
   auto address = [&](int chunk, int tap_r, int tap_s) {
     const int tapoff = (tap_r - 1) * tap_w + (tap_s - 1) * tap_1;  // wave-uniform
-    const int pbuf = PS > 0 ? (chunk & 1) * pbuf_bytes : 0;
+    const int pbuf = buf0 + (PS > 0 ? (chunk & 1) * pbuf_bytes : 0);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       int rb = rowb[i];
@@ -903,8 +929,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN), (BM / WM) * (BN / WN) =
 #undef DDS_STAGE
   wait_vm<0>();
 
+  if (KS > 1) add_halves<NI, NJ>(acc, smem, khalf, wave, lane);
   const auto pixel = [&](int row) { return m0 + row < p.M ? m0 + row : -1; };
-  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel);
+  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel, khalf == 0);
 }
 
 inline int ilog2_exact(int v) {
@@ -913,12 +940,13 @@ inline int ilog2_exact(int v) {
   return (1 << l) == v ? l : -1;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false>
+template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false, int KS = 1>
 bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   constexpr int FROWS = 1024 / KB;
   constexpr int NW = (BM / WM) * (BN / WN);
   if (p.Cx * (int)sizeof(T) % KB != 0) return false;
-  const int nchunks = p.Cx * (int)sizeof(T) / KB;
+  if (p.Cx * (int)sizeof(T) / KB % KS != 0) return false;
+  const int nchunks = p.Cx * (int)sizeof(T) / KB / KS;
   DmaGeom g;
   g.patch_rows = (BM + 2 * p.W + 2 + FROWS - 1) / FROWS * FROWS;
   g.dgrad = p.dgrad;
@@ -926,8 +954,8 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   g.dH = make_divisor(p.H);
   const int fills_per_wave = (g.patch_rows / FROWS + NW - 1) / NW;
   if (fills_per_wave > ((KB == 128 && PS == 0) ? 11 : 7)) return false;  // patch offsets kept per lane
-  if (PS == 0 ? nchunks != 1 : (nchunks < 2 || 7 * PS < fills_per_wave)) return false;
-  int operands = (PS > 0 ? 2 : 1) * g.patch_rows * KB + (RES ? 9 : 3) * BN * KB;
+  if (PS == 0 ? nchunks != 1 : (nchunks * KS < 2 || 7 * PS < fills_per_wave)) return false;
+  int operands = KS * ((PS > 0 ? 2 : 1) * g.patch_rows * KB + (RES ? 9 : 3) * BN * KB);
   constexpr int tile = BM * BN * (int)sizeof(T);  // the output tile is staged where the operands were, if two workgroups still fit a CU
   if (operands < tile && tile <= 72 * 1024) operands = tile;
   g.out_bytes = operands;
@@ -935,11 +963,11 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   if (smem > 160 * 1024) return false;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
   dim3 grid((p.M + BM - 1) / BM, (p.ldy + BN - 1) / BN);
-  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES><<<grid, 64 * NW, smem, s>>>(p, g);
+  conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS><<<grid, 64 * KS * NW, smem, s>>>(p, g);
   return true;
 }
 
@@ -983,6 +1011,12 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
     if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, s)) return true;
     if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
   }
+  // Launches that would leave half of the CUs without a 128 x 128 tile: 64 x 64 tiles whose channel chunks two halves of
+  // eight waves share, a quarter of the stages (and of whole cache lines). 64 images, alone: 512 channels at 4 x 4 47.6 ->
+  // 19.2 us, 256 at 8 x 8 26.6 -> 12.0 us; 128 at 16 x 16 (128 tiles) 17.2 against 16.3 us and no faster in the step.
+  // (fp32 stages are long enough as they are.)
+  if (sizeof(T) == 2 && (long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128) < 128 &&
+      launch_dma_inst<T, 64, 64, 32, 32, 1, 128, false, 2>(p, s)) return true;
   return launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, s);
 }
 
@@ -1002,8 +1036,9 @@ struct GatherGeom {
   int out_bytes;  // bytes of LDS below the row table: operand slots, then the epilogue's tiles
 };
 
-template <typename T, int BM, int BN, int WM, int WN, bool S2>
-__global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, GatherGeom g) {
+// KS = 2: eight waves, each four of which have operand slots of their own and walk half of the stages.
+template <typename T, int BM, int BN, int WM, int WN, bool S2, int KS>
+__global__ __launch_bounds__(256 * KS, 2) void conv_gather_kernel(ConvParams p_, GatherGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
   constexpr int KB = 64, FROWS = 16, CPR = 4, NKS = 2;  // bytes of a row, rows of a 1 KiB fill, 16-byte columns, k-steps
@@ -1019,7 +1054,8 @@ __global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, Gath
   int2* rowsrc = (int2*)(rowpix + BM);               // pixel of x at tap offset (0, 0); its row << 16 | column, signed
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = wave_wg & 3, khalf = wave_wg >> 2;
   const int wave_m = wave % (BM / WM), wave_n = wave / (BM / WM);
   const int cls = S2 ? 3 - (int)blockIdx.x / g.tiles_per_class : 0;
   const int ch = cls >> 1, cw = cls & 1;
@@ -1073,9 +1109,16 @@ __global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, Gath
   const int nk1 = ntr * nts * nchunks;  // stages of the layer itself; a folded shortcut's follow
   const int nk = nk1 + (S2 && p.x2 != nullptr && cls == 0 ? p.Cx2 * ES / KB : 0);
 
-  int fr = r0, fs = s0, fc = 0;  // position of the next stage to be copied
-  auto fill = [&](int kt, int slot) {
-    const uint32_t base = lds0 + slot * SLOT;
+  const int per_half = (nk + KS - 1) / KS;
+  const int kt0 = khalf * per_half;                  // first stage of this half
+  const int own = min(nk - kt0, per_half);           // and how many it has
+  // position of the next stage to be copied
+  const int tap0 = KS > 1 ? kt0 / nchunks : 0;
+  int fc = KS > 1 ? kt0 - tap0 * nchunks : 0;
+  int fr = KS > 1 && nts > 0 ? r0 + step * (tap0 / nts) : r0, fs = KS > 1 && nts > 0 ? s0 + step * (tap0 % nts) : s0;
+  auto fill = [&](int t, int slot) {
+    const uint32_t base = lds0 + (khalf * 3 + slot) * SLOT;
+    const int kt = kt0 + t;
     if (S2 && kt >= nk1) {  // the shortcut reads the pixel itself from its own tensor
       const int off = (kt - nk1) * KB;
       const char* x = (const char*)p.x2 + off;
@@ -1118,8 +1161,8 @@ __global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, Gath
       for (int j = 0; j < NJ; ++j) mb[i][j] = load_bits32(p.maskbits, (size_t)max(pix, 0), p.ldy, n0 + wave_n * WN + 32 * j, pix >= 0);
     }
   }
-  if (nk > 0) fill(0, 0);
-  if (nk > 1) fill(1, 1);
+  if (own > 0) fill(0, 0);
+  if (own > 1) fill(1, 1);
   int aoff[NI], boff[NJ];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -1140,12 +1183,13 @@ __global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, Gath
       for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
 
   int cur = 0, nxt = 2;  // slots of this stage and of the one two ahead
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) wait_vm<AP + WL>();  // only the next stage's copies are younger
+  for (int kt = 0; kt < per_half; ++kt) {
+    if (kt + 1 < own) wait_vm<AP + WL>();  // only the next stage's copies are younger
     else wait_vm<0>();
     wg_barrier();
-    if (kt + 2 < nk) fill(kt + 2, nxt);
-    const char* sb = smem + cur * SLOT;
+    if (KS > 1 && kt >= own) continue;
+    if (kt + 2 < own) fill(kt + 2, nxt);
+    const char* sb = smem + (khalf * 3 + cur) * SLOT;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       uint4 a[NI], b[NJ];
@@ -1162,25 +1206,26 @@ __global__ __launch_bounds__(256, 2) void conv_gather_kernel(ConvParams p_, Gath
     nxt = nxt == 2 ? 0 : nxt + 1;
   }
   wait_vm<0>();
+  if (KS > 1) add_halves<NI, NJ>(acc, smem, khalf, wave, lane);
   const auto pixel = [&](int row) { return rowpix[row]; };
-  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel);
+  tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel, khalf == 0);
 }
 
-template <typename T, int BM, int BN, int WM, int WN, bool S2>
+template <typename T, int BM, int BN, int WM, int WN, bool S2, int KS = 1>
 bool launch_gather_inst(const ConvParams& p, hipStream_t s) {
   GatherGeom g;
   const int mc = S2 ? p.Nimg * ((p.Ho + 1) / 2) * ((p.Wo + 1) / 2) : p.M;  // class (0, 0) is the largest
   g.tiles_per_class = (mc + BM - 1) / BM;
-  constexpr int slots = 3 * (BM + BN) * 64, tile = BM * BN * (int)sizeof(T);
+  constexpr int slots = KS * 3 * (BM + BN) * 64, tile = BM * BN * (int)sizeof(T);
   g.out_bytes = slots < tile && tile <= 72 * 1024 ? tile : slots;
   const int smem = g.out_bytes + 1024 + BM * 12;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)conv_gather_kernel<T, BM, BN, WM, WN, S2>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)hipFuncSetAttribute((const void*)conv_gather_kernel<T, BM, BN, WM, WN, S2, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
   dim3 grid((S2 ? 4 : 1) * g.tiles_per_class, (p.ldy + BN - 1) / BN);
-  conv_gather_kernel<T, BM, BN, WM, WN, S2><<<grid, 256, smem, s>>>(p, g);
+  conv_gather_kernel<T, BM, BN, WM, WN, S2, KS><<<grid, 256 * KS, smem, s>>>(p, g);
   return true;
 }
 
@@ -1188,6 +1233,10 @@ template <typename T, bool S2>
 bool launch_gather_t(const ConvParams& p, hipStream_t s) {
   if (p.ldy <= 32) return launch_gather_inst<T, 128, 32, 32, 32, S2>(p, s);
   if (p.ldy <= 64) return launch_gather_inst<T, 128, 64, 64, 32, S2>(p, s);
+  // few tiles: as in launch_dma (64 images of ResNet-18: 36 / 20 / 33 -> 19 / 12 / 19 us; with a line at 300 tiles the full
+  // batch went from 17.1 to 17.3 ms per 8 steps)
+  if (sizeof(T) == 2 && (long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128) < 128)
+    return launch_gather_inst<T, 64, 64, 32, 32, S2, 2>(p, s);
   return launch_gather_inst<T, 128, 128, 64, 64, S2>(p, s);
 }
 

@@ -77,7 +77,7 @@ def _conv_chain(precision, widths, h, w, W, B):
 @pytest.mark.parametrize("precision,widths,h,w,W,B", [
     ("bf16", (32, 32, 64), 2, 2, 1, 3), ("bf16", (64, 64, 128), 3, 5, 2, 9), ("bf16", (64, 128, 128), 9, 7, 3, 5),
     ("bf16", (64, 64, 32), 4, 47, 1, 2), ("bf16", (64, 64, 32), 5, 48, 1, 2), ("bf16", (32, 64), 3, 95, 1, 2),
-    ("bf16", (32, 64), 3, 96, 1, 2), ("bf16", (64, 128), 2, 160, 1, 2), ("f32", (32, 32, 64), 13, 3, 2, 7),
+    ("bf16", (64, 192, 256, 200), 4, 4, 2, 5), ("bf16", (32, 64), 3, 96, 1, 2), ("bf16", (64, 128), 2, 160, 1, 2), ("f32", (32, 32, 64), 13, 3, 2, 7),
     ("f32", (16, 48, 32), 6, 10, 2, 3)])
 def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
     # images whose rows and planes are no power of two, tiles that hold many images or end inside one, patches on both
@@ -96,7 +96,7 @@ def _stride2_net(c1, c2, k, h, w, W, B, precision="bf16"):
 
 @pytest.mark.parametrize("c1,c2,k,h,w,W,B", [
     (16, 32, 3, 7, 9, 2, 3), (24, 72, 3, 14, 13, 1, 9), (64, 64, 1, 11, 6, 3, 5), (64, 128, 3, 8, 8, 2, 9),
-    (32, 64, 3, 28, 30, 1, 3), (72, 136, 3, 3, 2, 2, 65), (8, 8, 1, 1, 5, 2, 30), (16, 16, 3, 2, 178, 1, 1)])
+    (32, 64, 3, 28, 30, 1, 3), (72, 136, 3, 3, 2, 2, 65), (96, 160, 3, 5, 4, 2, 3), (128, 256, 1, 4, 4, 1, 7), (8, 8, 1, 1, 5, 2, 30), (16, 16, 3, 2, 178, 1, 1)])
 def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     # odd sides, batches that are no whole 128-pixel tiles, channel counts off the 64-channel blocks, a single image
     # row, data-groups of less than a tile, the longest rows
