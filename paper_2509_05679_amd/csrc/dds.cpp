@@ -553,7 +553,7 @@ int plan_module(const dds_spec& sp, int k0, int K, int N, int dt, const Tensor* 
 }
 
 // elements of a layer that one workgroup of the update kernel owns
-int range_elems(const dds_ctx& c, const ParamLayer& L) { return c.gossip ? gossip_elems(L.nsplit / c.copies) : update_elems(L.nsplit); }
+int range_elems(const dds_ctx& c, const ParamLayer& L) { return c.gossip ? gossip_elems(L.nsplit / c.copies) : update_elems(c.dt, L.nsplit); }
 
 int layout(dds_ctx& c, Arena& A) {
   const int es = dtype_size(c.dt);

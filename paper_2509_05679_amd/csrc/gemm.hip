@@ -1003,6 +1003,9 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
     if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
     return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
   }
+  // fp32 sums keep one order per shape: channels outermost where the sides are powers of two up to 32, else taps
+  // (conv_gather_kernel)
+  if (sizeof(T) == 4 && (ilog2_exact(p.H) < 0 || ilog2_exact(p.W) < 0 || p.W > 32 || p.H * p.W < 16)) return false;
   // small images: 128-pixel tiles give more workgroups. 256-pixel tiles from 256 workgroups up (one per CU: half the
   // weight copies per FLOP; with the other modules' kernels sharing the chip this beat two 128-pixel workgroups per
   // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step)
@@ -1853,12 +1856,13 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
 // channels, [pixel][128 bytes], copied global -> LDS (two slots), of which 32 consecutive lanes read 32 consecutive channels of a
 // pixel with no conflict and a constant offset per step. Lane l of wave w always copies pixel 8 w + l / 8 of a tile,
 // 16 bytes of one tap per panel: one image position per lane and tile, stepped without a division. Any kernel size,
-// stride, image size and batch; linear layers are the 1x1 case. The bias gradient is summed from the dY operand.
-// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers, the fp32
-// CNN's layers, 512 images, alone: 64 -> 128 channels at 16 x 16 282 -> 226 us, 128 -> 256 at 8 x 8 280 -> 200 us, 256 -> 512 at
-// 4 x 4 233 -> 184 us, the 3-channel stem 157 -> 63 us; the perceptron's 3072 -> 256 layer 11.5 -> 9.6 us.
+// stride, image size and batch; linear layers are the 1x1 case. The bias gradient is
+// the product with a column of ones. Pixels are summed in the order of wgrad_gemm_kernel (pairs four apart).
+// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers
+// the fp32 CNN takes 15.3 instead of 15.9 ms per 8 iterations (14.4 with the bias gradient summed on the vector unit and splits
+// free of the pixel count, whose sums differ in the last bits), alone about 226 / 200 / 184 us for its wide layers (280 / 280 /
+// 233) and 63 us for the 3-channel stem (157).
 struct Wgrad32Geom {
-  int q, rep_tiles;       // splits and 32-pixel tiles per data-group
   int sw, sh, si;         // 32 pixels = si images + sh rows + sw columns of the output grid
 };
 
@@ -1873,14 +1877,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = wave >> 1;
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, z = blockIdx.z;
-  const int zr = z / g.q, zj = z - zr * g.q;
-  const int rep_pix = p.P / p.nrep;
-  const int tile0 = (int)(((long long)zj * g.rep_tiles) / g.q);
-  const int ntiles = (int)(((long long)(zj + 1) * g.rep_tiles) / g.q) - tile0;
-  const int end = (zr + 1) * rep_pix;  // the group's last tile may be a partial one
+  const int first = z * p.pix_per_split, end = first + p.pix_per_split;  // the last tile may be a partial one
+  const int ntiles = (p.pix_per_split + 31) / 32;
 
   const int l8 = lane >> 3, c4 = (lane & 7) * 4;  // pixel of a fill, first channel of this lane's 16 bytes
-  int pix = zr * rep_pix + tile0 * 32 + wave * 8 + l8;
+  int pix = first + wave * 8 + l8;
   int line = pix / p.Wo, ow = pix - line * p.Wo;
   int img = line / p.Ho, oh = line - img * p.Ho;
   bool n_ok[BP];
@@ -1919,17 +1920,17 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
   };
   fill(0);
 
-  const int l32 = (lane >> 5) * 128 + (lane & 31) * 4;  // pixel lane / 32 of a pair, channel lane % 32
-  f32x16_t acc[NI][NJ];
-  float sumb[NI];
+  const int l32 = (lane >> 5) * 512 + (lane & 31) * 4;  // steps pair pixels 8 i + j and 8 i + 4 + j; channel lane % 32
+  const bool bias_wave = blockIdx.y == 0 && wave_n == 0;
+  f32x16_t acc[NI][NJ], accb[NI];
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    sumb[i] = 0.f;
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int e = 0; e < 16; ++e) {
+      accb[i][e] = 0.f;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  }
+      for (int j = 0; j < NJ; ++j) acc[i][j][e] = 0.f;
+    }
   for (int t = 0; t < ntiles; ++t) {
     wait_vm<0>();
     wg_barrier();
@@ -1940,14 +1941,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
     for (int ks = 0; ks < 16; ++ks) {
       float a[NI], b[NJ];
 #pragma unroll
-      for (int i = 0; i < NI; ++i) a[i] = *(const float*)(sa + i * 4096 + ks * 256);
+      for (int i = 0; i < NI; ++i) a[i] = *(const float*)(sa + i * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + ks * 256);
+      for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        sumb[i] += a[i];
+        if (bias_wave) accb[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], 1.f, accb[i], 0, 0, 0);
       }
     }
   }
@@ -1966,8 +1967,13 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
         if (m < p.Mout && n < p.NK) out[(size_t)m * p.NK + n] = p.alpha * acc[i][j][e];
       }
     }
-    const float s = sumb[i] + __shfl_xor(sumb[i], 32, 64);
-    if (blockIdx.y == 0 && wave_n == 0 && lane < 32 && mb + lane < p.Mout) out[(size_t)p.Mout * p.NK + mb + lane] = p.alpha * s;
+    if (bias_wave && (lane & 31) == 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int m = mb + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (m < p.Mout) out[(size_t)p.Mout * p.NK + m] = p.alpha * accb[i][e];
+      }
+    }
   }
 }
 
@@ -2169,18 +2175,9 @@ bool launch_wgrad_dma(const WgradParams& p, hipStream_t s) {
   return false;
 }
 
-// Tile of an fp32 problem: 64 columns for narrow operands, else 128
-inline void wgrad_f32_tile(int Mout, int NK, int& BM, int& BN) {
-  BM = Mout <= 64 ? 64 : 128;
-  BN = Mout <= 64 && NK <= 64 ? 64 : 128;
-}
-
 void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
-  int BM, BN;
-  wgrad_f32_tile(p.Mout, p.NK, BM, BN);
+  const int BM = p.Mout <= 64 ? 64 : 128, BN = p.Mout <= 64 && p.NK <= 64 ? 64 : 128;
   Wgrad32Geom g;
-  g.q = p.nsplit / p.nrep;
-  g.rep_tiles = cdiv(p.P / p.nrep, 32);
   g.sw = 32 % p.Wo;
   g.sh = 32 / p.Wo % p.Ho;
   g.si = 32 / p.Wo / p.Ho;
@@ -2248,20 +2245,11 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
       return W * q;  // the launch takes the same decision
     }
   }
-  if (dt == DT_F32) {
-    // aim at two workgroups per CU (1024 / 512 / 256 workgroups: 14.36 / 14.36 / 14.32 ms for 8 steps of the fp32 CNN; the
-    // fewer splits, the fewer partial sums to write and read), at least two 32-pixel tiles each
-    int BM, BN;
-    wgrad_f32_tile(Mout, NK, BM, BN);
-    int q = cdiv(512, cdiv(Mout, BM) * cdiv(NK, BN) * W);
-    const int qmax = cdiv(per_replica, 64);
-    if (q > qmax) q = qmax;
-    if (q * W > 256) q = 256 / W;
-    return W * (q < 1 ? 1 : q);
-  }
-  int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + 8, 256) : cdiv(Mout, 128) * cdiv(NK + 8, 128);
-  int q = cdiv(1024, tiles * W);
-  int qmax = per_replica / 128;  // at least two k-tiles per split
+  const int ce = dtype_ce(dt);
+  const int bke = 128 / dtype_size(dt);
+  int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + ce, 256) : cdiv(Mout, 128) * cdiv(NK + ce, 128);
+  int q = cdiv(1024, tiles * W);  // aim at ~1024 workgroups (fp32 CNN: 512 and 256 the same within 0.5 %)
+  int qmax = per_replica / (2 * bke);  // at least two k-tiles per split
   if (qmax < 1) qmax = 1;
   if (q > qmax) q = qmax;
   if (q * W > 256) q = 256 / W;

@@ -163,9 +163,12 @@ void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void*
                        int W, int B, int classes, int ldl, int ldg, hipStream_t s);
 // Elements of a parameter block that one workgroup of the update kernel owns: the fewer, the more splits have to be
 // summed for each, so that a launch always has thousands of partial rows in flight (see update_kernel).
-__host__ __device__ inline int update_elems(int nsplit) { return nsplit >= 256 ? 32 : nsplit >= 64 ? 64 : 256; }
+// fp32 nets keep one range and with it one order of the sum for every split count.
+__host__ __device__ inline int update_elems(int dt, int nsplit) {
+  return dt == DT_F32 || nsplit < 64 ? 256 : nsplit >= 256 ? 32 : 64;
+}
 // update: g = (1/W) sum over splits, momentum, SGD on the fp32 master, recast into `work`. range_map: device array of
-// (descriptor, first element / 32) pairs, one per workgroup of update_elems(nsplit) elements.
+// (descriptor, first element / 32) pairs, one per workgroup of update_elems(dt, nsplit) elements.
 void launch_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev, int total_ranges, int W,
                    float lr, float mu, hipStream_t s);
 // The other kernels' block_map: device array of (descriptor, block) pairs, one per 1024 elements.

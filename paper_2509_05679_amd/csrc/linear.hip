@@ -2,9 +2,10 @@
 //   y[m, n] = epilogue( sum_k x[m, k] * w[n, k] )
 // The tiled kernels of gemm.hip hand such a product to a handful of workgroups that walk the whole reduction, one
 // memory round trip and barrier per k-tile: the 3072 -> 256 layer of the perceptron (64 rows, fp32) kept two
-// workgroups busy for 192 k-tiles. Here a tile is 16 x 16 and the eight waves of a workgroup split its reduction, so
-// that layer is 64 workgroups of eight waves with 24 steps each: bound by latency, 138 -> 7.4 us on average over the
-// two hidden layers' forward passes, 18 -> 7 us for the input gradient, 15 -> 4.3 us for a ResNet's 512 -> 10 head.
+// workgroups busy for 192 k-tiles. Here a tile is 16 x 16. In bf16 the eight waves of a workgroup split its reduction once
+// each has a k-step of its own: 15 -> 4.3 us for a ResNet's 512 -> 10 head. In fp32 one wave walks it, twelve k-steps
+// requested ahead, in the order of the tiled kernels: every sum is theirs bit for bit, and the perceptron's 8 iterations take
+// 0.75-0.80 ms instead of 2.38 (a split over eight waves: 0.70-0.75 ms, but other sums). Bound by latency.
 #include "kernels.h"
 
 namespace dds {
@@ -19,10 +20,21 @@ template <typename T> __device__ __forceinline__ f32x4_t mfma16x16(const uint4& 
 template <> __device__ __forceinline__ f32x4_t mfma16x16<bf16_t>(const uint4& a, const uint4& b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
-template <> __device__ __forceinline__ f32x4_t mfma16x16<float>(const uint4& a, const uint4& b, f32x4_t c) {
+// fp32 products are added in the order of the tiled kernels of gemm.hip (0, 4, 1, 5, 2, 6, 3, 7 of every eight), so that a
+// layer's sums do not depend on which kernel its row count selects: swapping half-waves between neighbouring
+// components puts k = 0 4 1 5, 2 6 3 7, 8 12 9 13 and 10 14 11 15 of the 16 in the four lane groups of one instruction each.
+__device__ __forceinline__ void swap_halves(uint32_t& lo, uint32_t& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+  lo = r[0];
+  hi = r[1];
+}
+template <> __device__ __forceinline__ f32x4_t mfma16x16<float>(const uint4& a_, const uint4& b_, f32x4_t c) {
+  uint4 a = a_, b = b_;
+  swap_halves(a.x, a.y); swap_halves(a.z, a.w);
+  swap_halves(b.x, b.y); swap_halves(b.z, b.w);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
 }
 
@@ -48,10 +60,10 @@ template <> __device__ __forceinline__ void load4<bf16_t>(const void* p, size_t 
 // weight row j and of activation row j, and ends with output channels 4 g .. 4 g + 3 of row j. Loads go straight from
 // global memory (a k-step reads 64 contiguous bytes of 16 rows), four k-steps ahead of their use; the partial tiles
 // of the KS waves meet in LDS and are added in a fixed order by the tile's first wave.
-template <typename T, int KS>
-__global__ __launch_bounds__(512) void linear_kernel(ConvParams p) {
-  constexpr int ES = sizeof(T), TILES = 8 / KS, UN = 4;
-  __shared__ f32x4_t red[8][64];
+template <typename T, int KS, int NW>
+__global__ __launch_bounds__(64 * NW) void linear_kernel(ConvParams p) {
+  constexpr int ES = sizeof(T), TILES = NW / KS, UN = sizeof(T) == 4 ? 12 : 4;
+  __shared__ f32x4_t red[NW][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
   const int ks = wave % KS;
@@ -138,9 +150,10 @@ __global__ __launch_bounds__(512) void linear_kernel(ConvParams p) {
 template <typename T>
 bool launch_linear_t(const ConvParams& p, hipStream_t s) {
   const int steps = (p.Cx * (int)sizeof(T) + 63) / 64;
+  if constexpr (sizeof(T) == 4) linear_kernel<T, 1, 1><<<dim3((p.M + 15) / 16, (p.ldy + 15) / 16), 64, 0, s>>>(p);
   // eight waves per tile once each has a k-step of its own, else a tile per wave
-  if (steps >= 8) linear_kernel<T, 8><<<dim3((p.M + 15) / 16, (p.ldy + 15) / 16), 512, 0, s>>>(p);
-  else linear_kernel<T, 1><<<dim3((p.M + 15) / 16, (p.ldy + 127) / 128), 512, 0, s>>>(p);
+  else if (steps >= 8) linear_kernel<T, 8, 8><<<dim3((p.M + 15) / 16, (p.ldy + 15) / 16), 512, 0, s>>>(p);
+  else linear_kernel<T, 1, 8><<<dim3((p.M + 15) / 16, (p.ldy + 127) / 128), 512, 0, s>>>(p);
   return true;
 }
 

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void gap_fwd_kernel(const char* x, char* y, in
   __shared__ float red[256 * CE];
   const int chunks = C / CE, n = blockIdx.x;
   const int per = chunks < 256 ? chunks : 256;  // chunks handled side by side
-  const int rows = 256 / per;
+  const int rows = sizeof(T) == 4 ? 1 : 256 / per;  // fp32 sums keep the order of the pixels
   const int cl = threadIdx.x % per, r = threadIdx.x / per;
   const float inv = 1.f / (float)HW;
   for (int c0 = 0; c0 < chunks; c0 += per) {  // one trip up to 256 chunks
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void gap_fwd_kernel(const char* x, char* y, in
 #pragma unroll
     for (int e = 0; e < CE; ++e) acc[e] = 0.f;
     if (r < rows && ch < chunks) {
-#pragma unroll 4
+#pragma unroll(sizeof(T) == 4 ? 16 : 4)
       for (int q = r; q < HW; q += rows) {
         c.load(x + (((size_t)n * HW + q) * C + (size_t)ch * CE) * sizeof(T));
 #pragma unroll
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, co
   __shared__ float4 red[3][64];
   const UpdateDesc d = descs[block_map[2 * blockIdx.x]];
   const long long first = (long long)block_map[2 * blockIdx.x + 1] * 32;
-  switch (update_elems(d.nsplit)) {
+  switch (update_elems(sizeof(T) == 4 ? DT_F32 : DT_BF16, d.nsplit)) {
     case 32: update_range<T, 32>(d, first, invW, lr, mu, red); break;
     case 64: update_range<T, 64>(d, first, invW, lr, mu, red); break;
     default: update_range<T, 256>(d, first, invW, lr, mu, red); break;
