@@ -5,7 +5,8 @@
 // workgroups busy for 192 k-tiles. Here a tile is 16 x 16. In bf16 the eight waves of a workgroup split its reduction once
 // each has a k-step of its own: 15 -> 4.3 us for a ResNet's 512 -> 10 head. In fp32 one wave walks it, twelve k-steps
 // requested ahead, in the order of the tiled kernels: every sum is theirs bit for bit, and the perceptron's 8 iterations take
-// 0.75-0.80 ms instead of 2.38 (a split over eight waves: 0.70-0.75 ms, but other sums). Bound by latency.
+// 0.75-0.80 ms instead of 2.38 (a split over eight waves: 0.70-0.75 ms, but other sums). Bound by latency, past one or two
+// tiles per CU by L2.
 #include "kernels.h"
 
 namespace dds {
@@ -55,10 +56,10 @@ template <> __device__ __forceinline__ void load4<bf16_t>(const void* p, size_t 
   v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xffff0000u);
 }
 
-// Eight waves; KS of them share one 16 x 16 tile (8 / KS tiles along n per workgroup). Weights are the MFMA A operand
+// NW waves; KS of them share one 16 x 16 tile (NW / KS tiles along n per workgroup). Weights are the MFMA A operand
 // (rows n), activations the B operand (columns m): lane l = 16 g + j supplies the 16 bytes g of a 64-byte k-step of
 // weight row j and of activation row j, and ends with output channels 4 g .. 4 g + 3 of row j. Loads go straight from
-// global memory (a k-step reads 64 contiguous bytes of 16 rows), four k-steps ahead of their use; the partial tiles
+// global memory (a k-step reads 64 contiguous bytes of 16 rows), UN k-steps ahead of their use; the partial tiles
 // of the KS waves meet in LDS and are added in a fixed order by the tile's first wave.
 template <typename T, int KS, int NW>
 __global__ __launch_bounds__(64 * NW) void linear_kernel(ConvParams p) {
@@ -157,15 +158,39 @@ bool launch_linear_t(const ConvParams& p, hipStream_t s) {
   return true;
 }
 
+// Where the 16 x 16 tiles pay. A tile reads its 16 weight and 16 activation rows from L2, so past one or two tiles per CU
+// the time grows with tiles x (trips of the load loop), while a tiled kernel of gemm.hip takes the time of one workgroup's
+// reduction, whatever the number of rows, until it has a workgroup for every CU: its k-steps times the cost of a stage,
+// which the width of its tile sets (32, 64 or 128 columns). Both sides were timed on 1298 shapes a type (16 to 24576 rows, 32 to
+// 2048 deep, 16 to 2048 columns). The lines below are where they meet: the side taken is the faster one or within 22 % of it
+// (bf16 of 160 to 224 channels takes 6.3 us where the tiled kernel takes 5.2).
+// us, linear / conv_gather_kernel / conv_gemm_kernel, columns x depth x rows:
+//   bf16 128 x 1024 x 512 4.5 / 9.3 / 23, x 1024 6.3 / 9.4 / 23, x 2048 9.9 / 9.4 / 23, x 8192 33 / 9.9 / 23
+//   bf16 64 x 256 x 2048 6.3 / 6.9 / 12, x 4096 9.9 / 6.9 / 12
+//   fp32 128 x 512 x 2048 12 / 42 / 47, x 8192 39 / 43 / 48, x 16384 73 / 43 / 48; 64 x 32 x 4096 6.2 / 6.3 / 9.8, x 8192 9.2 / 6.5 / 10
+// conv_gemm_kernel takes the channel counts that conv_gather_kernel refuses, at 1.1 to 2.5 times its time, and has lines of
+// its own (within 30 %, at the shortest reductions 53 %).
+bool few_tiles(int dt, const ConvParams& p, int steps) {
+  const bool gather = p.Cx % (64 / dtype_size(dt)) == 0 && p.ldy == p.Nout;
+  const int width = p.ldy <= 32 ? 0 : p.ldy <= 64 ? 1 : 2;  // column tile of the alternative
+  const long long rows = (p.M + 15) / 16, tiles = rows * ((p.ldy + 15) / 16);
+  if (dt == DT_F32) {  // one wave a tile, twelve steps a trip
+    const int line[2][3] = {{3000, 4500, 4500}, {1800, 2500, 4200}};
+    return tiles * ((steps + 11) / 12 * 12 + 8) <= (long long)line[gather][width] * (steps + 8);
+  }
+  if (steps < 8) return rows * ((p.ldy + 127) / 128) * ((steps + 3) / 4) <= (!gather ? 768 : width < 2 ? 512 : 256);
+  const int slope[2][3] = {{90, 90, 90}, {38, 45, 24}};
+  return tiles * ((steps + 31) / 32) <= 128 + slope[gather][width] * steps;
+}
+
 }  // namespace
 
-// True if the launch was taken: a plain product (1x1, stride 1, no padding) with so few rows and columns that the
-// 128- and 256-row tiles of gemm.hip would leave half of the CUs without a workgroup. (Above that line the tiled kernel
-// reads each operand byte from L2 once per 64 or more rows instead of once per 16.)
+// True if the launch was taken: a plain product (1x1, stride 1, no padding) of few rows and columns.
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s) {
   if (p.R != 1 || p.S != 1 || p.stride != 1 || p.pad != 0 || p.x2 != nullptr) return false;
   const long long tiles = (long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128);
   if (tiles > 128 || (p.ldy + 15) / 16 > 65535) return false;
+  if (!few_tiles(dt, p, (p.Cx * dtype_size(dt) + 63) / 64)) return false;
   if (p.nrep > 1 && (p.M % p.nrep != 0 || (p.M / p.nrep) % 16 != 0)) return false;
   return dt == DT_F32 ? launch_linear_t<float>(p, s) : launch_linear_t<bf16_t>(p, s);
 }

@@ -1,8 +1,11 @@
 """Small problems at the edges of the kernels' tiles and of the rules that choose between them, against the oracle.
 
 Tolerances: the ones of tests/parity.py (tiny = toy networks, where fp32 rounding is all there is)."""
+import numpy as np
 import pytest
+import torch
 
+from dds_inputs import make_params
 from dds_inputs.configs import Workload, ring_mixing, tiny_resnet
 from test_gpu_parity import _compare
 
@@ -116,3 +119,48 @@ def test_single_module_beside_its_weight_gradients_is_bit_identical(name, B, ste
     # one module: weight gradients on a stream of their own, against everything on the caller's stream
     from test_gpu_limits import test_run_ahead_across_iterations_is_bit_identical_to_serial_execution as compare
     compare(name, B, steps)
+
+
+def _middle_linear(precision, feat, hidden, out, W, B, seed):
+    # feat -> hidden | hidden -> out -> 10: one step forwards module 0, two steps module 1
+    ops = [{"op": "linear", "cin": feat, "cout": hidden}, {"op": "relu"}, {"op": "linear", "cin": hidden, "cout": out}, {"op": "relu"},
+           {"op": "linear", "cin": out, "cout": 10}, {"op": "softmax_ce"}]
+    wl = Workload(name=f"middle_linear_{hidden}_{out}", ops=ops, bounds=[0, 2, 6], K=2, W=W, B=B, in_shape=(feat, 1, 1), classes=10,
+                  precision=precision, lr=0.01, momentum=0.0, steps=4)
+    import paper_2509_05679_amd as P
+    tr = P.Trainer(P.Spec.from_workload(wl), W)
+    for k0, t in enumerate(make_params(wl, seed)):
+        tr.dds_set_params(k0, t)
+    return tr
+
+
+@pytest.mark.parametrize("precision,hidden,out,W,B", [("bf16", 512, 512, 4, 1024), ("f32", 512, 512, 4, 1024)])
+def test_linear_layers_of_many_rows_run_on_the_tiled_kernels(precision, hidden, out, W, B):
+    # (both kernels are right at these sizes; the 16 x 16 tiles take 63 and 73 us where the tiled kernel takes 13 and 44)
+    tr = _middle_linear(precision, 64, hidden, out, W, B, seed=30)
+    xs, ys = [torch.zeros((B, 64, 1, 1), device="cuda") for _ in range(W)], [torch.zeros(B, dtype=torch.int32, device="cuda") for _ in range(W)]
+    for _ in range(3):
+        tr.dds_step(xs, ys)
+    tr.dds_profile(2)
+    tr.dds_step(xs, ys)
+    times = tr.dds_profile_read()
+    tr.close()
+    assert times["forward_dma"][1] >= 1, times
+
+
+@pytest.mark.parametrize("feat,out,below,above", [(256, 64, 512, 8192), (252, 64, 512, 16384), (2048, 20, 64, 16384)])
+def test_fp32_sums_of_a_linear_layer_do_not_depend_on_its_rows(feat, out, below, above):
+    # the same rows below and above the line between linear.hip and the tiled kernels (conv_gather_kernel; 252 channels are
+    # no whole 64-byte chunks and stay on conv_gemm_kernel): the same sums in the same order, so bit for bit
+    import paper_2509_05679_amd as P
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    x = torch.randn((above, feat, 1, 1), device="cuda", generator=gen)
+    y = torch.zeros(above, dtype=torch.int32, device="cuda")
+    rows = []
+    for n in (below, above):
+        tr = _middle_linear("f32", feat, out, 16, 1, n, seed=31)
+        tr.dds_step([x[:n].contiguous()], [y[:n].contiguous()])
+        stored = tr.dds_debug_read(P.DDS_DBG_OUTPUT, 0, 0).view(np.float32).reshape(n, -1)
+        rows.append(stored[:below].copy())
+        tr.close()
+    assert np.abs(rows[0]).max() > 0 and np.array_equal(rows[0], rows[1])
