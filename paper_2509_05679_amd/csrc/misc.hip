@@ -141,46 +141,46 @@ __global__ void maxpool_bwd_kernel(const char* dy, const char* x, char* dx, int 
   for (int q = 0; q < 4; ++q) o[q].store(dx + off[q]);
 }
 
-// One workgroup per image: a pixel row is read by C / CE lanes, 16 bytes each, the other lanes take the next pixels,
-// and the partial sums of a channel chunk are folded through LDS in a fixed order. Bound by
-// latency at these sizes: 4.4 us for 194 and 5.8 us for 1024 images of 8 x 8 x 64; one thread per chunk that walked
-// all H*W pixels (a serial chain of 64 loads, 8 threads an image) took 24 us for both.
-template <typename T>
-__global__ __launch_bounds__(256) void gap_fwd_kernel(const char* x, char* y, int HW, int C) {
+// Global average pool. A workgroup is (16-byte channel chunks of a pixel, row-lanes, images): the row-lanes of an image take
+// every blockDim.y-th pixel and their partial sums are folded through LDS in a fixed order (blockIdx.y: chunks beyond the
+// workgroup's). fp32 sums keep the order of the pixels, so there a lane walks all of them (ROWS false).
+// Bound by latency while images are few, then by HBM. us, one thread per chunk that walks all pixels / one workgroup per
+// image / here: bf16 8 x 8 x 64, 194 images 11 / 3.9 / 4.0; 2 x 2 x 16, 8192 images 2.9 / 40 / 2.7 (an image's 128
+// row-lanes had four pixels); fp32 8 x 8 x 64, 194 images 8.8 / 8.2 / 8.1, 8192 images 22 / 77 / 22 (16 of 256 lanes were in use).
+template <typename T, bool ROWS>
+__global__ __launch_bounds__(256) void gap_fwd_kernel(const char* x, char* y, int N, int HW, int C) {
   constexpr int CE = Chunk<T>::CE;
-  __shared__ float red[256 * CE];
-  const int chunks = C / CE, n = blockIdx.x;
-  const int per = chunks < 256 ? chunks : 256;  // chunks handled side by side
-  const int rows = sizeof(T) == 4 ? 1 : 256 / per;  // fp32 sums keep the order of the pixels
-  const int cl = threadIdx.x % per, r = threadIdx.x / per;
-  const float inv = 1.f / (float)HW;
-  for (int c0 = 0; c0 < chunks; c0 += per) {  // one trip up to 256 chunks
-    const int ch = c0 + cl;
-    Chunk<T> c;
-    float acc[CE];
+  const int per = blockDim.x, rows = ROWS ? blockDim.y : 1, r = ROWS ? threadIdx.y : 0;
+  const int ch = blockIdx.y * per + threadIdx.x, n = blockIdx.x * blockDim.z + threadIdx.z;
+  const bool ok = n < N && ch < C / CE;
+  Chunk<T> c;
+  float acc[CE];
 #pragma unroll
-    for (int e = 0; e < CE; ++e) acc[e] = 0.f;
-    if (r < rows && ch < chunks) {
-#pragma unroll(sizeof(T) == 4 ? 16 : 4)
-      for (int q = r; q < HW; q += rows) {
-        c.load(x + (((size_t)n * HW + q) * C + (size_t)ch * CE) * sizeof(T));
+  for (int e = 0; e < CE; ++e) acc[e] = 0.f;
+  if (ok) {
+#pragma unroll(ROWS ? 4 : 16)
+    for (int q = r; q < HW; q += rows) {
+      c.load(x + (((size_t)n * HW + q) * C + (size_t)ch * CE) * sizeof(T));
 #pragma unroll
-        for (int e = 0; e < CE; ++e) acc[e] += c.f[e];
-      }
+      for (int e = 0; e < CE; ++e) acc[e] += c.f[e];
     }
-#pragma unroll
-    for (int e = 0; e < CE; ++e) red[e * 256 + threadIdx.x] = acc[e];
-    __syncthreads();
-    if (r == 0 && ch < chunks) {
-      for (int j = 1; j < rows; ++j)
-#pragma unroll
-        for (int e = 0; e < CE; ++e) acc[e] += red[e * 256 + j * per + cl];
-#pragma unroll
-      for (int e = 0; e < CE; ++e) c.f[e] = acc[e] * inv;
-      c.store(y + ((size_t)n * C + (size_t)ch * CE) * sizeof(T));
-    }
-    __syncthreads();
   }
+  if constexpr (ROWS) {
+    __shared__ float red[256 * CE];
+    const int at = (threadIdx.z * rows + r) * per + threadIdx.x;
+#pragma unroll
+    for (int e = 0; e < CE; ++e) red[e * 256 + at] = acc[e];
+    __syncthreads();
+    if (r != 0) return;
+    for (int j = 1; j < rows; ++j)
+#pragma unroll
+      for (int e = 0; e < CE; ++e) acc[e] += red[e * 256 + at + j * per];
+  }
+  if (!ok) return;
+  const float inv = 1.f / (float)HW;
+#pragma unroll
+  for (int e = 0; e < CE; ++e) c.f[e] = acc[e] * inv;
+  c.store(y + ((size_t)n * C + (size_t)ch * CE) * sizeof(T));
 }
 
 template <typename T>
@@ -589,7 +589,20 @@ void launch_maxpool_bwd(int dt, const void* dy, const void* x, void* dx, int N, 
 }
 
 void launch_gap_fwd(int dt, const void* x, void* y, int N, int HW, int C, hipStream_t s) {
-  DDS_DISPATCH(dt, gap_fwd_kernel, <<<N, 256, 0, s>>>((const char*)x, (char*)y, HW, C));
+  const int chunks = C / dtype_ce(dt);
+  if (dt == DT_F32) {  // one image a workgroup up to 1023 images, then as many as fill a wave
+    const int per = chunks < 256 ? chunks : 256, most = per < 64 ? 64 / per : 1, want = N / 512;
+    const int imgs = want < 1 ? 1 : want < most ? want : most;
+    gap_fwd_kernel<float, false><<<dim3(blocks_for(N, imgs), blocks_for(chunks, per)), dim3(per, 1, imgs), 0, s>>>((const char*)x, (char*)y, N, HW, C);
+    return;
+  }
+  // a row-lane for every pixel as long as the launch has less than 2^18 lanes: each one more is one more term to fold
+  const int per = chunks < 256 ? chunks : 256;
+  const long long want = (1ll << 18) / ((long long)N * chunks);
+  int rows = 256 / per < HW ? 256 / per : HW;
+  if (rows > want) rows = want < 1 ? 1 : (int)want;
+  const int imgs = 256 / (per * rows);
+  gap_fwd_kernel<bf16_t, true><<<dim3(blocks_for(N, imgs), blocks_for(chunks, per)), dim3(per, rows, imgs), 0, s>>>((const char*)x, (char*)y, N, HW, C);
 }
 
 void launch_gap_bwd(int dt, const void* dy, const void* x, void* dx, int N, int HW, int C, int relu_mask, hipStream_t s) {

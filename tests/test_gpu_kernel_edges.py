@@ -28,6 +28,18 @@ def test_global_average_pool_chunk_and_pixel_remainders(c, hw, B):
                       precision="f32", lr=0.05, momentum=0.0, steps=2), seed=21, T=2, every_step=True, tiny=True)
 
 
+@pytest.mark.parametrize("precision,c,hw,B", [
+    ("bf16", 8, 1, 3), ("bf16", 24, 2, 5), ("bf16", 40, 7, 9), ("bf16", 2056, 3, 2), ("bf16", 16, 2, 700), ("bf16", 72, 4, 1900),
+    ("f32", 12, 2, 600), ("f32", 4, 3, 5000)])
+def test_global_average_pool_lanes_per_image(precision, c, hw, B):
+    # bf16: one pixel, row-lanes that do not fill the workgroup, more chunks than a workgroup, more images than lanes allow a
+    # row-lane per pixel; fp32: several images a wave, images past the last
+    ops = [{"op": "conv", "cin": 3, "cout": c, "k": 1, "stride": 1, "pad": 0}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
+    _compare(Workload(name=f"gap_lanes_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
+                      precision=precision, lr=0.05, momentum=0.0, steps=2), seed=29, T=2, every_step=True, tiny=precision == "f32")
+
+
 @pytest.mark.parametrize("W,B", [(2, 7), (3, 8), (2, 31), (5, 32)])
 def test_mixing_update_ranges_by_split_count(W, B):
     # 7 / 8 / 31 / 32 splits per data-group: both sides of the lines between 256-, 64- and 32-element ranges
