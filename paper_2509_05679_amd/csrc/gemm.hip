@@ -1856,12 +1856,13 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
 // channels, [pixel][128 bytes], copied global -> LDS (two slots), of which 32 consecutive lanes read 32 consecutive channels of a
 // pixel with no conflict and a constant offset per step. Lane l of wave w always copies pixel 8 w + l / 8 of a tile,
 // 16 bytes of one tap per panel: one image position per lane and tile, stepped without a division. Any kernel size,
-// stride, image size and batch; linear layers are the 1x1 case. The bias gradient is
-// the product with a column of ones. Pixels are summed in the order of wgrad_gemm_kernel (pairs four apart).
-// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers
-// the fp32 CNN takes 15.3 instead of 15.9 ms per 8 iterations (14.4 with the bias gradient summed on the vector unit and splits
-// free of the pixel count, whose sums differ in the last bits), alone about 226 / 200 / 184 us for its wide layers (280 / 280 /
-// 233) and 63 us for the 3-channel stem (157).
+// stride, image size and batch; linear layers are the 1x1 case. The bias gradient is the product with a column of ones,
+// in the first column of workgroups: each of its waves adds one 32-row block of it to its four (two) products. (With
+// both blocks on one wave that wave issued six instructions for four, and the workgroup waited for it: 349 / 306 / 231 us
+// for the wide layers of the fp32 CNN, 512 images.) Pixels are summed in the order of wgrad_gemm_kernel (pairs four apart).
+// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers, alone:
+// 281 / 280 / 232 -> 252 / 239 / 198 us for those layers, 157 -> 85 us for the 3-channel stem; the fp32 CNN takes 14.6 instead of
+// 15.9 ms per 8 iterations.
 struct Wgrad32Geom {
   int sw, sh, si;         // 32 pixels = si images + sh rows + sw columns of the output grid
 };
@@ -1921,16 +1922,17 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
   fill(0);
 
   const int l32 = (lane >> 5) * 512 + (lane & 31) * 4;  // steps pair pixels 8 i + j and 8 i + 4 + j; channel lane % 32
-  const bool bias_wave = blockIdx.y == 0 && wave_n == 0;
-  f32x16_t acc[NI][NJ], accb[NI];
+  const int bias_block = NI > 1 ? wave_n : 0;  // the 32-row block whose bias gradient this wave sums
+  const bool bias_wave = blockIdx.y == 0 && wave_n < NI;
+  f32x16_t acc[NI][NJ], accb;
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
+  for (int e = 0; e < 16; ++e) {
+    accb[e] = 0.f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      accb[i][e] = 0.f;
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) acc[i][j][e] = 0.f;
-    }
+  }
   for (int t = 0; t < ntiles; ++t) {
     wait_vm<0>();
     wg_barrier();
@@ -1945,11 +1947,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
 #pragma unroll
       for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        if (bias_wave) accb[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], 1.f, accb[i], 0, 0, 0);
-      }
+      if (bias_wave) accb = __builtin_amdgcn_mfma_f32_32x32x2f32(bias_block == 0 ? a[0] : a[NI - 1], 1.f, accb, 0, 0, 0);
     }
   }
   wait_vm<0>();
@@ -1967,12 +1968,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
         if (m < p.Mout && n < p.NK) out[(size_t)m * p.NK + n] = p.alpha * acc[i][j][e];
       }
     }
-    if (bias_wave && (lane & 31) == 0) {
+  }
+  if (bias_wave && (lane & 31) == 0) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = mb + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-        if (m < p.Mout) out[(size_t)p.Mout * p.NK + m] = p.alpha * accb[i][e];
-      }
+    for (int e = 0; e < 16; ++e) {
+      const int m = m0 + (wave_m * NI + bias_block) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      if (m < p.Mout) out[(size_t)p.Mout * p.NK + m] = p.alpha * accb[e];
     }
   }
 }

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void gap_fwd_kernel(const char* x, char* y, in
 #pragma unroll
   for (int e = 0; e < CE; ++e) acc[e] = 0.f;
   if (ok) {
-#pragma unroll(ROWS ? 4 : 16)
+#pragma unroll ROWS ? 4 : 16
     for (int q = r; q < HW; q += rows) {
       c.load(x + (((size_t)n * HW + q) * C + (size_t)ch * CE) * sizeof(T));
 #pragma unroll
