@@ -1008,9 +1008,12 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
   if (sizeof(T) == 4 && (ilog2_exact(p.H) < 0 || ilog2_exact(p.W) < 0 || p.W > 32 || p.H * p.W < 16)) return false;
   // small images: 128-pixel tiles give more workgroups. 256-pixel tiles from 256 workgroups up (one per CU: half the
   // weight copies per FLOP; with the other modules' kernels sharing the chip this beat two 128-pixel workgroups per
-  // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step)
+  // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step). In fp32, where a launch is long enough for its own, 128 columns
+  // wide they wait for a second one per CU: 256 tiles of 512 channels at 4 x 4 2.26 -> 2.00 ms per step (launch 611 -> 588 us),
+  // of 96 channels 0.62 -> 0.52 ms, 384 of 128 channels at 8 x 8 1.05 -> 0.99 ms (329 -> 265 us); 512 tiles the other way, 2.29 against
+  // 2.40 ms at 256 channels. (64 columns wide a 128 x 128 tile would multiply half padding: 285 against 392 us per step.)
   const long long tiles256 = (long long)((p.M + 255) / 256) * ((p.ldy + 127) / 128);
-  if (tiles256 >= 256) {
+  if (tiles256 >= (sizeof(T) == 4 && p.ldy > 64 ? 512 : 256)) {
     if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, s)) return true;
     if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
   }

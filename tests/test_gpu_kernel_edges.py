@@ -100,6 +100,12 @@ def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
     _compare(_conv_chain(precision, widths, h, w, W, B), seed=26, T=2, every_step=precision == "f32", tiny=precision == "f32")
 
 
+@pytest.mark.parametrize("B", [4095, 8191])
+def test_fp32_conv3x3_tiles_by_pixel_count(B):
+    # 256 and 512 tiles of 256 pixels x 128 columns, the last one ragged: 128- and 256-pixel tiles
+    _compare(_conv_chain("f32", (32, 96), 4, 4, 1, B), seed=32, T=2, every_step=True, tiny=True)
+
+
 def _stride2_net(c1, c2, k, h, w, W, B, precision="bf16"):
     ops = [{"op": "conv", "cin": 3, "cout": c1, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
            {"op": "conv", "cin": c1, "cout": c2, "k": k, "stride": 2, "pad": k // 2}, {"op": "relu"},
