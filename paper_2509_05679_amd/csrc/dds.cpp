@@ -667,6 +667,19 @@ int layout(dds_ctx& c, Arena& A) {
   return DDS_OK;
 }
 
+// Mean work of the module's weight gradients that have an input gradient to run beside.
+double overlapped_wgrad_flops(const dds_ctx& c, const Module& m) {
+  double flops = 0.0;
+  int launches = 0;
+  for (const Node& nd : m.nodes) {
+    if (nd.kind != N_CONV || nd.gin == G_NONE) continue;
+    const ParamLayer& L = m.layers[nd.layer];
+    flops += 2.0 * c.N * m.tensors[nd.out].H * m.tensors[nd.out].W * L.Cout * L.Cin * L.RS;
+    ++launches;
+  }
+  return launches > 0 ? flops / launches : 0.0;
+}
+
 int build(dds_ctx& c, const dds_spec* sp, int K, int W, const int* delays) {
   if (!sp || !sp->layers || !sp->bounds) return fail(DDS_EINVAL, "null spec");
   if (K < 1 || K > 64) return fail(DDS_EINVAL, "K=%d out of range [1,64]", K);
@@ -1155,10 +1168,15 @@ int dds_create(const dds_spec* spec, int K, int W, const int* delays, void* aren
   if (e != hipSuccess) { dds_destroy(c); return fail(DDS_EHIP, "hipEventCreate failed: %s", hipGetErrorString(e)); }
   int nq = 4;
   if (const char* q = getenv("GPU_MAX_HW_QUEUES")) { const int v = atoi(q); if (v >= 1 && v <= 32) nq = v; }
-  if (K == 1 && nq >= 2) {
-    // A single module has no other module's kernels beside it: its weight gradients get a stream. (ResNet-20, one
-    // data-group of 194: 690 -> 655 us per step. With two modules the events cost what the overlap gains: 1.97 ->
-    // 2.05 ms per 8 steps of the 28 x 28 net, 13.5 -> 13.7 ms of the normalised ResNet-20.)
+  if (K == 1 && nq >= 2 && overlapped_wgrad_flops(*c, c->mods[0]) >= (c->dt == DT_F32 ? 0.4e9 : 1e9)) {
+    // A single module has no other module's kernels beside it: its weight gradients get a stream, if they are long enough.
+    // A launch on the side costs two event calls, 11 to 17 us on the host (which is what the ranges below come from) and 4 us
+    // between the kernels. us per step with and without, at a mean of so many GFLOP: bf16 ResNet-18 of 1.0 633 / 660, of 0.5
+    // 563-601 / 571, of 8.2 1213 / 1285; ResNet-20 of 1.1 603-623 / 613, of 0.8 564-626 / 580, of 0.07 470-618 / 402; ResNet-56 of 2.3
+    // 2113-2177 / 2358, of 0.6 1209-1542 / 1291; fp32 CNN of 0.9 958 / 979, of 0.5 945 / 943, of 0.2 924 / 910. Nets of nine layers
+    // pay up to twice the line (28 x 28 images, 2.2: 309 / 295).
+    // (With two modules the events cost what the overlap gains: 1.97 -> 2.05 ms per 8 steps of the 28 x 28 net, 13.5 -> 13.7 ms of
+    // the normalised ResNet-20.)
     Module& m = c->mods[0];
     e = hipStreamCreateWithFlags(&m.wstream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&m.wfork, hipEventDisableTiming);

@@ -132,9 +132,10 @@ def test_weight_gradients_of_any_image_size_fp32(c1, c2, k, h, w, W, B):
     _compare(_stride2_net(c1, c2, k, h, w, W, B, "f32"), seed=28, T=2, every_step=True, tiny=True)
 
 
-@pytest.mark.parametrize("name,B,steps", [("paper_r20_S1K1", 194, 20), ("paper_r20_S1K1", 7, 40)])
+@pytest.mark.parametrize("name,B,steps", [("paper_r20_S1K1", 194, 20), ("paper_r20_S1K1", 7, 40), ("paper_r20_S4K1", 96, 20)])
 def test_single_module_beside_its_weight_gradients_is_bit_identical(name, B, steps):
-    # one module: weight gradients on a stream of their own, against everything on the caller's stream
+    # one module: weight gradients on a stream of their own where they are long enough (the third case, 1.6 GFLOP on average),
+    # against everything on the caller's stream
     from test_gpu_limits import test_run_ahead_across_iterations_is_bit_identical_to_serial_execution as compare
     compare(name, B, steps)
 
