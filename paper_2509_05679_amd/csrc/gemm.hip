@@ -1032,8 +1032,9 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
 // the tap leaves the image) and BN weight rows, two stages ahead in three slots. Which pixel a tile row is, and where
 // its taps start, is worked out once per workgroup into a table in LDS.
 // S2 (dgrad of a stride-2 layer): output pixels are dealt to workgroups by parity class (h % 2, w % 2), blockIdx.x =
-// class * tiles_per_class + tile, the class with the most taps first; a class walks only the taps of its parity (4, 2, 2 and 1 of
-// nine), class (0, 0) also a folded 1x1 shortcut (x2, w2).
+// turn * tiles_per_class + tile, the class with the most taps first; a class walks only the taps of its parity (4, 2, 2 and 1 of
+// nine; 1, 0, 0 and 0 of a 1x1 kernel, whose one class with work launched last made its fp32 launch of 131072 x 256 outputs from 512
+// channels 136 us instead of about 102), class (0, 0) also a folded 1x1 shortcut (x2, w2).
 // Bound by the copies and the barrier of short reductions. Alone against conv_gemm_kernel (operands staged through
 // registers, outputs stored 8 bytes at a time), ResNet-18 shapes, 512 images: input gradients of the stride-2 layers
 // 91 / 67 / 71 -> 54 / 42 / 46 us, their forward passes with the 1x1 shortcuts 50 / 40 / 58 -> 40 / 33 / 39 us.
@@ -1063,11 +1064,12 @@ __global__ __launch_bounds__(256 * KS, 2) void conv_gather_kernel(ConvParams p_,
   const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave = wave_wg & 3, khalf = wave_wg >> 2;
   const int wave_m = wave % (BM / WM), wave_n = wave / (BM / WM);
-  const int cls = S2 ? 3 - (int)blockIdx.x / g.tiles_per_class : 0;
+  const int turn = S2 ? (int)blockIdx.x / g.tiles_per_class : 0;
+  const int cls = S2 ? (p.pad & 1 ? 3 - turn : turn) : 0;  // most taps first: odd rows and columns if pad is odd
   const int ch = cls >> 1, cw = cls & 1;
   const int Hc = S2 ? (p.Ho - ch + 1) >> 1 : p.Ho, Wc = S2 ? (p.Wo - cw + 1) >> 1 : p.Wo;  // this class's output grid
   const int Mc = p.Nimg * Hc * Wc;
-  const int m0 = (S2 ? (int)blockIdx.x - (3 - cls) * g.tiles_per_class : (int)blockIdx.x) * BM, n0 = blockIdx.y * BN;
+  const int m0 = ((int)blockIdx.x - turn * g.tiles_per_class) * BM, n0 = blockIdx.y * BN;
   if (m0 >= Mc) return;  // the classes of an odd-sized grid differ
   if (p.nrep > 1) {  // the launcher made sure that a tile never straddles two data-groups
     const int r = min(m0 / (Mc / p.nrep), p.nrep - 1);

@@ -124,6 +124,17 @@ def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
 
 
+@pytest.mark.parametrize("precision", ["f32", "bf16"])
+@pytest.mark.parametrize("k,pad,h,w", [(1, 0, 7, 6), (2, 0, 6, 9), (2, 1, 7, 7), (3, 0, 9, 8), (5, 2, 8, 5)])
+def test_stride2_input_gradients_by_padding(precision, k, pad, h, w):
+    # which parity class of the input gradient has the most taps (and is launched first) depends on the padding
+    ops = [{"op": "conv", "cin": 3, "cout": 32, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
+           {"op": "conv", "cin": 32, "cout": 64, "k": k, "stride": 2, "pad": pad}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": 64, "cout": 10}, {"op": "softmax_ce"}]
+    _compare(Workload(name=f"stride2_k{k}_pad{pad}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=37, in_shape=(3, h, w), classes=10,
+                      precision=precision, lr=0.05, momentum=0.0, steps=2), seed=33, T=2, every_step=precision == "f32", tiny=precision == "f32")
+
+
 @pytest.mark.parametrize("c1,c2,k,h,w,W,B", [
     (16, 36, 3, 7, 9, 2, 3), (32, 64, 1, 8, 8, 2, 9), (68, 132, 3, 13, 14, 1, 3), (16, 16, 3, 2, 88, 1, 1),
     (12, 16, 3, 1, 3, 3, 33)])
