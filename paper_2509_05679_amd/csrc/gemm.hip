@@ -8,6 +8,7 @@
 // pairing of k indices inside an instruction is consistent by construction.
 #include <cstdlib>
 
+#include "device_once.h"
 #include "kernels.h"
 
 namespace dds {
@@ -934,6 +935,13 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel, khalf == 0);
 }
 
+// Lets a kernel have all 160 KB of LDS on the current device. A failure is the launch's to report.
+inline void allow_whole_lds(DeviceOnce& once, const void* kernel) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return;
+  once(device, [kernel] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess; });
+}
+
 inline int ilog2_exact(int v) {
   int l = 0;
   while ((1 << l) < v) ++l;
@@ -961,11 +969,8 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   g.out_bytes = operands;
   const int smem = operands + 1024 + 256;
   if (smem > 160 * 1024) return false;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    attr_set = true;
-  }
+  static DeviceOnce lds;
+  allow_whole_lds(lds, (const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS>);
   dim3 grid((p.M + BM - 1) / BM, (p.ldy + BN - 1) / BN);
   conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS><<<grid, 64 * KS * NW, smem, s>>>(p, g);
   return true;
@@ -1227,11 +1232,8 @@ bool launch_gather_inst(const ConvParams& p, hipStream_t s) {
   constexpr int slots = KS * 3 * (BM + BN) * 64, tile = BM * BN * (int)sizeof(T);
   g.out_bytes = slots < tile && tile <= 72 * 1024 ? tile : slots;
   const int smem = g.out_bytes + 1024 + BM * 12;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)conv_gather_kernel<T, BM, BN, WM, WN, S2, KS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    attr_set = true;
-  }
+  static DeviceOnce lds;
+  allow_whole_lds(lds, (const void*)conv_gather_kernel<T, BM, BN, WM, WN, S2, KS>);
   dim3 grid((S2 ? 4 : 1) * g.tiles_per_class, (p.ldy + BN - 1) / BN);
   conv_gather_kernel<T, BM, BN, WM, WN, S2, KS><<<grid, 256 * KS, smem, s>>>(p, g);
   return true;
@@ -2068,11 +2070,8 @@ template <int TWLOG, int THLOG, bool S2>
 void launch_wgrad_dma_inst(const WgradParams& p, const WgradGeom& wg, int nsub, hipStream_t s) {
   constexpr int TW = 1 << TWLOG, TH = 1 << THLOG;
   constexpr int PROW = ((128 / (TW * TH)) * (TH + 2) * (TW + 2) + 7) / 8 * 8;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)wgrad_dma_kernel<TWLOG, THLOG, S2>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    attr_set = true;
-  }
+  static DeviceOnce lds;
+  allow_whole_lds(lds, (const void*)wgrad_dma_kernel<TWLOG, THLOG, S2>);
   const int smem = 2 * (16384 + PROW * 128) + 1024;  // RING slots + dump block
   dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
   wgrad_dma_kernel<TWLOG, THLOG, S2><<<grid, S2 ? 256 : 768, smem, s>>>(p, wg, p.zeros);
@@ -2147,12 +2146,9 @@ bool launch_wgrad_flat(const WgradParams& p, hipStream_t s) {
   int nsub = 1;
   if (p.nrep < 1 || p.nsplit % p.nrep != 0 || !wgrad_flat_geometry(p, p.nrep, wg, nsub)) return false;
   if (p.nsplit / p.nrep > wg.rep_tiles) return false;  // no empty split
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)wgrad_flat_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    (void)hipFuncSetAttribute((const void*)wgrad_flat_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    attr_set = true;
-  }
+  static DeviceOnce lds[2];
+  allow_whole_lds(lds[0], (const void*)wgrad_flat_kernel<false>);
+  allow_whole_lds(lds[1], (const void*)wgrad_flat_kernel<true>);
   const int smem = 2 * (16384 + wg.patch_rows * 128);
   dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
   if (p.stride == 2) wgrad_flat_kernel<true><<<grid, 256, smem, s>>>(p, wg);

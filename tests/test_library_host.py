@@ -190,3 +190,48 @@ def test_batchnorm_spec_validation_and_arena():
         with pytest.raises(P.DdsError) as e:
             P.dds_arena_bytes(_spec(bad, [0, len(bad)]), 1, 2)
         assert e.value.code == code
+
+
+_DEVICE_ONCE = r"""
+#include "device_once.h"
+#include <cstdio>
+#include <thread>
+#include <vector>
+int main() {
+  dds::DeviceOnce once;
+  std::atomic<int> runs[3] = {{0}, {0}, {0}};
+  auto act = [&](int d) { return once(d, [&, d] { ++runs[d]; return true; }); };
+  if (!act(0) || !act(0) || runs[0] != 1) return 1;             // once on a device
+  if (!act(1) || runs[1] != 1 || !act(0) || runs[0] != 1) return 2;  // and once on the next one
+  int tries = 0;
+  auto fails_first = [&] { return ++tries > 1; };
+  if (once(2, fails_first) || !once(2, fails_first) || !once(2, fails_first) || tries != 2) return 3;
+  if (!once(64, fails_first) || !once(64, fails_first) || tries != 4) return 4;  // no bit of its own
+  dds::DeviceOnce shared;
+  std::atomic<int> done{0};
+  std::vector<std::thread> threads;
+  for (int i = 0; i < 16; ++i)
+    threads.emplace_back([&, i] { if (shared(i % 4, [&] { return true; })) ++done; });
+  for (auto& t : threads) t.join();
+  return done == 16 ? 0 : 5;
+}
+"""
+
+
+def test_device_once_runs_on_every_device_and_again_after_a_failure(tmp_path):
+    # what raises the LDS limit of a kernel: per device and not per process, and not forgotten when it fails
+    import subprocess
+    src = tmp_path / "once.cpp"
+    src.write_text(_DEVICE_ONCE)
+    exe = tmp_path / "once"
+    subprocess.run(["g++", "-std=c++17", "-pthread", "-I", os.path.join(ROOT, "paper_2509_05679_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    assert subprocess.run([str(exe)]).returncode == 0
+
+
+def test_no_kernel_attribute_is_remembered_per_process():
+    csrc = os.path.join(ROOT, "paper_2509_05679_amd", "csrc")
+    for name in os.listdir(csrc):
+        text = open(os.path.join(csrc, name)).read()
+        assert not re.search(r"static\s+bool", text), name
+        assert text.count("hipFuncSetAttribute(") <= (1 if name == "gemm.hip" else 0), name
