@@ -95,8 +95,8 @@ def _conv_chain(precision, widths, h, w, W, B):
     ("bf16", (64, 192, 256, 200), 4, 4, 2, 5), ("bf16", (32, 64), 3, 96, 1, 2), ("bf16", (64, 128), 2, 160, 1, 2), ("f32", (32, 32, 64), 13, 3, 2, 7),
     ("f32", (16, 48, 32), 6, 10, 2, 3)])
 def test_conv3x3_image_sizes(precision, widths, h, w, W, B):
-    # images whose rows and planes are no power of two, tiles that hold many images or end inside one, patches on both
-    # sides of the most rows a launch can fetch (W = 47 / 95 / 159)
+    # images whose rows and planes are no power of two, tiles that hold many images or end inside one; W = 95 / 96: both sides of the
+    # longest rows of the 256 x 64 tiles of one 64-byte chunk (the other tiles' limits: test_conv3x3_longest_rows_of_each_tile)
     _compare(_conv_chain(precision, widths, h, w, W, B), seed=26, T=2, every_step=precision == "f32", tiny=precision == "f32")
 
 
@@ -120,7 +120,7 @@ def _stride2_net(c1, c2, k, h, w, W, B, precision="bf16"):
     (32, 64, 3, 28, 30, 1, 3), (72, 136, 3, 3, 2, 2, 65), (96, 160, 3, 5, 4, 2, 3), (128, 256, 1, 4, 4, 1, 7), (8, 8, 1, 1, 5, 2, 30), (16, 16, 3, 2, 178, 1, 1)])
 def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     # odd sides, batches that are no whole 128-pixel tiles, channel counts off the 64-channel blocks, a single image
-    # row, data-groups of less than a tile, the longest rows
+    # row, data-groups of less than a tile, long rows
     _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
 
 
@@ -139,7 +139,7 @@ def test_stride2_input_gradients_by_padding(precision, k, pad, h, w):
     (16, 36, 3, 7, 9, 2, 3), (32, 64, 1, 8, 8, 2, 9), (68, 132, 3, 13, 14, 1, 3), (16, 16, 3, 2, 88, 1, 1),
     (12, 16, 3, 1, 3, 3, 33)])
 def test_weight_gradients_of_any_image_size_fp32(c1, c2, k, h, w, W, B):
-    # channel counts off the 32-channel panels and 64-channel blocks, partial tiles, the longest rows
+    # channel counts off the 32-channel panels and 64-channel blocks, partial tiles, rows of more than one tile
     _compare(_stride2_net(c1, c2, k, h, w, W, B, "f32"), seed=28, T=2, every_step=True, tiny=True)
 
 
@@ -194,3 +194,38 @@ def test_fp32_sums_of_a_linear_layer_do_not_depend_on_its_rows(feat, out, below,
         rows.append(stored[:below].copy())
         tr.close()
     assert np.abs(rows[0]).max() > 0 and np.array_equal(rows[0], rows[1])
+
+
+@pytest.mark.parametrize("widths,h,w,W,B", [
+    ((64, 64), 15, 13, 1, 90),    # 17550 pixels: 256 x 64 tiles of 128-byte rows, odd sides, the last tile ragged
+    ((64, 64), 5, 47, 1, 70),     # ... the longest rows they fetch
+    ((64, 64), 5, 48, 1, 69),     # one more: 256 x 64 tiles of 64-byte rows
+    ((64, 128), 3, 159, 1, 1),    # 128 x 128 tiles, the longest rows (160: conv_gather_kernel, above)
+    ((128, 128), 3, 75, 1, 2),    # 64 x 64 tiles with a shared reduction, the longest rows
+    ((128, 128), 3, 76, 1, 2),    # one more: 128 x 128 tiles
+    ((64, 64), 2, 190, 1, 2),     # weight gradient on padded positions, the longest rows
+    ((64, 64), 2, 191, 1, 2),     # one more: wgrad_gemm_kernel
+])
+def test_conv3x3_longest_rows_of_each_tile(widths, h, w, W, B):
+    _compare(_conv_chain("bf16", widths, h, w, W, B), seed=34, T=2)
+
+
+@pytest.mark.parametrize("w", [764, 766])
+def test_stride2_weight_gradients_longest_rows(w):
+    # 382 and 383 output columns: wgrad_flat_kernel and wgrad_gemm_kernel
+    _compare(_stride2_net(16, 16, 3, 2, w, 1, 2), seed=35, T=2)
+
+
+def test_shared_reductions_with_weights_per_data_group():
+    # four data-groups of 256 or more pixels in one launch of few tiles: both kernels whose 64 x 64 tiles two halves of a workgroup
+    # share, forward and input gradients (3x3 at 8 x 8 and 4 x 4, stride 2 with the folded shortcut)
+    from test_gpu_gossip import _compare as compare_gossip
+    ops = [{"op": "conv", "cin": 3, "cout": 128, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
+           {"op": "conv", "cin": 128, "cout": 128, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
+           {"op": "res_begin"}, {"op": "conv", "cin": 128, "cout": 256, "k": 3, "stride": 2, "pad": 1}, {"op": "relu"},
+           {"op": "conv", "cin": 256, "cout": 256, "k": 3, "stride": 1, "pad": 1},
+           {"op": "res_add", "scale": 1.0, "shortcut": {"cin": 128, "cout": 256, "k": 1, "stride": 2, "pad": 0}}, {"op": "relu"},
+           {"op": "gap"}, {"op": "linear", "cin": 256, "cout": 10}, {"op": "softmax_ce"}]
+    wl = Workload(name="shared_reductions", ops=ops, bounds=[0, 4, len(ops)], K=2, W=4, B=16, in_shape=(3, 8, 8), classes=10,
+                  precision="bf16", lr=0.05, momentum=0.0, steps=4)
+    compare_gossip(wl, seed=36, T=4, mixing=ring_mixing(4, 0.3), tiny=False)
