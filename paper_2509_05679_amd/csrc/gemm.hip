@@ -1,11 +1,20 @@
-// MFMA implicit-GEMM kernels for gfx950: convolution / linear forward and dgrad
-// (one kernel, two gather modes) and wgrad with a split pixel reduction.
+// MFMA implicit-GEMM kernels for gfx950: convolution / linear forward and input gradient, and weight gradients with a
+// split pixel reduction. Operands of the first two kernels of each list are copied global -> LDS without passing through registers.
+//   forward and input gradient: conv3x3_dma_kernel (3x3 stride 1), conv_gather_kernel (any other layer of whole 64-byte
+//     channel chunks), conv_gemm_kernel (the rest, e.g. the 3-channel stem)
+//   weight gradient, bf16: wgrad_dma_kernel (sides that are powers of two, whole 128-pixel tiles), wgrad_flat_kernel (other
+//     sizes), wgrad_gemm_kernel (the rest); fp32: wgrad_f32_kernel
+// (Plain products of few rows: linear.hip. 16-channel layers: narrow.hip.)
 //
-// Both kernels stage K-contiguous operand tiles in LDS ([row][k], 16-byte padded
-// rows) and feed v_mfma_f32_32x32x16_bf16 (bf16) or v_mfma_f32_32x32x2_f32 (fp32)
-// with one 16-byte LDS read per operand fragment. Lanes 0-31 read the first 16
-// bytes of a 32-byte k-step and lanes 32-63 the second, for A and B alike, so the
+// Operand tiles are K-contiguous in LDS ([row][k]; wgrad_dma_kernel, wgrad_flat_kernel and wgrad_f32_kernel keep [pixel][channel])
+// and feed v_mfma_f32_32x32x16_bf16 (bf16) or v_mfma_f32_32x32x2_f32 (fp32) with one 16-byte LDS read per operand fragment.
+// Lanes 0-31 read the first 16 bytes of a 32-byte k-step and lanes 32-63 the second, for A and B alike, so the
 // pairing of k indices inside an instruction is consistent by construction.
+//
+// fp32 sums keep one order per problem, whichever kernel or tile its size selects: a program's fp32 results change by single
+// ReLU decisions when the last bits of a sum do. That is why here and in linear.hip and misc.hip (update, pooling) some rules
+// name the type; see launch_dma, wgrad_choose_split, linear_kernel, gap_fwd_kernel and update_elems. (The mixing update of
+// misc.hip is not held to it: its sum runs over the row-lanes that the split count selects.)
 #include <cstdlib>
 
 #include "device_once.h"
@@ -20,21 +29,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 
 struct bf16_t { uint16_t v; };
-
-__device__ __forceinline__ float bf2f(uint16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);  // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-template <typename T> __device__ __forceinline__ float load_elem(const void* p, size_t i);
-template <> __device__ __forceinline__ float load_elem<float>(const void* p, size_t i) { return ((const float*)p)[i]; }
-template <> __device__ __forceinline__ float load_elem<bf16_t>(const void* p, size_t i) { return bf2f(((const uint16_t*)p)[i]); }
-template <typename T> __device__ __forceinline__ void store_elem(void* p, size_t i, float v);
-template <> __device__ __forceinline__ void store_elem<float>(void* p, size_t i, float v) { ((float*)p)[i] = v; }
-template <> __device__ __forceinline__ void store_elem<bf16_t>(void* p, size_t i, float v) { ((uint16_t*)p)[i] = f2bf(v); }
 
 template <typename T> __device__ __forceinline__ void mfma16B(const uint4& a, const uint4& b, f32x16_t& c);
 template <> __device__ __forceinline__ void mfma16B<bf16_t>(const uint4& a, const uint4& b, f32x16_t& c) {
@@ -1008,8 +1002,10 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
     if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
     return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
   }
-  // fp32 sums keep one order per shape: channels outermost where the sides are powers of two up to 32, else taps
-  // (conv_gather_kernel)
+  // fp32 sums of several chunks: channels outermost where the sides are powers of two up to 32, else taps outermost
+  // (conv_gather_kernel, as conv_gemm_kernel before it). This kernel would take such sides, too. Forward launches of a step, 7 x 7
+  // to 56 x 56: 128 and more channels 5-12 % faster (28 x 28, 128 channels, 32 images 117 -> 106 us), 64 channels slower below
+  // 100000 pixels (14 x 14, 194 images 74 -> 103 us). The order is kept.
   if (sizeof(T) == 4 && (ilog2_exact(p.H) < 0 || ilog2_exact(p.W) < 0 || p.W > 32 || p.H * p.W < 16)) return false;
   // small images: 128-pixel tiles give more workgroups. 256-pixel tiles from 256 workgroups up (one per CU: half the
   // weight copies per FLOP; with the other modules' kernels sharing the chip this beat two 128-pixel workgroups per
@@ -1039,7 +1035,7 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
 // S2 (dgrad of a stride-2 layer): output pixels are dealt to workgroups by parity class (h % 2, w % 2), blockIdx.x =
 // turn * tiles_per_class + tile, the class with the most taps first; a class walks only the taps of its parity (4, 2, 2 and 1 of
 // nine; 1, 0, 0 and 0 of a 1x1 kernel, whose one class with work launched last made its fp32 launch of 131072 x 256 outputs from 512
-// channels 136 us instead of about 102), class (0, 0) also a folded 1x1 shortcut (x2, w2).
+// channels 143 us instead of 109, the head's included), class (0, 0) also a folded 1x1 shortcut (x2, w2).
 // Bound by the copies and the barrier of short reductions. Alone against conv_gemm_kernel (operands staged through
 // registers, outputs stored 8 bytes at a time), ResNet-18 shapes, 512 images: input gradients of the stride-2 layers
 // 91 / 67 / 71 -> 54 / 42 / 46 us, their forward passes with the 1x1 shortcuts 50 / 40 / 58 -> 40 / 33 / 39 us.
@@ -1053,7 +1049,7 @@ template <typename T, int BM, int BN, int WM, int WN, bool S2, int KS>
 __global__ __launch_bounds__(256 * KS, 2) void conv_gather_kernel(ConvParams p_, GatherGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
-  constexpr int KB = 64, FROWS = 16, CPR = 4, NKS = 2;  // bytes of a row, rows of a 1 KiB fill, 16-byte columns, k-steps
+  constexpr int KB = 64, FROWS = 16, NKS = 2;  // bytes of a row (four 16-byte columns), rows of a 1 KiB fill, k-steps
   constexpr int AP = BM / FROWS / 4;                     // fills per wave and stage: gathered rows ...
   constexpr int RG = BN / FROWS, WL = RG >= 4 ? RG / 4 : 1;  // ... and weight rows (two waves copy the same ones if RG < 4)
   constexpr int SLOT = (BM + BN) * KB;
@@ -1484,16 +1480,13 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   constexpr int PROW = (IMGS * PP + 7) / 8 * 8;   // patch rows, whole 8-row fills
   constexpr int FY = (16 + NWV - 1) / NWV;        // dY fills per wave (16 per tile)
   constexpr int PF = (PROW / 8 + NWV - 1) / NWV;  // patch fills per wave
-  constexpr int NF = FY + PF;  // fills per lane per tile (surplus ones go to a dump block)
   constexpr int NT = S2 ? 4 : 3;                  // taps accumulated by one wave
+  // Two slots: tiles in flight in LDS (the next one is copied while this one is multiplied) keep a workgroup at 84 KB,
+  // so that a conv workgroup of another module fits on the same CU; a third slot (copies two tiles ahead,
+  // 126 KB) was 1-2 % slower per training step on every configuration although each launch alone was not.
   constexpr int SLOT = 16384 + PROW * 128;
   extern __shared__ __align__(16) char smem[];
   const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
-  // Tiles in flight in LDS. Two (the next tile is copied while this one is multiplied) keep a workgroup at 85 KB,
-  // so that a conv workgroup of another module fits on the same CU; a third slot (copies two tiles ahead,
-  // 127 KB) was 1-2 % slower per training step on every configuration although each launch alone was not.
-  constexpr int RING = 2;
-  const uint32_t lds_dump = lds_ring + RING * SLOT;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1565,24 +1558,21 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
     const bool yok = live_t && ycol_ok;
 #pragma unroll
     for (int u = 0; u < FY; ++u) {  // dY rows: tile pixel 8*(wave + NWV u) + l8
-      const bool live = live_t && wave + NWV * u < 16;  // wave-uniform
-      if (RING == 2 && !live) continue;  // only a fixed count of fills per tile (wait_vm<NF>) needs the surplus ones
-      dma16(yok && live ? ysrc + (size_t)u * (NWV * 8) * ybytes : zsrc, live ? base + (wave + NWV * u) * 1024 : lds_dump);
+      if (!(live_t && wave + NWV * u < 16)) continue;  // wave-uniform
+      dma16(yok ? ysrc + (size_t)u * (NWV * 8) * ybytes : zsrc, base + (wave + NWV * u) * 1024);
     }
 #pragma unroll
     for (int u = 0; u < PF; ++u) {  // patch rows
       const int wl = wave + NWV * u;
-      const bool live = live_t && wl < pw_total;  // wave-uniform
-      if (RING == 2 && !live) continue;
+      if (!(live_t && wl < pw_total)) continue;  // wave-uniform
       const int gh = h0 + (pflag[u] & 255) - 1;
-      const bool ok = live && xcol_ok && (pflag[u] >> 8) && (unsigned)gh < (unsigned)p.Ho;
-      dma16(ok ? xsrc + prel[u] : zsrc, live ? base + 16384 + wl * 1024 : lds_dump);
+      const bool ok = xcol_ok && (pflag[u] >> 8) && (unsigned)gh < (unsigned)p.Ho;
+      dma16(ok ? xsrc + prel[u] : zsrc, base + 16384 + wl * 1024);
     }
   };
 
-  // the first two tiles are requested before the rest of the set-up, which runs under their latency
+  // the first tile is requested before the rest of the set-up, which runs under its latency
   fill_tile(0, 0);
-  if (RING == 3) fill_tile(1, 1);
 
   // fragment addressing (see lds_tr16): lane -> (16-lane group, row inside the 4-row block, 8-byte segment)
   const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;
@@ -1629,17 +1619,16 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   const bool idle_wave = k0 + wave_m * 32 >= p.Mout || c0 + wave_n * 32 >= p.Cx;
 
   for (int t = 0; t < ntiles; ++t) {
-    if (RING == 3) wait_vm<NF>();  // everything but the youngest tile's fills has landed
-    else wait_vm<0>();
+    wait_vm<0>();
     wg_barrier();
-    fill_tile(t + RING - 1, (t + RING - 1) % RING);
-    uint32_t ybuf = lds_ring + (t % RING) * SLOT + a_lane;
+    fill_tile(t + 1, (t + 1) & 1);
+    uint32_t ybuf = lds_ring + (t & 1) * SLOT + a_lane;
     uint32_t bp[2][4];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        bp[hh][v] = lds_ring + (t % RING) * SLOT + 16384 + baddr[hh][v];
+        bp[hh][v] = lds_ring + (t & 1) * SLOT + 16384 + baddr[hh][v];
         // opaque: otherwise every (lane part + compile-time part) sum is precomputed outside the
         // tile loop, one register each, instead of riding in the instruction's offset field
         asm volatile("" : "+v"(bp[hh][v]));
@@ -2072,7 +2061,7 @@ void launch_wgrad_dma_inst(const WgradParams& p, const WgradGeom& wg, int nsub, 
   constexpr int PROW = ((128 / (TW * TH)) * (TH + 2) * (TW + 2) + 7) / 8 * 8;
   static DeviceOnce lds;
   allow_whole_lds(lds, (const void*)wgrad_dma_kernel<TWLOG, THLOG, S2>);
-  const int smem = 2 * (16384 + PROW * 128) + 1024;  // RING slots + dump block
+  const int smem = 2 * (16384 + PROW * 128);  // two slots
   dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
   wgrad_dma_kernel<TWLOG, THLOG, S2><<<grid, S2 ? 256 : 768, smem, s>>>(p, wg, p.zeros);
 }
@@ -2120,7 +2109,8 @@ int wgrad_s2_taps(int R, int (&sub)[4], int (&rmap)[2][2]) {
   return nsub;
 }
 
-// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size; nsplit and the pointers are not looked at.
+// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size; of nsplit and the pointers only `zeros` is
+// looked at.
 bool wgrad_flat_geometry(const WgradParams& p, int W, WgradFlatGeom& wg, int& nsub) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
   const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
@@ -2134,7 +2124,7 @@ bool wgrad_flat_geometry(const WgradParams& p, int W, WgradFlatGeom& wg, int& ns
   if (positions + 128 + 2 * wg.Q >= (1ll << 31) || (long long)p.Nimg * p.H * p.W >= (1ll << 31)) return false;
   wg.rep_tiles = (int)((positions + 127) / 128);
   wg.patch_rows = (128 + (s2 ? wg.Q + 1 : 2 * wg.Q + 2) + 7) / 8 * 8;
-  if (2 * (16384 + wg.patch_rows * 128) > 160 * 1024) return false;  // rows of at most 180 (stride 2: 360) pixels
+  if (2 * (16384 + wg.patch_rows * 128) > 160 * 1024) return false;  // rows of at most 190 (stride 2: 382) output pixels
   wg.dQ = make_divisor(wg.Q);
   wg.dH = make_divisor(p.Ho + 1);
   nsub = s2 ? wgrad_s2_taps(p.R, wg.sub, wg.rmap) : 1;
@@ -2228,6 +2218,8 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
     // 3.45 / 3.13 ms against 2.64 at 256 under an earlier stream layout; now 64 / 128 / 192 / 256 -> 2.59 / 2.47 /
     // 2.46 / 2.48 ms. With two modules (ResNet-20 shapes) 256 beats 128 (1.47 vs 1.67 ms): the caller passes 128
     // when three or more modules share the chip (half the partial-sum traffic at equal speed), else 256.
+    // wgrad_flat_kernel takes the same target: half of it 0.87-1.10, twice 0.93-1.22 of the step time over 118 nets of 7 x 7
+    // to 28 x 28 images.
     WgradParams probe = shape;
     probe.nsplit = W;
     probe.nrep = W;
@@ -2250,7 +2242,9 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
   const int ce = dtype_ce(dt);
   const int bke = 128 / dtype_size(dt);
   int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + ce, 256) : cdiv(Mout, 128) * cdiv(NK + ce, 128);
-  int q = cdiv(1024, tiles * W);  // aim at ~1024 workgroups (fp32 CNN: 512 and 256 the same within 0.5 %)
+  // about 1024 workgroups of wgrad_gemm_kernel's tiles; in fp32, too, whose launches have other tiles, so that a sum is split as it
+  // always was (fp32 CNN: 512 and 256 the same within 0.5 %)
+  int q = cdiv(1024, tiles * W);
   int qmax = per_replica / (2 * bke);  // at least two k-tiles per split
   if (qmax < 1) qmax = 1;
   if (q > qmax) q = qmax;

@@ -133,7 +133,7 @@ struct UpdateDesc {
 };
 
 // Both return the kernel family that took the launch: 0 = generic implicit GEMM (register-staged),
-// 1 = the asynchronous global->LDS kernels (conv3x3_dma_kernel / wgrad_dma_kernel and their relatives).
+// 1 = the asynchronous global->LDS kernels (conv3x3_dma, conv_gather, wgrad_dma, wgrad_flat, wgrad_f32) and narrow.hip's.
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 // plain products of few rows (linear.hip); false: not taken, nothing launched
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
@@ -163,7 +163,7 @@ void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void*
                        int W, int B, int classes, int ldl, int ldg, hipStream_t s);
 // Elements of a parameter block that one workgroup of the update kernel owns: the fewer, the more splits have to be
 // summed for each, so that a launch always has thousands of partial rows in flight (see update_kernel).
-// fp32 nets keep one range and with it one order of the sum for every split count.
+// fp32 nets keep one range and with it one order of the sum for every split count (on the exact-mean path: gossip_elems).
 __host__ __device__ inline int update_elems(int dt, int nsplit) {
   return dt == DT_F32 || nsplit < 64 ? 256 : nsplit >= 256 ? 32 : 64;
 }
@@ -176,6 +176,7 @@ void launch_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev
 // u_r = w_r - lr*direction_r from data-group r's own splits, then w_s = sum_r P[s][r] u_r into master
 // and `work`. descs / range_map: the entries of data-group 0, one per workgroup of gossip_elems(nsplit) elements.
 // P: device, W x W row-major.
+// (In fp32 as well, so that there the order of a sum depends on the split count.)
 __host__ __device__ inline int gossip_elems(int nsplit) { return nsplit >= 32 ? 32 : nsplit >= 8 ? 64 : 256; }
 void launch_gossip_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev, int total_ranges,
                           const float* P_dev, int W, long long rep_stride, float lr, float mu, hipStream_t s);
