@@ -227,8 +227,8 @@ double dds_gemm_flops_per_step(const dds_ctx* ctx);
  * the chip to itself; 0: off. Enabling also clears the totals.
  * dds_profile_read fills 18 doubles: for each of six classes summed milliseconds, number of
  * launches, summed algorithmic FLOPs (2*M*N*K). Classes 0 forward, 1 dgrad, 2 wgrad launches
- * taken by the kernels that stage operands in registers (the stem, linear layers of few rows); 3, 4, 5 the
- * same three kinds taken by the asynchronous global->LDS kernels and the 16-channel ones. */
+ * taken by the generic implicit-GEMM kernels; 3, 4, 5 the same three kinds taken by the
+ * kernels made for 3x3 stride-1 layers and, for wgrad, stride-2 ones. */
 int dds_profile(dds_ctx* ctx, int enable);
 int dds_profile_read(const dds_ctx* ctx, double* out18);
 

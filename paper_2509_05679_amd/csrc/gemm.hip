@@ -2030,7 +2030,8 @@ int launch_conv_one(const ConvParams& p, hipStream_t s) {
   constexpr int BKB = 64;
   if (p.nrep <= 1 && launch_linear(sizeof(T) == 4 ? DT_F32 : DT_BF16, p, s)) return 0;  // a data-group's slice
   if (sizeof(T) == 2 && launch_conv_narrow(p, s)) return 1;
-  if (launch_dma<T>(p, s) || launch_gather<T>(p, s)) return 1;
+  if (launch_dma<T>(p, s)) return 1;
+  if (launch_gather<T>(p, s)) return 0;
   // dgrad of a stride-2 convolution: workgroups per parity class (class (0,0) is the largest)
   const bool s2 = p.dgrad && p.stride == 2 && p.Cx % (BKB / (int)sizeof(T)) == 0 &&
                   (p.x2 == nullptr || p.Cx2 % (BKB / (int)sizeof(T)) == 0);
@@ -2203,7 +2204,7 @@ int launch_conv(int dt, const ConvParams& p, hipStream_t s) {
 int launch_wgrad(int dt, const WgradParams& p, hipStream_t s) {
   if (dt != DT_F32) return launch_wgrad_bf16(p, s);
   launch_wgrad_f32(p, s);
-  return 1;
+  return 0;
 }
 
 int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) {

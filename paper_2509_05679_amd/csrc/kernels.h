@@ -132,8 +132,9 @@ struct UpdateDesc {
   int Cout, RS, Cinpad, Cin, Coutpad;
 };
 
-// Both return the kernel family that took the launch: 0 = generic implicit GEMM (register-staged),
-// 1 = the asynchronous global->LDS kernels (conv3x3_dma, conv_gather, wgrad_dma, wgrad_flat, wgrad_f32) and narrow.hip's.
+// Both return the kernel family that took the launch, the class of dds_profile_read: 1 = the kernels made for 3x3 stride-1
+// layers and, among the weight gradients, stride-2 ones (conv3x3_dma, wgrad_dma, wgrad_flat, narrow.hip's), 0 = those that
+// take any layer (conv_gather, conv_gemm, linear, wgrad_gemm, wgrad_f32).
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 // plain products of few rows (linear.hip); false: not taken, nothing launched
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
