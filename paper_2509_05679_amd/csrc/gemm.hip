@@ -19,6 +19,7 @@
 
 #include "device_once.h"
 #include "kernels.h"
+#include "lds_copy.h"
 
 namespace dds {
 namespace {
@@ -572,17 +573,6 @@ __global__ __launch_bounds__(256, 2) void conv_gemm_kernel(ConvParams p_, int ti
 // whose sides are powers of two; 8 x 32 pixels + halo), alone: 512 images of 32 x 32 x 64 58.9 -> 56.5 us, 128 -> 128
 // channels at 16 x 16 unchanged at 45 us (860 TFLOP/s); per 8 iterations ResNet-20 in one module 5.77 -> 5.55 ms,
 // ResNet-56 23.0 -> 22.5 ms, and 28 x 28 images, which ran on conv_gemm_kernel, 3.08 -> 2.72 ms.
-__device__ __forceinline__ void dma16(const void* gsrc, uint32_t lds_base_uniform) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gsrc), "s"(lds_base_uniform) : "memory", "m0");
-}
-// Same copy with the address split into a wave-uniform 64-bit base (SGPR pair) and a per-lane
-// unsigned 32-bit byte offset: the per-copy address arithmetic stays on the scalar unit.
-__device__ __forceinline__ void dma16s(const void* gbase_uniform, uint32_t goff, uint32_t lds_base_uniform) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(goff), "s"(gbase_uniform), "s"(lds_base_uniform) : "memory", "m0");
-}
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // End of a workgroup of the asynchronous kernels: every copy has landed in this wave, acc holds its WM x WN tile.
 // The residual / mask tiles are staged in the first `room` bytes of LDS (the operand buffers are free now) so that the
 // epilogue pays one global round trip instead of one per 32-pixel column, and the output tile leaves from there in
@@ -681,18 +671,6 @@ __device__ __forceinline__ void add_halves(f32x16_t (&acc)[NJ][NI], char* smem, 
 #pragma unroll
     for (int i = 0; i < NI; ++i)
       if (khalf == 0) acc[j][i] += buf[(j * NI + i) * 64];
-}
-
-// floor(n / d) == __umulhi(n, mul) >> shift for 0 <= n < 2^31: mul = floor(2^(31+l) / d) + 1 with 2^(l-1) < d <= 2^l
-// exceeds 2^(31+l) / d by at most 2^l / d, which the division of a 31-bit n never sees
-struct Divisor {
-  uint32_t mul;
-  int shift;
-};
-inline Divisor make_divisor(int d) {  // d >= 2
-  int l = 1;
-  while ((1ll << l) < d) ++l;
-  return Divisor{(uint32_t)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
 }
 
 struct DmaGeom {
@@ -927,13 +905,6 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   if (KS > 1) add_halves<NI, NJ>(acc, smem, khalf, wave, lane);
   const auto pixel = [&](int row) { return m0 + row < p.M ? m0 + row : -1; };
   tile_out<T, BM, BN, WM, WN>(p, acc, mb, smem, g.out_bytes, n0, wave, wave_m, wave_n, lane, lpix, pixel, khalf == 0);
-}
-
-// Lets a kernel have all 160 KB of LDS on the current device. A failure is the launch's to report.
-inline void allow_whole_lds(DeviceOnce& once, const void* kernel) {
-  int device = 0;
-  if (hipGetDevice(&device) != hipSuccess) return;
-  once(device, [kernel] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess; });
 }
 
 inline int ilog2_exact(int v) {
@@ -2181,7 +2152,7 @@ void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
 }
 
 int launch_wgrad_bf16(const WgradParams& p, hipStream_t s) {
-  if (launch_wgrad_narrow(p, s) || launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s)) return 1;
+  if (launch_wgrad_slim(&p, 1, s) || launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s)) return 1;
   if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
     wgrad_gemm_kernel<bf16_t, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
@@ -2211,7 +2182,12 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
   const int Mout = shape.Mout, NK = shape.NK, P = shape.P;
   const int per_replica = P / W;  // pixels of one replica's mini-batch
   if (dt != DT_F32) {
-    if (const int n = wgrad_narrow_split(shape, W)) return n;
+    if (const int tiles = wgrad_slim_tiles(shape, W)) {
+      // workgroups 128 / 256 / 384 / 512 / 768, ms per 8 steps: ResNet-56 20.3 / 19.8 / 19.7 / 19.9 / 20.7, ResNet-20 in one
+      // module 4.70 / 4.49 / 4.48 / 4.46 / 4.51, its normalised form in two 13.3 / 12.6 / 12.4 / 12.4 / 12.6
+      const int q = cdiv(384, W);
+      return W * (q < tiles ? q : tiles);
+    }
     // Asynchronous kernel: 64 x 64 output blocks per (sub-pixel, channel block); a data-group's 128-pixel
     // tiles are dealt to its splits. Take the fewest splits that give the launch target_wgs workgroups:
     // the partial sums cost HBM traffic (written here, read by the update) in proportion to the split

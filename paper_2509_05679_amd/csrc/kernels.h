@@ -141,10 +141,12 @@ bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
 int launch_wgrad(int dt, const WgradParams& p, hipStream_t s);
-// bf16 3x3 stride-1 layers with 16-channel rows (narrow.hip): the split count such a layer gets (0: not its), and
-// the launch (false: not taken, nothing launched)
-int wgrad_narrow_split(const WgradParams& shape, int W);
-bool launch_wgrad_narrow(const WgradParams& p, hipStream_t s);
+// Layers that one weight-gradient launch can take at most.
+constexpr int kWgradGroupMax = 16;
+// bf16 3x3 stride-1 layers of 8, 16 or 32 input channels (narrow.hip): tiles of a data-group (0: not such a layer), and the
+// launch for n layers of one input width (false: not taken, nothing launched)
+int wgrad_slim_tiles(const WgradParams& shape, int W);
+bool launch_wgrad_slim(const WgradParams* p, int n, hipStream_t s);
 // Chooses the split count of the pixel reduction for a wgrad problem: a multiple of the replica
 // count W, so that no split mixes two replicas. shape: every field that describes the layer
 // (Nimg, H, W, Cx, Ho, Wo, Mout, ldy, R, S, stride, pad, NK, P, zeros non-null); nsplit,

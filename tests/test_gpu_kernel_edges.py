@@ -124,6 +124,16 @@ def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
     _compare(_stride2_net(c1, c2, k, h, w, W, B), seed=27, T=2)
 
 
+@pytest.mark.parametrize("widths,h,w,W,B", [
+    ((8, 16, 16, 32, 32, 8), 1, 1, 1, 1), ((16, 64, 16, 8), 3, 3, 2, 16), ((32, 16, 64, 8), 3, 3, 1, 17), ((64, 32, 32, 16), 15, 15, 3, 5),
+    ((32, 32, 32), 2, 378, 1, 2), ((32, 32), 2, 388, 1, 1), ((16, 16, 16), 31, 15, 2, 9), ((20, 12, 24), 5, 4, 2, 7)])
+def test_weight_gradients_of_narrow_layers(widths, h, w, W, B):
+    # 8, 16 and 32 input channels, each with one or two blocks of output rows; one pixel, data-groups of exactly one and of one and a
+    # bit 256-position tiles (3 x 3 with 16 and 17 images, 15 x 15), the longest rows with 32 channels and the first beyond them,
+    # channel counts that fill no row
+    _compare(_conv_chain("bf16", widths, h, w, W, B), seed=34, T=2)
+
+
 @pytest.mark.parametrize("precision", ["f32", "bf16"])
 @pytest.mark.parametrize("k,pad,h,w", [(1, 0, 7, 6), (2, 0, 6, 9), (2, 1, 7, 7), (3, 0, 9, 8), (5, 2, 8, 5)])
 def test_stride2_input_gradients_by_padding(precision, k, pad, h, w):
