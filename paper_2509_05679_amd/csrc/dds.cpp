@@ -98,6 +98,8 @@ struct Node {
   long long bn_rows_per_split = 0;
   int fold_sc = -1;        // first conv of a projection block: node of the 1x1 shortcut whose dgrad rides in this one's
   bool dgrad_folded = false;  // shortcut node: no dgrad launch of its own
+  int wgroup = -1;            // launch that this layer's weight gradient goes with ...
+  bool wgroup_last = false;   // ... and the backward pass has reached its last layer
 };
 
 struct GradBuf {
@@ -111,6 +113,7 @@ struct Module {
   std::vector<Node> nodes;
   std::vector<ParamLayer> layers;  // canonical (spec) order
   std::vector<GradBuf> grads;
+  std::vector<std::vector<WgradParams>> wgroups;  // weight gradients that wait for the rest of their launch
   size_t slot_bytes = 0;
   char* ring = nullptr;
   // Recompute policy (modules with d > 0): a ring slot keeps only what other iterations or modules read (the
@@ -555,6 +558,73 @@ int plan_module(const dds_spec& sp, int k0, int K, int N, int dt, const Tensor* 
 // elements of a layer that one workgroup of the update kernel owns
 int range_elems(const dds_ctx& c, const ParamLayer& L) { return c.gossip ? gossip_elems(L.nsplit / c.copies) : update_elems(c.dt, L.nsplit); }
 
+// What describes the weight gradient of a layer, but for its pointers and splits.
+WgradParams wgrad_shape(const dds_ctx& c, const Module& m, const Node& nd) {
+  const ParamLayer& L = m.layers[nd.layer];
+  const Tensor& ti = m.tensors[nd.in];
+  const Tensor& to = m.tensors[nd.out];
+  WgradParams w{};
+  w.Nimg = c.N; w.H = ti.H; w.W = ti.W; w.Cx = ti.Cpad; w.Ho = to.H; w.Wo = to.W;
+  w.Mout = L.Cout;
+  w.ldy = to.Cpad;
+  w.R = L.R; w.S = L.R; w.stride = L.stride; w.pad = L.pad;
+  w.NK = L.RS * L.Cinpad;
+  w.P = c.N * to.H * to.W;
+  // Only a mixing step needs the data-groups' sums one by one; the exact mean is the sum over all images. (fp32 nets keep
+  // the order of their sums.)
+  w.nrep = c.gossip || c.dt == DT_F32 ? c.W : 1;
+  w.Pl = L.pstride;
+  w.alpha = nd.alpha;
+  return w;
+}
+
+// Deals the weight gradients of a module to launches, in the order of the backward pass, and chooses their split counts.
+void plan_wgrads(dds_ctx& c, Module& m) {
+  // A launch costs 5 to 7 us beside its tiles (start, first copies, last stores), and the fewer of them share the chip's
+  // workgroups the fewer partial sums are written and read again. A launch is closed when it has some 100 tiles for each
+  // workgroup (about 150 us): layers of that size alone gain nothing and read their gradients later, out of memory instead of a cache.
+  // ms per 8 steps with one layer a launch / closed at 2048 / 4096 / 8192 / 16384 tiles / never: ResNet-20 in one module 4.33 / 3.55 / 3.55 /
+  // 3.50 / 3.48 / 3.50, 64 images of ResNet-18 4.97 / 4.27 / 4.28 / 4.29 / 4.30 / 4.32, ResNet-56 19.7 / 18.6 / 18.4 / 18.1 / 18.3 / 18.3, ResNet-18
+  // 17.5 / 17.5 / 17.8 / 17.3 / 17.2 / 17.3, wide ResNet-34 (32768 tiles a layer) 208 with its layers alone, 210 in groups.
+  constexpr long long enough = 16384;
+  struct Open { int key; long long work; std::vector<int> nodes; };
+  std::vector<Open> open;
+  auto close = [&](Open& o) {
+    std::vector<WgradParams> shapes;
+    for (int ni : o.nodes) {
+      shapes.push_back(wgrad_shape(c, m, m.nodes[ni]));
+      shapes.back().zeros = &c;  // non-null: only the shape matters here
+    }
+    std::vector<int> splits(shapes.size());
+    wgrad_choose_splits(c.dt, shapes.data(), (int)shapes.size(), splits.data());
+    for (size_t i = 0; i < o.nodes.size(); ++i) {
+      Node& nd = m.nodes[o.nodes[i]];
+      m.layers[nd.layer].nsplit = splits[i];
+      nd.wgroup = (int)m.wgroups.size();
+      nd.wgroup_last = i + 1 == o.nodes.size();
+    }
+    m.wgroups.emplace_back();
+    m.wgroups.back().reserve(o.nodes.size());
+    o.nodes.clear();
+    o.work = 0;
+  };
+  for (int ni = (int)m.nodes.size() - 1; ni >= 0; --ni) {
+    if (m.nodes[ni].kind != N_CONV) continue;
+    WgradParams w = wgrad_shape(c, m, m.nodes[ni]);
+    w.zeros = &c;
+    const WgradWork work = wgrad_work(c.dt, w);
+    Open* o = nullptr;
+    for (Open& k : open)
+      if (k.key == work.key) o = &k;
+    if (!o) { open.push_back(Open{work.key, 0, {}}); o = &open.back(); }
+    o->nodes.push_back(ni);
+    o->work += (long long)work.blocks * work.tiles * w.nrep;
+    if (work.key == 0 || o->work >= enough || (int)o->nodes.size() == kWgradGroupMax) close(*o);
+  }
+  for (Open& o : open)
+    if (!o.nodes.empty()) close(o);
+}
+
 int layout(dds_ctx& c, Arena& A) {
   const int es = dtype_size(c.dt);
   for (int k0 = 0; k0 < c.K; ++k0) {
@@ -607,6 +677,7 @@ int layout(dds_ctx& c, Arena& A) {
       m.snap_master = (float*)A.take((size_t)m.n_master * 4 * c.copies * m.R);
       if (c.dt == DT_BF16) m.snap_work = A.take((size_t)m.n_master * es * c.copies * m.R);
     }
+    plan_wgrads(c, m);
     for (Node& nd : m.nodes) {
       if (nd.kind == N_BN) {  // one parameter-gradient row per data-group
         ParamLayer& L = m.layers[nd.layer];
@@ -616,20 +687,6 @@ int layout(dds_ctx& c, Arena& A) {
       }
       if (nd.kind != N_CONV) continue;
       ParamLayer& L = m.layers[nd.layer];
-      const Tensor& to = m.tensors[nd.out];
-      const int P = c.N * to.H * to.W;
-      {
-        const Tensor& tin = m.tensors[nd.in];
-        WgradParams w{};
-        w.zeros = &w;  // non-null: only the shape matters here
-        w.Nimg = c.N; w.H = tin.H; w.W = tin.W; w.Cx = tin.Cpad; w.Ho = to.H; w.Wo = to.W;
-        w.Mout = L.Cout; w.ldy = to.Cpad;
-        w.R = L.R; w.S = L.R; w.stride = L.stride; w.pad = L.pad;
-        w.NK = L.RS * L.Cinpad;
-        w.P = P;
-        // with three or more module programs on concurrent streams a wgrad launch need not fill the chip alone
-        L.nsplit = wgrad_choose_split(c.dt, w, c.W, c.K >= 3 ? 128 : 256);
-      }
       L.partial = (float*)A.take((size_t)L.nsplit * L.pstride * 4);
       if (L.need_stash) {
         L.stash_elems = (long long)L.Cin * L.RS * L.Coutpad;
@@ -914,6 +971,7 @@ void run_forward(dds_ctx& c, Module& m, int slot, int in_slot, hipStream_t s, in
 // has a buffer of its own, so nothing is overwritten before the join at the end. ws == s: one after the other.
 int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStream_t ws) {
   const int slot = sc.bwd_slot, in_slot = sc.in_bwd_slot;
+  for (std::vector<WgradParams>& group : m.wgroups) group.clear();  // (a step that failed half way)
   for (int ni = (int)m.nodes.size() - 1; ni >= 0; --ni) {
     const Node& nd = m.nodes[ni];
     if (nd.kind == N_CE) continue;  // dlogits were produced by the loss kernel
@@ -928,31 +986,26 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
         const int ldg = to.Cpad;
         // The weight gradient reads no weights: one launch serves every data-group, and since no
         // split mixes two of them, data-group r's gradient is the sum of its own nsplit / W splits.
-        WgradParams w{};
+        WgradParams w = wgrad_shape(c, m, nd);
         w.dy = gout;
         w.x = x;
         w.partial = L.partial;
         w.zeros = c.zeros;
-        w.Nimg = c.N; w.H = ti.H; w.W = ti.W; w.Cx = ti.Cpad; w.Ho = to.H; w.Wo = to.W;
-        w.Mout = L.Cout;
-        w.ldy = ldg;
-        w.R = L.R; w.S = L.R; w.stride = L.stride; w.pad = L.pad;
-        w.NK = L.RS * L.Cinpad;
-        w.P = c.N * to.H * to.W;
         w.nsplit = L.nsplit;
-        w.nrep = c.W;
         w.pix_per_split = w.P / L.nsplit;
-        w.Pl = L.pstride;
-        w.alpha = nd.alpha;
-        if (ws != s) {
-          HIP_TRY(hipEventRecord(m.wfork, s));
-          HIP_TRY(hipStreamWaitEvent(ws, m.wfork, 0));
-        }
-        {
+        // It waits for the other layers of its launch, but when every launch is timed: the sums do not depend on which it is.
+        std::vector<WgradParams>& group = m.wgroups[nd.wgroup];
+        group.push_back(w);
+        if (nd.wgroup_last || c.profiling) {
+          if (ws != s) {
+            HIP_TRY(hipEventRecord(m.wfork, s));
+            HIP_TRY(hipStreamWaitEvent(ws, m.wfork, 0));
+          }
           ProfScope ps(c, ws, 2, 2.0 * w.P * L.Cout * L.Cin * L.RS);
-          ps.cls += 3 * launch_wgrad(c.dt, w, ws);
+          ps.cls += 3 * launch_wgrad(c.dt, group.data(), (int)group.size(), ws);
+          ++c.launches;
+          group.clear();
         }
-        ++c.launches;
         if (nd.gin != G_NONE) {
           ConvParams p{};
           p.x = gout;

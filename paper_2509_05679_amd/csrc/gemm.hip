@@ -2,11 +2,11 @@
 // split pixel reduction. Operands of the first two kernels of each list are copied global -> LDS without passing through registers.
 //   forward and input gradient: conv3x3_dma_kernel (3x3 stride 1), conv_gather_kernel (any other layer of whole 64-byte
 //     channel chunks), conv_gemm_kernel (the rest, e.g. the 3-channel stem)
-//   weight gradient, bf16: wgrad_dma_kernel (sides that are powers of two, whole 128-pixel tiles), wgrad_flat_kernel (other
+//   weight gradient, bf16: wgrad_dma_body (sides that are powers of two, whole 128-pixel tiles), wgrad_flat_body (other
 //     sizes), wgrad_gemm_kernel (the rest); fp32: wgrad_f32_kernel
 // (Plain products of few rows: linear.hip. 16-channel layers: narrow.hip.)
 //
-// Operand tiles are K-contiguous in LDS ([row][k]; wgrad_dma_kernel, wgrad_flat_kernel and wgrad_f32_kernel keep [pixel][channel])
+// Operand tiles are K-contiguous in LDS ([row][k]; wgrad_dma_body, wgrad_flat_body and wgrad_f32_kernel keep [pixel][channel])
 // and feed v_mfma_f32_32x32x16_bf16 (bf16) or v_mfma_f32_32x32x2_f32 (fp32) with one 16-byte LDS read per operand fragment.
 // Lanes 0-31 read the first 16 bytes of a 32-byte k-step and lanes 32-63 the second, for A and B alike, so the
 // pairing of k indices inside an instruction is consistent by construction.
@@ -1420,11 +1420,17 @@ __device__ __forceinline__ uint2 lds_tr16(const char* p) {
 
 // Geometry the host passes along with WgradParams.
 struct WgradGeom {
-  int tiles_h;     // 128-pixel tiles per image (a power of two; 1 when a tile holds whole images)
   int cblocks;     // 64-channel blocks of the real input tensor
-  int sub[4];      // S2: sub-pixel (dy * 2 + dx) served by blockIdx.y / cblocks
+  int sub[4];      // S2: sub-pixel (dy * 2 + dx) served by block row / cblocks
   int rmap[2][2];  // S2: real kernel row for (virtual row R', dy), -1 if none; the same table serves columns
-  int xcd_remap;   // splits are a multiple of eight: workgroups of one split are dealt to one XCD (see the kernel)
+  // wgrad_dma_body
+  int tiles_h;     // 128-pixel tiles per image (a power of two; 1 when a tile holds whole images)
+  // wgrad_flat_body
+  int Q;           // position pitch of an image row, Wo + 1
+  int imgs_rep;    // images per data-group
+  int rep_tiles;   // 128-position tiles per data-group
+  int patch_rows;  // 128 + 2Q + 2 (S2: 128 + Q + 1) rounded up to 8
+  Divisor dQ, dH;  // by Q and by Ho + 1
 };
 
 // S2 = false: 3x3, stride 1, pad 1 (nine taps, TW x TH tiles of the image itself).
@@ -1443,7 +1449,7 @@ __device__ __forceinline__ uint2 lds_tr16_at(uint32_t lds_byte_address) {
 // three tap groups (one per kernel row, 12 waves, three per SIMD) so that the LDS reads of one wave
 // hide behind the MFMAs of the others; a group's row shift is folded into its lanes' base addresses.
 template <int TWLOG, int THLOG, bool S2>
-__global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p, WgradGeom wg, const void* zeros) {
+__device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
   constexpr int TW = 1 << TWLOG, TH = 1 << THLOG, PW = TW + 2, PP = (TH + 2) * PW;
   constexpr int IMGS = 128 / (TW * TH);
   static_assert(IMGS >= 1 && IMGS * TW * TH == 128, "a tile is 128 pixels");
@@ -1456,28 +1462,12 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   // so that a conv workgroup of another module fits on the same CU; a third slot (copies two tiles ahead,
   // 126 KB) was 1-2 % slower per training step on every configuration although each launch alone was not.
   constexpr int SLOT = 16384 + PROW * 128;
-  extern __shared__ __align__(16) char smem[];
   const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = (wave >> 1) & 1;
   const int tg = wave >> 2;  // tap group: kernel row of this wave's three taps (stride 1)
-  // Workgroup -> (k-block, sub-pixel / c-block, split). Every (k, c) block of one split reads the same dY rows and
-  // X patches, so they should meet in one L2: workgroups are handed to the eight XCDs round-robin in launch order,
-  // hence launch index i lands on XCD i % 8 as the (i / 8)-th workgroup of that XCD. With a split count that is
-  // a multiple of eight, XCD x takes the splits z = x (mod 8) and runs all blocks of a split back to back, so
-  // they are resident together and walk the pixel tiles at the same pace.
-  int bx = blockIdx.x, by = blockIdx.y, z = blockIdx.z;
-  if (wg.xcd_remap) {
-    const int nblk = gridDim.x * gridDim.y;
-    const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const int xcd = lin & 7, j = lin >> 3;
-    const int blk = j % nblk;
-    z = (j / nblk) * 8 + xcd;
-    bx = blk % gridDim.x;
-    by = blk / gridDim.x;
-  }
   const int k0 = bx * 64;
   const int sub = S2 ? wg.sub[by / wg.cblocks] : 0;
   const int sdy = sub >> 1, sdx = sub & 1;
@@ -1486,8 +1476,8 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   // tiles allow (tile counts differ by at most one), so a split never mixes two data-groups.
   const int q = p.nsplit / p.nrep, rep_tiles = (p.P >> 7) / p.nrep;
   const int zr = z / q, zj = z - zr * q;
-  const int tile0 = zr * rep_tiles + (zj * rep_tiles) / q;
-  const int ntiles = zr * rep_tiles + ((zj + 1) * rep_tiles) / q - tile0;
+  const int tile0 = zr * rep_tiles + (int)(((long long)zj * rep_tiles) / q);
+  const int ntiles = zr * rep_tiles + (int)(((long long)(zj + 1) * rep_tiles) / q) - tile0;
   const size_t ybytes = (size_t)p.ldy * 2, xbytes = (size_t)p.Cx * 2;
 
   // A tile is 128 consecutive pixels of the flattened (image, row, column) index of the output
@@ -1496,7 +1486,7 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
   // the row / column facts that decide whether that row is padding.
   const int l8 = lane >> 3;
   const int c16 = ((lane & 7) ^ ((l8 & 3) << 1)) * 16;  // global 16-byte column for LDS slot lane&7 of a row with row&3 == l8&3
-  const char* zsrc = (const char*)zeros + c16;
+  const char* zsrc = (const char*)p.zeros + c16;
   constexpr int pw_total = PROW >> 3;
   const bool ycol_ok = k0 + (c16 >> 1) < p.ldy;   // this lane's 8 output channels exist
   const bool xcol_ok = c0 + (c16 >> 1) < p.Cx;    // ... and its 8 input channels (tensors narrower than a 64-channel block)
@@ -1652,7 +1642,7 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
 }
 
 // ------------------------------------------------------------------ the same weight gradients for any image size (bf16)
-// wgrad_dma_kernel wants images whose sides are powers of two and data-groups of whole 128-pixel tiles. Everything
+// wgrad_dma_body wants images whose sides are powers of two and data-groups of whole 128-pixel tiles. Everything
 // else 3x3 stride 1, 3x3 stride 2 or 1x1 stride 2 comes here. The pixels of a data-group are numbered with a row pitch of Wo + 1 and one
 // extra row above every image, so that each row's padding is the extra column before it and each image's the extra
 // row: a tile is 128 consecutive such positions, dY and X are copied with zeros at the extra ones, and the taps are
@@ -1662,22 +1652,10 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_dma_kernel(WgradParams p
 // Bound, as there, by the barrier and the LDS reads around a tile's MFMAs. 64 -> 64 channels at 14 x 14, 194 images, with
 // 196 workgroups of wgrad_gemm_kernel (operands transposed in registers) 62 us, here 12 us; 32 -> 64 at stride 2 from
 // 28 x 28 42 -> 16 us.
-struct WgradFlatGeom {
-  int cblocks;     // 64-channel blocks of the input tensor
-  int sub[4];      // S2: sub-pixel (dy * 2 + dx) served by blockIdx.y / cblocks
-  int rmap[2][2];  // S2: see WgradGeom
-  int Q;           // position pitch of an image row, Wo + 1
-  int imgs_rep;    // images per data-group
-  int rep_tiles;   // 128-position tiles per data-group
-  int patch_rows;  // 128 + 2Q + 2 (S2: 128 + Q + 1) rounded up to 8
-  Divisor dQ, dH;  // by Q and by Ho + 1
-};
-
 template <bool S2>
-__global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams p, WgradFlatGeom wg) {
+__device__ __forceinline__ void wgrad_flat_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
   constexpr int NWV = S2 ? 4 : 12;  // waves: four per tap group, each a 32(k) x 32(c) quarter; stride 1: one group per kernel row
   constexpr int NT = S2 ? 4 : 3;    // taps accumulated by one wave
-  extern __shared__ __align__(16) char smem[];
   const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
   const int slot_bytes = 16384 + wg.patch_rows * 128;
 
@@ -1685,8 +1663,7 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = (wave >> 1) & 1;
   const int tg = wave >> 2;
-  const int by = blockIdx.y, z = blockIdx.z;
-  const int k0 = blockIdx.x * 64;
+  const int k0 = bx * 64;
   const int sub = S2 ? wg.sub[by / wg.cblocks] : 0;
   const int sdy = sub >> 1, sdx = sub & 1;
   const int c0 = (S2 ? by % wg.cblocks : by) * 64;
@@ -1733,7 +1710,7 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
   };
   fill_tile(0, 0);
 
-  // fragment addressing as in wgrad_dma_kernel; the patch row of tile position u at tap (R, S) is u + R Q + S
+  // fragment addressing as in wgrad_dma_body; the patch row of tile position u at tap (R, S) is u + R Q + S
   const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;
   const int rsub = lq >> 2, seg = lq & 3;
   const int a_c = 4 * wave_m + 2 * grp16 + (seg >> 1);
@@ -1814,6 +1791,46 @@ __global__ __launch_bounds__(S2 ? 256 : 768) void wgrad_flat_kernel(WgradParams 
         if (live[tap]) out[(size_t)k * p.NK + tapreal[tap] * p.Cx + cin] = p.alpha * acc[tap][e];
     }
     if (bias_wave && (lane & 31) == 0) out[(size_t)p.Mout * p.NK + k] = p.alpha * accb[e];
+  }
+}
+
+// One launch takes several layers (all of stride 1, or all of stride 2): workgroup -> (layer, k-block, sub-pixel / c-block,
+// split). Every (k, c) block of one split reads the same dY rows and X patches, so they should meet in one L2: workgroups are
+// handed to the eight XCDs round-robin in launch order, hence launch index i lands on XCD i % 8 as the (i / 8)-th workgroup
+// of that XCD. Where the split count is a multiple of eight, XCD x takes the splits z = x (mod 8) and runs all blocks of
+// a split back to back, so they are resident together and walk the pixel tiles at the same pace (a layer's workgroups start at a
+// multiple of eight).
+struct WgradLayer {
+  WgradParams p;
+  WgradGeom g;
+  int tiling;  // 0..3: wgrad_dma_body for rows of 32, 16, 8, 4 pixels; 4: wgrad_flat_body
+  int first;   // first workgroup
+  int gx, gy;  // k-blocks, (sub-pixel, c-block) pairs
+};
+struct WgradGroup {
+  int n;
+  WgradLayer layer[kWgradGroupMax];
+};
+static_assert(sizeof(WgradGroup) <= 4096, "kernel arguments");
+
+template <bool S2>
+__global__ __launch_bounds__(S2 ? 256 : 768, S2 ? 2 : 1) void wgrad_tiles_kernel(WgradGroup grp) {
+  extern __shared__ __align__(16) char smem[];
+  int li = 0;
+  while (li + 1 < grp.n && (int)blockIdx.x >= grp.layer[li + 1].first) ++li;
+  const WgradLayer& l = grp.layer[li];
+  const int lin = blockIdx.x - l.first, nblk = l.gx * l.gy;
+  if (lin >= nblk * l.p.nsplit) return;
+  const int xcds = (l.p.nsplit & 7) == 0 ? 3 : 0;  // log2
+  const int j = lin >> xcds;
+  const int z = ((j / nblk) << xcds) + (lin & ((1 << xcds) - 1)), blk = j % nblk;
+  const int bx = blk % l.gx, by = blk / l.gx;
+  switch (l.tiling) {
+    case 0: wgrad_dma_body<5, 2, S2>(l.p, l.g, smem, bx, by, z); break;
+    case 1: wgrad_dma_body<4, 3, S2>(l.p, l.g, smem, bx, by, z); break;
+    case 2: wgrad_dma_body<3, 3, S2>(l.p, l.g, smem, bx, by, z); break;
+    case 3: wgrad_dma_body<2, 2, S2>(l.p, l.g, smem, bx, by, z); break;
+    default: wgrad_flat_body<S2>(l.p, l.g, smem, bx, by, z);
   }
 }
 
@@ -2027,43 +2044,24 @@ int launch_conv_one(const ConvParams& p, hipStream_t s) {
   return 0;
 }
 
-template <int TWLOG, int THLOG, bool S2>
-void launch_wgrad_dma_inst(const WgradParams& p, const WgradGeom& wg, int nsub, hipStream_t s) {
-  constexpr int TW = 1 << TWLOG, TH = 1 << THLOG;
-  constexpr int PROW = ((128 / (TW * TH)) * (TH + 2) * (TW + 2) + 7) / 8 * 8;
-  static DeviceOnce lds;
-  allow_whole_lds(lds, (const void*)wgrad_dma_kernel<TWLOG, THLOG, S2>);
-  const int smem = 2 * (16384 + PROW * 128);  // two slots
-  dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
-  wgrad_dma_kernel<TWLOG, THLOG, S2><<<grid, S2 ? 256 : 768, smem, s>>>(p, wg, p.zeros);
-}
-
-// bf16 problems whose splits are whole 128-pixel tiles go to the asynchronous kernel: 3x3
-// stride 1 pad 1, and the stride-2 layers (3x3 pad 1, 1x1 pad 0) on even-sized images.
-// On success: sub-pixels served (1 for stride 1), 64-channel blocks, tile geometry.
-bool wgrad_dma_eligible(const WgradParams& p, int* nsub_out, int* cblocks_out, int* lw_out = nullptr, int* th_log_out = nullptr,
-                        int* tiles_h_out = nullptr) {
+// bf16 problems of whole 128-pixel tiles per data-group (nrep of them) go to wgrad_dma_body: 3x3 stride 1 pad 1, and the
+// stride-2 layers (3x3 pad 1, 1x1 pad 0) on even-sized images. Returns its tiling, -1 if it is none of them.
+int wgrad_dma_tiling(const WgradParams& p, int nrep, int* tiles_h) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
   const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
                   p.H == 2 * p.Ho && p.W == 2 * p.Wo;
-  if (!s1 && !s2) return false;
-  // every data-group's pixels are whole 128-pixel tiles, and no split is empty
-  if (p.nrep < 1 || p.nsplit % p.nrep != 0 || p.P % (128 * p.nrep) != 0 || p.nsplit > p.P / 128) return false;
-  if (p.Cx % 8 != 0 || (p.Cx > 64 && p.Cx % 64 != 0) || p.zeros == nullptr) return false;
+  if (!s1 && !s2) return -1;
+  if (nrep < 1 || p.P % (128 * nrep) != 0) return -1;
+  if (p.Cx % 8 != 0 || (p.Cx > 64 && p.Cx % 64 != 0) || p.zeros == nullptr) return -1;
   // byte offsets of patch rows relative to the tile origin are 32-bit
-  if ((long long)(128 + 2 * p.W + 4) * 4 * p.Cx * 2 >= (1ll << 31) || p.Cx * 2 + 256 > kZeroBytes) return false;
+  if ((long long)(128 + 2 * p.W + 4) * 4 * p.Cx * 2 >= (1ll << 31) || p.Cx * 2 + 256 > kZeroBytes) return -1;
   const int lw = ilog2_exact(p.Wo), lh = ilog2_exact(p.Ho);
-  if (lw < 2 || lh < 0 || p.Wo > 32) return false;
-  int th_log, tiles_h;
-  if (p.Ho * p.Wo >= 128) { th_log = 7 - lw; tiles_h = p.Ho >> th_log; if (th_log > lh) return false; }
-  else { th_log = lh; tiles_h = 1; }
-  if (!((lw == 5 && th_log == 2) || (lw == 4 && th_log == 3) || (lw == 3 && th_log == 3) || (lw == 2 && th_log == 2))) return false;
-  *nsub_out = s2 && p.R == 3 ? 4 : 1;
-  *cblocks_out = cdiv(p.Cx, 64);
-  if (lw_out) *lw_out = lw;
-  if (th_log_out) *th_log_out = th_log;
-  if (tiles_h_out) *tiles_h_out = tiles_h;
-  return true;
+  if (lw < 2 || lh < 0 || p.Wo > 32) return -1;
+  int th_log;
+  if (p.Ho * p.Wo >= 128) { th_log = 7 - lw; *tiles_h = p.Ho >> th_log; if (th_log > lh) return -1; }
+  else { th_log = lh; *tiles_h = 1; }
+  if (!((lw == 5 && th_log == 2) || (lw == 4 && th_log == 3) || (lw == 3 && th_log == 3) || (lw == 2 && th_log == 2))) return -1;
+  return 5 - lw;
 }
 
 // Sub-pixels of a stride-2 layer in launch order and the real tap of (virtual tap, sub-pixel offset):
@@ -2081,17 +2079,15 @@ int wgrad_s2_taps(int R, int (&sub)[4], int (&rmap)[2][2]) {
   return nsub;
 }
 
-// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size; of nsplit and the pointers only `zeros` is
-// looked at.
-bool wgrad_flat_geometry(const WgradParams& p, int W, WgradFlatGeom& wg, int& nsub) {
+// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size: wgrad_flat_body. False: not one of them.
+bool wgrad_flat_geometry(const WgradParams& p, int nrep, WgradGeom& wg) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
   const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
                   p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2;
-  if ((!s1 && !s2) || W < 1 || p.Nimg % W != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return false;
+  if ((!s1 && !s2) || nrep < 1 || p.Nimg % nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return false;
   if (p.zeros == nullptr) return false;
-  wg.cblocks = cdiv(p.Cx, 64);
   wg.Q = p.Wo + 1;
-  wg.imgs_rep = p.Nimg / W;
+  wg.imgs_rep = p.Nimg / nrep;
   const long long positions = (long long)wg.imgs_rep * (p.Ho + 1) * wg.Q;
   if (positions + 128 + 2 * wg.Q >= (1ll << 31) || (long long)p.Nimg * p.H * p.W >= (1ll << 31)) return false;
   wg.rep_tiles = (int)((positions + 127) / 128);
@@ -2099,44 +2095,58 @@ bool wgrad_flat_geometry(const WgradParams& p, int W, WgradFlatGeom& wg, int& ns
   if (2 * (16384 + wg.patch_rows * 128) > 160 * 1024) return false;  // rows of at most 190 (stride 2: 382) output pixels
   wg.dQ = make_divisor(wg.Q);
   wg.dH = make_divisor(p.Ho + 1);
-  nsub = s2 ? wgrad_s2_taps(p.R, wg.sub, wg.rmap) : 1;
   return true;
 }
 
-bool launch_wgrad_flat(const WgradParams& p, hipStream_t s) {
-  WgradFlatGeom wg{};
-  int nsub = 1;
-  if (p.nrep < 1 || p.nsplit % p.nrep != 0 || !wgrad_flat_geometry(p, p.nrep, wg, nsub)) return false;
-  if (p.nsplit / p.nrep > wg.rep_tiles) return false;  // no empty split
-  static DeviceOnce lds[2];
-  allow_whole_lds(lds[0], (const void*)wgrad_flat_kernel<false>);
-  allow_whole_lds(lds[1], (const void*)wgrad_flat_kernel<true>);
-  const int smem = 2 * (16384 + wg.patch_rows * 128);
-  dim3 grid(cdiv(p.Mout, 64), nsub * wg.cblocks, p.nsplit);
-  if (p.stride == 2) wgrad_flat_kernel<true><<<grid, 256, smem, s>>>(p, wg);
-  else wgrad_flat_kernel<false><<<grid, 768, smem, s>>>(p, wg);
-  return true;
-}
-
-bool launch_wgrad_dma(const WgradParams& p, hipStream_t s) {
-  int nsub_e, cblocks, lw, th_log, tiles_h;
-  if (!wgrad_dma_eligible(p, &nsub_e, &cblocks, &lw, &th_log, &tiles_h)) return false;
-  const bool s2 = p.stride == 2;
-  WgradGeom wg{};
-  wg.tiles_h = tiles_h;
-  wg.cblocks = cblocks;
-  wg.xcd_remap = p.nsplit % 8 == 0 ? 1 : 0;
-  int nsub = 1;
-  if (s2) nsub = wgrad_s2_taps(p.R, wg.sub, wg.rmap);
-#define DDS_WG_CASE(TWL, THL)                                                        \
-  if (lw == TWL && th_log == THL) {                                                  \
-    if (s2) launch_wgrad_dma_inst<TWL, THL, true>(p, wg, nsub, s);                   \
-    else launch_wgrad_dma_inst<TWL, THL, false>(p, wg, nsub, s);                     \
-    return true;                                                                     \
+// The layer's part of a launch of wgrad_tiles_kernel but for its place in it (p.nrep is looked at, p.nsplit and the pointers but
+// for `zeros` are not); false: not a layer of this kernel. rep_tiles: 128-position tiles of a data-group; smem: LDS.
+bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem) {
+  l.p = p;
+  l.tiling = wgrad_dma_tiling(p, p.nrep, &l.g.tiles_h);
+  int rows;
+  if (l.tiling >= 0) {
+    const int tw = p.Wo, th = p.Ho * p.Wo >= 128 ? 128 / tw : p.Ho;
+    rows = ((128 / (tw * th)) * (th + 2) * (tw + 2) + 7) / 8 * 8;
+    *rep_tiles = p.P / (128 * p.nrep);
+  } else {
+    l.tiling = 4;
+    if (!wgrad_flat_geometry(p, p.nrep, l.g)) return false;
+    rows = l.g.patch_rows;
+    *rep_tiles = l.g.rep_tiles;
   }
-  DDS_WG_CASE(5, 2) DDS_WG_CASE(4, 3) DDS_WG_CASE(3, 3) DDS_WG_CASE(2, 2)
-#undef DDS_WG_CASE
-  return false;
+  *smem = 2 * (16384 + rows * 128);  // two slots
+  const int nsub = p.stride == 2 ? wgrad_s2_taps(p.R, l.g.sub, l.g.rmap) : 1;
+  l.g.cblocks = cdiv(p.Cx, 64);
+  l.gx = cdiv(p.Mout, 64);
+  l.gy = nsub * l.g.cblocks;
+  return true;
+}
+
+// False: not taken, nothing launched.
+bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
+  if (n < 1 || n > kWgradGroupMax) return false;
+  WgradGroup g{};
+  int wgs = 0, smem = 0;
+  for (int i = 0; i < n; ++i) {
+    WgradLayer& l = g.layer[i];
+    int tiles = 0, need = 0;
+    if (p[i].nrep < 1 || p[i].nsplit % p[i].nrep != 0 || p[i].stride != p[0].stride || !wgrad_layer(p[i], l, &tiles, &need)) return false;
+    const int q = p[i].nsplit / p[i].nrep;
+    if (q < 1 || q > tiles) return false;  // no empty split
+    l.first = wgs;
+    wgs += (l.gx * l.gy * p[i].nsplit + 7) / 8 * 8;
+    smem = smem > need ? smem : need;
+  }
+  g.n = n;
+  static DeviceOnce lds[2];
+  if (p[0].stride == 2) {
+    allow_whole_lds(lds[1], (const void*)wgrad_tiles_kernel<true>);
+    wgrad_tiles_kernel<true><<<wgs, 256, smem, s>>>(g);
+  } else {
+    allow_whole_lds(lds[0], (const void*)wgrad_tiles_kernel<false>);
+    wgrad_tiles_kernel<false><<<wgs, 768, smem, s>>>(g);
+  }
+  return true;
 }
 
 void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
@@ -2151,8 +2161,9 @@ void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
   else wgrad_f32_kernel<64, 64><<<grid, 256, 0, s>>>(p, g);
 }
 
-int launch_wgrad_bf16(const WgradParams& p, hipStream_t s) {
-  if (launch_wgrad_slim(&p, 1, s) || launch_wgrad_dma(p, s) || launch_wgrad_flat(p, s)) return 1;
+int launch_wgrad_bf16(const WgradParams* pp, int n, hipStream_t s) {
+  if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return 1;
+  const WgradParams& p = pp[0];  // the others have no key to share a launch under
   if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
     wgrad_gemm_kernel<bf16_t, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
@@ -2172,50 +2183,32 @@ int launch_conv(int dt, const ConvParams& p, hipStream_t s) {
   return dt == DT_F32 ? launch_conv_t<float>(p, s) : launch_conv_t<bf16_t>(p, s);
 }
 
-int launch_wgrad(int dt, const WgradParams& p, hipStream_t s) {
-  if (dt != DT_F32) return launch_wgrad_bf16(p, s);
-  launch_wgrad_f32(p, s);
+int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s) {
+  if (dt != DT_F32) return launch_wgrad_bf16(p, n, s);
+  for (int i = 0; i < n; ++i) launch_wgrad_f32(p[i], s);
   return 0;
 }
 
-int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) {
-  const int Mout = shape.Mout, NK = shape.NK, P = shape.P;
-  const int per_replica = P / W;  // pixels of one replica's mini-batch
-  if (dt != DT_F32) {
-    if (const int tiles = wgrad_slim_tiles(shape, W)) {
-      // workgroups 128 / 256 / 384 / 512 / 768, ms per 8 steps: ResNet-56 20.3 / 19.8 / 19.7 / 19.9 / 20.7, ResNet-20 in one
-      // module 4.70 / 4.49 / 4.48 / 4.46 / 4.51, its normalised form in two 13.3 / 12.6 / 12.4 / 12.4 / 12.6
-      const int q = cdiv(384, W);
-      return W * (q < tiles ? q : tiles);
-    }
-    // Asynchronous kernel: 64 x 64 output blocks per (sub-pixel, channel block); a data-group's 128-pixel
-    // tiles are dealt to its splits. Take the fewest splits that give the launch target_wgs workgroups:
-    // the partial sums cost HBM traffic (written here, read by the update) in proportion to the split
-    // count. Measured on the ResNet-18 step (four modules on four hardware queues): 1024 / 512 workgroups cost
-    // 3.45 / 3.13 ms against 2.64 at 256 under an earlier stream layout; now 64 / 128 / 192 / 256 -> 2.59 / 2.47 /
-    // 2.46 / 2.48 ms. With two modules (ResNet-20 shapes) 256 beats 128 (1.47 vs 1.67 ms): the caller passes 128
-    // when three or more modules share the chip (half the partial-sum traffic at equal speed), else 256.
-    // wgrad_flat_kernel takes the same target: half of it 0.87-1.10, twice 0.93-1.22 of the step time over 118 nets of 7 x 7
-    // to 28 x 28 images.
-    WgradParams probe = shape;
-    probe.nsplit = W;
-    probe.nrep = W;
-    WgradFlatGeom flat{};
-    int nsub = 0, cblocks = 0, rep_tiles = 0;
-    if (wgrad_dma_eligible(probe, &nsub, &cblocks)) rep_tiles = per_replica / 128;
-    else if (wgrad_flat_geometry(probe, W, flat, nsub)) { cblocks = flat.cblocks; rep_tiles = flat.rep_tiles; }
-    if (rep_tiles > 0) {
-      const int blocks = cdiv(Mout, 64) * nsub * cblocks;
-      // a stride-2 workgroup has four waves where a stride-1 one has twelve, and the four sub-pixels of a 3x3
-      // kernel carry 4 : 2 : 2 : 1 taps: twice the workgroups (2.24 ms per ResNet-18 step; 2.26 with one or four times)
-      if (shape.stride == 2) target_wgs *= 2;
-      int q = cdiv(target_wgs, blocks * W);
-      if (q > rep_tiles) q = rep_tiles;
-      if (q * W > 256) q = 256 / W;
-      if (q < 1) q = 1;
-      return W * q;  // the launch takes the same decision
-    }
+WgradWork wgrad_work(int dt, const WgradParams& shape) {
+  WgradWork w{};
+  if (dt == DT_F32) return w;
+  int smem = 0;
+  WgradLayer l;
+  if (const int tiles = wgrad_slim_tiles(shape, shape.nrep, &w.key)) {
+    w.blocks = 1;
+    w.tiles = tiles;
+    w.key += 4;
+  } else if (wgrad_layer(shape, l, &w.tiles, &smem)) {
+    w.blocks = l.gx * l.gy;
+    w.key = shape.stride;
   }
+  return w;
+}
+
+// Split count of the kernels that take any layer.
+static int wgrad_generic_split(int dt, const WgradParams& shape) {
+  const int Mout = shape.Mout, NK = shape.NK, W = shape.nrep;
+  const int per_replica = shape.P / W;  // pixels of one replica's mini-batch
   const int ce = dtype_ce(dt);
   const int bke = 128 / dtype_size(dt);
   int tiles = (Mout <= 64) ? cdiv(Mout, 64) * cdiv(NK + ce, 256) : cdiv(Mout, 128) * cdiv(NK + ce, 128);
@@ -2229,6 +2222,34 @@ int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs) 
   if (q < 1) q = 1;
   while (q > 1 && per_replica % q != 0) --q;  // splits never straddle replicas
   return W * q;
+}
+
+void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) {
+  const WgradWork w0 = wgrad_work(dt, shapes[0]);
+  if (w0.key == 0) {
+    for (int i = 0; i < n; ++i) nsplit[i] = wgrad_generic_split(dt, shapes[i]);
+    return;
+  }
+  long long total = 0;
+  for (int i = 0; i < n; ++i) {
+    const WgradWork w = wgrad_work(dt, shapes[i]);
+    total += (long long)w.blocks * w.tiles * shapes[i].nrep;
+  }
+  // Workgroups of the launch. The partial sums cost HBM traffic in proportion to the split counts (written here, read by the
+  // update), and a workgroup of the wide kernel keeps others of its kind off the CU: half of the chip, three quarters where each
+  // has 32 tiles all the same. ms per 8 steps with 128 / 192 / 256: ResNet-18 in four modules 17.3 / 17.0 / 17.4, 64 images of it 4.3 /
+  // 4.4 / 4.6; ResNet-20 in one module 3.50 / 3.58 / 3.59. A stride-2 workgroup has four waves where a stride-1 one has twelve, and the
+  // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many. Narrow layers: two or three share a CU (256 / 384 / 512:
+  // ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its normalised form in two 11.9 / 11.7 / 11.5).
+  int target_wgs = w0.key > 4 ? 512 : total >= 192 * 32 ? 192 : 128;
+  if (w0.key == 2) target_wgs *= 2;
+  const long long per_wg = (total + target_wgs - 1) / target_wgs;  // tiles a workgroup walks
+  for (int i = 0; i < n; ++i) {
+    const WgradWork w = wgrad_work(dt, shapes[i]);
+    long long q = (w.tiles + per_wg - 1) / per_wg;
+    if (q * shapes[i].nrep > 512) q = 512 / shapes[i].nrep;
+    nsplit[i] = shapes[i].nrep * (int)(q < 1 ? 1 : q);
+  }
 }
 
 }  // namespace dds

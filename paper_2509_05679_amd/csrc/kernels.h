@@ -140,19 +140,22 @@ int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
-int launch_wgrad(int dt, const WgradParams& p, hipStream_t s);
+// n layers of one key (wgrad_work), or one of any kind
+int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);
+// Layers of one key, if it is not 0, may share a launch; a split of theirs is at least one of `tiles` tiles of a data-group,
+// and each is walked by `blocks` workgroups. shape: every field that describes the layer (Nimg, H, W, Cx, Ho, Wo, Mout, ldy,
+// R, S, stride, pad, NK, P, nrep, zeros non-null); nsplit, pix_per_split and the other pointers are ignored.
+struct WgradWork { int key, blocks, tiles; };
+WgradWork wgrad_work(int dt, const WgradParams& shape);
 // Layers that one weight-gradient launch can take at most.
 constexpr int kWgradGroupMax = 16;
-// bf16 3x3 stride-1 layers of 8, 16 or 32 input channels (narrow.hip): tiles of a data-group (0: not such a layer), and the
-// launch for n layers of one input width (false: not taken, nothing launched)
-int wgrad_slim_tiles(const WgradParams& shape, int W);
+// bf16 3x3 stride-1 layers of 8, 16 or 32 input channels (narrow.hip): tiles of one of nrep data-groups (0: not such a layer)
+// with the kernel's variant, and the launch for n layers of one variant (false: not taken, nothing launched)
+int wgrad_slim_tiles(const WgradParams& shape, int nrep, int* variant);
 bool launch_wgrad_slim(const WgradParams* p, int n, hipStream_t s);
-// Chooses the split count of the pixel reduction for a wgrad problem: a multiple of the replica
-// count W, so that no split mixes two replicas. shape: every field that describes the layer
-// (Nimg, H, W, Cx, Ho, Wo, Mout, ldy, R, S, stride, pad, NK, P, zeros non-null); nsplit,
-// pix_per_split and the pointers are ignored.
-// target_wgs: workgroups the asynchronous kernel's launch should reach (fewer splits = less partial-sum traffic).
-int wgrad_choose_split(int dt, const WgradParams& shape, int W, int target_wgs);
+// Chooses the split counts of the pixel reductions of layers that share a launch (n > 1: one key): multiples of nrep, so that no
+// split mixes two data-groups.
+void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit);
 
 void launch_ingest(int dt, const IngestParams& p, hipStream_t s);
 void launch_maxpool_fwd(int dt, const void* x, void* y, int N, int H, int W, int C, hipStream_t s);

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void conv16_direct_kernel(ConvParams p) {
 // dW[k][tap][c] = sum over pixels p of dY[p][k] * X[p + tap][c] for 3x3 stride-1 pad-1 layers of 8, 16 or 32 input
 // and at most 32 (8 or 16 input: 64) output channels. All of dW is 32 NM x 32 NT (n = tap * Cx + c; the layout of a partial row),
 // which one wave holds in its accumulators: the four waves of a workgroup share the pixels, not the channels, and add their
-// sums in LDS when the workgroup has walked its split. Pixels of a data-group are numbered as in wgrad_flat_kernel (a
+// sums in LDS when the workgroup has walked its split. Pixels of a data-group are numbered as in wgrad_flat_body (a
 // row pitch of W + 1, an extra row above every image; zeros at the extra positions), so that any image size will do, a tile is
 // `tile` consecutive positions and the nine taps are constant distances. Tiles travel global -> LDS in two slots as plain
 // [position][channels] rows; ds_read_b64_tr_b16 hands a lane four positions of one channel, and because every lane supplies the
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void conv16_direct_kernel(ConvParams p) {
 // Bound by memory (64 to 144 bytes of a pixel against 4.6 to 18 kFLOP) and by one barrier per tile. A launch takes several
 // layers: workgroup -> (layer, split). Alone, 1024 images: 16 -> 16 channels at 32 x 32 27.8 -> 19.1 us (512 workgroups, 3.5 TB/s;
 // a kernel that staged its tiles through registers before), 32 -> 32 at 16 x 16 27.9 -> 18.3 us and the stem with 16 outputs 95 -> 14.4
-// us (64 x 64 blocks of wgrad_dma_kernel, 3/4 and 31/32 padding before), with 64 outputs and 512 images 50 -> 21.6 us. Tiles of
+// us (64 x 64 blocks of wgrad_dma_body, 3/4 and 31/32 padding before), with 64 outputs and 512 images 50 -> 21.6 us. Tiles of
 // 256 positions (54 KB limit below) against 512: 19.1 / 22.5 us for the 16-channel layers.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
@@ -404,9 +404,11 @@ bool launch_conv_narrow(const ConvParams& p, hipStream_t s) {
   return true;
 }
 
-int wgrad_slim_tiles(const WgradParams& shape, int W) {
+int wgrad_slim_tiles(const WgradParams& shape, int nrep, int* variant) {
   SlimLayer l{};
-  return slim_layer(shape, W, l) ? l.rep_tiles : 0;
+  if (!slim_layer(shape, nrep, l)) return 0;
+  *variant = shape.Cx + slim_blocks(shape);
+  return l.rep_tiles;
 }
 
 bool launch_wgrad_slim(const WgradParams* p, int n, hipStream_t s) {

@@ -261,3 +261,27 @@ def test_shared_reductions_with_weights_per_data_group():
     wl = Workload(name="shared_reductions", ops=ops, bounds=[0, 4, len(ops)], K=2, W=4, B=16, in_shape=(3, 8, 8), classes=10,
                   precision="bf16", lr=0.05, momentum=0.0, steps=4)
     compare_gossip(wl, seed=36, T=4, mixing=ring_mixing(4, 0.3), tiny=False)
+
+
+@pytest.mark.parametrize("widths,h,w,W,B", [
+    ((16,) * 19, 16, 16, 2, 5),                       # more layers of one kind than a launch takes (16)
+    ((64, 64, 128, 64, 72, 64), 8, 8, 1, 33),         # whole 128-pixel tiles and others (72 channels in) share a launch
+    ((64,) * 5, 32, 32, 1, 700)])                     # launches closed by their work: 5600 tiles a layer, three layers
+def test_weight_gradients_that_share_a_launch(widths, h, w, W, B):
+    # while launches are timed every layer has one of its own: the same bits
+    import paper_2509_05679_amd as P
+    wl = _conv_chain("bf16", widths, h, w, W, B)
+    gen = torch.Generator(device="cuda").manual_seed(38)
+    xs = [torch.randn((B, 3, h, w), device="cuda", generator=gen) for _ in range(W)]
+    ys = [torch.randint(10, (B,), device="cuda", generator=gen, dtype=torch.int32) for _ in range(W)]
+    init, runs = make_params(wl, 38), []
+    for mode in (0, 2):
+        tr = P.Trainer(P.Spec.from_workload(wl), W)
+        tr.dds_set_params(0, init[0])
+        tr.dds_profile(mode)
+        for _ in range(3):
+            tr.dds_step(xs, ys)
+        runs.append(tr.dds_get_params(0))
+        tr.close()
+    assert np.isfinite(runs[0]).all() and np.array_equal(runs[0], runs[1])
+    assert not np.array_equal(runs[0], np.concatenate([p.ravel() for p in init[0]]))
