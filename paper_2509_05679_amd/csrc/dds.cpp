@@ -1221,13 +1221,15 @@ int dds_create(const dds_spec* spec, int K, int W, const int* delays, void* aren
   if (e != hipSuccess) { dds_destroy(c); return fail(DDS_EHIP, "hipEventCreate failed: %s", hipGetErrorString(e)); }
   int nq = 4;
   if (const char* q = getenv("GPU_MAX_HW_QUEUES")) { const int v = atoi(q); if (v >= 1 && v <= 32) nq = v; }
-  if (K == 1 && nq >= 2 && overlapped_wgrad_flops(*c, c->mods[0]) >= (c->dt == DT_F32 ? 0.4e9 : 1e9)) {
-    // A single module has no other module's kernels beside it: its weight gradients get a stream, if they are long enough.
-    // A launch on the side costs two event calls, 11 to 17 us on the host (which is what the ranges below come from) and 4 us
-    // between the kernels. us per step with and without, at a mean of so many GFLOP: bf16 ResNet-18 of 1.0 633 / 660, of 0.5
-    // 563-601 / 571, of 8.2 1213 / 1285; ResNet-20 of 1.1 603-623 / 613, of 0.8 564-626 / 580, of 0.07 470-618 / 402; ResNet-56 of 2.3
-    // 2113-2177 / 2358, of 0.6 1209-1542 / 1291; fp32 CNN of 0.9 958 / 979, of 0.5 945 / 943, of 0.2 924 / 910. Nets of nine layers
-    // pay up to twice the line (28 x 28 images, 2.2: 309 / 295).
+  const double wflops = K == 1 ? overlapped_wgrad_flops(*c, c->mods[0]) : 0.0;
+  const double pixels = (double)c->N * c->in_h * c->in_w;
+  if (nq >= 2 && (c->dt == DT_F32 ? wflops >= 0.4e9 : wflops >= 1e10 || (wflops >= 1e9 && pixels >= 4e5))) {
+    // A single module has no other module's kernels beside it: its weight gradients get a stream, if they are long enough, by
+    // their work or by the size of their tensors. A launch on the side costs two event calls, 11 to 17 us on the host and 4 us
+    // between the kernels. us per step with and without, at a mean of so many GFLOP and so many 1000 input pixels: bf16 ResNet-18 of 0.9,
+    // 16 530 / 485, of 7, 131 1053 / 1032, of 14, 262 1547 / 1614; ResNet-20 of 1.0, 262 454 / 435, of 2.0, 524 672 / 694, of 3.0, 795 898 /
+    // 946; ResNet-56 of 0.6, 131 890 / 861, of 2.3, 524 1627 / 1699; wide ResNet-34 of 4, 16 2088 / 2098, of 16, 66 3487 / 3618; four layers at
+    // 28 x 28 and 14 x 14 pixels of 1, 201 286 / 270, of 2, 401 380 / 387; fp32 CNN of 0.2 928 / 901, of 0.9 958 / 968, of 14 1876 / 2140.
     // (With two modules the events cost what the overlap gains: 1.97 -> 2.05 ms per 8 steps of the 28 x 28 net, 13.5 -> 13.7 ms of
     // the normalised ResNet-20.)
     Module& m = c->mods[0];
