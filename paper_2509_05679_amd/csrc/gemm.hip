@@ -24,7 +24,6 @@
 namespace dds {
 namespace {
 
-#define DDS_LDS_AS __attribute__((address_space(3)))
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
@@ -2017,7 +2016,7 @@ template <typename T>
 int launch_conv_one(const ConvParams& p, hipStream_t s) {
   constexpr int BKB = 64;
   if (p.nrep <= 1 && launch_linear(sizeof(T) == 4 ? DT_F32 : DT_BF16, p, s)) return 0;  // a data-group's slice
-  if (sizeof(T) == 2 && launch_conv_narrow(p, s)) return 1;
+  if (sizeof(T) == 2 && launch_conv_narrow(p, s)) return p.Cx == 16;
   if (launch_dma<T>(p, s)) return 1;
   if (launch_gather<T>(p, s)) return 0;
   // dgrad of a stride-2 convolution: workgroups per parity class (class (0,0) is the largest)

@@ -133,12 +133,12 @@ struct UpdateDesc {
 };
 
 // Both return the kernel family that took the launch, the class of dds_profile_read: 1 = the kernels made for 3x3 stride-1
-// layers and, among the weight gradients, stride-2 ones (conv3x3_dma, wgrad_dma, wgrad_flat, narrow.hip's), 0 = those that
-// take any layer (conv_gather, conv_gemm, linear, wgrad_gemm, wgrad_f32).
+// layers and, among the weight gradients, stride-2 ones (conv3x3_dma, conv_direct, wgrad_tiles, wgrad_slim), 0 = those that
+// take any layer (conv_gather, conv_gemm, linear, wgrad_gemm, wgrad_f32) and the forward pass of a stem (conv_direct, 8 channels).
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 // plain products of few rows (linear.hip); false: not taken, nothing launched
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
-// bf16 3x3 stride-1 layers with 16-channel rows (narrow.hip); false: not taken, nothing launched
+// bf16 3x3 stride-1 layers with 16-channel rows, stems (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
 // n layers of one key (wgrad_work), or one of any kind
 int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);

@@ -4,6 +4,8 @@
 
 #include "device_once.h"
 
+#define DDS_LDS_AS __attribute__((address_space(3)))
+
 namespace dds {
 namespace {
 

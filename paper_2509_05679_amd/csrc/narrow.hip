@@ -5,9 +5,8 @@
 // in LDS) spends its time on padding. These kernels use v_mfma_f32_16x16x32_bf16 with the 16 output channels as
 // the rows and 16 consecutive pixels as the columns of one accumulator tile, and keep everything else out of
 // the way:
-//   forward / dgrad: all nine taps of the weights (4.6 KB) live in registers as the A operand; the B operand of
-//   a tap is read straight from global memory, 16 bytes per lane (eight channels of one pixel, shifted by the
-//   tap) -- neighbouring taps re-read the same cache lines from the vector cache, so no LDS and no barrier;
+//   forward / dgrad (and the forward pass of a stem): all nine taps of the weights (4.6 KB) live in registers as the A operand; the B
+//   operand of a tap is 16 bytes per lane (eight channels of one pixel, shifted by the tap) of a patch in LDS;
 //   weight gradient (also of the 8- and 32-channel layers): see wgrad_slim_kernel below.
 #include "device_once.h"
 #include "kernels.h"
@@ -30,113 +29,194 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// 3x3, stride 1, pad 1, 16 input channels (channel stride 16), at most 16 output channels (stride 16).
-// One wave owns GROUPS runs of 16 consecutive pixels of the flattened (image, row, column) index; the image width
-// is a multiple of 16, so a run lies inside one image row. Lane l = 16 g + j holds, as B operand of MFMA t,
-// channels 8 (g & 1) .. +8 of pixel j shifted by tap 2 t + (g >> 1), and as A operand the same k-slice of weight
-// row j; the accumulator gives it output channels 4 g .. 4 g + 3 of pixel j: one 8-byte store, and the four lane
-// groups together write the 512 contiguous bytes of the run.
+// 3x3, stride 1, pad 1, CIN = 8 or 16 input channels (their stride), at most 16 NB output channels (stride 16 NB).
+// A workgroup owns 64 GROUPS consecutive pixels of the flattened (image, row, column) index; in it the nine taps of a pixel
+// are the pixels at distance -W-1 .. W+1, so its patch is 64 GROUPS + 2W + 2 consecutive pixels, copied global -> LDS as they lie.
+// A wave owns GROUPS runs of 16 pixels. An MFMA multiplies 32 / CIN taps: lane l = 16 g + j holds, as B operand, eight channels of
+// pixel j shifted by its tap (16 channels: tap 2 t + (g >> 1), channels 8 (g & 1) .. +8; 8 channels: tap 4 t + g), and as A operand
+// the same k-slice of a weight row of each of the NB blocks; rows are dealt to the blocks so that the accumulators give it the 4 NB
+// output channels from 4 NB g on of pixel j: 8, 16 or 32 consecutive bytes, and a wave whole lines. Taps outside the image (and past the ninth) read zeros that lie behind the patch: one
+// select per tap, of an address that is the same in every run up to the instruction's offset.
+// ROWS16: the image width is a multiple of 16, so a run lies inside one image row whose place is a scalar.
 // DGRAD: x is the output gradient, w the transposed snapshot [cin][tap][cout], tap (r, s) gathers at
 // (h + 1 - r, w + 1 - s); the epilogue options are the ones of ConvParams.
-template <bool DGRAD, int GROUPS>
-__global__ __launch_bounds__(256) void conv16_direct_kernel(ConvParams p) {
+// Bound by memory, then by what every tile costs beside it. 16 -> 16 channels at 32 x 32, 1024 images, alone: operands read straight
+// from global memory 24.8 us forward (with a residual 28.5) and 24.3 us backward, of which the five operand reads of a run, at 24
+// cycles of the vector cache each, are 13; here 20.1 (23.2) and 20.6 us (69 to 103 MB). Stem to 16 channels (a gather through registers in 256 x 32
+// tiles before) 40.4 -> 16.4 us, to 64 channels, 512 images, 49.6 -> 32.1 us.
+// 1 in each half of a packed bf16 pair >= 0 that is not zero (one instruction: min as unsigned 16-bit numbers)
+__device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
+  typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, pair), (u16x2_t){1, 1}));
+}
+
+template <int CIN, int NB, bool DGRAD, bool ROWS16, int GROUPS>
+__global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fills, Divisor dW, Divisor dH) {
+  constexpr int PB = CIN * 2, PLOG = CIN == 16 ? 1 : 0, TPM = 32 / CIN, NM = (9 + TPM - 1) / TPM, OB = 32 * NB;  // OB: bytes of an output pixel
+  extern __shared__ __align__(16) char smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
   const int lane = threadIdx.x & 63;
-  const int wave = (blockIdx.x * 256 + threadIdx.x) >> 6;
   const int j = lane & 15, g = lane >> 4;
-  const int half = g & 1;
-  const int ngroups = p.M >> 4;
-  const int grp0 = wave * GROUPS;
-  if (grp0 >= ngroups) return;
-  const int HW = p.H * p.W;
+  const int half = CIN == 16 ? g & 1 : 0, tapl = CIN == 16 ? g >> 1 : g;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = blockIdx.x * (64 * GROUPS), row0 = wave * (16 * GROUPS), pix0 = m0 + row0;
+
+  // the patch; pixels before the tensor's first or after its last repeat that pixel (no tap inside an image reads them)
+  for (int f = wave; f < fills; f += 4) {
+    const int piece = f * 64 + lane;
+    const int pix = min(max(m0 - p.W - 1 + (piece >> PLOG), 0), p.M - 1);
+    dma16((const char*)p.x + ((((size_t)(uint32_t)pix << PLOG) + (piece & ((1 << PLOG) - 1))) << 4), lds0 + f * 1024);
+  }
+  const uint32_t zeros = fills * 1024;
+  if (threadIdx.x < GROUPS * PB) *(uint4*)(smem + zeros + threadIdx.x * 16) = make_uint4(0u, 0u, 0u, 0u);
 
   const char* wbase = (const char*)p.w;
   const float* bias = p.bias;
-  if (p.nrep > 1) {  // a run never leaves its image, a workgroup may: weights are picked per wave
-    const int img = (grp0 << 4) / HW;
-    const int r = min(img / (p.Nimg / p.nrep), p.nrep - 1);
+  if (p.nrep > 1) {  // the pixels of a wave belong to one data-group, those of a workgroup may not
+    const int r = min(pix0 / (p.M / p.nrep), p.nrep - 1);
     wbase += (size_t)r * p.w_rep;
     if (bias) bias += (size_t)r * p.bias_rep;
   }
-  // weights: MFMA t, lane (j, g): row j, tap 2 t + (g >> 1), channels 8 half .. +8; zero past Nout and past tap 8
-  uint4 wa[5];
-  int dr[5], ds[5];
-  bool tap_ok[5];
+  // weights: MFMA t, block b, lane (j, g): row j of the block, this lane's tap and channels; zero past Nout and past tap 8
+  uint4 wa[NB][NM];
+  int dr[NM], ds[NM];
+  uint32_t toff[NM];    // LDS address at the wave's first run
+  uint32_t leaves = 0;  // nibble t: tap t of this lane leaves the image at its top row, bottom row, first or last run
 #pragma unroll
-  for (int t = 0; t < 5; ++t) {
-    const int tap = 2 * t + (g >> 1);
-    tap_ok[t] = tap < 9;
-    const int tt = tap_ok[t] ? tap : 0;
+  for (int t = 0; t < NM; ++t) {
+    const int tap = TPM * t + tapl, tt = tap < 9 ? tap : 0;
     const int r = tt / 3, s = tt - 3 * r;
     dr[t] = DGRAD ? 1 - r : r - 1;
     ds[t] = DGRAD ? 1 - s : s - 1;
-    const bool ok = tap_ok[t] && j < p.Nout;
-    const uint4 v = *(const uint4*)(wbase + ((size_t)((ok ? j : 0) * 9 + tt) * 16 + half * 8) * 2);
-    wa[t] = ok ? v : make_uint4(0u, 0u, 0u, 0u);
-  }
-  float ab[4];
+    toff[t] = tap < 9 ? (uint32_t)((p.W + 1 + row0 + j + dr[t] * p.W + ds[t]) * PB + half * 16) : zeros;
+    leaves |= ((dr[t] < 0 ? 1u : 0u) | (dr[t] > 0 ? 2u : 0u) | (ds[t] < 0 && j == 0 ? 4u : 0u) | (ds[t] > 0 && j == 15 ? 8u : 0u)) << (4 * t);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int n = 4 * g + e;
-    ab[e] = (bias != nullptr && n < p.Nout) ? p.alpha * bias[n] : 0.f;
+    for (int b = 0; b < NB; ++b) {
+      const int n = 4 * NB * (j >> 2) + 4 * b + (j & 3);
+      const bool ok = tap < 9 && n < p.Nout;
+      const uint4 v = *(const uint4*)(wbase + ((size_t)((ok ? n : 0) * 9 + tt) * CIN + half * 8) * 2);
+      wa[b][t] = ok ? v : make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  // epilogue operands of this lane's channels; a run past the last pixel reads the last one's
+  const uint32_t lane_out = (uint32_t)(j * OB + 8 * NB * g);
+  uint2 rs[GROUPS][NB], mk[GROUPS][NB];
+  uint32_t keep[GROUPS];
+  auto pixel_at = [&](int u) { return (size_t)(ROWS16 ? min(pix0 + 16 * u, p.M - 16) : min(pix0 + 16 * u + j, p.M - 1)); };
+  const uint32_t lane_in = ROWS16 ? lane_out : (uint32_t)(8 * NB * g);
+  auto load_channels = [&](const void* src, int u, uint2 (&v)[NB]) {
+    const char* at = (const char*)src + pixel_at(u) * OB + lane_in;
+    if (NB == 1) {
+      v[0] = *(const uint2*)at;
+    } else {
+#pragma unroll
+      for (int b = 0; b + 1 < NB; b += 2) {
+        const uint4 q = *(const uint4*)(at + 8 * b);
+        v[b] = make_uint2(q.x, q.y);
+        v[b + 1] = make_uint2(q.z, q.w);
+      }
+    }
+  };
+  if (p.res) {
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) load_channels(p.res, u, rs[u]);
+  }
+  if (p.maskbits) {  // NB == 1 (dgrad)
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) keep[u] = *(const uint16_t*)((const char*)p.maskbits + pixel_at(u) * 2 + (ROWS16 ? 2 * j : 0));
+  } else if (p.mask) {
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) load_channels(p.mask, u, mk[u]);
+  }
+  float ab[NB][4];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ab[b][e] = 0.f;
+  if (bias) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int n = 4 * NB * g + 4 * b + e;
+        const float v = p.alpha * bias[min(n, p.Nout - 1)];
+        ab[b][e] = n < p.Nout ? v : 0.f;
+      }
   }
   const float lower = p.relu ? 0.f : -__builtin_inff();
+  wait_vm<0>();
+  __syncthreads();
 
 #pragma unroll
   for (int u = 0; u < GROUPS; ++u) {
-    const int grp = grp0 + u;
-    if (grp >= ngroups) break;  // wave-uniform
-    const int pix = (grp << 4) + j;
-    const int img = pix / HW, rem = pix - img * HW;
-    const int h = rem / p.W, w = rem - h * p.W;
-    const char* ximg = (const char*)p.x + (size_t)img * HW * 32 + half * 16;
-    uint4 xb[5];
+    const int run = pix0 + 16 * u;
+    if (run >= p.M) break;  // wave-uniform
+    const bool in = ROWS16 || run + j < p.M;
+    uint4 xb[NM];
+    {
+      const int pix = ROWS16 ? run : run + j;
+      const uint32_t line = __umulhi((uint32_t)pix, dW.mul) >> dW.shift;
+      const int h = (int)(line - (__umulhi(line, dH.mul) >> dH.shift) * (uint32_t)p.H), w = pix - (int)line * p.W;
+      const uint32_t edges = (h == 0 ? 0x11111u : 0u) | (h == p.H - 1 ? 0x22222u : 0u) | (w == 0 ? 0x44444u : 0u) |
+                             (w + 16 == p.W ? 0x88888u : 0u);
+      const uint32_t out = leaves & edges;
 #pragma unroll
-    for (int t = 0; t < 5; ++t) {
-      const int hh = h + dr[t], ww = w + ds[t];
-      const bool ok = tap_ok[t] && (unsigned)hh < (unsigned)p.H && (unsigned)ww < (unsigned)p.W;
-      const uint4 v = *(const uint4*)(ximg + (size_t)(ok ? hh * p.W + ww : rem) * 32);  // unconditional, clamped
-      xb[t] = ok ? v : make_uint4(0u, 0u, 0u, 0u);
+      for (int t = 0; t < NM; ++t) {
+        const bool leave = ROWS16 ? (out & (0xfu << (4 * t))) != 0 : (unsigned)(h + dr[t]) >= (unsigned)p.H || (unsigned)(w + ds[t]) >= (unsigned)p.W;
+        xb[t] = *(const uint4*)(smem + (leave ? zeros : toff[t]) + 16 * u * PB);
+      }
     }
-    // epilogue operands of this lane's four channels (8 bytes each), also unconditional
-    const size_t o = (size_t)pix * 16 + 4 * g;
-    uint2 rs = make_uint2(0u, 0u), mk = make_uint2(0u, 0u);
-    uint32_t keep = 0xfu;
-    if (p.res) rs = *(const uint2*)((const uint16_t*)p.res + o);
-    if (p.maskbits) keep = ((uint32_t)((const uint16_t*)p.maskbits)[pix] >> (4 * g)) & 0xfu;
-    else if (p.mask) {
-      mk = *(const uint2*)((const uint16_t*)p.mask + o);
-      keep = ((int)(mk.x << 16) >= 0x10000 ? 1u : 0u) | ((int)mk.x >= 0x10000 ? 2u : 0u) |
-             ((int)(mk.y << 16) >= 0x10000 ? 4u : 0u) | ((int)mk.y >= 0x10000 ? 8u : 0u);
-    }
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    uint32_t out[2 * NB], signs = 0;  // signs: this lane's 4 NB stored, rounded values that are > 0
 #pragma unroll
-    for (int t = 0; t < 5; ++t) acc = mfma16(wa[t], xb[t], acc);
-    const float r4[4] = {__uint_as_float(rs.x << 16), __uint_as_float(rs.x & 0xffff0000u),
-                         __uint_as_float(rs.y << 16), __uint_as_float(rs.y & 0xffff0000u)};
-    float v[4];
-    uint32_t signs = 0;
+    for (int b = 0; b < NB; ++b) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float t = fmaf(p.alpha, acc[e], ab[e]) + r4[e];
-      t = __builtin_amdgcn_fmed3f(t, lower, __builtin_inff());
-      v[e] = ((keep >> e) & 1u) ? t : 0.f;
+      for (int t = 0; t < NM; ++t) acc = mfma16(wa[b][t], xb[t], acc);
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaf(p.alpha, acc[e], ab[b][e]);
+      if (p.res) {
+        v[0] += __uint_as_float(rs[u][b].x << 16); v[1] += __uint_as_float(rs[u][b].x & 0xffff0000u);
+        v[2] += __uint_as_float(rs[u][b].y << 16); v[3] += __uint_as_float(rs[u][b].y & 0xffff0000u);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_fmed3f(v[e], lower, __builtin_inff());  // one instruction; NaN -> lower
+      if (p.maskbits) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)  // bit -> 0 / all ones, then and
+          v[e] = __uint_as_float(__float_as_uint(v[e]) & (uint32_t)__builtin_amdgcn_sbfe((int)(keep[u] >> (4 * g)), e, 1));
+      } else if (p.mask) {
+        if ((int)(mk[u][b].x << 16) < 0x10000) v[0] = 0.f;
+        if ((int)mk[u][b].x < 0x10000) v[1] = 0.f;
+        if ((int)(mk[u][b].y << 16) < 0x10000) v[2] = 0.f;
+        if ((int)mk[u][b].y < 0x10000) v[3] = 0.f;
+      }
+      out[2 * b] = pack_bf16_rne(v[0], v[1]);
+      out[2 * b + 1] = pack_bf16_rne(v[2], v[3]);
+      if (p.bits_out) {  // (behind a ReLU: no value is negative)
+        const uint32_t t = nonzero2(out[2 * b]) | nonzero2(out[2 * b + 1]) << 2;  // channels 0, 2 in bits 0, 2; 1, 3 in bits 16, 18
+        signs |= ((t | t >> 15) & 0xfu) << (4 * b);
+      }
     }
-    uint2 out;
-    out.x = pack_bf16_rne(v[0], v[1]);
-    out.y = pack_bf16_rne(v[2], v[3]);
-    *(uint2*)((uint16_t*)p.y + o) = out;
+    char* y = (char*)p.y + (size_t)run * OB + lane_out;
+    if (in) {
+      if (NB == 1) *(uint2*)y = make_uint2(out[0], out[1]);
+#pragma unroll
+      for (int b = 0; b + 1 < NB; b += 2) *(uint4*)(y + 8 * b) = make_uint4(out[2 * b], out[2 * b + 1], out[(2 * b + 2) % (2 * NB)], out[(2 * b + 3) % (2 * NB)]);
+    }
     if (p.bits_out) {
-      // the sign of the stored (rounded) value, as every other producer defines the plane
-      signs = ((int)(out.x << 16) >= 0x10000 ? 1u : 0u) | ((int)out.x >= 0x10000 ? 2u : 0u) |
-              ((int)(out.y << 16) >= 0x10000 ? 4u : 0u) | ((int)out.y >= 0x10000 ? 8u : 0u);
-      uint32_t word = signs << (4 * g);
-      word |= (uint32_t)__shfl_xor((int)word, 16, 64);
-      word |= (uint32_t)__shfl_xor((int)word, 32, 64);
-      if (g == 0) ((uint16_t*)p.bits_out)[pix] = (uint16_t)word;
+      char* bits = (char*)p.bits_out + (size_t)run * (2 * NB);
+      if (NB == 1) {  // two lanes hold a byte
+        const uint32_t byte = signs | (uint32_t)__shfl_xor((int)signs, 16, 64) << 4;
+        if (!(g & 1) && in) *(uint8_t*)(bits + (uint32_t)(2 * j + (g >> 1))) = (uint8_t)byte;
+      } else if (NB == 2) {
+        if (in) *(uint8_t*)(bits + (uint32_t)(4 * j + g)) = (uint8_t)signs;
+      } else {
+        if (in) *(uint16_t*)(bits + (uint32_t)(8 * j + 2 * g)) = (uint16_t)signs;
+      }
     }
   }
 }
-
 
 // ------------------------------------------------------------------ weight gradient, rows of at most 32 input channels
 // dW[k][tap][c] = sum over pixels p of dY[p][k] * X[p + tap][c] for 3x3 stride-1 pad-1 layers of 8, 16 or 32 input
@@ -156,7 +236,6 @@ __global__ __launch_bounds__(256) void conv16_direct_kernel(ConvParams p) {
 // 256 positions (54 KB limit below) against 512: 19.1 / 22.5 us for the 16-channel layers.
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-#define DDS_LDS_AS __attribute__((address_space(3)))
 __device__ __forceinline__ uint2 lds_tr16_b64(uint32_t lds_byte_address) {
   s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t DDS_LDS_AS*)(size_t)lds_byte_address);
   return __builtin_bit_cast(uint2, v);
@@ -379,6 +458,8 @@ bool slim_layer(const WgradParams& p, int W, SlimLayer& l) {
 // wgrad_slim_kernel's NM
 inline int slim_blocks(const WgradParams& p) { return p.ldy <= 16 && p.Cx <= 16 ? 0 : p.ldy <= 32 ? 1 : 2; }
 
+inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
 template <int XB, int NM>
 void launch_slim_inst(const SlimGroup& g, int wgs, int smem, hipStream_t s) {
   static DeviceOnce lds;
@@ -388,19 +469,38 @@ void launch_slim_inst(const SlimGroup& g, int wgs, int smem, hipStream_t s) {
 
 }  // namespace
 
-// True if the launch was taken: bf16, 3x3 stride 1 pad 1, 16-channel input and output rows, image width a multiple of 16.
+template <int CIN, int NB, bool DGRAD, bool ROWS16>
+void launch_direct_inst(const ConvParams& p, hipStream_t s) {
+  constexpr int GROUPS = NB == 4 ? 2 : 4, PB = CIN * 2;
+  const int fills = cdiv((64 * GROUPS + 2 * p.W + 2) * PB, 1024);
+  static DeviceOnce lds;
+  allow_whole_lds(lds, (const void*)conv_direct_kernel<CIN, NB, DGRAD, ROWS16, GROUPS>);
+  conv_direct_kernel<CIN, NB, DGRAD, ROWS16, GROUPS><<<cdiv(p.M, 64 * GROUPS), 256, fills * 1024 + GROUPS * PB * 16, s>>>(p, fills, make_divisor(p.W), make_divisor(p.H));
+}
+template <int CIN, int NB, bool DGRAD>
+void launch_direct(const ConvParams& p, hipStream_t s) {
+  if (p.W % 16 == 0) launch_direct_inst<CIN, NB, DGRAD, true>(p, s);
+  else launch_direct_inst<CIN, NB, DGRAD, false>(p, s);
+}
+
+// True if the launch was taken: bf16, 3x3 stride 1 pad 1, from rows of 16 channels to rows of 16 in either direction and,
+// forward, from rows of 8 (the stem) to rows of 16, 32 or 64.
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s) {
   if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.H != p.Ho || p.W != p.Wo) return false;
-  if (p.Cx != 16 || p.ldy != 16 || p.Nout > 16 || p.out_f32 || p.x2 != nullptr) return false;
-  if (p.W % 16 != 0 || p.M % 16 != 0 || p.M != p.Nimg * p.H * p.W) return false;
-  // a wave's runs (64 pixels) must not straddle two data-groups
-  if (p.nrep > 1 && (p.Nimg % p.nrep != 0 || (p.H * p.W) % 64 != 0)) return false;
-  constexpr int GROUPS = 4;
-  const int ngroups = p.M / 16;
-  const int waves = (ngroups + GROUPS - 1) / GROUPS;
-  const int blocks = (waves + 3) / 4;
-  if (p.dgrad) conv16_direct_kernel<true, GROUPS><<<blocks, 256, 0, s>>>(p);
-  else conv16_direct_kernel<false, GROUPS><<<blocks, 256, 0, s>>>(p);
+  if (p.out_f32 || p.x2 != nullptr || p.Nout > p.ldy || p.M != p.Nimg * p.H * p.W) return false;
+  if (p.H < 2 || p.W < 2 || p.W > 2000) return false;  // make_divisor; the patch in LDS
+  // a wave's runs must not straddle two data-groups
+  if (p.nrep > 1 && (p.Nimg % p.nrep != 0 || (p.Nimg / p.nrep * (long long)p.H * p.W) % 64 != 0)) return false;
+  if (p.Cx == 16 && p.ldy == 16) {
+    if (p.dgrad) launch_direct<16, 1, true>(p, s);
+    else launch_direct<16, 1, false>(p, s);
+    return true;
+  }
+  if (p.Cx != 8 || p.dgrad) return false;
+  if (p.ldy == 16) launch_direct<8, 1, false>(p, s);
+  else if (p.ldy == 32) launch_direct<8, 2, false>(p, s);
+  else if (p.ldy == 64) launch_direct<8, 4, false>(p, s);
+  else return false;
   return true;
 }
 

@@ -134,6 +134,15 @@ def test_weight_gradients_of_narrow_layers(widths, h, w, W, B):
     _compare(_conv_chain("bf16", widths, h, w, W, B), seed=34, T=2)
 
 
+@pytest.mark.parametrize("widths,h,w,W,B", [
+    ((16, 16), 2, 2, 1, 1), ((16, 16, 12), 5, 7, 3, 4), ((12, 16, 16), 16, 16, 1, 2), ((16, 16), 3, 48, 2, 5), ((32, 16, 16), 8, 6, 2, 3),
+    ((64, 16), 4, 16, 1, 3), ((60, 16), 5, 13, 1, 3), ((16, 16), 2, 2000, 1, 1), ((16, 16), 2, 2001, 1, 1)])
+def test_direct_convolutions_of_narrow_layers(widths, h, w, W, B):
+    # stems of 16, 32 and 64 output rows, also not filled ones, and 16 -> 16 layers in both directions; rows of 16 pixels and others, less
+    # than a run, a ragged last tile, the longest rows and the first beyond them
+    _compare(_conv_chain("bf16", widths, h, w, W, B), seed=39, T=2)
+
+
 @pytest.mark.parametrize("precision", ["f32", "bf16"])
 @pytest.mark.parametrize("k,pad,h,w", [(1, 0, 7, 6), (2, 0, 6, 9), (2, 1, 7, 7), (3, 0, 9, 8), (5, 2, 8, 5)])
 def test_stride2_input_gradients_by_padding(precision, k, pad, h, w):
