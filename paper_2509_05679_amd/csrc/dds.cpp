@@ -555,8 +555,12 @@ int plan_module(const dds_spec& sp, int k0, int K, int N, int dt, const Tensor* 
   return DDS_OK;
 }
 
-// elements of a layer that one workgroup of the update kernel owns
-int range_elems(const dds_ctx& c, const ParamLayer& L) { return c.gossip ? gossip_elems(L.nsplit / c.copies) : update_elems(c.dt, L.nsplit); }
+// workgroups of the update kernel that a layer takes
+int update_blocks(const dds_ctx& c, const ParamLayer& L) {
+  if (!c.gossip) return update_tiles(c.dt, L.nsplit, L.Cout, L.RS, L.Cinpad);
+  const int e = gossip_elems(L.nsplit / c.copies);
+  return (int)((L.n + e - 1) / e);
+}
 
 // What describes the weight gradient of a layer, but for its pointers and splits.
 WgradParams wgrad_shape(const dds_ctx& c, const Module& m, const Node& nd) {
@@ -703,7 +707,7 @@ int layout(dds_ctx& c, Arena& A) {
     // descriptor tables
     int nb_u = 0, nb_s = 0, nb_r = 0;
     for (ParamLayer& L : m.layers) {
-      nb_r += (int)((L.n + range_elems(c, L) - 1) / range_elems(c, L));
+      nb_r += update_blocks(c, L);
       nb_u += (int)((L.n + 1023) / 1024);
       if (L.need_stash) nb_s += L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64);  // 64 x 64 tiles per tap
     }
@@ -1113,7 +1117,10 @@ int upload_tables(dds_ctx& c) {
       d.Cout = L.Cout; d.RS = L.RS; d.Cinpad = L.Cinpad; d.Cin = L.Cin; d.Coutpad = L.Coutpad;
       for (int b = 0; b < (int)((L.n + 1023) / 1024); ++b) { mu.push_back(di); mu.push_back(b); }
       if (r == 0)
-        for (long long e = 0; e < L.n; e += range_elems(c, L)) { mr.push_back(di); mr.push_back((int)(e / 32)); }
+        for (int b = 0; b < update_blocks(c, L); ++b) {  // the mixing update takes ranges, by their first element / 32
+          mr.push_back(di);
+          mr.push_back(c.gossip ? b * (gossip_elems(q) / 32) : b);
+        }
       if (L.need_stash)
         for (int b = 0; b < L.RS * ((L.Cin + 63) / 64) * ((L.Coutpad + 63) / 64); ++b) { ms.push_back(di); ms.push_back(b); }
     }
@@ -1474,14 +1481,15 @@ int dds_step(dds_ctx* c, const float* const* x, const int32_t* const* y, float l
     if (sc.b >= 0) {
       if (int rc = run_backward(*c, m, sc, s, m.wstream && !c->serial && !c->profile_serial ? m.wstream : s)) return rc;
       if (!c->gossip) {
-        launch_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, c->W, step, c->mu, s);
+        launch_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, sc.snap_write, c->W, step, c->mu, s);
+        ++c->launches;
       } else {
         // u_r = w_r - lr * direction_r from every data-group's own splits, then the mixing step, in one kernel
         launch_gossip_update(c->dt, m.descs_dev, m.map_range_dev, m.ranges_update, c->P_dev, c->W, m.n_master, step,
                              c->mu, s);
+        launch_stash(c->dt, m.descs_dev, m.map_stash_dev, m.blocks_stash * c->copies, sc.snap_write, s);
+        c->launches += 2;
       }
-      launch_stash(c->dt, m.descs_dev, m.map_stash_dev, m.blocks_stash * c->copies, sc.snap_write, s);
-      c->launches += 2;
       if (m.recompute) HIP_TRY(snapshot_params(*c, m, sc.snap_write, s));
     }
     if (multi) HIP_TRY(hipEventRecord(m.done[t & 1], s));

@@ -169,13 +169,20 @@ void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void*
                        int W, int B, int classes, int ldl, int ldg, hipStream_t s);
 // Elements of a parameter block that one workgroup of the update kernel owns: the fewer, the more splits have to be
 // summed for each, so that a launch always has thousands of partial rows in flight (see update_kernel).
-// fp32 nets keep one range and with it one order of the sum for every split count (on the exact-mean path: gossip_elems).
+// fp32 nets keep one size and with it one order of the sum for every split count (on the exact-mean path: gossip_elems).
 __host__ __device__ inline int update_elems(int dt, int nsplit) {
-  return dt == DT_F32 || nsplit < 64 ? 256 : nsplit >= 256 ? 32 : 64;
+  return dt == DT_F32 ? 256 : nsplit <= 8 ? 1024 : nsplit <= 64 ? 256 : 64;
 }
-// update: g = (1/W) sum over splits, momentum, SGD on the fp32 master, recast into `work`. range_map: device array of
-// (descriptor, first element / 32) pairs, one per workgroup of update_elems(dt, nsplit) elements.
-void launch_update(int dt, const UpdateDesc* descs_dev, const int* range_map_dev, int total_ranges, int W,
+// Input channels of a tile of the update kernel, a power of two (8 to 32; a tile has at least two output channels).
+__host__ __device__ inline int update_width(int Cinpad) { return Cinpad <= 8 ? 8 : Cinpad <= 16 ? 16 : 32; }
+// Workgroups of the update kernel for one layer.
+inline int update_tiles(int dt, int nsplit, int Cout, int RS, int Cinpad) {
+  const int e = update_elems(dt, nsplit), kc = update_width(Cinpad), kk = e / kc;
+  return RS * ((Cout + kk - 1) / kk) * ((Cinpad + kc - 1) / kc) + (Cout + e - 1) / e;
+}
+// update: g = (1/W) sum over splits, momentum, SGD on the fp32 master, recast into `work`, transposed into snapshot `slot`.
+// tile_map: device array of (descriptor, tile) pairs, one per workgroup.
+void launch_update(int dt, const UpdateDesc* descs_dev, const int* tile_map_dev, int total_tiles, int slot, int W,
                    float lr, float mu, hipStream_t s);
 // The other kernels' block_map: device array of (descriptor, block) pairs, one per 1024 elements.
 // General mixing matrix (W weight copies, rep_stride elements apart; a descriptor's nsplit = splits per data-group):

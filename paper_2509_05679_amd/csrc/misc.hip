@@ -252,30 +252,47 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* logits, co
 }
 
 // ------------------------------------------------------------------ update
-// One workgroup owns E consecutive elements of one parameter block (map entry: descriptor, first element / 32) and all of
-// its nsplit partial rows. A row of the workgroup's range is read by E / 4 lanes, 16 bytes each, so the 256 threads
-// read R = 1024 / E rows at a time, eight such reads in flight per thread; row-lane r sums the splits r, r + R, ...
-// HBM-bound when enough of them are in flight: 4 bytes per partial value. E falls with the split count
-// (update_elems): a 16-channel layer has 1024 splits of 2320 values, and with 256-element ranges its ten workgroups
-// walked 256 rows one after another: 94 us for the update of the single-module ResNet-20 step (57 MB of partial
-// sums), 53 us per module of ResNet-56. 32-element ranges spread the same bytes over 73 workgroups of 32 row-lanes:
-// 33 and 19 us.
+// One workgroup owns a tile of E weights of one tap, E / KC output channels x KC input channels (update_width: whole cache lines of a
+// partial row where the layer is that wide), or E biases, and all of their nsplit partial rows (map entry: descriptor, tile). A row of the tile is read by E / 4 lanes, 16 bytes each, so the 256
+// threads read R = 1024 / E rows at a time, eight such reads in flight per thread; row-lane r sums the splits r, r + R, ...
+// The new weights leave three times: fp32 master, compute-precision copy, and, transposed through LDS, the snapshot
+// [cin][tap][cout] that the backward pass of a later iteration multiplies by. (With the snapshot in a launch of its own, which read
+// the master again, the pair took 125 us of a ResNet-18 step, modules one after another, here 75; 135 / 85 of ResNet-56, 20 / 16 of ResNet-20
+// in one module; the three-layer perceptron, bound by its launches, went from 0.79 to 0.70 ms per 8 steps.)
+// HBM-bound when enough reads are in flight: 4 bytes per partial value. E falls with the split count (update_elems).
 // Order of the sum (bit-reproducible for a given split count): eight interleaved running sums, a fixed tree over
 // them, a tree over the row-lanes of a wave, a fixed tree over the four waves through LDS.
 // g = sum/W; v = mu*v + g; w -= lr*v (or lr*g).
 __device__ __forceinline__ void add4(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
 
 template <typename T, int E>
-__device__ __forceinline__ void update_range(const UpdateDesc& d, long long first, float invW, float lr, float mu, float4 (*red)[64]) {
+__device__ __forceinline__ void update_tile(const UpdateDesc& d, int tile_index, int slot, float invW, float lr, float mu, float4* red, float* tile) {
   constexpr int LPR = E / 4;      // lanes per row
   constexpr int R = 256 / LPR;    // row-lanes of the workgroup
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r0 = threadIdx.x / LPR;
-  const long long base = first + (threadIdx.x % LPR) * 4;
+  const int r0 = threadIdx.x / LPR, l = threadIdx.x % LPR;
+  const int KC = update_width(d.Cinpad), KK = E / KC, cshift = __builtin_ctz(KC) - 2, kshift = __builtin_ctz(KK) - 1;
+  const int kblocks = (d.Cout + KK - 1) / KK, cblocks = (d.Cinpad + KC - 1) / KC;
+  const bool weights = tile_index < d.RS * cblocks * kblocks;
+  int kb = 0, cb = 0, tap = 0;
+  long long base;
+  bool live;
+  if (weights) {
+    const int q = tile_index / kblocks;
+    kb = tile_index - q * kblocks;
+    tap = q / cblocks;
+    cb = q - tap * cblocks;
+    const int k = kb * KK + (l >> cshift), c = cb * KC + (l & ((1 << cshift) - 1)) * 4;
+    live = k < d.Cout && c < d.Cinpad;
+    base = ((long long)k * d.RS + tap) * d.Cinpad + c;
+  } else {
+    base = (long long)d.Cout * d.RS * d.Cinpad + (long long)(tile_index - d.RS * cblocks * kblocks) * E + l * 4;
+    live = base < d.n;
+  }
   float4 a[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (base < d.n) {  // rows are pstride = n rounded up to 4 floats long: the vector read stays inside the row
+  if (live) {  // rows are pstride = n rounded up to 4 floats long: the vector read stays inside the row
     const float* src = d.partial + base;
     for (int j = r0; j < d.nsplit; j += 8 * R) {
 #pragma unroll
@@ -292,59 +309,83 @@ __device__ __forceinline__ void update_range(const UpdateDesc& d, long long firs
 #pragma unroll
   for (int o = 32; o >= LPR; o >>= 1)
     add4(a[0], make_float4(__shfl_xor(a[0].x, o, 64), __shfl_xor(a[0].y, o, 64), __shfl_xor(a[0].z, o, 64), __shfl_xor(a[0].w, o, 64)));
-  if (wave > 0 && lane < LPR) red[wave - 1][lane] = a[0];
-  __syncthreads();
-  if (wave > 0 || lane >= LPR || base >= d.n) return;
-  {
-    const float4 r1 = red[0][lane], r2 = red[1][lane], r3 = red[2][lane];
-    a[0].x = (a[0].x + r1.x) + (r2.x + r3.x); a[0].y = (a[0].y + r1.y) + (r2.y + r3.y);
-    a[0].z = (a[0].z + r1.z) + (r2.z + r3.z); a[0].w = (a[0].w + r1.w) + (r2.w + r3.w);
+  if (E < 1024) {
+    if (wave > 0 && lane < LPR) red[(wave - 1) * 64 + lane] = a[0];
+    __syncthreads();
   }
-  float g[4] = {a[0].x * invW, a[0].y * invW, a[0].z * invW, a[0].w * invW};
-  if (base + 4 <= d.n) {
-    float4 w = *(const float4*)(d.master + base);
-    if (d.momentum) {
-      float4 v = *(const float4*)(d.momentum + base);
-      v.x = mu * v.x + g[0]; v.y = mu * v.y + g[1]; v.z = mu * v.z + g[2]; v.w = mu * v.w + g[3];
-      *(float4*)(d.momentum + base) = v;
-      g[0] = v.x; g[1] = v.y; g[2] = v.z; g[3] = v.w;
+  if (E == 1024 || (wave == 0 && lane < LPR)) {
+    if (E < 1024) {
+      const float4 r1 = red[lane], r2 = red[64 + lane], r3 = red[128 + lane];
+      a[0].x = (a[0].x + r1.x) + (r2.x + r3.x); a[0].y = (a[0].y + r1.y) + (r2.y + r3.y);
+      a[0].z = (a[0].z + r1.z) + (r2.z + r3.z); a[0].w = (a[0].w + r1.w) + (r2.w + r3.w);
     }
-    w.x -= lr * g[0]; w.y -= lr * g[1]; w.z -= lr * g[2]; w.w -= lr * g[3];
-    *(float4*)(d.master + base) = w;
-    if (d.work) {
-      if (sizeof(T) == 2) {
-        uint2 o;
-        o.x = (uint32_t)f2bf(w.x) | ((uint32_t)f2bf(w.y) << 16);
-        o.y = (uint32_t)f2bf(w.z) | ((uint32_t)f2bf(w.w) << 16);
-        *(uint2*)((char*)d.work + base * 2) = o;
-      } else {
-        *(float4*)((char*)d.work + base * 4) = w;
+    float g[4] = {a[0].x * invW, a[0].y * invW, a[0].z * invW, a[0].w * invW};
+    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (live && base + 4 <= d.n) {
+      w = *(const float4*)(d.master + base);
+      if (d.momentum) {
+        float4 v = *(const float4*)(d.momentum + base);
+        v.x = mu * v.x + g[0]; v.y = mu * v.y + g[1]; v.z = mu * v.z + g[2]; v.w = mu * v.w + g[3];
+        *(float4*)(d.momentum + base) = v;
+        g[0] = v.x; g[1] = v.y; g[2] = v.z; g[3] = v.w;
       }
-    }
-  } else {
-    for (long long i = base; i < d.n; ++i) {
-      float w = d.master[i];
-      float gg = g[i - base];
-      if (d.momentum) { const float v = mu * d.momentum[i] + gg; d.momentum[i] = v; gg = v; }
-      w -= lr * gg;
-      d.master[i] = w;
+      w.x -= lr * g[0]; w.y -= lr * g[1]; w.z -= lr * g[2]; w.w -= lr * g[3];
+      *(float4*)(d.master + base) = w;
       if (d.work) {
-        if (sizeof(T) == 2) ((uint16_t*)d.work)[i] = f2bf(w);
-        else ((float*)d.work)[i] = w;
+        if (sizeof(T) == 2) {
+          uint2 o;
+          o.x = (uint32_t)f2bf(w.x) | ((uint32_t)f2bf(w.y) << 16);
+          o.y = (uint32_t)f2bf(w.z) | ((uint32_t)f2bf(w.w) << 16);
+          *(uint2*)((char*)d.work + base * 2) = o;
+        } else {
+          *(float4*)((char*)d.work + base * 4) = w;
+        }
+      }
+    } else if (live) {  // the last biases of a layer
+      for (long long i = base; i < d.n; ++i) {
+        float wi = d.master[i];
+        float gg = g[i - base];
+        if (d.momentum) { const float v = mu * d.momentum[i] + gg; d.momentum[i] = v; gg = v; }
+        wi -= lr * gg;
+        d.master[i] = wi;
+        if (d.work) {
+          if (sizeof(T) == 2) ((uint16_t*)d.work)[i] = f2bf(wi);
+          else ((float*)d.work)[i] = wi;
+        }
       }
     }
+    if (weights && d.stash) {  // zeros for the output channels past the last
+      float* at = tile + (l & ((1 << cshift) - 1)) * 4 * (KK + 1) + (l >> cshift);
+      at[0] = w.x; at[KK + 1] = w.y; at[2 * (KK + 1)] = w.z; at[3 * (KK + 1)] = w.w;
+    }
+  }
+  if (!weights || !d.stash) return;  // the whole workgroup
+  __syncthreads();
+  // two output channels of one input channel per thread and turn
+#pragma unroll
+  for (int i = 0; i < (E / 2 + 255) / 256; ++i) {
+    const int o = i * 256 + threadIdx.x;
+    if (E < 512 && o >= E / 2) break;
+    const int cl = o >> kshift, kl = (o & ((1 << kshift) - 1)) * 2;
+    const int c = cb * KC + cl, k = kb * KK + kl;
+    if (c >= d.Cin || k >= d.Coutpad) continue;
+    const float v0 = tile[cl * (KK + 1) + kl], v1 = tile[cl * (KK + 1) + kl + 1];
+    const size_t at = (size_t)slot * d.stash_slot_elems + ((size_t)c * d.RS + tap) * d.Coutpad + k;
+    if (sizeof(T) == 2) *(uint32_t*)((uint16_t*)d.stash + at) = (uint32_t)f2bf(v0) | ((uint32_t)f2bf(v1) << 16);
+    else *(float2*)((float*)d.stash + at) = make_float2(v0, v1);
   }
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, const int* block_map, float invW, float lr, float mu) {
-  __shared__ float4 red[3][64];
-  const UpdateDesc d = descs[block_map[2 * blockIdx.x]];
-  const long long first = (long long)block_map[2 * blockIdx.x + 1] * 32;
+__global__ __launch_bounds__(256) void update_kernel(const UpdateDesc* descs, const int* tile_map, int slot, float invW, float lr, float mu) {
+  __shared__ float4 red[3 * 64];
+  __shared__ float tile[32 * 33];
+  const UpdateDesc d = descs[tile_map[2 * blockIdx.x]];
+  const int t = tile_map[2 * blockIdx.x + 1];
   switch (update_elems(sizeof(T) == 4 ? DT_F32 : DT_BF16, d.nsplit)) {
-    case 32: update_range<T, 32>(d, first, invW, lr, mu, red); break;
-    case 64: update_range<T, 64>(d, first, invW, lr, mu, red); break;
-    default: update_range<T, 256>(d, first, invW, lr, mu, red); break;
+    case 64: update_tile<T, 64>(d, t, slot, invW, lr, mu, red, tile); break;
+    case 256: update_tile<T, 256>(d, t, slot, invW, lr, mu, red, tile); break;
+    default: update_tile<T, 1024>(d, t, slot, invW, lr, mu, red, tile); break;
   }
 }
 
@@ -616,10 +657,9 @@ void launch_softmax_ce(int dt, const float* logits, const int32_t* labels, void*
   DDS_DISPATCH(dt, softmax_ce_kernel, <<<W, 256, 0, s>>>(logits, labels, (char*)dlogits, loss, B, classes, ldl, ldg));
 }
 
-void launch_update(int dt, const UpdateDesc* descs, const int* block_map, int total_blocks, int W, float lr, float mu,
-                   hipStream_t s) {
-  if (total_blocks <= 0) return;
-  DDS_DISPATCH(dt, update_kernel, <<<total_blocks, 256, 0, s>>>(descs, block_map, 1.f / (float)W, lr, mu));
+void launch_update(int dt, const UpdateDesc* descs, const int* tile_map, int total_tiles, int slot, int W, float lr, float mu, hipStream_t s) {
+  if (total_tiles <= 0) return;
+  DDS_DISPATCH(dt, update_kernel, <<<total_tiles, 256, 0, s>>>(descs, tile_map, slot, 1.f / (float)W, lr, mu));
 }
 
 void launch_recast(int dt, const UpdateDesc* descs, const int* block_map, int total_blocks, hipStream_t s) {
