@@ -296,8 +296,8 @@ def test_weight_gradients_that_share_a_launch(widths, h, w, W, B):
     assert not np.array_equal(runs[0], np.concatenate([p.ravel() for p in init[0]]))
 
 
-@pytest.mark.parametrize("precision,B", [("bf16", 8), ("bf16", 9), ("bf16", 64), ("bf16", 65), ("f32", 9)])
-def test_update_tiles_by_split_count(precision, B):
+@pytest.mark.parametrize("B", [8, 9, 64, 65])
+def test_update_tiles_by_split_count(B):
     # one split per image of 15 x 15 pixels: both sides of the lines between tiles of 1024, 256 and 64 weights; tiles of 8, 16 and 32 input
-    # channels, output channels that fill no tile
-    _compare(_conv_chain(precision, (16, 16, 32, 32, 12), 15, 15, 1, B), seed=40, T=2, tiny=precision == "f32")
+    # channels, output channels that fill no tile (fp32 nets have one tile size: the other tests)
+    _compare(_conv_chain("bf16", (16, 16, 32, 32, 12), 15, 15, 1, B), seed=40, T=2)
