@@ -3,7 +3,7 @@
 //   forward and input gradient: conv3x3_dma_kernel (3x3 stride 1), conv_gather_kernel (any other layer of whole 64-byte
 //     channel chunks), conv_gemm_kernel (the rest, e.g. the 3-channel stem)
 //   weight gradient, bf16: wgrad_dma_body (sides that are powers of two, whole 128-pixel tiles), wgrad_flat_body (other
-//     sizes), wgrad_gemm_kernel (the rest); fp32: wgrad_f32_kernel
+//     sizes), wgrad_rows_body (1x1, linear), wgrad_gemm_kernel (the rest); fp32: wgrad_f32_kernel
 // (Plain products of few rows: linear.hip. 16-channel layers: narrow.hip.)
 //
 // Operand tiles are K-contiguous in LDS ([row][k]; wgrad_dma_body, wgrad_flat_body and wgrad_f32_kernel keep [pixel][channel])
@@ -1793,7 +1793,84 @@ __device__ __forceinline__ void wgrad_flat_body(const WgradParams& p, const Wgra
   }
 }
 
-// One launch takes several layers (all of stride 1, or all of stride 2): workgroup -> (layer, k-block, sub-pixel / c-block,
+// Linear layers and 1x1 convolutions of stride 1 (bf16): no image, no taps; tiles of 128 rows, the rest as above. Against
+// operands transposed in registers (wgrad_gemm_kernel), each launch alone, a net of three linear layers: 512 -> 512 in the middle at
+// 16 / 512 / 4096 rows 32 / 44 / 58 -> 22 / 23 / 33 us, 2048 -> 32 at 16384 rows 120 -> 65 us. A head shares the launch of its module's
+// stride-2 layers, where the old kernel took 11 to 16 us with one to twelve workgroups.
+__device__ __forceinline__ void wgrad_rows_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
+  constexpr int SLOT = 32768;
+  const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = wave >> 1;
+  const int k0 = bx * 64, c0 = by * 64;
+  const int q = p.nsplit / p.nrep;
+  const int zr = z / q, zj = z - zr * q;
+  const int tile0 = (int)(((long long)zj * wg.rep_tiles) / q);
+  const int ntiles = (int)(((long long)(zj + 1) * wg.rep_tiles) / q) - tile0;
+  const int rows_rep = p.P / p.nrep, row0 = zr * rows_rep;
+
+  const int l8 = lane >> 3;
+  const int c16 = ((lane & 7) ^ ((l8 & 3) << 1)) * 16;  // global 16-byte column for LDS slot lane&7 of a row with row&3 == l8&3
+  const char* zsrc = (const char*)p.zeros + c16;
+  const bool ycol_ok = k0 + (c16 >> 1) < p.ldy, xcol_ok = c0 + (c16 >> 1) < p.Cx;
+  const char* ybase = (const char*)p.dy + (size_t)k0 * 2 + c16;
+  const char* xbase = (const char*)p.x + (size_t)c0 * 2 + c16;
+  auto fill_tile = [&](int t, int slot) {
+    if (t >= ntiles) return;
+    const uint32_t base = lds_ring + slot * SLOT;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // eight rows of each operand
+      const int f = wave + 4 * u, row = (tile0 + t) * 128 + f * 8 + l8;
+      const bool ok = row < rows_rep;
+      const size_t r = (size_t)(row0 + row);
+      dma16(ok && ycol_ok ? ybase + r * (uint32_t)(p.ldy * 2) : zsrc, base + f * 1024);
+      dma16(ok && xcol_ok ? xbase + r * (uint32_t)(p.Cx * 2) : zsrc, base + 16384 + f * 1024);
+    }
+  };
+  fill_tile(0, 0);
+
+  const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;  // fragment addressing as in wgrad_dma_body
+  const int rsub = lq >> 2, seg = lq & 3;
+  const int a_c = 4 * wave_m + 2 * grp16 + (seg >> 1), b_c = 4 * wave_n + 2 * grp16 + (seg >> 1);
+  const int lrow = (8 * khalf + rsub) * 128 + 8 * (seg & 1);
+  const int a_lane = lrow + ((a_c ^ (rsub << 1)) << 4), b_lane = lrow + 16384 + ((b_c ^ (rsub << 1)) << 4);
+  f32x16_t acc, accb;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = accb[e] = 0.f;
+  const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+  const bool idle_wave = k0 + wave_m * 32 >= p.Mout || c0 + wave_n * 32 >= p.Cx;
+  const bool bias_wave = wave_n == 0 && by == 0;
+
+  for (int t = 0; t < ntiles; ++t) {
+    wait_vm<0>();
+    wg_barrier();
+    fill_tile(t + 1, (t + 1) & 1);
+    if (idle_wave) continue;
+    const uint32_t base = lds_ring + (t & 1) * SLOT;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const uint2 a0 = lds_tr16_at(base + a_lane + ks * 2048), a1 = lds_tr16_at(base + a_lane + ks * 2048 + 512);
+      const uint2 b0 = lds_tr16_at(base + b_lane + ks * 2048), b1 = lds_tr16_at(base + b_lane + ks * 2048 + 512);
+      const uint4 a = make_uint4(a0.x, a0.y, a1.x, a1.y);
+      mfma16B<bf16_t>(a, make_uint4(b0.x, b0.y, b1.x, b1.y), acc);
+      if (bias_wave) mfma16B<bf16_t>(a, ones, accb);  // bias gradient: column sums of dY
+    }
+  }
+  wait_vm<0>();
+
+  float* out = p.partial + (size_t)z * p.Pl;
+  const int cin = c0 + wave_n * 32 + (lane & 31);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int k = k0 + wave_m * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    if (k >= p.Mout) continue;
+    if (cin < p.Cx) out[(size_t)k * p.NK + cin] = p.alpha * acc[e];
+    if (bias_wave && (lane & 31) == 0) out[(size_t)p.Mout * p.NK + k] = p.alpha * accb[e];
+  }
+}
+
+// One launch takes several layers (3x3 ones of stride 1, or those of stride 2 and 1x1 ones): workgroup -> (layer, k-block, sub-pixel / c-block,
 // split). Every (k, c) block of one split reads the same dY rows and X patches, so they should meet in one L2: workgroups are
 // handed to the eight XCDs round-robin in launch order, hence launch index i lands on XCD i % 8 as the (i / 8)-th workgroup
 // of that XCD. Where the split count is a multiple of eight, XCD x takes the splits z = x (mod 8) and runs all blocks of
@@ -1802,7 +1879,7 @@ __device__ __forceinline__ void wgrad_flat_body(const WgradParams& p, const Wgra
 struct WgradLayer {
   WgradParams p;
   WgradGeom g;
-  int tiling;  // 0..3: wgrad_dma_body for rows of 32, 16, 8, 4 pixels; 4: wgrad_flat_body
+  int tiling;  // 0..3: wgrad_dma_body for rows of 32, 16, 8, 4 pixels; 4: wgrad_flat_body; 5: wgrad_rows_body
   int first;   // first workgroup
   int gx, gy;  // k-blocks, (sub-pixel, c-block) pairs
 };
@@ -1829,7 +1906,9 @@ __global__ __launch_bounds__(S2 ? 256 : 768, S2 ? 2 : 1) void wgrad_tiles_kernel
     case 1: wgrad_dma_body<4, 3, S2>(l.p, l.g, smem, bx, by, z); break;
     case 2: wgrad_dma_body<3, 3, S2>(l.p, l.g, smem, bx, by, z); break;
     case 3: wgrad_dma_body<2, 2, S2>(l.p, l.g, smem, bx, by, z); break;
-    default: wgrad_flat_body<S2>(l.p, l.g, smem, bx, by, z);
+    case 4: wgrad_flat_body<S2>(l.p, l.g, smem, bx, by, z); break;
+    default:
+      if (S2) wgrad_rows_body(l.p, l.g, smem, bx, by, z);
   }
 }
 
@@ -2101,6 +2180,16 @@ bool wgrad_flat_geometry(const WgradParams& p, int nrep, WgradGeom& wg) {
 // for `zeros` are not); false: not a layer of this kernel. rep_tiles: 128-position tiles of a data-group; smem: LDS.
 bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem) {
   l.p = p;
+  l.g.cblocks = cdiv(p.Cx, 64);
+  l.gx = cdiv(p.Mout, 64);
+  l.gy = l.g.cblocks;
+  if (p.R == 1 && p.S == 1 && p.stride == 1 && p.pad == 0) {
+    if (p.nrep < 1 || p.P % p.nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0 || p.zeros == nullptr) return false;
+    l.tiling = 5;
+    *rep_tiles = l.g.rep_tiles = cdiv(p.P / p.nrep, 128);
+    *smem = 2 * 32768;
+    return true;
+  }
   l.tiling = wgrad_dma_tiling(p, p.nrep, &l.g.tiles_h);
   int rows;
   if (l.tiling >= 0) {
@@ -2114,12 +2203,12 @@ bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem)
     *rep_tiles = l.g.rep_tiles;
   }
   *smem = 2 * (16384 + rows * 128);  // two slots
-  const int nsub = p.stride == 2 ? wgrad_s2_taps(p.R, l.g.sub, l.g.rmap) : 1;
-  l.g.cblocks = cdiv(p.Cx, 64);
-  l.gx = cdiv(p.Mout, 64);
-  l.gy = nsub * l.g.cblocks;
+  if (p.stride == 2) l.gy *= wgrad_s2_taps(p.R, l.g.sub, l.g.rmap);
   return true;
 }
+
+// Waves of a workgroup: which of the two kernels takes the layer.
+inline int wgrad_waves(const WgradParams& p) { return p.stride == 2 || p.R == 1 ? 4 : 12; }
 
 // False: not taken, nothing launched.
 bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
@@ -2129,7 +2218,7 @@ bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) {
     WgradLayer& l = g.layer[i];
     int tiles = 0, need = 0;
-    if (p[i].nrep < 1 || p[i].nsplit % p[i].nrep != 0 || p[i].stride != p[0].stride || !wgrad_layer(p[i], l, &tiles, &need)) return false;
+    if (p[i].nrep < 1 || p[i].nsplit % p[i].nrep != 0 || wgrad_waves(p[i]) != wgrad_waves(p[0]) || !wgrad_layer(p[i], l, &tiles, &need)) return false;
     const int q = p[i].nsplit / p[i].nrep;
     if (q < 1 || q > tiles) return false;  // no empty split
     l.first = wgs;
@@ -2138,7 +2227,7 @@ bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
   }
   g.n = n;
   static DeviceOnce lds[2];
-  if (p[0].stride == 2) {
+  if (wgrad_waves(p[0]) == 4) {
     allow_whole_lds(lds[1], (const void*)wgrad_tiles_kernel<true>);
     wgrad_tiles_kernel<true><<<wgs, 256, smem, s>>>(g);
   } else {
@@ -2161,7 +2250,7 @@ void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
 }
 
 int launch_wgrad_bf16(const WgradParams* pp, int n, hipStream_t s) {
-  if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return 1;
+  if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return pp[0].R == 3 || pp[0].stride == 2;
   const WgradParams& p = pp[0];  // the others have no key to share a launch under
   if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
@@ -2199,7 +2288,7 @@ WgradWork wgrad_work(int dt, const WgradParams& shape) {
     w.key += 4;
   } else if (wgrad_layer(shape, l, &w.tiles, &smem)) {
     w.blocks = l.gx * l.gy;
-    w.key = shape.stride;
+    w.key = wgrad_waves(shape) == 4 ? 2 : 1;
   }
   return w;
 }

@@ -301,3 +301,13 @@ def test_update_tiles_by_split_count(B):
     # one split per image of 15 x 15 pixels: both sides of the lines between tiles of 1024, 256 and 64 weights; tiles of 8, 16 and 32 input
     # channels, output channels that fill no tile (fp32 nets have one tile size: the other tests)
     _compare(_conv_chain("bf16", (16, 16, 32, 32, 12), 15, 15, 1, B), seed=40, T=2)
+
+
+@pytest.mark.parametrize("c1,c2,h,w,W,B", [(8, 12, 1, 1, 2, 64), (72, 136, 1, 1, 3, 43), (64, 64, 4, 4, 1, 8), (128, 200, 3, 5, 2, 9), (16, 40, 1, 129, 1, 1)])
+def test_weight_gradients_of_pointwise_layers(c1, c2, h, w, W, B):
+    # 1x1 convolutions and the head: one whole tile of 128 rows, one row more, less than a tile, channel counts off the 64-channel blocks
+    ops = [{"op": "conv", "cin": 3, "cout": c1, "k": 1, "stride": 1, "pad": 0}, {"op": "relu"},
+           {"op": "conv", "cin": c1, "cout": c2, "k": 1, "stride": 1, "pad": 0}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": c2, "cout": 10}, {"op": "softmax_ce"}]
+    _compare(Workload(name=f"pointwise_{c1}_{c2}", ops=ops, bounds=[0, len(ops)], K=1, W=W, B=B, in_shape=(3, h, w), classes=10,
+                      precision="bf16", lr=0.05, momentum=0.0, steps=2), seed=41, T=2)
