@@ -1429,11 +1429,11 @@ struct WgradGeom {
   int imgs_rep;    // images per data-group
   int rep_tiles;   // 128-position tiles per data-group
   int patch_rows;  // 128 + 2Q + 2 (S2: 128 + Q + 1) rounded up to 8
-  Divisor dQ, dH;  // by Q and by Ho + 1
+  Divisor dQ, dH;  // by Q and by Ho + 1 (wgrad_rows_body: by Wo and by Ho)
 };
 
 // S2 = false: 3x3, stride 1, pad 1 (nine taps, TW x TH tiles of the image itself).
-// S2 = true: a stride-2 convolution (3x3 pad 1, or 1x1 pad 0) seen as a stride-1 one on the
+// S2 = true: a 3x3 stride-2 pad-1 convolution seen as a stride-1 one on the
 // input regrouped into 2x2 sub-pixels: output pixel (oy, ox) and real tap r read input row
 // 2*oy + r - pad, i.e. sub-pixel row dy of super-pixel row oy - 1 or oy. A workgroup takes the
 // 64 channels of ONE sub-pixel (dy, dx); its patch is that sub-grid (gathered at pixel stride
@@ -1642,7 +1642,7 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
 
 // ------------------------------------------------------------------ the same weight gradients for any image size (bf16)
 // wgrad_dma_body wants images whose sides are powers of two and data-groups of whole 128-pixel tiles. Everything
-// else 3x3 stride 1, 3x3 stride 2 or 1x1 stride 2 comes here. The pixels of a data-group are numbered with a row pitch of Wo + 1 and one
+// else 3x3 stride 1 or 2 comes here. The pixels of a data-group are numbered with a row pitch of Wo + 1 and one
 // extra row above every image, so that each row's padding is the extra column before it and each image's the extra
 // row: a tile is 128 consecutive such positions, dY and X are copied with zeros at the extra ones, and the taps are
 // constant distances (-Q-1 .. Q+1, Q = Wo + 1) with nothing to test in the inner loop. Price: (Ho+1)(Wo+1) / (Ho Wo)
@@ -1793,7 +1793,7 @@ __device__ __forceinline__ void wgrad_flat_body(const WgradParams& p, const Wgra
   }
 }
 
-// Linear layers and 1x1 convolutions of stride 1 (bf16): no image, no taps; tiles of 128 rows, the rest as above. Against
+// Linear layers and 1x1 convolutions of stride 1 and 2 (bf16): no taps; tiles of 128 output pixels, the rest as above. Against
 // operands transposed in registers (wgrad_gemm_kernel), each launch alone, a net of three linear layers: 512 -> 512 in the middle at
 // 16 / 512 / 4096 rows 32 / 44 / 58 -> 22 / 23 / 33 us, 2048 -> 32 at 16384 rows 120 -> 65 us. A head shares the launch of its module's
 // stride-2 layers, where the old kernel took 11 to 16 us with one to twelve workgroups.
@@ -1823,9 +1823,14 @@ __device__ __forceinline__ void wgrad_rows_body(const WgradParams& p, const Wgra
     for (int u = 0; u < 4; ++u) {  // eight rows of each operand
       const int f = wave + 4 * u, row = (tile0 + t) * 128 + f * 8 + l8;
       const bool ok = row < rows_rep;
-      const size_t r = (size_t)(row0 + row);
-      dma16(ok && ycol_ok ? ybase + r * (uint32_t)(p.ldy * 2) : zsrc, base + f * 1024);
-      dma16(ok && xcol_ok ? xbase + r * (uint32_t)(p.Cx * 2) : zsrc, base + 16384 + f * 1024);
+      const uint32_t r = (uint32_t)(row0 + row);
+      uint32_t rx = r;  // row of X: the pixel itself, or the one at twice its row and column
+      if (p.stride == 2) {
+        const uint32_t line = p.Wo > 1 ? __umulhi(r, wg.dQ.mul) >> wg.dQ.shift : r, im = p.Ho > 1 ? __umulhi(line, wg.dH.mul) >> wg.dH.shift : line;
+        rx = (im * p.H + 2 * (line - im * p.Ho)) * p.W + 2 * (r - line * p.Wo);
+      }
+      dma16(ok && ycol_ok ? ybase + (size_t)r * (uint32_t)(p.ldy * 2) : zsrc, base + f * 1024);
+      dma16(ok && xcol_ok ? xbase + (size_t)rx * (uint32_t)(p.Cx * 2) : zsrc, base + 16384 + f * 1024);
     }
   };
   fill_tile(0, 0);
@@ -2123,11 +2128,10 @@ int launch_conv_one(const ConvParams& p, hipStream_t s) {
 }
 
 // bf16 problems of whole 128-pixel tiles per data-group (nrep of them) go to wgrad_dma_body: 3x3 stride 1 pad 1, and the
-// stride-2 layers (3x3 pad 1, 1x1 pad 0) on even-sized images. Returns its tiling, -1 if it is none of them.
+// stride-2 ones on even-sized images. Returns its tiling, -1 if it is none of them.
 int wgrad_dma_tiling(const WgradParams& p, int nrep, int* tiles_h) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
-  const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
-                  p.H == 2 * p.Ho && p.W == 2 * p.Wo;
+  const bool s2 = p.R == 3 && p.S == 3 && p.stride == 2 && p.pad == 1 && p.H == 2 * p.Ho && p.W == 2 * p.Wo;
   if (!s1 && !s2) return -1;
   if (nrep < 1 || p.P % (128 * nrep) != 0) return -1;
   if (p.Cx % 8 != 0 || (p.Cx > 64 && p.Cx % 64 != 0) || p.zeros == nullptr) return -1;
@@ -2142,26 +2146,17 @@ int wgrad_dma_tiling(const WgradParams& p, int nrep, int* tiles_h) {
   return 5 - lw;
 }
 
-// Sub-pixels of a stride-2 layer in launch order and the real tap of (virtual tap, sub-pixel offset):
-// 3x3 pad 1: rows 2oy-1, 2oy, 2oy+1; 1x1 pad 0: row 2oy
-int wgrad_s2_taps(int R, int (&sub)[4], int (&rmap)[2][2]) {
-  if (R == 3) { rmap[0][0] = -1; rmap[0][1] = 0; rmap[1][0] = 1; rmap[1][1] = 2; }
-  else { rmap[0][0] = -1; rmap[0][1] = -1; rmap[1][0] = 0; rmap[1][1] = -1; }
-  int nsub = 0;
-  // heaviest sub-pixels first: (1,1) accumulates four taps, (0,0) one
-  for (int s = 3; s >= 0; --s) {
-    const int dy = s >> 1, dx = s & 1;
-    const bool any_r = rmap[0][dy] >= 0 || rmap[1][dy] >= 0, any_s = rmap[0][dx] >= 0 || rmap[1][dx] >= 0;
-    if (any_r && any_s) sub[nsub++] = s;
-  }
-  return nsub;
+// Sub-pixels of a 3x3 stride-2 layer in launch order and the real tap of (virtual tap, sub-pixel offset): rows 2oy-1, 2oy, 2oy+1
+int wgrad_s2_taps(int (&sub)[4], int (&rmap)[2][2]) {
+  rmap[0][0] = -1; rmap[0][1] = 0; rmap[1][0] = 1; rmap[1][1] = 2;
+  for (int s = 3; s >= 0; --s) sub[3 - s] = s;  // heaviest sub-pixels first: (1,1) accumulates four taps, (0,0) one
+  return 4;
 }
 
-// 3x3 stride 1 pad 1, 3x3 stride 2 pad 1 and 1x1 stride 2 pad 0 of any image size: wgrad_flat_body. False: not one of them.
+// 3x3 pad 1, stride 1 and 2, of any image size: wgrad_flat_body. False: not one of them.
 bool wgrad_flat_geometry(const WgradParams& p, int nrep, WgradGeom& wg) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
-  const bool s2 = p.stride == 2 && p.R == p.S && ((p.R == 3 && p.pad == 1) || (p.R == 1 && p.pad == 0)) &&
-                  p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2;
+  const bool s2 = p.R == 3 && p.S == 3 && p.stride == 2 && p.pad == 1 && p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2;
   if ((!s1 && !s2) || nrep < 1 || p.Nimg % nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return false;
   if (p.zeros == nullptr) return false;
   wg.Q = p.Wo + 1;
@@ -2183,9 +2178,12 @@ bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem)
   l.g.cblocks = cdiv(p.Cx, 64);
   l.gx = cdiv(p.Mout, 64);
   l.gy = l.g.cblocks;
-  if (p.R == 1 && p.S == 1 && p.stride == 1 && p.pad == 0) {
+  if (p.R == 1 && p.S == 1 && p.pad == 0 && (p.stride == 1 || (p.stride == 2 && p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2))) {
     if (p.nrep < 1 || p.P % p.nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0 || p.zeros == nullptr) return false;
+    if ((long long)p.Nimg * p.H * p.W >= (1ll << 31)) return false;
     l.tiling = 5;
+    l.g.dQ = make_divisor(p.Wo > 1 ? p.Wo : 2);
+    l.g.dH = make_divisor(p.Ho > 1 ? p.Ho : 2);
     *rep_tiles = l.g.rep_tiles = cdiv(p.P / p.nrep, 128);
     *smem = 2 * 32768;
     return true;
@@ -2203,7 +2201,7 @@ bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem)
     *rep_tiles = l.g.rep_tiles;
   }
   *smem = 2 * (16384 + rows * 128);  // two slots
-  if (p.stride == 2) l.gy *= wgrad_s2_taps(p.R, l.g.sub, l.g.rmap);
+  if (p.stride == 2) l.gy *= wgrad_s2_taps(l.g.sub, l.g.rmap);
   return true;
 }
 
