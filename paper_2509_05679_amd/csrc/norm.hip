@@ -108,16 +108,23 @@ __device__ __forceinline__ void load_coef(const float* row, const Lane& l, float
 
 // Second half of the workgroup reduction. red[v * 256 + thread] holds quantity v (0-7: first sum of the
 // thread's eight channels, 8-15: second sum) of every thread; thread = row-thread t * cg + channel group g.
-// One thread per (v, g) adds the rpp row-threads in order and writes scale * total to
-// out[channel * 2 + (v >> 3)], channel = 8 g + (v & 7).
+// `parts` neighbouring threads (a power of two) share an output (v, g): each adds every parts-th row-thread in order, so that
+// no chain of dependent LDS reads and fp64 additions is longer than 16 for rows of 8, 16, 32, ... channels (one thread per output
+// walked 128 row-threads of a 16-channel row); a tree joins them. scale * total goes to out[channel * 2 + (v >> 3)],
+// channel = 8 g + (v & 7).
 __device__ __forceinline__ void fold_rows(const double* red, int cg, int rpp, int ld, double scale, double* out) {
-  for (int o = threadIdx.x; o < 16 * cg; o += 256) {
+  const int outputs = 16 * cg;
+  int plog = 0;
+  while ((outputs << (plog + 1)) <= 256) ++plog;
+  const int parts = 1 << plog, part = threadIdx.x & (parts - 1);
+  for (int o = threadIdx.x >> plog; o < outputs; o += 256 >> plog) {
     const int v = o / cg, g = o - v * cg;
     const int c = 8 * g + (v & 7);
-    if (c >= ld) continue;
     double a = 0.0;
-    for (int t = 0; t < rpp; ++t) a += red[v * 256 + t * cg + g];
-    out[c * 2 + (v >> 3)] = scale * a;
+#pragma unroll 4
+    for (int t = part; t < rpp; t += parts) a += red[v * 256 + t * cg + g];
+    for (int d = 1; d < parts; d <<= 1) a += __shfl_xor(a, d, 64);  // the partners have the same o
+    if (part == 0 && c < ld) out[c * 2 + (v >> 3)] = scale * a;
   }
 }
 
@@ -156,8 +163,8 @@ __global__ __launch_bounds__(256) void bn_fwd_stats_kernel(BnParams p) {
   fold_rows(red, cg, l.rpp, p.ld, 1.0, p.scratch + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * p.ld * 2);
 }
 
-// grid (ceil(ld / 16), W), 256 threads = 16 split lanes x 16 channels: folds the nsplit partial sums of a
-// channel (lane j takes splits j, j+16, ...; the sixteen lanes are combined in a fixed order) once per
+// grid (ceil(ld / 4), W), 256 threads = 64 split lanes x 4 channels: folds the nsplit partial sums of a
+// channel (lane j takes splits j, j+64, ...; a tree over the sixteen lanes of a wave, then the four waves in order) once per
 // data-group and leaves the per-channel factors of the streaming kernel in coef[rep][.][ld], so that each of its
 // threads starts with a few 16-byte loads instead of dozens of scalar ones.
 // Forward (sum x, sum x^2): mean, rstd (and the gamma in use) into `stats`; coef rows: scale, shift. Backward (sum g,
@@ -167,26 +174,29 @@ __global__ __launch_bounds__(256) void bn_fwd_stats_kernel(BnParams p) {
 // dx = k0 * dy - k1 - xhat * k2. Channels past C (row padding) get zeros.
 template <bool BWD>
 __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p) {
-  const int rep = blockIdx.y, lane4 = threadIdx.x >> 4;
-  const int c = blockIdx.x * 16 + (threadIdx.x & 15);
-  const bool live = c < p.ld;
+  const int rep = blockIdx.y, lane4 = threadIdx.x >> 2;
+  const int c = blockIdx.x * 4 + (threadIdx.x & 3);  // ld is a multiple of four
   double a = 0.0, b = 0.0;
-  if (live) {
-#pragma unroll 8
-    for (int sp = lane4; sp < p.nsplit; sp += 16) {
-      const double2 in = *(const double2*)(p.scratch + (((size_t)rep * p.nsplit + sp) * p.ld + c) * 2);
-      a += in.x;
-      b += in.y;
-    }
+#pragma unroll 4
+  for (int sp = lane4; sp < p.nsplit; sp += 64) {
+    const double2 in = *(const double2*)(p.scratch + (((size_t)rep * p.nsplit + sp) * p.ld + c) * 2);
+    a += in.x;
+    b += in.y;
   }
-  __shared__ double red[2][16][16];
-  red[0][lane4][threadIdx.x & 15] = a;
-  red[1][lane4][threadIdx.x & 15] = b;
+#pragma unroll
+  for (int d = 4; d < 64; d <<= 1) {
+    a += __shfl_xor(a, d, 64);
+    b += __shfl_xor(b, d, 64);
+  }
+  __shared__ double red[2][4][4];
+  if ((threadIdx.x & 63) < 4) {
+    red[0][threadIdx.x >> 6][threadIdx.x & 3] = a;
+    red[1][threadIdx.x >> 6][threadIdx.x & 3] = b;
+  }
   __syncthreads();
-  if (lane4 != 0 || !live) return;
-  const int ch = threadIdx.x & 15;
+  if (threadIdx.x >= 4) return;
   a = b = 0.0;
-  for (int j = 0; j < 16; ++j) { a += red[0][j][ch]; b += red[1][j][ch]; }
+  for (int j = 0; j < 4; ++j) { a += red[0][j][threadIdx.x]; b += red[1][j][threadIdx.x]; }
   const double m = (double)p.rows_per_rep;
   const bool real = c < p.C;
   float* st = p.stats + (size_t)rep * 3 * p.ld;
@@ -370,7 +380,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(BnParams p) {
 
 void launch_bn_forward(int dt, const BnParams& p, hipStream_t s) {
   dim3 grid(p.nsplit, p.W);
-  dim3 fgrid((p.ld + 15) / 16, p.W);
+  dim3 fgrid(p.ld / 4, p.W);
   DDS_BN_DISPATCH(dt, bn_fwd_stats_kernel, <<<grid, 256, 0, s>>>(p));
   bn_finalize_kernel<false><<<fgrid, 256, 0, s>>>(p);
   DDS_BN_DISPATCH(dt, bn_fwd_apply_kernel, <<<grid, 256, 0, s>>>(p));
@@ -378,7 +388,7 @@ void launch_bn_forward(int dt, const BnParams& p, hipStream_t s) {
 
 void launch_bn_backward(int dt, const BnParams& p, hipStream_t s) {
   dim3 grid(p.nsplit, p.W);
-  dim3 fgrid((p.ld + 15) / 16, p.W);
+  dim3 fgrid(p.ld / 4, p.W);
   DDS_BN_DISPATCH(dt, bn_bwd_stats_kernel, <<<grid, 256, 0, s>>>(p));
   bn_finalize_kernel<true><<<fgrid, 256, 0, s>>>(p);
   DDS_BN_DISPATCH(dt, bn_bwd_apply_kernel, <<<grid, 256, 0, s>>>(p));
