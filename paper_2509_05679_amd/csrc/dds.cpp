@@ -94,8 +94,7 @@ struct Node {
   // batch normalisation (N_BN): layer = its gamma / beta block
   float eps = 0.f;
   size_t stats_off = 0;    // mean, rstd, gamma of the forwarded mini-batch, inside the ring slot
-  int bn_nsplit = 0;       // row splits per data-group
-  long long bn_rows_per_split = 0;
+  BnPlan bn{};
   int fold_sc = -1;        // first conv of a projection block: node of the 1x1 shortcut whose dgrad rides in this one's
   bool dgrad_folded = false;  // shortcut node: no dgrad launch of its own
   int wgroup = -1;            // launch that this layer's weight gradient goes with ...
@@ -657,12 +656,8 @@ int layout(dds_ctx& c, Arena& A) {
         o = align_up(o + (size_t)c.W * 3 * tb.Cpad * 4, 256);
       }
       const long long rows_per_rep = (long long)c.B * tb.H * tb.W;
-      // about 32 KiB of the tensor per workgroup, at most 512 splits per data-group
-      long long ns = rows_per_rep * tb.Cpad * es / 32768;
-      ns = ns < 1 ? 1 : ns > 512 ? 512 : ns;
-      nd.bn_rows_per_split = (rows_per_rep + ns - 1) / ns;
-      nd.bn_nsplit = (int)((rows_per_rep + nd.bn_rows_per_split - 1) / nd.bn_rows_per_split);
-      const size_t sb = (size_t)c.W * nd.bn_nsplit * tb.Cpad * 2 * sizeof(double);
+      nd.bn = bn_plan(c.W, rows_per_rep, tb.Cpad, es);
+      const size_t sb = (size_t)c.W * nd.bn.nsums * tb.Cpad * 2 * sizeof(double);
       const size_t cb = (size_t)c.W * kBnCoefRows * tb.Cpad * sizeof(float);
       bn_scratch_bytes = sb > bn_scratch_bytes ? sb : bn_scratch_bytes;
       bn_coef_bytes = cb > bn_coef_bytes ? cb : bn_coef_bytes;
@@ -891,9 +886,12 @@ BnParams bn_params(dds_ctx& c, Module& m, const Node& nd, int slot, const float*
   p.W = c.W;
   p.C = L.Cout;
   p.ld = to.Cpad;
-  p.nsplit = nd.bn_nsplit;
+  p.nsums = nd.bn.nsums;
+  p.nsplit = nd.bn.nsplit;
   p.rows_per_rep = (long long)c.B * to.H * to.W;
-  p.rows_per_split = nd.bn_rows_per_split;
+  p.rows_per_sum = nd.bn.rows_per_sum;
+  p.rows_per_split = nd.bn.rows_per_split;
+  p.fold = nd.bn.fold;
   p.eps = nd.eps;
   p.alpha = nd.alpha;
   p.relu = nd.relu;

@@ -88,6 +88,14 @@ struct WgradParams {
 //   forward : y = relu?( alpha * (gamma * (x - mean) * rstd + beta) + res ), stats <- mean, rstd, gamma
 //   backward: dgamma / dbeta partial rows (one per (data-group, split)), dx from dy, x and the saved stats
 constexpr int kBnCoefRows = 5;
+struct BnPlan {
+  int nsums, nsplit;
+  long long rows_per_sum, rows_per_split;
+  bool fold;
+};
+BnPlan bn_plan(int W, long long rows_per_rep, int ld, int es);
+constexpr int kBnFoldLd = 64, kBnFoldSums = 2048;
+
 struct BnParams {
   const void* x;      // input of the normalisation (the convolution output), dtype T
   void* y;            // forward output, dtype T
@@ -100,12 +108,14 @@ struct BnParams {
   long long rep_stride;  // floats between the parameters of consecutive data-groups (0: shared)
   int gstride;
   float* stats;       // [W][3][ld]: mean, rstd, gamma of this mini-batch
-  double* scratch;    // [W][nsplit][ld][2] per-split sums (forward: x, x^2; backward: g, g * xhat)
+  double* scratch;    // [W][nsums][ld][2] per-split sums (forward: x, x^2; backward: g, g * xhat)
   float* coef;        // [W][kBnCoefRows][ld] per-channel factors of the streaming kernel that follows
   float* partial;     // backward: [W][pstride] parameter-gradient rows, one per data-group
   long long pstride;
-  int W, C, ld, nsplit;
-  long long rows_per_rep, rows_per_split;
+  int W, C, ld;
+  int nsums, nsplit;  // row splits of a data-group: of the kernels that sum, of those that stream
+  long long rows_per_rep, rows_per_sum, rows_per_split;
+  bool fold;          // the streaming kernels join the splits' sums themselves
   float eps, alpha;
   int relu;
 };

@@ -313,9 +313,10 @@ def test_weight_gradients_of_pointwise_layers(c1, c2, h, w, W, B):
                       precision="bf16", lr=0.05, momentum=0.0, steps=2), seed=41, T=2)
 
 
-@pytest.mark.parametrize("c,hw,B", [(24, 32, 22), (24, 3, 2), (36, 7, 9), (64, 5, 3), (136, 4, 5)])
+@pytest.mark.parametrize("c,hw,B", [(24, 32, 22), (24, 3, 2), (36, 7, 9), (64, 5, 3), (64, 32, 9), (136, 4, 5)])
 def test_batch_norm_sums_shared_by_threads(c, hw, B):
-    # four, two and one thread per sum, channel groups that do not divide the workgroup; more than 64 splits of a data-group
+    # four, two and one thread per sum, channel groups that do not divide the workgroup; as many splits as the streaming kernels
+    # fold (64 of 24 channels), more than they do (72 of 64), rows too wide for it
     from test_gpu_batchnorm import _compare as compare_bn
     ops = [{"op": "conv", "cin": 3, "cout": c, "k": 1, "stride": 1, "pad": 0}, {"op": "bn", "c": c, "eps": 1e-5},
            {"op": "relu"}, {"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
