@@ -29,6 +29,12 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
+// 1 in each half of a packed bf16 pair >= 0 that is not zero (one instruction: min as unsigned 16-bit numbers)
+__device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
+  typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, pair), (u16x2_t){1, 1}));
+}
+
 // 3x3, stride 1, pad 1, CIN = 8 or 16 input channels (their stride), at most 16 NB output channels (stride 16 NB).
 // A workgroup owns 64 GROUPS consecutive pixels of the flattened (image, row, column) index; in it the nine taps of a pixel
 // are the pixels at distance -W-1 .. W+1, so its patch is 64 GROUPS + 2W + 2 consecutive pixels, copied global -> LDS as they lie.
@@ -44,12 +50,6 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_
 // from global memory 24.8 us forward (with a residual 28.5) and 24.3 us backward, of which the five operand reads of a run, at 24
 // cycles of the vector cache each, are 13; here 20.1 (23.2) and 20.6 us (69 to 103 MB). Stem to 16 channels (a gather through registers in 256 x 32
 // tiles before) 40.4 -> 16.4 us, to 64 channels, 512 images, 49.6 -> 32.1 us.
-// 1 in each half of a packed bf16 pair >= 0 that is not zero (one instruction: min as unsigned 16-bit numbers)
-__device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
-  typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, pair), (u16x2_t){1, 1}));
-}
-
 template <int CIN, int NB, bool DGRAD, bool ROWS16, int GROUPS>
 __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fills, Divisor dW, Divisor dH) {
   constexpr int PB = CIN * 2, PLOG = CIN == 16 ? 1 : 0, TPM = 32 / CIN, NM = (9 + TPM - 1) / TPM, OB = 32 * NB;  // OB: bytes of an output pixel
