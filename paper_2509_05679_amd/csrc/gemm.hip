@@ -2264,6 +2264,12 @@ int launch_wgrad_bf16(const WgradParams* pp, int n, hipStream_t s) {
 
 }  // namespace
 
+void allow_whole_lds(DeviceOnce& once, const void* kernel) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return;
+  once(device, [kernel] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess; });
+}
+
 int launch_conv(int dt, const ConvParams& p, hipStream_t s) {
   return dt == DT_F32 ? launch_conv_t<float>(p, s) : launch_conv_t<bf16_t>(p, s);
 }

@@ -33,12 +33,9 @@ inline Divisor make_divisor(int d) {  // d >= 2
   return Divisor{(uint32_t)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
 }
 
-// Lets a kernel have all 160 KB of LDS on the current device. A failure is the launch's to report.
-inline void allow_whole_lds(DeviceOnce& once, const void* kernel) {
-  int device = 0;
-  if (hipGetDevice(&device) != hipSuccess) return;
-  once(device, [kernel] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess; });
-}
-
 }  // namespace
+
+// Lets a kernel have all 160 KB of LDS on the current device (gemm.hip). A failure is the launch's to report.
+void allow_whole_lds(DeviceOnce& once, const void* kernel);
+
 }  // namespace dds
