@@ -222,18 +222,21 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fill
 // dW[k][tap][c] = sum over pixels p of dY[p][k] * X[p + tap][c] for 3x3 stride-1 pad-1 layers of 8, 16 or 32 input
 // and at most 32 (8 or 16 input: 64) output channels. All of dW is 32 NM x 32 NT (n = tap * Cx + c; the layout of a partial row),
 // which one wave holds in its accumulators: the four waves of a workgroup share the pixels, not the channels, and add their
-// sums in LDS when the workgroup has walked its split. Pixels of a data-group are numbered as in wgrad_flat_body (a
-// row pitch of W + 1, an extra row above every image; zeros at the extra positions), so that any image size will do, a tile is
-// `tile` consecutive positions and the nine taps are constant distances. Tiles travel global -> LDS in two slots as plain
-// [position][channels] rows; ds_read_b64_tr_b16 hands a lane four positions of one channel, and because every lane supplies the
-// address of its own four channels, one fragment of 32 columns may hold 1, 2 or 4 taps. Rows and columns past the real ones
-// multiply whatever lies there and are never stored. (An infinite activation makes NaN of taps that meet it from an extra
-// position; the centre tap of the same filter is then infinite or NaN whatever the kernel.)
+// sums in LDS when the workgroup has walked its split. A tile is `tile` consecutive pixels of a data-group; their dY rows are
+// copied as they lie. X is numbered as in wgrad_flat_body (a row pitch of W + 1, an extra row above every image; zeros at
+// the extra positions), so that any image size will do and the nine taps are constant distances from a pixel's position.
+// Tiles travel global -> LDS in two slots as plain [pixel or position][channels] rows; ds_read_b64_tr_b16 hands a lane four of
+// them of one channel, and because every lane supplies the address of its own row and four channels, the rows may be any
+// pixels' positions, and one fragment of 32 columns may hold 1, 2 or 4 taps. Rows and columns past the real ones
+// multiply whatever lies there and are never stored. No product pairs a pixel with a tap that does not see it: an
+// infinite or NaN activation meets zeros of dY only where that gradient itself is zero.
 // Bound by memory (64 to 144 bytes of a pixel against 4.6 to 18 kFLOP) and by one barrier per tile. A launch takes several
 // layers: workgroup -> (layer, split). Alone, 1024 images: 16 -> 16 channels at 32 x 32 27.8 -> 19.1 us (512 workgroups, 3.5 TB/s;
 // a kernel that staged its tiles through registers before), 32 -> 32 at 16 x 16 27.9 -> 18.3 us and the stem with 16 outputs 95 -> 14.4
 // us (64 x 64 blocks of wgrad_dma_body, 3/4 and 31/32 padding before), with 64 outputs and 512 images 50 -> 21.6 us. Tiles of
-// 256 positions (54 KB limit below) against 512: 19.1 / 22.5 us for the 16-channel layers.
+// 256 (54 KB limit below) against 512: 19.1 / 22.5 us for the 16-channel layers. (dY numbered by positions too, with zeros at the
+// extra ones, saves the division of a row address, 1 to 2 % of a launch at 32 x 32 and 10 % of 32 channels at 224 x 224, and makes NaN of
+// border taps that an infinite activation does not reach.)
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 __device__ __forceinline__ uint2 lds_tr16_b64(uint32_t lds_byte_address) {
@@ -252,13 +255,15 @@ struct SlimLayer {
   const void* x;
   float* partial;
   long long Pl;
-  Divisor dQ, dH;        // by Q and by H + 1
+  Divisor dQ, dH1;       // by Q and by H + 1 (positions)
+  Divisor dW, dH;        // by W and by H (pixels), of sides above one
   int first;             // first workgroup of this layer
   int q, rep_tiles;      // splits and tiles per data-group
   int H, W, Q, imgs_rep; // Q: position pitch of an image row, W + 1
-  int tile;              // positions per tile, a multiple of 256
+  int tile;              // pixels per tile, a multiple of 256
   int ylog;              // a row of dY is 16 << ylog bytes
-  int xfills;            // 1 KiB fills of a tile's X patch
+  int xfills;            // 1 KiB fills of a tile's X patch at most
+  int slots;             // tiles in LDS
   int Mout;
   float alpha;
 };
@@ -273,7 +278,7 @@ struct SlimGroup {
 template <int XB, int NM>
 __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   constexpr int MT = NM == 0 ? 16 : 32;     // rows and columns of a tile of dW
-  constexpr int KS = 512 / MT;              // positions per MFMA
+  constexpr int KS = 512 / MT;              // pixels per MFMA
   constexpr int NA = MT * MT / 64;          // accumulators of a lane and tile
   constexpr int MB = NM == 0 ? 1 : NM;
   constexpr int Cx = XB / 2, NK = 9 * Cx, NT = (NK + MT - 1) / MT;
@@ -292,12 +297,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   const int tile0 = (int)(((long long)zj * p.rep_tiles) / p.q);
   const int ntiles = (int)(((long long)(zj + 1) * p.rep_tiles) / p.q) - tile0;
   const int ylog = p.ylog, T = p.tile, Q = p.Q, H1 = p.H + 1, W = p.W, imgs = p.imgs_rep, xfills = p.xfills;
+  const bool two = p.slots == 2;
   const int ybytes = T << (ylog + 4);       // dY part of a slot
   const int slot_bytes = ybytes + xfills * 1024;
   const int yfills = ybytes >> 10;
-  const Divisor dQ = p.dQ, dH = p.dH;
+  const Divisor dQ = p.dQ, dH1 = p.dH1, dW = p.dW, dH = p.dH;
   const char* zeros = (const char*)grp.zeros;
-  const size_t pix0 = (size_t)zr * imgs * p.H * W;  // first pixel of the data-group
+  const int pixels = imgs * p.H * W;        // of a data-group
+  const size_t pix0 = (size_t)zr * pixels;  // its first
   const char* dy = (const char*)p.dy + (pix0 << (ylog + 4));
   const char* x = (const char*)p.x + (pix0 << (XLOG + 4));
 
@@ -305,33 +312,41 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   // image i = L / (H + 1), the positions before u hold L extra columns and i + 1 extra rows of W
   auto pixel = [&](int u) {
     const uint32_t uu = (uint32_t)max(u, 0);
-    const uint32_t line = __umulhi(uu, dQ.mul) >> dQ.shift, im = __umulhi(line, dH.mul) >> dH.shift;
+    const uint32_t line = __umulhi(uu, dQ.mul) >> dQ.shift, im = __umulhi(line, dH1.mul) >> dH1.shift;
     const int w = (int)(uu - __umul24(line, Q)), h1 = (int)(line - __umul24(im, H1));
     const int pix = (int)(uu - line) - (int)__umul24(im + 1, W);
     return u >= 0 && w < W && h1 > 0 && (int)im < imgs ? pix : -1;
   };
+  // pixel of the data-group -> its position, less the Q of the first image's extra row (pixels past the last one count on into
+  // further images, whose positions hold zeros)
+  auto position = [&](uint32_t n) {
+    const uint32_t line = W > 1 ? __umulhi(n, dW.mul) >> dW.shift : n, im = p.H > 1 ? __umulhi(line, dH.mul) >> dH.shift : line;
+    return n + line + __umul24(im, Q);
+  };
   auto fill_tile = [&](int t, int slot) {
     if (t >= ntiles) return;
-    const int u0 = (tile0 + t) * T;
+    const int n0 = (tile0 + t) * T;
     const uint32_t base = lds0 + slot * slot_bytes;
     for (int f = wave; f < yfills; f += 4) {
       const int piece = f * 64 + lane;
-      const int pix = pixel(u0 + (piece >> ylog));
+      const int pix = n0 + (piece >> ylog);
       const char* src = dy + ((((size_t)(uint32_t)pix << ylog) + (piece & ((1 << ylog) - 1))) << 4);
-      dma16(pix >= 0 ? src : zeros, base + f * 1024);
+      dma16(pix < pixels ? src : zeros, base + f * 1024);
     }
-    for (int f = wave; f < xfills; f += 4) {
+    const int u0 = (int)position(n0);  // position of the patch: u0 + Q less Q + 1
+    const int fills = (int)((position(n0 + T - 1) - u0 + 2 * Q + 3) * XB + 1023) >> 10;
+    for (int f = wave; f < fills; f += 4) {
       const int piece = f * 64 + lane;
-      const int pix = pixel(u0 - Q - 1 + (piece >> XLOG));
+      const int pix = pixel(u0 - 1 + (piece >> XLOG));
       const char* src = x + ((((size_t)(uint32_t)pix << XLOG) + (piece & ((1 << XLOG) - 1))) << 4);
       dma16(pix >= 0 ? src : zeros, base + ybytes + f * 1024);
     }
   };
   fill_tile(0, 0);
 
-  // fragment addressing: a 16-lane group reads four positions of 16 channels at a time, lane -> (position, four channels)
+  // fragment addressing: a 16-lane group reads four pixels of 16 channels at a time, lane -> (pixel, four channels)
   const int lq = lane & 15, rsub = lq >> 2, seg = lq & 3;
-  const int cgrp = NM == 0 ? 0 : (lane >> 4) & 1, kgrp = NM == 0 ? lane >> 4 : lane >> 5;  // 16-channel half, eight positions of a step
+  const int cgrp = NM == 0 ? 0 : (lane >> 4) & 1, kgrp = NM == 0 ? lane >> 4 : lane >> 5;  // 16-channel half, eight pixels of a step
   const int row0 = wave * (T >> 2) + 8 * kgrp + rsub;  // the waves take a quarter of a tile each
   const uint32_t a_lane = ((uint32_t)row0 << (ylog + 4)) + cgrp * 32 + seg * 8;
   uint32_t b_lane[NT];
@@ -339,7 +354,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   for (int b = 0; b < NT; ++b) {
     const int n = MT * b + 16 * cgrp + 4 * seg;
     const int tap = min(n / Cx, 8), c = n % Cx;
-    b_lane[b] = (row0 + (tap / 3) * Q + tap % 3) * XB + c * 2 + ybytes;
+    b_lane[b] = ((tap / 3) * Q + tap % 3) * XB + c * 2 + ybytes;
   }
   acc_t acc[MB][NT], accb[MB];
 #pragma unroll
@@ -356,12 +371,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   for (int t = 0; t < ntiles; ++t) {
     wait_vm<0>();
     wg_barrier();
-    fill_tile(t + 1, (t + 1) & 1);
-    const uint32_t base = lds0 + (t & 1) * slot_bytes;
-    uint32_t ya = base + a_lane, xb[NT];
-#pragma unroll
-    for (int b = 0; b < NT; ++b) xb[b] = base + b_lane[b];
-    for (int i = 0; i < T >> 8; ++i) {  // 64 positions of this wave
+    if (two) fill_tile(t + 1, (t + 1) & 1);
+    const uint32_t base = lds0 + (two ? t & 1 : 0) * slot_bytes;
+    const uint32_t n0 = (tile0 + t) * T, x0 = base - position(n0) * XB;  // x0 + position * XB: LDS row of the top left tap
+    uint32_t ya = base + a_lane;
+    for (int i = 0; i < T >> 8; ++i) {  // 64 pixels of this wave
 #pragma unroll
       for (int ks = 0; ks < 64 / KS; ++ks) {
         uint4 a[MB];
@@ -371,9 +385,11 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
           a[m] = make_uint4(a0.x, a0.y, a1.x, a1.y);
         }
         ya += yks;
+        const uint32_t n = n0 + row0 + 64 * i + KS * ks;
+        const uint32_t xa = x0 + position(n) * XB, xc = x0 + position(n + 4) * XB;
 #pragma unroll
         for (int b = 0; b < NT; ++b) {
-          const uint2 b0 = lds_tr16_b64(xb[b] + ks * KS * XB), b1 = lds_tr16_b64(xb[b] + (ks * KS + 4) * XB);
+          const uint2 b0 = lds_tr16_b64(xa + b_lane[b]), b1 = lds_tr16_b64(xc + b_lane[b]);
           const uint4 bf = make_uint4(b0.x, b0.y, b1.x, b1.y);
 #pragma unroll
           for (int m = 0; m < MB; ++m) acc[m][b] = slim_mfma(a[m], bf, acc[m][b]);
@@ -381,8 +397,10 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
 #pragma unroll
         for (int m = 0; m < MB; ++m) accb[m] = slim_mfma(a[m], ones, accb[m]);  // bias gradient: column sums of dY
       }
-#pragma unroll
-      for (int b = 0; b < NT; ++b) xb[b] += 64 * XB;
+    }
+    if (!two) {
+      wg_barrier();
+      fill_tile(t + 1, 0);
     }
   }
   wait_vm<0>();
@@ -434,22 +452,33 @@ bool slim_layer(const WgradParams& p, int W, SlimLayer& l) {
   if (l.ylog < 0) return false;
   l.H = p.H; l.W = p.W; l.Q = p.W + 1;
   l.imgs_rep = p.Nimg / W;
-  const long long positions = (long long)l.imgs_rep * (p.H + 1) * l.Q;
-  // positions are 32-bit numbers, rows of positions and sides 24-bit ones
-  if (positions + 1024 + 4 * l.Q >= (1ll << 31) || (long long)l.imgs_rep * (p.H + 1) + 2048 >= (1 << 24) || p.H >= (1 << 23) || p.W >= (1 << 23)) return false;
+  const long long positions = (long long)l.imgs_rep * (p.H + 1) * l.Q, pixels = (long long)l.imgs_rep * p.H * p.W;
+  // positions are 32-bit numbers (a tile's last pixels may lie in images past the last), rows of positions and sides 24-bit ones
+  if (positions + 4096 + 4ll * l.Q >= (1ll << 31) || (long long)l.imgs_rep * (p.H + 1) + 2048 >= (1 << 24) || p.H >= (1 << 23) || p.W >= (1 << 23)) return false;
   const int xb = p.Cx * 2;
+  // what a tile's pixels cross of boundaries `every` pixels apart; tiles begin at multiples of their size
+  auto crossed = [](long long tile, long long every) {
+    return every % tile == 0 ? 0 : tile % every == 0 ? tile / every - 1 : (tile - 2) / every + 1;
+  };
+  l.slots = 2;
   for (l.tile = 512;; l.tile = 256) {  // three workgroups of two slots each share a CU
-    l.xfills = (int)(((long long)(l.tile + 2 * l.Q + 2) * xb + 1023) / 1024);
-    const long long smem = 2ll * ((l.tile << (l.ylog + 4)) + 1024ll * l.xfills);
-    if (smem <= 54000) break;
+    const long long rows = crossed(l.tile, p.W), images = crossed(l.tile, (long long)p.H * p.W);
+    l.xfills = (int)(((l.tile + rows + (images + 2) * l.Q + 2) * xb + 1023) / 1024);
+    const long long slot = (l.tile << (l.ylog + 4)) + 1024ll * l.xfills;
+    if (2 * slot <= 54000) break;
     if (l.tile == 256) {
-      if (smem > 160 * 1024) return false;  // rows of at most about 1900 (8 channels) to 380 (32) pixels
+      // One tile at a time, copy and products in turn: rows of more than 1021 (16 channels in and out) or 380 (32) pixels, 680 or 253 where tiles run from one
+      // image into the next. 378 pixels of 32 channels 97 us with the stem, with two slots 86, wgrad_gemm_kernel 490.
+      if (2 * slot > 160 * 1024) l.slots = 1;
+      if (slot > 160 * 1024) return false;
       break;
     }
   }
-  l.rep_tiles = (int)((positions + l.tile - 1) / l.tile);
+  l.rep_tiles = (int)((pixels + l.tile - 1) / l.tile);
   l.dQ = make_divisor(l.Q);
-  l.dH = make_divisor(p.H + 1);
+  l.dH1 = make_divisor(p.H + 1);
+  l.dW = make_divisor(p.W > 1 ? p.W : 2);
+  l.dH = make_divisor(p.H > 1 ? p.H : 2);
   l.Mout = p.Mout;
   l.alpha = p.alpha;
   return true;
@@ -525,7 +554,7 @@ bool launch_wgrad_slim(const WgradParams* p, int n, hipStream_t s) {
     l.dy = p[i].dy; l.x = p[i].x; l.partial = p[i].partial; l.Pl = p[i].Pl;
     l.first = wgs;
     wgs += p[i].nsplit;
-    const int need = 2 * ((l.tile << (l.ylog + 4)) + 1024 * l.xfills);
+    const int need = l.slots * ((l.tile << (l.ylog + 4)) + 1024 * l.xfills);
     smem = smem > need ? smem : need;
   }
   g.n = n;

@@ -126,11 +126,13 @@ def test_weight_gradients_of_any_image_size(c1, c2, k, h, w, W, B):
 
 @pytest.mark.parametrize("widths,h,w,W,B", [
     ((8, 16, 16, 32, 32, 8), 1, 1, 1, 1), ((16, 64, 16, 8), 3, 3, 2, 16), ((32, 16, 64, 8), 3, 3, 1, 17), ((64, 32, 32, 16), 15, 15, 3, 5),
-    ((32, 32, 32), 2, 378, 1, 2), ((32, 32), 2, 388, 1, 1), ((16, 16, 16), 31, 15, 2, 9), ((20, 12, 24), 5, 4, 2, 7)])
+    ((32, 32, 32), 2, 378, 1, 2), ((32, 32), 2, 388, 1, 1), ((16, 16, 16), 31, 15, 2, 9), ((20, 12, 24), 5, 4, 2, 7),
+    ((32, 32), 16, 16, 1, 1), ((32, 16), 15, 15, 1, 2), ((32, 32), 3, 253, 1, 2), ((32, 32), 3, 254, 1, 2), ((32, 32), 128, 380, 1, 1),
+    ((32, 32), 3, 680, 1, 2), ((32, 32), 3, 681, 1, 2)])
 def test_weight_gradients_of_narrow_layers(widths, h, w, W, B):
     # 8, 16 and 32 input channels, each with one or two blocks of output rows; one pixel, data-groups of exactly one and of one and a
-    # bit 256-position tiles (3 x 3 with 16 and 17 images, 15 x 15), the longest rows with 32 channels and the first beyond them,
-    # channel counts that fill no row
+    # bit 256-pixel tiles (16 x 16 with one and 15 x 15 with two images), the longest rows of two tiles in LDS and of one with 32 channels and
+    # the first beyond them, channel counts that fill no row
     _compare(_conv_chain("bf16", widths, h, w, W, B), seed=34, T=2)
 
 
@@ -322,3 +324,28 @@ def test_batch_norm_sums_shared_by_threads(c, hw, B):
            {"op": "relu"}, {"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
     compare_bn(Workload(name=f"bn_sums_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=2, B=B, in_shape=(3, hw, hw), classes=10,
                         precision="f32", lr=0.05, momentum=0.0, steps=2), seed=42, T=2, every_step=True, tiny=True)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B", [(8, 16, 8, 8, 5), (8, 64, 15, 15, 3), (16, 16, 16, 32, 3), (16, 16, 5, 7, 40), (16, 32, 2, 600, 3),
+                                            (32, 32, 32, 32, 3), (32, 32, 3, 300, 3), (32, 16, 2, 600, 2)])
+def test_a_pixel_reaches_only_the_taps_that_see_it(cin, cout, h, w, B):
+    # a NaN in a corner of the input of a 3x3 layer: its weight gradient is NaN at the four taps that see the corner, and nowhere else
+    # (the ReLU behind the layer turns the NaNs of the forward pass into zeros, so nothing else in the net is touched)
+    import paper_2509_05679_amd as P
+    ops = [{"op": "conv", "cin": cin, "cout": cout, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}, {"op": "gap"},
+           {"op": "linear", "cin": cout, "cout": 10}, {"op": "softmax_ce"}]
+    wl = Workload(name=f"corner_{cin}_{cout}", ops=ops, bounds=[0, len(ops)], K=1, W=1, B=B, in_shape=(cin, h, w), classes=10,
+                  precision="bf16", lr=0.05, momentum=0.0, steps=1)
+    gen = torch.Generator(device="cuda").manual_seed(44)
+    for bottom in (0, 1):
+        for right in (0, 1):
+            x = torch.randn((B, cin, h, w), device="cuda", generator=gen)
+            x[B // 2, 1, -bottom, -right] = float("nan")
+            tr = P.Trainer(P.Spec.from_workload(wl), 1)
+            tr.dds_set_params(0, make_params(wl, 44)[0])
+            tr.dds_step([x], [torch.zeros(B, dtype=torch.int32, device="cuda")])
+            got = ~np.isfinite(tr.dds_get_params(0))
+            tr.close()
+            want = np.zeros((cout, cin, 3, 3), bool)
+            want[:, 1, bottom:bottom + 2, right:right + 2] = True
+            assert np.array_equal(got[:want.size].reshape(want.shape), want) and not got[want.size:].any(), (bottom, right)
