@@ -37,7 +37,8 @@ __device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
 
 // 3x3, stride 1, pad 1, CIN = 8 or 16 input channels (their stride), at most 16 NB output channels (stride 16 NB).
 // A workgroup owns 64 GROUPS consecutive pixels of the flattened (image, row, column) index; in it the nine taps of a pixel
-// are the pixels at distance -W-1 .. W+1, so its patch is 64 GROUPS + 2W + 2 consecutive pixels, copied global -> LDS as they lie.
+// are the pixels at distance -W-1 .. W+1, so its patch is 64 GROUPS + 2W + 2 consecutive pixels, copied global -> LDS as they lie; of wider
+// images it is three runs of 64 GROUPS + 2 pixels, W apart (`pitch` is the distance of two kernel rows in LDS: W or a run's length).
 // A wave owns GROUPS runs of 16 pixels. An MFMA multiplies 32 / CIN taps: lane l = 16 g + j holds, as B operand, eight channels of
 // pixel j shifted by its tap (16 channels: tap 2 t + (g >> 1), channels 8 (g & 1) .. +8; 8 channels: tap 4 t + g), and as A operand
 // the same k-slice of a weight row of each of the NB blocks; rows are dealt to the blocks so that the accumulators give it the 4 NB
@@ -49,9 +50,11 @@ __device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
 // Bound by memory, then by what every tile costs beside it. 16 -> 16 channels at 32 x 32, 1024 images, alone: operands read straight
 // from global memory 24.8 us forward (with a residual 28.5) and 24.3 us backward, of which the five operand reads of a run, at 24
 // cycles of the vector cache each, are 13; here 20.1 (23.2) and 20.6 us (69 to 103 MB). Stem to 16 channels (a gather through registers in 256 x 32
-// tiles before) 40.4 -> 16.4 us, to 64 channels, 512 images, 49.6 -> 32.1 us.
+// tiles before) 40.4 -> 16.4 us, to 64 channels, 512 images, 49.6 -> 32.1 us. 16 -> 16 channels, rows of 512 / 1024 / 2000 pixels, 2^20 of
+// them: one run 36 / 52 / 75 us forward, 33 / 46 / 72 us backward, three runs 29 / 26 / 24 and 25 / 23 / 22 us, operands from global memory
+// 29 and 25 us at every width.
 template <int CIN, int NB, bool DGRAD, bool ROWS16, int GROUPS>
-__global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fills, Divisor dW, Divisor dH) {
+__global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fills, int pitch, Divisor dW, Divisor dH) {
   constexpr int PB = CIN * 2, PLOG = CIN == 16 ? 1 : 0, TPM = 32 / CIN, NM = (9 + TPM - 1) / TPM, OB = 32 * NB;  // OB: bytes of an output pixel
   extern __shared__ __align__(16) char smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
@@ -63,8 +66,10 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fill
 
   // the patch; pixels before the tensor's first or after its last repeat that pixel (no tap inside an image reads them)
   for (int f = wave; f < fills; f += 4) {
-    const int piece = f * 64 + lane;
-    const int pix = min(max(m0 - p.W - 1 + (piece >> PLOG), 0), p.M - 1);
+    const int piece = f * 64 + lane, row = piece >> PLOG;
+    int pix = m0 - p.W - 1 + row;
+    if (p.W > pitch) pix += (row >= pitch ? p.W - pitch : 0) + (row >= 2 * pitch ? p.W - pitch : 0);
+    pix = min(max(pix, 0), p.M - 1);
     dma16((const char*)p.x + ((((size_t)(uint32_t)pix << PLOG) + (piece & ((1 << PLOG) - 1))) << 4), lds0 + f * 1024);
   }
   const uint32_t zeros = fills * 1024;
@@ -88,7 +93,7 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fill
     const int r = tt / 3, s = tt - 3 * r;
     dr[t] = DGRAD ? 1 - r : r - 1;
     ds[t] = DGRAD ? 1 - s : s - 1;
-    toff[t] = tap < 9 ? (uint32_t)((p.W + 1 + row0 + j + dr[t] * p.W + ds[t]) * PB + half * 16) : zeros;
+    toff[t] = tap < 9 ? (uint32_t)((pitch + 1 + row0 + j + dr[t] * pitch + ds[t]) * PB + half * 16) : zeros;
     leaves |= ((dr[t] < 0 ? 1u : 0u) | (dr[t] > 0 ? 2u : 0u) | (ds[t] < 0 && j == 0 ? 4u : 0u) | (ds[t] > 0 && j == 15 ? 8u : 0u)) << (4 * t);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -501,10 +506,8 @@ void launch_slim_inst(const SlimGroup& g, int wgs, int smem, hipStream_t s) {
 template <int CIN, int NB, bool DGRAD, bool ROWS16>
 void launch_direct_inst(const ConvParams& p, hipStream_t s) {
   constexpr int GROUPS = NB == 4 ? 2 : 4, PB = CIN * 2;
-  const int fills = cdiv((64 * GROUPS + 2 * p.W + 2) * PB, 1024);
-  static DeviceOnce lds;
-  allow_whole_lds(lds, (const void*)conv_direct_kernel<CIN, NB, DGRAD, ROWS16, GROUPS>);
-  conv_direct_kernel<CIN, NB, DGRAD, ROWS16, GROUPS><<<cdiv(p.M, 64 * GROUPS), 256, fills * 1024 + GROUPS * PB * 16, s>>>(p, fills, make_divisor(p.W), make_divisor(p.H));
+  const int pitch = min(p.W, 64 * GROUPS + 2), fills = cdiv((64 * GROUPS + 2 + 2 * pitch) * PB, 1024);
+  conv_direct_kernel<CIN, NB, DGRAD, ROWS16, GROUPS><<<cdiv(p.M, 64 * GROUPS), 256, fills * 1024 + GROUPS * PB * 16, s>>>(p, fills, pitch, make_divisor(p.W), make_divisor(p.H));
 }
 template <int CIN, int NB, bool DGRAD>
 void launch_direct(const ConvParams& p, hipStream_t s) {
@@ -517,7 +520,7 @@ void launch_direct(const ConvParams& p, hipStream_t s) {
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s) {
   if (p.R != 3 || p.S != 3 || p.stride != 1 || p.pad != 1 || p.H != p.Ho || p.W != p.Wo) return false;
   if (p.out_f32 || p.x2 != nullptr || p.Nout > p.ldy || p.M != p.Nimg * p.H * p.W) return false;
-  if (p.H < 2 || p.W < 2 || p.W > 2000) return false;  // make_divisor; the patch in LDS
+  if (p.H < 2 || p.W < 2) return false;  // make_divisor
   // a wave's runs must not straddle two data-groups
   if (p.nrep > 1 && (p.Nimg % p.nrep != 0 || (p.Nimg / p.nrep * (long long)p.H * p.W) % 64 != 0)) return false;
   if (p.Cx == 16 && p.ldy == 16) {

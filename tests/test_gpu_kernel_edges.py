@@ -138,10 +138,12 @@ def test_weight_gradients_of_narrow_layers(widths, h, w, W, B):
 
 @pytest.mark.parametrize("widths,h,w,W,B", [
     ((16, 16), 2, 2, 1, 1), ((16, 16, 12), 5, 7, 3, 4), ((12, 16, 16), 16, 16, 1, 2), ((16, 16), 3, 48, 2, 5), ((32, 16, 16), 8, 6, 2, 3),
-    ((64, 16), 4, 16, 1, 3), ((60, 16), 5, 13, 1, 3), ((16, 16), 2, 2000, 1, 1), ((16, 16), 2, 2001, 1, 1)])
+    ((64, 16), 4, 16, 1, 3), ((60, 16), 5, 13, 1, 3), ((16, 16), 2, 2000, 1, 1), ((16, 16), 2, 2001, 1, 1),
+    ((16, 16), 3, 258, 1, 2), ((16, 16), 3, 259, 2, 2), ((32, 16, 16), 5, 272, 1, 2), ((64, 16), 3, 130, 1, 2), ((60, 16), 4, 131, 1, 2),
+    ((64, 16), 3, 144, 1, 2)])
 def test_direct_convolutions_of_narrow_layers(widths, h, w, W, B):
     # stems of 16, 32 and 64 output rows, also not filled ones, and 16 -> 16 layers in both directions; rows of 16 pixels and others, less
-    # than a run, a ragged last tile, the longest rows and the first beyond them
+    # than a run, a ragged last tile; rows on both sides of the line (258 pixels, 130 with 64 outputs) from which a tile's patch is three runs
     _compare(_conv_chain("bf16", widths, h, w, W, B), seed=39, T=2)
 
 
@@ -349,3 +351,25 @@ def test_a_pixel_reaches_only_the_taps_that_see_it(cin, cout, h, w, B):
             want = np.zeros((cout, cin, 3, 3), bool)
             want[:, 1, bottom:bottom + 2, right:right + 2] = True
             assert np.array_equal(got[:want.size].reshape(want.shape), want) and not got[want.size:].any(), (bottom, right)
+
+
+def test_direct_convolutions_of_wide_images_copy_three_runs():
+    # 16 -> 16 channels, 2^20 pixels in rows of 32 and of 1024: forward and input gradient 41 and 98 us with a patch that holds the pixels
+    # between the three image rows too, 49 us with three runs at 1024
+    import paper_2509_05679_amd as P
+
+    def best(h, w, B):
+        wl = _conv_chain("bf16", (16, 16), h, w, 1, B)
+        tr = P.Trainer(P.Spec.from_workload(wl), 1)
+        tr.dds_set_params(0, make_params(wl, 45)[0])
+        xs, ys = [torch.zeros((B, 3, h, w), device="cuda")], [torch.zeros(B, dtype=torch.int32, device="cuda")]
+        times = []
+        for _ in range(8):
+            tr.dds_profile(2)
+            tr.dds_step(xs, ys)
+            got = tr.dds_profile_read()
+            times.append(got["forward_dma"][0] + got["dgrad_dma"][0])
+        tr.close()
+        return min(times)
+
+    assert best(256, 1024, 4) < 1.7 * best(32, 32, 1024)
