@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("W,B", [(1, 63), (2, 32), (3, 85), (2, 128)])
 def test_update_ranges_by_split_count(W, B):
-    # 16-channel layers at 16 x 16 pixels have one split per image: 63 / 64 / 255 / 256 of them lie on both sides of the
-    # lines between 256-, 64- and 32-element ranges
+    # 16-channel layers at 16 x 16 pixels have one split per image: 63 and 64 of them are summed by tiles of 256 weights, 255 and 256
+    # by tiles of 64 (the lines themselves: test_update_tiles_by_split_count)
     _compare(tiny_resnet(K=1, W=W, B=B, hw=16, c=16, precision="bf16"), seed=20, T=2)
 
 
@@ -302,9 +302,9 @@ def test_weight_gradients_that_share_a_launch(widths, h, w, W, B):
 
 @pytest.mark.parametrize("B", [8, 9, 64, 65])
 def test_update_tiles_by_split_count(B):
-    # one split per image of 15 x 15 pixels: both sides of the lines between tiles of 1024, 256 and 64 weights; tiles of 8, 16 and 32 input
+    # one split per image of 16 x 16 pixels: both sides of the lines between tiles of 1024, 256 and 64 weights; tiles of 8, 16 and 32 input
     # channels, output channels that fill no tile (fp32 nets have one tile size: the other tests)
-    _compare(_conv_chain("bf16", (16, 16, 32, 32, 12), 15, 15, 1, B), seed=40, T=2)
+    _compare(_conv_chain("bf16", (16, 16, 32, 32, 12), 16, 16, 1, B), seed=40, T=2)
 
 
 @pytest.mark.parametrize("c1,c2,h,w,W,B", [(8, 12, 1, 1, 2, 64), (72, 136, 1, 1, 3, 43), (64, 64, 4, 4, 1, 8), (128, 200, 3, 5, 2, 9), (16, 40, 1, 129, 1, 1)])
