@@ -214,7 +214,8 @@ def main():
     # Roofline of the dominant kernel class: the MFMA implicit-GEMM kernels (forward, dgrad
     # and wgrad of every conv / linear layer). Two further, untimed passes bracket each of
     # those launches with HIP events on the stream it is launched on (dds_profile):
-    # achieved = algorithmic FLOPs (2*M*N*K per launch) / summed launch durations.
+    # achieved = algorithmic FLOPs (2*M*N*K per launch) / summed launch durations. A weight-gradient launch that several
+    # layers share counts once for each, with that layer's part of the time.
     #  - serial pass (mode 2): modules run one after another, every launch has the chip to
     #    itself: this is the per-kernel figure reported as `achieved`;
     #  - concurrent pass (mode 1): the K modules share the chip as in the timed region, so

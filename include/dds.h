@@ -221,12 +221,17 @@ double dds_gemm_flops_per_step(const dds_ctx* ctx);
 /* Per-launch timing of the MFMA kernels for the benchmark's roofline record. While
  * enabled every conv/linear forward, dgrad and wgrad launch is bracketed by HIP events on
  * the stream it is launched on and dds_step synchronises at its end (do not time
- * throughput in this mode). enable = 1: modules stay on their concurrent streams, so a
+ * throughput in this mode). The launches are those of any other step; one that several
+ * layers share (weight gradients of a module) is timed once, and each of its layers counts
+ * with the part of the time that its part of the launch's tiles is.
+ * enable = 1: modules stay on their concurrent streams, so a
  * launch's duration includes the time it shares the chip with other modules' kernels;
  * enable = 2: modules run one after another on the caller's stream, so every launch has
- * the chip to itself; 0: off. Enabling also clears the totals.
+ * the chip to itself; 0: off. Enabling also clears the totals. (enable = 3, for tests: as 2, with
+ * every layer's weight gradient in a launch of its own, cut into as many partial sums as in the
+ * shared one. The same bits; not the launches nor the times of a step.)
  * dds_profile_read fills 18 doubles: for each of six classes summed milliseconds, number of
- * launches, summed algorithmic FLOPs (2*M*N*K). Classes 0 forward, 1 dgrad, 2 wgrad launches
+ * layers launched, summed algorithmic FLOPs (2*M*N*K). Classes 0 forward, 1 dgrad, 2 wgrad layers
  * taken by the generic implicit-GEMM kernels; 3, 4, 5 the same three kinds taken by the
  * kernels made for 3x3 stride-1 layers and, for wgrad, stride-2 ones. */
 int dds_profile(dds_ctx* ctx, int enable);

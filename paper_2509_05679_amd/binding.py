@@ -249,12 +249,14 @@ class Trainer:
         return dev.cpu().numpy()
 
     def dds_profile(self, enable):
-        """0 / False: off; 1 / True: time launches on their concurrent streams; 2: modules serialised."""
+        """0 / False: off; 1 / True: time launches on their concurrent streams; 2: modules serialised;
+        3 (tests): as 2, no weight-gradient launch shared."""
         _check(lib.dds_profile(self.ctx, int(enable)))
 
     def dds_profile_read(self):
-        """{class: (ms, launches, flops)}; classes forward / dgrad / wgrad on the generic kernels and
-        forward_dma / dgrad_dma / wgrad_dma on the asynchronous global->LDS kernels."""
+        """{class: (ms, layers, flops)}; classes forward / dgrad / wgrad on the generic kernels and
+        forward_dma / dgrad_dma / wgrad_dma on the asynchronous global->LDS kernels. A launch that several
+        layers share is timed once and divided among them by their tiles."""
         out = (C.c_double * 18)()
         _check(lib.dds_profile_read(self.ctx, out))
         names = ("forward", "dgrad", "wgrad", "forward_dma", "dgrad_dma", "wgrad_dma")

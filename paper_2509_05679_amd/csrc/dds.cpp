@@ -112,7 +112,9 @@ struct Module {
   std::vector<Node> nodes;
   std::vector<ParamLayer> layers;  // canonical (spec) order
   std::vector<GradBuf> grads;
-  std::vector<std::vector<WgradParams>> wgroups;  // weight gradients that wait for the rest of their launch
+  // weight gradients that wait for the rest of their launch, with their algorithmic FLOPs
+  struct WgradQueue { std::vector<WgradParams> layers; std::vector<double> flops; };
+  std::vector<WgradQueue> wgroups;
   size_t slot_bytes = 0;
   char* ring = nullptr;
   // Recompute policy (modules with d > 0): a ring slot keeps only what other iterations or modules read (the
@@ -197,8 +199,10 @@ struct dds_ctx {
                         // caller's stream (per-kernel timing without other modules sharing the chip)
   // optional per-launch timing of the MFMA kernels (events on the launching stream)
   bool profiling = false;
-  bool profile_serial = false;  // dds_profile(ctx, 2): modules run one after another while profiling
-  struct ProfRec { int cls; double flops; hipEvent_t a, b; };
+  bool profile_serial = false;  // dds_profile(ctx, 2 or 3): modules run one after another while profiling
+  bool wgrads_alone = false;    // dds_profile(ctx, 3): every layer's weight gradient in a launch of its own
+  // one layer of a timed launch: its class, its work and its part of the launch's time; the last layer gives the events back
+  struct ProfRec { int cls; double flops, part; hipEvent_t a, b; bool last; };
   std::vector<ProfRec> prof_pending;
   std::vector<hipEvent_t> prof_pool;
   // classes: 0 forward, 1 dgrad, 2 wgrad on the generic kernels; 3, 4, 5 the same on the asynchronous kernels
@@ -607,7 +611,8 @@ void plan_wgrads(dds_ctx& c, Module& m) {
       nd.wgroup_last = i + 1 == o.nodes.size();
     }
     m.wgroups.emplace_back();
-    m.wgroups.back().reserve(o.nodes.size());
+    m.wgroups.back().layers.reserve(o.nodes.size());
+    m.wgroups.back().flops.reserve(o.nodes.size());
     o.nodes.clear();
     o.work = 0;
   };
@@ -856,18 +861,47 @@ hipEvent_t prof_event(dds_ctx& c) {
   return e;
 }
 
-// cls: 0 forward, 1 dgrad, 2 wgrad; + 3 once the launch reports the asynchronous kernel family
+// Brackets a launch with events. cls: 0 forward, 1 dgrad, 2 wgrad; + 3 once the launch reports the asynchronous kernel family
 struct ProfScope {
   dds_ctx& c; hipStream_t s; int cls; double flops; hipEvent_t a = nullptr;
   bool on;
+  std::vector<dds_ctx::ProfRec> layers;  // of a launch that several layers share (cls and flops are not looked at then)
   ProfScope(dds_ctx& c_, hipStream_t s_, int cls_, double flops_, bool enabled = true)
       : c(c_), s(s_), cls(cls_), flops(flops_), on(c_.profiling && enabled) {
     if (on) { a = prof_event(c); (void)hipEventRecord(a, s); }
   }
   ~ProfScope() {
-    if (on) { hipEvent_t b = prof_event(c); (void)hipEventRecord(b, s); c.prof_pending.push_back({cls, flops, a, b}); }
+    if (!on) return;
+    hipEvent_t b = prof_event(c);
+    (void)hipEventRecord(b, s);
+    if (layers.empty()) layers.push_back({cls, flops, 1.0, a, b, true});
+    for (size_t i = 0; i < layers.size(); ++i) {
+      layers[i].a = a;
+      layers[i].b = b;
+      layers[i].last = i + 1 == layers.size();
+      c.prof_pending.push_back(layers[i]);
+    }
   }
 };
+
+// The layers of a weight-gradient launch: its time is theirs in proportion to the tiles that they put into it. (Asked for
+// before the launch: host work between the two events would be timed.)
+std::vector<dds_ctx::ProfRec> wgrad_layers(const dds_ctx& c, const Module::WgradQueue& group) {
+  std::vector<dds_ctx::ProfRec> layers;
+  if (!c.profiling) return layers;
+  std::vector<double> tiles;
+  double all = 0.0;
+  for (const WgradParams& w : group.layers) {
+    const WgradWork work = wgrad_work(c.dt, w);
+    tiles.push_back(work.key == 0 ? 1.0 : (double)work.blocks * work.tiles * w.nrep);
+    all += tiles.back();
+  }
+  for (size_t i = 0; i < tiles.size(); ++i) {
+    const WgradParams& w = group.layers[i];
+    layers.push_back({w.R == 3 || w.stride == 2 ? 5 : 2, group.flops[i], tiles[i] / all, nullptr, nullptr, false});
+  }
+  return layers;
+}
 
 // Fields of a batch-normalisation launch that forward and backward share; slot = ring slot of the mini-batch.
 BnParams bn_params(dds_ctx& c, Module& m, const Node& nd, int slot, const float* master) {
@@ -973,7 +1007,7 @@ void run_forward(dds_ctx& c, Module& m, int slot, int in_slot, hipStream_t s, in
 // has a buffer of its own, so nothing is overwritten before the join at the end. ws == s: one after the other.
 int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStream_t ws) {
   const int slot = sc.bwd_slot, in_slot = sc.in_bwd_slot;
-  for (std::vector<WgradParams>& group : m.wgroups) group.clear();  // (a step that failed half way)
+  for (Module::WgradQueue& group : m.wgroups) { group.layers.clear(); group.flops.clear(); }  // (a step that failed half way)
   for (int ni = (int)m.nodes.size() - 1; ni >= 0; --ni) {
     const Node& nd = m.nodes[ni];
     if (nd.kind == N_CE) continue;  // dlogits were produced by the loss kernel
@@ -995,18 +1029,23 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
         w.zeros = c.zeros;
         w.nsplit = L.nsplit;
         w.pix_per_split = w.P / L.nsplit;
-        // It waits for the other layers of its launch, but when every launch is timed: the sums do not depend on which it is.
-        std::vector<WgradParams>& group = m.wgroups[nd.wgroup];
-        group.push_back(w);
-        if (nd.wgroup_last || c.profiling) {
+        // It waits for the other layers of its launch; the sums do not depend on which it is.
+        Module::WgradQueue& group = m.wgroups[nd.wgroup];
+        group.layers.push_back(w);
+        group.flops.push_back(2.0 * w.P * L.Cout * L.Cin * L.RS);
+        if (nd.wgroup_last || c.wgrads_alone) {
           if (ws != s) {
             HIP_TRY(hipEventRecord(m.wfork, s));
             HIP_TRY(hipStreamWaitEvent(ws, m.wfork, 0));
           }
-          ProfScope ps(c, ws, 2, 2.0 * w.P * L.Cout * L.Cin * L.RS);
-          ps.cls += 3 * launch_wgrad(c.dt, group.data(), (int)group.size(), ws);
+          std::vector<dds_ctx::ProfRec> layers = wgrad_layers(c, group);
+          ProfScope ps(c, ws, 2, 0.0);
+          ps.layers = std::move(layers);
+          if (!launch_wgrad(c.dt, group.layers.data(), (int)group.layers.size(), ws))
+            for (dds_ctx::ProfRec& r : ps.layers) r.cls = 2;
           ++c.launches;
-          group.clear();
+          group.layers.clear();
+          group.flops.clear();
         }
         if (nd.gin != G_NONE) {
           ConvParams p{};
@@ -1506,12 +1545,14 @@ int dds_step(dds_ctx* c, const float* const* x, const int32_t* const* y, float l
     for (auto& r : c->prof_pending) {
       float ms = 0.f;
       if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
-        c->prof_ms[r.cls] += ms;
+        c->prof_ms[r.cls] += ms * r.part;
         c->prof_flops[r.cls] += r.flops;
         c->prof_count[r.cls] += 1;
       }
-      c->prof_pool.push_back(r.a);
-      c->prof_pool.push_back(r.b);
+      if (r.last) {
+        c->prof_pool.push_back(r.a);
+        c->prof_pool.push_back(r.b);
+      }
     }
     c->prof_pending.clear();
   }
@@ -1588,7 +1629,8 @@ int dds_profile(dds_ctx* c, int enable) {
   if (!c) return fail(DDS_EINVAL, "null ctx");
   c->chained = false;
   c->profiling = enable != 0;
-  c->profile_serial = enable == 2;
+  c->profile_serial = enable == 2 || enable == 3;
+  c->wgrads_alone = enable == 3;
   for (int i = 0; i < 6; ++i) { c->prof_ms[i] = 0; c->prof_flops[i] = 0; c->prof_count[i] = 0; }
   return DDS_OK;
 }

@@ -2247,7 +2247,7 @@ void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
 }
 
 int launch_wgrad_bf16(const WgradParams* pp, int n, hipStream_t s) {
-  if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return pp[0].R == 3 || pp[0].stride == 2;
+  if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return 1;
   const WgradParams& p = pp[0];  // the others have no key to share a launch under
   if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);

@@ -142,15 +142,15 @@ struct UpdateDesc {
   int Cout, RS, Cinpad, Cin, Coutpad;
 };
 
-// Both return the kernel family that took the launch, the class of dds_profile_read: 1 = the kernels made for 3x3 stride-1
-// layers and, among the weight gradients, stride-2 ones (conv3x3_dma, conv_direct, wgrad_tiles, wgrad_slim), 0 = those that
-// take any layer (conv_gather, conv_gemm, linear, wgrad_gemm, wgrad_f32) and the forward pass of a stem (conv_direct, 8 channels).
+// Returns the class of dds_profile_read: 1 = the kernels made for 3x3 stride-1 layers (conv3x3_dma, conv_direct), 0 = those that
+// take any layer (conv_gather, conv_gemm, linear) and the forward pass of a stem (conv_direct, 8 channels).
 int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 // plain products of few rows (linear.hip); false: not taken, nothing launched
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows, stems (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
-// n layers of one key (wgrad_work), or one of any kind
+// n layers of one key (wgrad_work), or one of any kind. Returns 1 if wgrad_tiles or wgrad_slim took them, whose 3x3 and stride-2
+// layers have a class of their own, 0 if wgrad_gemm or wgrad_f32 did.
 int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);
 // Layers of one key, if it is not 0, may share a launch; a split of theirs is at least one of `tiles` tiles of a data-group,
 // and each is walked by `blocks` workgroups. shape: every field that describes the layer (Nimg, H, W, Cx, Ho, Wo, Mout, ldy,

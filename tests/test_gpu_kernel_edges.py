@@ -281,21 +281,23 @@ def test_shared_reductions_with_weights_per_data_group():
     ((64, 64, 128, 64, 72, 64), 8, 8, 1, 33),         # whole 128-pixel tiles and others (72 channels in) share a launch
     ((64,) * 5, 32, 32, 1, 700)])                     # launches closed by their work: 5600 tiles a layer, three layers
 def test_weight_gradients_that_share_a_launch(widths, h, w, W, B):
-    # while launches are timed every layer has one of its own: the same bits
+    # against every layer in a launch of its own, with the splits that it has in the shared one: the same bits
     import paper_2509_05679_amd as P
     wl = _conv_chain("bf16", widths, h, w, W, B)
     gen = torch.Generator(device="cuda").manual_seed(38)
     xs = [torch.randn((B, 3, h, w), device="cuda", generator=gen) for _ in range(W)]
     ys = [torch.randint(10, (B,), device="cuda", generator=gen, dtype=torch.int32) for _ in range(W)]
     init, runs = make_params(wl, 38), []
-    for mode in (0, 2):
+    for mode in (0, 3):
         tr = P.Trainer(P.Spec.from_workload(wl), W)
         tr.dds_set_params(0, init[0])
         tr.dds_profile(mode)
         for _ in range(3):
             tr.dds_step(xs, ys)
-        runs.append(tr.dds_get_params(0))
+        runs.append((tr.dds_get_params(0), tr.dds_launches_last_step()))
         tr.close()
+    (runs, launches) = zip(*runs)
+    assert launches[1] - launches[0] >= 2
     assert np.isfinite(runs[0]).all() and np.array_equal(runs[0], runs[1])
     assert not np.array_equal(runs[0], np.concatenate([p.ravel() for p in init[0]]))
 
@@ -373,3 +375,25 @@ def test_direct_convolutions_of_wide_images_copy_three_runs():
         return min(times)
 
     assert best(256, 1024, 4) < 1.7 * best(32, 32, 1024)
+
+
+@pytest.mark.parametrize("name", ["cfg2_resnet18", "cfg1_cnn"])
+def test_profiling_times_the_launches_of_any_other_step(name):
+    import paper_2509_05679_amd as P
+    wl = workload(name, B=16)
+    tr = P.Trainer(P.Spec.from_workload(wl), wl.W)
+    for k0, t in enumerate(make_params(wl, 46)):
+        tr.dds_set_params(k0, t)
+    xs = [torch.zeros((16, *wl.in_shape), device="cuda") for _ in range(wl.W)]
+    ys = [torch.zeros(16, dtype=torch.int32, device="cuda") for _ in range(wl.W)]
+    for _ in range(2 * (wl.K - 1) + 1):
+        tr.dds_step(xs, ys)
+    launches = tr.dds_launches_last_step()
+    for mode in (1, 2):
+        tr.dds_profile(mode)
+        tr.dds_step(xs, ys)
+        got = tr.dds_profile_read()
+        assert tr.dds_launches_last_step() == launches
+        assert sum(v[2] for v in got.values()) == pytest.approx(tr.dds_gemm_flops_per_step(), rel=1e-12)
+        assert all(v[0] > 0 for v in got.values() if v[1])
+    tr.close()
