@@ -988,7 +988,7 @@ void run_forward(dds_ctx& c, Module& m, int slot, int in_slot, hipStream_t s, in
         p.res = nd.res >= 0 ? tptr(c, m, nd.res, slot, in_slot) : nullptr;
         p.bits_out = nd.relu ? bits_ptr(c, m, nd.out, slot, in_slot) : nullptr;
         launch_bn_forward(c.dt, p, s);
-        ++c.launches;
+        c.launches += p.fold ? 1 : 2;
         break;
       }
       case N_MAXPOOL:
@@ -1092,7 +1092,7 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
         p.dy = gout;
         p.dx = gin;
         launch_bn_backward(c.dt, p, s);
-        c.launches += 2;
+        c.launches += p.fold ? 2 : 3;
         break;
       }
       case N_MAXPOOL:

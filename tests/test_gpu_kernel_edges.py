@@ -397,3 +397,22 @@ def test_profiling_times_the_launches_of_any_other_step(name):
         assert sum(v[2] for v in got.values()) == pytest.approx(tr.dds_gemm_flops_per_step(), rel=1e-12)
         assert all(v[0] > 0 for v in got.values() if v[1])
     tr.close()
+
+
+@pytest.mark.parametrize("c,bn_launches", [(16, 4), (136, 6)])
+def test_launches_of_a_normalised_net_are_counted(c, bn_launches):
+    # the splits' sums of rows of up to 64 channels are joined by the streaming kernels, those of wider rows by a launch of their own in
+    # either direction
+    import paper_2509_05679_amd as P
+    tail = [{"op": "relu"}, {"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
+    counts = []
+    for bn in ([], [{"op": "bn", "c": c, "eps": 1e-5}]):
+        ops = [{"op": "conv", "cin": 3, "cout": c, "k": 3, "stride": 1, "pad": 1}] + bn + tail
+        wl = Workload(name=f"launches_{c}", ops=ops, bounds=[0, len(ops)], K=1, W=1, B=4, in_shape=(3, 8, 8), classes=10,
+                      precision="bf16", lr=0.05, momentum=0.0, steps=1)
+        tr = P.Trainer(P.Spec.from_workload(wl), 1)
+        tr.dds_set_params(0, make_params(wl, 47)[0])
+        tr.dds_step([torch.zeros((4, 3, 8, 8), device="cuda")], [torch.zeros(4, dtype=torch.int32, device="cuda")])
+        counts.append(tr.dds_launches_last_step())
+        tr.close()
+    assert counts[1] - counts[0] == bn_launches
