@@ -1041,7 +1041,9 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
           std::vector<dds_ctx::ProfRec> layers = wgrad_layers(c, group);
           ProfScope ps(c, ws, 2, 0.0);
           ps.layers = std::move(layers);
-          if (!launch_wgrad(c.dt, group.layers.data(), (int)group.layers.size(), ws))
+          const int family = launch_wgrad(c.dt, group.layers.data(), (int)group.layers.size(), ws);
+          if (family < 0) return fail(DDS_EUNSUPPORTED, "module %d: no kernel takes the weight gradients planned for a launch", m.k0);
+          if (family == 0)
             for (dds_ctx::ProfRec& r : ps.layers) r.cls = 2;
           ++c.launches;
           group.layers.clear();

@@ -2248,8 +2248,9 @@ void launch_wgrad_f32(const WgradParams& p, hipStream_t s) {
 
 int launch_wgrad_bf16(const WgradParams* pp, int n, hipStream_t s) {
   if (launch_wgrad_slim(pp, n, s) || launch_wgrad_tiles(pp, n, s)) return 1;
-  const WgradParams& p = pp[0];  // the others have no key to share a launch under
-  if (p.Mout <= 64 && p.NK + 8 <= 128) {  // e.g. the stem: 3 input channels, 9 taps
+  const WgradParams& p = pp[0];
+  if (n != 1 || (long long)p.nsplit * p.pix_per_split != p.P) return -1;  // no layer shares wgrad_gemm_kernel, whose splits are equal
+  if (p.Mout <= 64 && p.NK + 8 <= 128) {  // few input channels and taps, e.g. a 3x3 stem without padding
     dim3 grid(cdiv(p.Mout, 64), 1, p.nsplit);
     wgrad_gemm_kernel<bf16_t, 64, 128, 32, 64><<<grid, 256, 0, s>>>(p);
   } else if (p.Mout <= 64) {

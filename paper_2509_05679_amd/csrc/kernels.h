@@ -150,7 +150,7 @@ bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows, stems (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
 // n layers of one key (wgrad_work), or one of any kind. Returns 1 if wgrad_tiles or wgrad_slim took them, whose 3x3 and stride-2
-// layers have a class of their own, 0 if wgrad_gemm or wgrad_f32 did.
+// layers have a class of their own, 0 if wgrad_gemm or wgrad_f32 did; -1, nothing launched, if their splits fit none of them.
 int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);
 // Layers of one key, if it is not 0, may share a launch; a split of theirs is at least one of `tiles` tiles of a data-group,
 // and each is walked by `blocks` workgroups. shape: every field that describes the layer (Nimg, H, W, Cx, Ho, Wo, Mout, ldy,

@@ -229,6 +229,62 @@ def test_device_once_runs_on_every_device_and_again_after_a_failure(tmp_path):
     assert subprocess.run([str(exe)]).returncode == 0
 
 
+_WGRAD_PLANS = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace dds;
+static const int zeros = 0;
+static WgradParams layer(int cin, int cout, int hw, int images, int nrep) {
+  WgradParams w{};
+  w.zeros = &zeros;
+  w.Nimg = images; w.H = w.Ho = w.W = w.Wo = hw; w.Cx = cin; w.Mout = w.ldy = cout;
+  w.R = w.S = 3; w.stride = w.pad = 1; w.NK = 9 * cin; w.P = images * hw * hw; w.nrep = nrep; w.alpha = 1.f;
+  return w;
+}
+int main() {
+  // splits of the two 16-channel layers of a net of 16 x 16 images: the mean of 63, 64, 255 and 256, a mixing step of 7, 8, 31 and 32 a data-group
+  const int images[8][2] = {{63, 1}, {64, 1}, {255, 1}, {256, 1}, {14, 2}, {24, 3}, {62, 2}, {160, 5}};
+  for (auto& c : images) {
+    const WgradParams two[2] = {layer(16, 16, 16, c[0], c[1]), layer(16, 16, 16, c[0], c[1])};
+    int q[2];
+    wgrad_choose_splits(DT_BF16, two, 2, q);
+    printf("%d %d ", q[0], q[1]);
+  }
+  for (int n : {8, 9, 64, 65}) {  // ... and of one layer of 16 or 32 input channels
+    int q[2];
+    const WgradParams a = layer(16, 16, 16, n, 1), b = layer(32, 32, 16, n, 1);
+    wgrad_choose_splits(DT_BF16, &a, 1, q);
+    wgrad_choose_splits(DT_BF16, &b, 1, q + 1);
+    printf("%d %d ", q[0], q[1]);
+  }
+  // refused before anything is launched: a layer of another kernel, more splits than tiles, splits that are not equal
+  WgradParams uneven = layer(64, 64, 16, 8, 1);
+  uneven.R = uneven.S = 5; uneven.pad = 2; uneven.NK = 25 * 64; uneven.nsplit = 3; uneven.pix_per_split = uneven.P / 3;
+  WgradParams mixed[2] = {layer(64, 64, 16, 8, 1), uneven};
+  mixed[0].nsplit = mixed[1].nsplit = 8;
+  mixed[0].pix_per_split = mixed[1].pix_per_split = uneven.P / 8;
+  WgradParams many = layer(16, 16, 16, 1, 1);
+  many.nsplit = 3;
+  many.pix_per_split = many.P / 3;
+  printf("%d %d %d\n", launch_wgrad(DT_BF16, mixed, 2, nullptr), launch_wgrad(DT_BF16, &many, 1, nullptr), launch_wgrad(DT_BF16, &uneven, 1, nullptr));
+}
+"""
+
+
+def test_split_counts_of_narrow_layers_and_refused_weight_gradients(tmp_path):
+    # the counts that the GPU tests of the update by split count name, and no launch that drops a layer or some of its pixels
+    import subprocess
+    pkg = os.path.join(ROOT, "paper_2509_05679_amd")
+    src = tmp_path / "plans.cpp"
+    src.write_text(_WGRAD_PLANS)
+    exe = tmp_path / "plans"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(pkg, "csrc"), str(src), "-o", str(exe),
+                    os.path.join(pkg, "libdds.so"), "-Wl,-rpath," + pkg, "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True)
+    out = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=60, check=True).stdout.split()
+    splits = [63, 64, 255, 256, 14, 24, 62, 160, 8, 9, 64, 65]
+    assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [-1, -1, -1]
+
+
 def test_no_kernel_attribute_is_remembered_per_process():
     csrc = os.path.join(ROOT, "paper_2509_05679_amd", "csrc")
     for name in os.listdir(csrc):
