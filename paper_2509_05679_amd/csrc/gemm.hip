@@ -2327,17 +2327,28 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) 
     const WgradWork w = wgrad_work(dt, shapes[i]);
     total += (long long)w.blocks * w.tiles * shapes[i].nrep;
   }
+  bool one_per_cu = false;  // by LDS
+  for (int i = 0; i < n && w0.key == 2; ++i) {
+    WgradLayer l;
+    int tiles = 0, lds = 0;
+    wgrad_layer(shapes[i], l, &tiles, &lds);
+    one_per_cu = one_per_cu || lds > 80 * 1024;
+  }
   // Workgroups of the launch. The partial sums cost HBM traffic in proportion to the split counts (written here, read by the
   // update), and a workgroup of the wide kernel keeps others of its kind off the CU: half of the chip, three quarters where each
   // has 32 tiles all the same. ms per 8 steps with 128 / 192 / 256: ResNet-18 in four modules 17.3 / 17.0 / 17.4, 64 images of it 4.3 /
   // 4.4 / 4.6; ResNet-20 in one module 3.50 / 3.58 / 3.59. A stride-2 workgroup has four waves where a stride-1 one has twelve, and the
-  // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many. Narrow layers are bound by the latency of their copies: as many
+  // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many, or two rounds where rows are so long that one takes
+  // more than half of a CU's LDS and 384 would be one and a half (128 -> 128 channels from 512 x 512 pixels, two images, 453 -> 270 us). A stride-1 layer that
+  // shares its launch with no other has no launch to save its partial sums for: the chip (3 -> 256 channels at 32 x 32, 62
+  // images, 128 / 256: 30.7 / 19.0 us). Narrow layers are bound by the latency of their copies: as many
   // as share the chip (256 / 384 / 512: ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its
   // normalised form in two 11.9 / 11.7 / 11.5), three a CU up to 16 channels on both sides (512 / 768: 3.05 / 3.03, ResNet-56 15.19 /
   // 15.13, the normalised ResNet-20 9.83 / 9.79; a launch alone 50 / 41 us in ResNet-56), two with wider rows, by their LDS.
   const bool three = shapes[0].Cx <= 16 && shapes[0].ldy <= 16;
   int target_wgs = w0.key > 4 ? (three ? 768 : 512) : total >= 192 * 32 ? 192 : 128;
-  if (w0.key == 2) target_wgs *= 2;
+  if (w0.key == 2) target_wgs = one_per_cu && target_wgs == 192 ? 512 : 2 * target_wgs;
+  if (w0.key == 1 && n == 1) target_wgs = 256;
   const long long per_wg = (total + target_wgs - 1) / target_wgs;  // tiles a workgroup walks
   for (int i = 0; i < n; ++i) {
     const WgradWork w = wgrad_work(dt, shapes[i]);

@@ -257,6 +257,13 @@ int main() {
     wgrad_choose_splits(DT_BF16, &b, 1, q + 1);
     printf("%d %d ", q[0], q[1]);
   }
+  // a layer that has its launch to itself: workgroups for the whole chip, in 64 x 64 blocks; a stride-2 layer of rows so long that one workgroup takes a CU: two rounds
+  int alone[2];
+  WgradParams stem = layer(8, 256, 32, 62, 1), wide = layer(128, 128, 512, 2, 1);
+  wgrad_choose_splits(DT_BF16, &stem, 1, alone);
+  wide.stride = 2; wide.Ho = wide.Wo = 256; wide.P /= 4;
+  wgrad_choose_splits(DT_BF16, &wide, 1, alone + 1);
+  printf("%d %d ", 4 * alone[0], 16 * alone[1]);
   // refused before anything is launched: a layer of another kernel, more splits than tiles, splits that are not equal
   WgradParams uneven = layer(64, 64, 16, 8, 1);
   uneven.R = uneven.S = 5; uneven.pad = 2; uneven.NK = 25 * 64; uneven.nsplit = 3; uneven.pix_per_split = uneven.P / 3;
@@ -282,7 +289,7 @@ def test_split_counts_of_narrow_layers_and_refused_weight_gradients(tmp_path):
                     os.path.join(pkg, "libdds.so"), "-Wl,-rpath," + pkg, "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True)
     out = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=60, check=True).stdout.split()
     splits = [63, 64, 255, 256, 14, 24, 62, 160, 8, 9, 64, 65]
-    assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [-1, -1, -1]
+    assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [248, 512, -1, -1, -1]
 
 
 def test_no_kernel_attribute_is_remembered_per_process():
