@@ -741,6 +741,13 @@ double overlapped_wgrad_flops(const dds_ctx& c, const Module& m) {
   return launches > 0 ? flops / launches : 0.0;
 }
 
+// No two weight gradients of the module share a launch (other kernel sizes than 3x3 and 1x1), and three or more run beside input gradients.
+bool wgrads_unshared(const Module& m) {
+  size_t layers = 0;
+  for (const Node& nd : m.nodes) layers += nd.kind == N_CONV;
+  return layers >= 4 && layers == m.wgroups.size();
+}
+
 int build(dds_ctx& c, const dds_spec* sp, int K, int W, const int* delays) {
   if (!sp || !sp->layers || !sp->bounds) return fail(DDS_EINVAL, "null spec");
   if (K < 1 || K > 64) return fail(DDS_EINVAL, "K=%d out of range [1,64]", K);
@@ -1269,13 +1276,14 @@ int dds_create(const dds_spec* spec, int K, int W, const int* delays, void* aren
   if (const char* q = getenv("GPU_MAX_HW_QUEUES")) { const int v = atoi(q); if (v >= 1 && v <= 32) nq = v; }
   const double wflops = K == 1 ? overlapped_wgrad_flops(*c, c->mods[0]) : 0.0;
   const double pixels = (double)c->N * c->in_h * c->in_w;
-  if (nq >= 2 && (c->dt == DT_F32 ? wflops >= 0.4e9 : wflops >= 1e10 || (wflops >= 1e9 && pixels >= 4e5))) {
+  if (nq >= 2 && (c->dt == DT_F32 ? wflops >= 0.4e9 : wflops >= 1e10 || (wflops >= 1e9 && (pixels >= 4e5 || wgrads_unshared(c->mods[0]))))) {
     // A single module has no other module's kernels beside it: its weight gradients get a stream, if they are long enough, by
     // their work or by the size of their tensors. A launch on the side costs two event calls, 11 to 17 us on the host and 4 us
     // between the kernels. us per step with and without, at a mean of so many GFLOP and so many 1000 input pixels: bf16 ResNet-18 of 0.9,
     // 16 530 / 485, of 7, 131 1053 / 1032, of 14, 262 1547 / 1614; ResNet-20 of 1.0, 262 454 / 435, of 2.0, 524 672 / 694, of 3.0, 795 898 /
     // 946; ResNet-56 of 0.6, 131 890 / 861, of 2.3, 524 1627 / 1699; wide ResNet-34 of 4, 16 2088 / 2098, of 16, 66 3487 / 3618; four layers at
-    // 28 x 28 and 14 x 14 pixels of 1, 201 286 / 270, of 2, 401 380 / 387; fp32 CNN of 0.2 928 / 901, of 0.9 958 / 968, of 14 1876 / 2140.
+    // 28 x 28 and 14 x 14 pixels of 1, 201 286 / 270, of 2, 401 380 / 387; fp32 CNN of 0.2 928 / 901, of 0.9 958 / 968, of 14 1876 / 2140. Weight gradients that share
+    // no launch are many and long: 5x5 layers, three of 2, 14 265 / 304, four of 5, 50 530 / 560, six 590 / 640, but two 1.03 to 1.18 times slower.
     // (With two modules the events cost what the overlap gains: 1.97 -> 2.05 ms per 8 steps of the 28 x 28 net, 13.5 -> 13.7 ms of
     // the normalised ResNet-20.)
     Module& m = c->mods[0];

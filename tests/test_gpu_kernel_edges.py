@@ -416,3 +416,34 @@ def test_launches_of_a_normalised_net_are_counted(c, bn_launches):
         counts.append(tr.dds_launches_last_step())
         tr.close()
     assert counts[1] - counts[0] == bn_launches
+
+
+def test_weight_gradients_that_share_no_launch_run_beside_the_input_gradients(monkeypatch):
+    # one module of 5x5 layers: 315 us a step with a stream of their own, 358 us (as with DDS_SERIAL) without
+    import paper_2509_05679_amd as P
+    ops = []
+    for cin, cout in ((3, 64), (64, 72), (72, 128), (128, 64)):
+        ops += [{"op": "conv", "cin": cin, "cout": cout, "k": 5, "stride": 1, "pad": 2}, {"op": "relu"}]
+    ops += [{"op": "gap"}, {"op": "linear", "cin": 64, "cout": 10}, {"op": "softmax_ce"}]
+    wl = Workload(name="beside", ops=ops, bounds=[0, len(ops)], K=1, W=4, B=8, in_shape=(3, 14, 14), classes=10, precision="bf16", lr=0.05,
+                  momentum=0.0, steps=1)
+    xs, ys = [torch.zeros((8, 3, 14, 14), device="cuda") for _ in range(4)], [torch.zeros(8, dtype=torch.int32, device="cuda") for _ in range(4)]
+
+    def best():
+        tr = P.Trainer(P.Spec.from_workload(wl), 4)
+        tr.dds_set_params(0, make_params(wl, 48)[0])
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(6):
+            t0.record()
+            for _ in range(20):
+                tr.dds_step(xs, ys)
+            t1.record()
+            t1.synchronize()
+            times.append(t0.elapsed_time(t1))
+        tr.close()
+        return min(times)
+
+    beside = best()
+    monkeypatch.setenv("DDS_SERIAL", "1")
+    assert beside < 0.95 * best()
