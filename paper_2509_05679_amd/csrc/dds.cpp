@@ -1027,8 +1027,8 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
       case N_CONV: {
         const ParamLayer& L = m.layers[nd.layer];
         const int ldg = to.Cpad;
-        // The weight gradient reads no weights: one launch serves every data-group, and since no
-        // split mixes two of them, data-group r's gradient is the sum of its own nsplit / W splits.
+        // The weight gradient reads no weights: one launch serves every data-group. With a mixing matrix (and in fp32) no
+        // split mixes two of them, so that data-group r's gradient is the sum of its own nsplit / W splits.
         WgradParams w = wgrad_shape(c, m, nd);
         w.dy = gout;
         w.x = x;

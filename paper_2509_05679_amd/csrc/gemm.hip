@@ -13,7 +13,7 @@
 //
 // fp32 sums keep one order per problem, whichever kernel or tile its size selects: a program's fp32 results change by single
 // ReLU decisions when the last bits of a sum do. That is why here and in linear.hip and misc.hip (update, pooling) some rules
-// name the type; see launch_dma, wgrad_choose_split, linear_kernel, gap_fwd_kernel and update_elems. (The mixing update of
+// name the type; see launch_dma, wgrad_generic_split, linear_kernel, gap_fwd_kernel and update_elems. (The mixing update of
 // misc.hip is not held to it: its sum runs over the row-lanes that the split count selects.)
 #include <cstdlib>
 
@@ -2341,12 +2341,11 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) 
   // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many, or two rounds where rows are so long that one takes
   // more than half of a CU's LDS and 384 would be one and a half (128 -> 128 channels from 512 x 512 pixels, two images, 453 -> 270 us). A stride-1 layer that
   // shares its launch with no other has no launch to save its partial sums for: the chip (3 -> 256 channels at 32 x 32, 62
-  // images, 128 / 256: 30.7 / 19.0 us). Narrow layers are bound by the latency of their copies: as many
-  // as share the chip (256 / 384 / 512: ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its
-  // normalised form in two 11.9 / 11.7 / 11.5), three a CU up to 16 channels on both sides (512 / 768: 3.05 / 3.03, ResNet-56 15.19 /
-  // 15.13, the normalised ResNet-20 9.83 / 9.79; a launch alone 50 / 41 us in ResNet-56), two with wider rows, by their LDS.
-  const bool three = shapes[0].Cx <= 16 && shapes[0].ldy <= 16;
-  int target_wgs = w0.key > 4 ? (three ? 768 : 512) : total >= 192 * 32 ? 192 : 128;
+  // images, 128 / 256: 30.7 / 19.0 us). Narrow layers: two or three share a CU
+  // (256 / 384 / 512: ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its normalised form in two
+  // 11.9 / 11.7 / 11.5; 768 for layers of up to 16 channels, three of whose workgroups fit a CU: ResNet-20 in one 3.02 / 3.01, in one with
+  // normalisation 12.2 / 12.3, ResNet-56 the same).
+  int target_wgs = w0.key > 4 ? 512 : total >= 192 * 32 ? 192 : 128;
   if (w0.key == 2) target_wgs = one_per_cu && target_wgs == 192 ? 512 : 2 * target_wgs;
   if (w0.key == 1 && n == 1) target_wgs = 256;
   const long long per_wg = (total + target_wgs - 1) / target_wgs;  // tiles a workgroup walks

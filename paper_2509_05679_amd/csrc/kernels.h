@@ -78,8 +78,8 @@ struct WgradParams {
   int pix_per_split; // wgrad_gemm_kernel: pixels per split (P / nsplit, splits are equal)
   int nsplit;
   int nrep;          // data-groups: equal runs of consecutive images; nsplit is a multiple of it and no split
-                     // holds pixels of two data-groups (the asynchronous kernel deals each group's 128-pixel
-                     // tiles to its nsplit / nrep splits as evenly as whole tiles allow)
+                     // holds pixels of two data-groups (the asynchronous kernels deal each group's tiles to its
+                     // nsplit / nrep splits as evenly as whole tiles allow). 1: only the sum over all images is asked for
   long long Pl;     // floats between consecutive splits (>= Mout*NK + Mout)
   float alpha;
 };

@@ -32,6 +32,13 @@ inline Divisor make_divisor(int d) {  // d >= 2
   while ((1ll << l) < d) ++l;
   return Divisor{(uint32_t)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
 }
+// The same with 1 among the divisors: floor(n / d) == divide(n, make_divisor1(d))
+inline Divisor make_divisor1(int d) {
+  int l = 0;
+  while ((1ll << l) < d) ++l;
+  return Divisor{(uint32_t)(((1ull << (31 + l)) / (unsigned)d) + 1), l};
+}
+__device__ __forceinline__ uint32_t divide(uint32_t n, Divisor d) { return __umulhi(2 * n, d.mul) >> d.shift; }
 
 }  // namespace
 

@@ -65,12 +65,19 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fill
   const int m0 = blockIdx.x * (64 * GROUPS), row0 = wave * (16 * GROUPS), pix0 = m0 + row0;
 
   // the patch; pixels before the tensor's first or after its last repeat that pixel (no tap inside an image reads them)
-  for (int f = wave; f < fills; f += 4) {
-    const int piece = f * 64 + lane, row = piece >> PLOG;
-    int pix = m0 - p.W - 1 + row;
-    if (p.W > pitch) pix += (row >= pitch ? p.W - pitch : 0) + (row >= 2 * pitch ? p.W - pitch : 0);
-    pix = min(max(pix, 0), p.M - 1);
+  auto copy = [&](int f, int pix) {
+    const int piece = f * 64 + lane;
+    pix = min(max(pix + (piece >> PLOG), 0), p.M - 1);
     dma16((const char*)p.x + ((((size_t)(uint32_t)pix << PLOG) + (piece & ((1 << PLOG) - 1))) << 4), lds0 + f * 1024);
+  };
+  const int jump = p.W - pitch;
+  if (jump == 0) {
+    for (int f = wave; f < fills; f += 4) copy(f, m0 - p.W - 1);
+  } else {
+    for (int f = wave; f < fills; f += 4) {
+      const int row = (f * 64 + lane) >> PLOG;
+      copy(f, m0 - p.W - 1 + (row >= pitch ? jump : 0) + (row >= 2 * pitch ? jump : 0));
+    }
   }
   const uint32_t zeros = fills * 1024;
   if (threadIdx.x < GROUPS * PB) *(uint4*)(smem + zeros + threadIdx.x * 16) = make_uint4(0u, 0u, 0u, 0u);
@@ -240,8 +247,8 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvParams p, int fill
 // a kernel that staged its tiles through registers before), 32 -> 32 at 16 x 16 27.9 -> 18.3 us and the stem with 16 outputs 95 -> 14.4
 // us (64 x 64 blocks of wgrad_dma_body, 3/4 and 31/32 padding before), with 64 outputs and 512 images 50 -> 21.6 us. Tiles of
 // 256 (54 KB limit below) against 512: 19.1 / 22.5 us for the 16-channel layers. (dY numbered by positions too, with zeros at the
-// extra ones, saves the division of a row address, 1 to 2 % of a launch at 32 x 32 and 10 % of 32 channels at 224 x 224, and makes NaN of
-// border taps that an infinite activation does not reach.)
+// extra ones, saves the division of a row address and makes NaN of border taps that an infinite activation does not reach; 16 -> 16 channels
+// at 32 x 32 with their stem 34.4 us so and 32.0 here.)
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
 __device__ __forceinline__ uint2 lds_tr16_b64(uint32_t lds_byte_address) {
@@ -261,7 +268,7 @@ struct SlimLayer {
   float* partial;
   long long Pl;
   Divisor dQ, dH1;       // by Q and by H + 1 (positions)
-  Divisor dW, dH;        // by W and by H (pixels), of sides above one
+  Divisor dW, dH;        // by W and by H (pixels): make_divisor1
   int first;             // first workgroup of this layer
   int q, rep_tiles;      // splits and tiles per data-group
   int H, W, Q, imgs_rep; // Q: position pitch of an image row, W + 1
@@ -325,7 +332,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_slim_kernel(SlimGroup grp) {
   // pixel of the data-group -> its position, less the Q of the first image's extra row (pixels past the last one count on into
   // further images, whose positions hold zeros)
   auto position = [&](uint32_t n) {
-    const uint32_t line = W > 1 ? __umulhi(n, dW.mul) >> dW.shift : n, im = p.H > 1 ? __umulhi(line, dH.mul) >> dH.shift : line;
+    const uint32_t line = divide(n, dW), im = divide(line, dH);
     return n + line + __umul24(im, Q);
   };
   auto fill_tile = [&](int t, int slot) {
@@ -482,8 +489,8 @@ bool slim_layer(const WgradParams& p, int W, SlimLayer& l) {
   l.rep_tiles = (int)((pixels + l.tile - 1) / l.tile);
   l.dQ = make_divisor(l.Q);
   l.dH1 = make_divisor(p.H + 1);
-  l.dW = make_divisor(p.W > 1 ? p.W : 2);
-  l.dH = make_divisor(p.H > 1 ? p.H : 2);
+  l.dW = make_divisor1(p.W);
+  l.dH = make_divisor1(p.H);
   l.Mout = p.Mout;
   l.alpha = p.alpha;
   return true;

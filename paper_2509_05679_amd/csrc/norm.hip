@@ -466,8 +466,8 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(BnParams p) {
 // Row splits. Sums: about 32 KiB of the tensor each, at most 512 of a data-group. For rows of at most kBnFoldLd channels the
 // streaming kernel can fold the splits itself: 2 us of it (16 channels, 776 images of 32 x 32: 9.8 -> 11.9 us) for a launch of 4 us
 // and the gap before it. A lane folds eight splits, so there are fewer of them then (kBnFoldSums / ld), and streaming workgroups have at
-// least twice the bytes that they fold, as long as there is one per CU. Not where that would halve the workgroups that sum
-// and leave CUs without one (64 channels, 128 images of 32 x 32 each: 512 splits -> 32). Steps of normalised ResNet-20, with the
+// least twice the bytes that they fold, as long as there is one per CU. Not where that would leave fewer than half of the workgroups that
+// sum and CUs without one (64 channels, 128 images of 32 x 32 each: 512 splits -> 32). Steps of normalised ResNet-20, with the
 // launch / here: one data-group of 194 in one module 0.962 / 0.889 ms, in two 0.690 / 0.607, four in one 1.660 / 1.538, in
 // two 1.292 / 1.231.
 BnPlan bn_plan(int W, long long rows_per_rep, int ld, int es) {

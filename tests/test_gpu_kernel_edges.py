@@ -257,7 +257,7 @@ def test_conv3x3_longest_rows_of_each_tile(widths, h, w, W, B):
 
 @pytest.mark.parametrize("w", [764, 766])
 def test_stride2_weight_gradients_longest_rows(w):
-    # 382 and 383 output columns: wgrad_flat_kernel and wgrad_gemm_kernel
+    # 382 and 383 output columns: wgrad_flat_body and wgrad_gemm_kernel
     _compare(_stride2_net(16, 16, 3, 2, w, 1, 2), seed=35, T=2)
 
 
