@@ -2344,8 +2344,11 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) 
   // images, 128 / 256: 30.7 / 19.0 us). Narrow layers: two or three share a CU
   // (256 / 384 / 512: ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its normalised form in two
   // 11.9 / 11.7 / 11.5; 768 for layers of up to 16 channels, three of whose workgroups fit a CU: ResNet-20 in one 3.02 / 3.01, in one with
-  // normalisation 12.2 / 12.3, ResNet-56 the same).
-  int target_wgs = w0.key > 4 ? 512 : total >= 192 * 32 ? 192 : 128;
+  // normalisation 12.2 / 12.3, ResNet-56 the same), less an eighth: tiles of images and batches of powers of two make every one of 512
+  // workgroups, and the update of so many splits and other modules' launches lose more than this one gains (512 / 448 / 384: ResNet-20
+  // in two modules, four data-groups of 64 2.67 / 2.61 / 2.62, of 128 4.00 / 3.89 / 3.93, of 194 5.18 / 5.22 / 5.28, in one, 256 images, 3.36 /
+  // 3.32 / 3.33; ResNet-56, four of 64, 5.39 / 5.31 / 5.28).
+  int target_wgs = w0.key > 4 ? 448 : total >= 192 * 32 ? 192 : 128;
   if (w0.key == 2) target_wgs = one_per_cu && target_wgs == 192 ? 512 : 2 * target_wgs;
   if (w0.key == 1 && n == 1) target_wgs = 256;
   const long long per_wg = (total + target_wgs - 1) / target_wgs;  // tiles a workgroup walks

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("W,B", [(1, 63), (2, 32), (3, 85), (2, 128)])
 def test_update_ranges_by_split_count(W, B):
-    # 16-channel layers at 16 x 16 pixels have one split per image: 63 and 64 of them are summed by tiles of 256 weights, 255 and 256
-    # by tiles of 64 (the lines themselves: test_update_tiles_by_split_count)
+    # 16-channel layers at 16 x 16 pixels have one split per image: 63 and 64 of them are summed by tiles of 256 weights; of 255 and 256
+    # images one per two, summed by tiles of 64 (the lines themselves: test_update_tiles_by_split_count)
     _compare(tiny_resnet(K=1, W=W, B=B, hw=16, c=16, precision="bf16"), seed=20, T=2)
 
 

@@ -242,7 +242,7 @@ static WgradParams layer(int cin, int cout, int hw, int images, int nrep) {
   return w;
 }
 int main() {
-  // splits of the two 16-channel layers of a net of 16 x 16 images: the mean of 63, 64, 255 and 256, a mixing step of 7, 8, 31 and 32 a data-group
+  // splits of the two 16-channel layers of a net of 16 x 16 images: the mean of 63, 64, 255 and 256 (two images a split: 448 workgroups), a mixing step of 7, 8, 31 and 32 a data-group
   const int images[8][2] = {{63, 1}, {64, 1}, {255, 1}, {256, 1}, {14, 2}, {24, 3}, {62, 2}, {160, 5}};
   for (auto& c : images) {
     const WgradParams two[2] = {layer(16, 16, 16, c[0], c[1]), layer(16, 16, 16, c[0], c[1])};
@@ -288,7 +288,7 @@ def test_split_counts_of_narrow_layers_and_refused_weight_gradients(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(pkg, "csrc"), str(src), "-o", str(exe),
                     os.path.join(pkg, "libdds.so"), "-Wl,-rpath," + pkg, "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True)
     out = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=60, check=True).stdout.split()
-    splits = [63, 64, 255, 256, 14, 24, 62, 160, 8, 9, 64, 65]
+    splits = [63, 64, 128, 128, 14, 24, 62, 160, 8, 9, 64, 65]
     assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [248, 512, -1, -1, -1]
 
 
