@@ -603,7 +603,7 @@ void plan_wgrads(dds_ctx& c, Module& m) {
       shapes.back().zeros = &c;  // non-null: only the shape matters here
     }
     std::vector<int> splits(shapes.size());
-    wgrad_choose_splits(c.dt, shapes.data(), (int)shapes.size(), splits.data());
+    wgrad_choose_splits(c.dt, shapes.data(), (int)shapes.size(), c.K == 1, splits.data());
     for (size_t i = 0; i < o.nodes.size(); ++i) {
       Node& nd = m.nodes[o.nodes[i]];
       m.layers[nd.layer].nsplit = splits[i];

@@ -2316,7 +2316,7 @@ static int wgrad_generic_split(int dt, const WgradParams& shape) {
   return W * q;
 }
 
-void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) {
+void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, bool one_module, int* nsplit) {
   const WgradWork w0 = wgrad_work(dt, shapes[0]);
   if (w0.key == 0) {
     for (int i = 0; i < n; ++i) nsplit[i] = wgrad_generic_split(dt, shapes[i]);
@@ -2341,7 +2341,8 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) 
   // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many, or two rounds where rows are so long that one takes
   // more than half of a CU's LDS and 384 would be one and a half (128 -> 128 channels from 512 x 512 pixels, two images, 453 -> 270 us). A stride-1 layer that
   // shares its launch with no other has no launch to save its partial sums for: the chip (3 -> 256 channels at 32 x 32, 62
-  // images, 128 / 256: 30.7 / 19.0 us). Narrow layers: two or three share a CU
+  // images, 128 / 256: 30.7 / 19.0 us), but not where other modules want it too (a net of 32 and 64 channels in two modules, us per 8
+  // steps, 128 / 256: 400 images of 32 x 32 2025 / 2099, 256 of them 1603 / 1676, 300 of 28 x 28 1571 / 1560). Narrow layers: two or three share a CU
   // (256 / 384 / 512: ResNet-56 in eight modules 18.6 / 18.3 / 18.2, ResNet-20 in one 3.56 / 3.50 / 3.48, its normalised form in two
   // 11.9 / 11.7 / 11.5; 768 for layers of up to 16 channels, three of whose workgroups fit a CU: ResNet-20 in one 3.02 / 3.01, in one with
   // normalisation 12.2 / 12.3, ResNet-56 the same), less an eighth: tiles of images and batches of powers of two make every one of 512
@@ -2350,7 +2351,7 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit) 
   // 3.32 / 3.33; ResNet-56, four of 64, 5.39 / 5.31 / 5.28).
   int target_wgs = w0.key > 4 ? 448 : total >= 192 * 32 ? 192 : 128;
   if (w0.key == 2) target_wgs = one_per_cu && target_wgs == 192 ? 512 : 2 * target_wgs;
-  if (w0.key == 1 && n == 1) target_wgs = 256;
+  if (w0.key == 1 && n == 1 && one_module) target_wgs = 256;
   const long long per_wg = (total + target_wgs - 1) / target_wgs;  // tiles a workgroup walks
   for (int i = 0; i < n; ++i) {
     const WgradWork w = wgrad_work(dt, shapes[i]);

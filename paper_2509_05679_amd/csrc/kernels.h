@@ -164,8 +164,8 @@ constexpr int kWgradGroupMax = 16;
 int wgrad_slim_tiles(const WgradParams& shape, int nrep, int* variant);
 bool launch_wgrad_slim(const WgradParams* p, int n, hipStream_t s);
 // Chooses the split counts of the pixel reductions of layers that share a launch (n > 1: one key): multiples of nrep, so that no
-// split mixes two data-groups.
-void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, int* nsplit);
+// split mixes two data-groups. one_module: no other module's launches share the chip.
+void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, bool one_module, int* nsplit);
 
 void launch_ingest(int dt, const IngestParams& p, hipStream_t s);
 void launch_maxpool_fwd(int dt, const void* x, void* y, int N, int H, int W, int C, hipStream_t s);

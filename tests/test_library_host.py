@@ -247,23 +247,24 @@ int main() {
   for (auto& c : images) {
     const WgradParams two[2] = {layer(16, 16, 16, c[0], c[1]), layer(16, 16, 16, c[0], c[1])};
     int q[2];
-    wgrad_choose_splits(DT_BF16, two, 2, q);
+    wgrad_choose_splits(DT_BF16, two, 2, true, q);
     printf("%d %d ", q[0], q[1]);
   }
   for (int n : {8, 9, 64, 65}) {  // ... and of one layer of 16 or 32 input channels
     int q[2];
     const WgradParams a = layer(16, 16, 16, n, 1), b = layer(32, 32, 16, n, 1);
-    wgrad_choose_splits(DT_BF16, &a, 1, q);
-    wgrad_choose_splits(DT_BF16, &b, 1, q + 1);
+    wgrad_choose_splits(DT_BF16, &a, 1, true, q);
+    wgrad_choose_splits(DT_BF16, &b, 1, true, q + 1);
     printf("%d %d ", q[0], q[1]);
   }
-  // a layer that has its launch to itself: workgroups for the whole chip, in 64 x 64 blocks; a stride-2 layer of rows so long that one workgroup takes a CU: two rounds
-  int alone[2];
+  // a layer that has its launch to itself: workgroups for the whole chip, in 64 x 64 blocks, or for half of it beside other modules; a stride-2 layer of rows so long that one workgroup takes a CU: two rounds
+  int alone[3];
   WgradParams stem = layer(8, 256, 32, 62, 1), wide = layer(128, 128, 512, 2, 1);
-  wgrad_choose_splits(DT_BF16, &stem, 1, alone);
+  wgrad_choose_splits(DT_BF16, &stem, 1, true, alone);
+  wgrad_choose_splits(DT_BF16, &stem, 1, false, alone + 2);
   wide.stride = 2; wide.Ho = wide.Wo = 256; wide.P /= 4;
-  wgrad_choose_splits(DT_BF16, &wide, 1, alone + 1);
-  printf("%d %d ", 4 * alone[0], 16 * alone[1]);
+  wgrad_choose_splits(DT_BF16, &wide, 1, true, alone + 1);
+  printf("%d %d %d ", 4 * alone[0], 4 * alone[2], 16 * alone[1]);
   // refused before anything is launched: a layer of another kernel, more splits than tiles, splits that are not equal
   WgradParams uneven = layer(64, 64, 16, 8, 1);
   uneven.R = uneven.S = 5; uneven.pad = 2; uneven.NK = 25 * 64; uneven.nsplit = 3; uneven.pix_per_split = uneven.P / 3;
@@ -289,7 +290,7 @@ def test_split_counts_of_narrow_layers_and_refused_weight_gradients(tmp_path):
                     os.path.join(pkg, "libdds.so"), "-Wl,-rpath," + pkg, "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64"], check=True)
     out = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=60, check=True).stdout.split()
     splits = [63, 64, 128, 128, 14, 24, 62, 160, 8, 9, 64, 65]
-    assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [248, 512, -1, -1, -1]
+    assert [int(v) for v in out] == [v for q in splits for v in (q, q)] + [248, 124, 512, -1, -1, -1]
 
 
 def test_no_kernel_attribute_is_remembered_per_process():
