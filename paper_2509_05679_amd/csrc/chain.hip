@@ -1,0 +1,474 @@
+// Runs of consecutive 3x3 stride-1 layers of equal width (16, 32 or 64 channels), bf16, in one launch: forward or input gradient.
+//
+// An image of these layers fits in LDS (32 KB at 32 x 32 x 16, 16 x 16 x 32 takes 16 KB, 8 x 8 x 64 takes 8 KB), and nothing but the
+// weights ties one image to another: a workgroup reads whole images once, takes them through every layer of the run and only
+// writes each layer's output (what the other pass and the weight gradients read). A launch per layer costs 5 to 8 us whatever
+// its work, reads every tensor again and leaves its first copies and its last stores without anything beside them.
+#include "device_once.h"
+#include "kernels.h"
+#include "lds_copy.h"
+
+namespace dds {
+namespace {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+
+__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  f32x2_t v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+
+__device__ __forceinline__ f32x4_t mfma16(const uint4& a, const uint4& b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 lds_read16(uint32_t at) {
+  const u32x4_t v = *(const u32x4_t DDS_LDS_AS*)(size_t)at;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint2 lds_read8(uint32_t at) {
+  const u32x2_t v = *(const u32x2_t DDS_LDS_AS*)(size_t)at;
+  return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ void lds_write16(uint32_t at, uint32_t a, uint32_t b, uint32_t c, uint32_t d) { *(u32x4_t DDS_LDS_AS*)(size_t)at = (u32x4_t){a, b, c, d}; }
+__device__ __forceinline__ void lds_write8(uint32_t at, uint32_t a, uint32_t b) { *(u32x2_t DDS_LDS_AS*)(size_t)at = (u32x2_t){a, b}; }
+
+// 1 in each half of a packed bf16 pair >= 0 that is not zero: min(., 1) (which the compiler would turn into comparisons and selects)
+__device__ __forceinline__ uint32_t nonzero2(uint32_t pair) {
+  uint32_t r;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(pair), "s"(0x00010001u));
+  return r;
+}
+// halves of a packed pair times 0 or 1 each
+__device__ __forceinline__ uint32_t keep2(uint32_t pair, uint32_t ones) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2_t, pair) * __builtin_bit_cast(u16x2_t, ones));
+}
+
+constexpr int kWaves = 8;
+constexpr int sign_slots(int C) { return C == 16 ? 3 : 2; }
+
+struct ChainGeom {
+  int imgs;            // images of a workgroup
+  uint32_t plane;      // bytes of LDS of 16 channels of one layer's images, by positions
+  uint32_t buf_bytes;  // of all channels, whole 1 KiB fills
+  uint32_t sign_bytes; // input gradient: of the images' signs, whole fills
+  Divisor dP;          // by the plane's 16-byte pieces
+  Divisor dQ, dH1;     // by W + 1 and H + 1 (positions)
+  Divisor dW, dH;      // by W and H (pixels)
+};
+
+// How a workgroup of eight waves is laid out. A wave owns runs of 16 pixels (columns of v_mfma_f32_16x16x32_bf16) and NBW of the C / 16
+// blocks of output channels (its rows); a step multiplies 32 input channels, two taps' worth of them at 16 channels.
+template <int C>
+struct Shape {
+  static constexpr int PB = 2 * C, CPP = PB / 16, NBLK = C / 16;  // CPP: 16-byte pieces of a pixel
+  static constexpr int WN = C == 64 ? 2 : 1, WM = kWaves / WN;    // waves over the output channels and over the pixels
+  static constexpr int NBW = NBLK / WN;
+  static constexpr int SPP = C / 32 * 3;                          // C > 16: steps of a tap row, whose weights are refilled together
+};
+
+// Images lie in LDS by positions: a row pitch of Q = W + 1 whose first column, and one row above every image and below the last, is
+// padding and stays zero, so that the nine taps are constant distances from a pixel's position and no tap needs a test. Each 16
+// channels have a plane of their own (32 bytes a position: of the sixteen lanes that one cycle of a 16-byte read serves, quads of even or odd
+// bit parity, no two meet in a bank, wherever the run starts, and a tap's column is a constant in the instruction). Two
+// buffers, one of them the layer's input, the other its output; the output buffer still holds the input of the layer before, which is
+// what a residual layer adds: each lane reads the four or eight channels that it is about to overwrite. Outputs leave for memory at
+// the start of the next layer, 16 bytes a lane as they lie, and their signs with them.
+// Weights: at 16 channels in registers (20 of them). Else in LDS as operand fragments (1 KB each, read as they lie); a tap row's are replaced by
+// the next layer's as soon as all waves have multiplied it, so they arrive under the rest of the layer.
+// The bias is what the accumulators start from. (Input gradients have neither bias nor ReLU.)
+// Bound by LDS reads, matrix unit and the epilogue's vector instructions about equally, which a single workgroup on a CU walks one after the other;
+// for many images by the stores. us per layer of a run of 14 against a launch each (and 7 to 9 us a launch on top): 16 channels at 32 x 32, 194
+// images 2.6 against 7.2 to 8, 1024 images 7.4 forward and 9.0 backward (33 MB written, 4.5 TB/s) against 22; 32 at 16 x 16 1.9 against 5.6 and 5.5 against 14;
+// 64 at 8 x 8 2.8 and 2.4 against 5.8, 5.1 against 12. (With operands read where they are used, each product waited for its LDS read: 3.9 us at 16
+// channels and 194 images; with one set of weights in registers and signs read by the epilogue, backward 10.2 us at 1024.)
+template <int C, int RUNS, bool DGRAD>
+__global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 : 2) void conv_chain_kernel(ChainParams p, ChainGeom g) {
+  typedef Shape<C> S;
+  constexpr int PB = S::PB, CPP = S::CPP, NBLK = S::NBLK, NBW = S::NBW, WM = S::WM;
+  extern __shared__ __align__(16) char smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / S::WN, wn = wave % S::WN;
+  const int HW = p.H * p.W, Q = p.W + 1;
+  const int img0 = blockIdx.x * g.imgs, imgs = min(g.imgs, p.Nimg - img0);
+  const int pixels = imgs * HW;
+  const size_t pix0 = (size_t)img0 * HW;  // the workgroup's images are consecutive pixels of every tensor
+  const int wrep = p.nrep > 1 ? img0 / (p.Nimg / p.nrep) : 0;  // the launcher made sure that they share a data-group
+  const size_t wrep_off = (size_t)wrep * p.w_rep;
+  const int plane = (int)g.plane, row = Q * 32;  // row: distance of two image rows
+  const uint32_t wbuf = 2 * g.buf_bytes;
+
+  // Row r of a block of weights holds output channel chan_of(block, r), so that a lane ends with 4 (C == 16) or 8 consecutive ones
+  auto chan_of = [](int b, int r) { return C == 16 ? r : 32 * (b >> 1) + 8 * (r >> 2) + 4 * (b & 1) + (r & 3); };
+  // tap whose operand is the pixel a rows below and b columns right of the neighbourhood's top left corner
+  auto tap_of = [](int a, int b) { return DGRAD ? 8 - 3 * a - b : 3 * a + b; };
+  // C == 16: steps 0-2 hold (0, step) and (1, step), step 3 (2, 0) and (2, 1), step 4 (2, 2); lane (j, q) has 16 bytes of row j at position q / 2
+  uint4 wreg[C == 16 ? 5 : 1], next_wreg[C == 16 ? 5 : 1];
+  auto load_weights = [&](const void* w, uint4 (&a)[C == 16 ? 5 : 1]) {
+    if (C == 16) {
+#pragma unroll
+      for (int t = 0; t < 5; ++t) {
+        const int tap = t < 3 ? tap_of(q >> 1, t) : tap_of(2, t == 3 ? q >> 1 : 2);
+        a[t] = *(const uint4*)((const char*)w + wrep_off + (uint32_t)((j * 9 + tap) * PB + (q & 1) * 16));
+        if (t == 4 && q >= 2) a[t] = make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+  };
+  constexpr int PER = S::SPP * NBLK;  // fragments of a tap row
+  constexpr int FP = (PER + kWaves - 1) / kWaves;  // copies of a tap row by each wave (past the end: the last fragment again)
+  auto fill_weights = [&](const void* w, int a) {
+#pragma unroll
+    for (int i = 0; i < FP; ++i) {
+      const int f = min(wave + kWaves * i, PER - 1);
+      const int step = f / NBLK, n = chan_of(f % NBLK, j);
+      const int b = C == 32 ? step : step >> 1, k = C == 32 ? q * 16 : (step & 1) * 64 + q * 16;
+      dma16((const char*)w + wrep_off + (uint32_t)((n * 9 + tap_of(a, b)) * PB + k), lds0 + wbuf + (a * PER + f) * 1024);
+    }
+  };
+  // input images by positions; the padding comes from the block of zeros
+  auto fill_images = [&](const void* src, uint32_t dst) {
+    const char* base = (const char*)src + pix0 * PB;
+    for (int f = wave; f < (int)(g.buf_bytes >> 10); f += kWaves) {
+      const uint32_t piece = f * 64 + lane, pl = divide(piece, g.dP), in_plane = piece - pl * (uint32_t)(plane >> 4);
+      const uint32_t u = in_plane >> 1, line = divide(u, g.dQ), im = divide(line, g.dH1);
+      const int w = (int)(u - line * Q) - 1, h = (int)(line - im * (p.H + 1)) - 1;
+      const bool in = w >= 0 && h >= 0 && (int)im < imgs && pl < NBLK;
+      const char* at = base + (uint32_t)((im * HW + h * p.W + w) * PB + pl * 32 + (in_plane & 1) * 16);
+      dma16(in ? at : (const char*)p.zeros, lds0 + dst + f * 1024);
+    }
+  };
+  ChainLayer L = p.layer[0];
+  fill_images(p.x, 0);
+  load_weights(L.w, wreg);
+  if (C != 16) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) fill_weights(L.w, a);
+  }
+  if (p.res) {
+    fill_images(p.res, g.buf_bytes);
+  } else {
+    for (uint32_t a = tid * 16; a < g.buf_bytes; a += 1024 * kWaves) lds_write16(lds0 + g.buf_bytes + a, 0u, 0u, 0u, 0u);
+  }
+
+  // pixel of the workgroup -> its position's LDS address in the first plane of the first buffer
+  auto position = [&](uint32_t n) {
+    const uint32_t line = divide(n, g.dW), im = divide(line, g.dH);
+    return (int)(lds0 + ((line + im + 1) * Q + (n - line * p.W) + 1) * 32);  // im images above, one padding row each
+  };
+  // Sums of these with a layer's offsets are formed where they are used: the compiler would keep every one of them in a register.
+  auto opaque = [](int v) { asm volatile("" : "+v"(v)); return v; };
+  // LDS address, in the layer's input buffer, of this lane's part of the operand at the top left corner of its pixel's neighbourhood, for every
+  // run (runs past the last pixel read it again); own: distance to the lane's output channels of that pixel
+  int at[RUNS];
+#pragma unroll
+  for (int u = 0; u < RUNS; ++u)
+    at[u] = position((uint32_t)min((wm + WM * u) * 16 + j, pixels - 1)) - row - 32 + (q & 1) * 16 + (q >> 1) * (C == 16 ? row : plane);
+  const int own = row + 32 + (C == 16 ? q * 8 - (q & 1) * 16 - (q >> 1) * row : 2 * wn * plane);
+  // the 16-byte pieces of an output that this thread stores (past the end: the last one again)
+  constexpr int NS = (RUNS * WM * 16 * CPP + 64 * kWaves - 1) / (64 * kWaves);
+  int piece[NS], piece_at[NS];
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    piece[k] = min(tid + 64 * kWaves * k, pixels * CPP - 1);
+    const int c = piece[k] % CPP;
+    piece_at[k] = position((uint32_t)piece[k] / CPP) + (c & 1) * 16 + (c >> 1) * plane;
+  }
+  auto store_out = [&](int buf, char* y, char* bits) {
+    uint32_t s[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      const uint4 v = lds_read16(opaque(piece_at[k]) + buf);
+      *(uint4*)(y + ((uint32_t)opaque(piece[k]) << 4)) = v;
+      if (!DGRAD) s[k] = nonzero2(v.x) | nonzero2(v.y) << 2 | nonzero2(v.z) << 4 | nonzero2(v.w) << 6;  // behind a ReLU: nothing is negative
+    }
+    if (!DGRAD && bits) {  // pair e's low half belongs to bit 2 e, its high half (bit 16) to bit 2 e + 1
+#pragma unroll
+      for (int k = 0; k < NS; ++k) *(uint8_t*)(bits + (uint32_t)opaque(piece[k])) = (uint8_t)(s[k] | s[k] >> 15);
+    }
+  };
+  // What else a layer reads from memory is asked for a layer ahead: its bias (forward), or the signs of its outputs (input gradient), bytes
+  // as they lie, copied to slots behind the weights (16 channels, whose layers are the shortest: two layers ahead).
+  constexpr int SG = DGRAD ? 1 : 0;
+  const size_t sign0 = pix0 * (C / 8);  // first byte of this workgroup's images in a sign plane, copied from the 16-byte line that holds it
+  const uint32_t signs = wbuf + (C == 16 ? 0 : 3 * PER * 1024);
+  auto load_bias = [&](const ChainLayer& l, f32x4_t (&b)[NBW]) {
+    const float* at = l.bias ? l.bias + (size_t)wrep * p.bias_rep : (const float*)p.zeros;
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) b[i] = *(const f32x4_t*)(at + chan_of(wn * NBW + i, 4 * q));
+  };
+  auto fill_signs = [&](const ChainLayer& l, int slot) {  // one copy by each wave (past the end: the last one again)
+    const char* from = l.maskbits ? (const char*)l.maskbits : (const char*)p.zeros;
+    const size_t last = l.maskbits ? ((size_t)p.Nimg * HW * (C / 8) - 1) & ~(size_t)15 : 0;  // (blocks of the arena are whole lines)
+    const int f = min(wave, (int)(g.sign_bytes >> 10) - 1);
+    const size_t off = (sign0 & ~(size_t)15) + (size_t)(f * 64 + lane) * 16;
+    dma16(from + (off < last ? off : last), lds0 + signs + slot * g.sign_bytes + f * 1024);
+  };
+  constexpr int SLOTS = sign_slots(C);
+  const uint32_t sign_at = lds0 + signs + (uint32_t)(sign0 & 15) + (C == 16 ? 0 : 4 * wn + q);
+  f32x4_t start[NBW] = {}, next_start[NBW] = {};
+  if (!DGRAD) load_bias(L, start);
+  if (DGRAD) fill_signs(L, 0);
+  if (DGRAD && C == 16 && p.n > 1) fill_signs(p.layer[1], 1);
+  wait_vm<0>();
+  wg_barrier();
+
+  // A wave's loads, copies and stores retire in the order of their issue; copies are waited for by the number of younger operations, so
+  // that neither the stores nor the copies of later pieces are.
+  char *prev_y = nullptr, *prev_bits = nullptr;
+  for (int l = 0; l < p.n; ++l) {
+    const int src = l & 1 ? (int)g.buf_bytes : 0, dst = (int)g.buf_bytes - src;
+    const bool more = l + 1 < p.n;
+    const ChainLayer next = p.layer[more ? l + 1 : l];
+    if (!DGRAD) load_bias(next, next_start);  // (the last layer: its own again)
+    load_weights(next.w, next_wreg);
+    if (l > 0) store_out(src, prev_y, prev_bits);
+    if (DGRAD && C == 16 && l + 2 < p.n) fill_signs(p.layer[l + 2], (l + 2) % SLOTS);
+
+    // Operands of one item (a step and G of the runs) are requested while the item before is multiplied; left to itself the compiler
+    // reads each one just ahead of its product and waits for it.
+    f32x4_t acc[RUNS][NBW];
+    constexpr int G = RUNS == 1 ? 1 : RUNS > 4 && C == 16 ? 2 : RUNS < 4 ? RUNS : 4, NG = (RUNS + G - 1) / G;
+    uint4 x[2][G];
+    if (C == 16) {
+      const int last = 2 * row + (q >> 1) * (32 - row);  // steps 3 and 4: the neighbourhood's last row
+      auto request = [&](int i, uint4 (&v)[G]) {
+        const int t = i / NG;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          const int u = i % NG * G + k;
+          if (u >= RUNS) continue;
+          v[k] = lds_read16(t < 3 ? at[u] + 32 * t : t == 3 ? at[u] + last : q >= 2 ? (int)lds0 : at[u] + last + 64);  // (no tap: position 0, which is padding)
+        }
+      };
+      request(0, x[0]);
+#pragma unroll
+      for (int i = 0; i < 5 * NG; ++i) {
+        if (i + 1 < 5 * NG) request(i + 1, x[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          const int u = i % NG * G + k;
+          if (u < RUNS) acc[u][0] = mfma16(wreg[i / NG], x[i & 1][k], i < NG ? start[0] : acc[u][0]);
+        }
+      }
+    } else {
+      const uint32_t wfrag = lds0 + wbuf + wn * NBW * 1024 + lane * 16;
+      constexpr int KS = C == 16 ? 1 : C / 32, ITEMS = 3 * KS * NG;  // of a tap row: columns b, within them k-steps, within them groups of runs
+      uint4 w[2][NBW];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        auto request = [&](int i, uint4 (&v)[G]) {
+          const int st = i / NG, b = st / KS, ks = st % KS;
+          if (i % NG == 0)
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) w[st & 1][n] = lds_read16(wfrag + (a * PER + st * NBLK + n) * 1024);
+#pragma unroll
+          for (int k = 0; k < G; ++k) {
+            const int u = i % NG * G + k;
+            if (u < RUNS) v[k] = lds_read16(at[u] + ks * 2 * plane + 32 * b);
+          }
+        };
+        request(0, x[0]);
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+          if (i + 1 < ITEMS) request(i + 1, x[(i + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < G; ++k) {
+            const int u = i % NG * G + k;
+            if (u >= RUNS) continue;
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) acc[u][n] = mfma16(w[i / NG & 1][n], x[i & 1][k], a == 0 && i < NG ? start[n] : acc[u][n]);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < RUNS; ++u) at[u] = opaque(at[u] + (a < 2 ? row : -2 * row));
+        // This row's weights have been read by everyone, and the next row's, copied during the layer before, are there (behind the last row:
+        // this layer's signs). Younger than they: the copies behind them, this layer's stores, the next layer's weights so far.
+        constexpr int OPS = NS, OPSB = DGRAD ? NS : 2 * NS;  // without and with the signs of the layer before (the bias is not counted on)
+        const bool with_bits = !DGRAD && prev_bits;
+        if (a == 0) {
+          if (with_bits) wait_vm<FP + SG + OPSB>();
+          else wait_vm<FP + SG + OPS>();
+        } else if (a == 1) {
+          if (!more) wait_vm<SG + OPS>();
+          else if (with_bits) wait_vm<SG + OPSB + FP>();
+          else wait_vm<SG + OPS + FP>();
+        } else if (DGRAD) {
+          if (more) wait_vm<OPS + 2 * FP>();
+          else wait_vm<OPS>();
+        }
+        wg_barrier();
+        if (more) fill_weights(next.w, a);
+        if (DGRAD && a == 2 && more) fill_signs(next, (l + 1) & 1);
+      }
+    }
+
+    // epilogue, a few runs at a time: what they add, arithmetic, stores
+    const int to_own = own + dst - src, to_next = dst - src;
+    constexpr int NV = 4 * NBW, GRP = C == 16 ? 4 : 2;
+    const float lower = !DGRAD && L.relu ? 0.f : -__builtin_inff();
+    const uint32_t all = DGRAD && !L.maskbits ? 0xffffu : 0u;
+#pragma unroll
+    for (int u0 = 0; u0 < RUNS; u0 += GRP) {
+      float v[GRP][NV];
+      if (L.add) {
+        uint32_t r[GRP][NV / 2];
+#pragma unroll
+        for (int i = 0; i < GRP && u0 + i < RUNS; ++i) {
+          const uint32_t mine = at[u0 + i] + to_own;
+          if (C == 16) { const uint2 t = lds_read8(mine); r[i][0] = t.x; r[i][1] = t.y; }
+          else { const uint4 t = lds_read16(mine); r[i][0] = t.x; r[i][1] = t.y; r[i][NV / 2 - 2] = t.z; r[i][NV / 2 - 1] = t.w; }
+        }
+#pragma unroll
+        for (int i = 0; i < GRP && u0 + i < RUNS; ++i)
+#pragma unroll
+          for (int e = 0; e < NV; ++e)
+            v[i][e] = fmaf(L.alpha, acc[u0 + i][e >> 2][e & 3], __uint_as_float(e & 1 ? r[i][e >> 1] & 0xffff0000u : r[i][e >> 1] << 16));
+      } else {
+#pragma unroll
+        for (int i = 0; i < GRP && u0 + i < RUNS; ++i)
+#pragma unroll
+          for (int e = 0; e < NV; ++e) v[i][e] = L.alpha * acc[u0 + i][e >> 2][e & 3];
+      }
+      uint32_t keep[GRP];
+      if (DGRAD) {
+        const int n0 = opaque(wm * 16 + j);
+#pragma unroll
+        for (int i = 0; i < GRP && u0 + i < RUNS; ++i) {
+          const uint32_t from = sign_at + l % SLOTS * g.sign_bytes + min(n0 + WM * 16 * (u0 + i), pixels - 1) * (C / 8);
+          if (C == 16) keep[i] = *(const uint16_t DDS_LDS_AS*)(size_t)from;
+          else keep[i] = *(const uint8_t DDS_LDS_AS*)(size_t)from;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < GRP && u0 + i < RUNS; ++i) {
+        const int u = u0 + i;
+        if (!DGRAD)
+#pragma unroll
+          for (int e = 0; e < NV; ++e) v[i][e] = __builtin_amdgcn_fmed3f(v[i][e], lower, __builtin_inff());  // one instruction; NaN -> lower
+        uint32_t o[NV / 2];
+#pragma unroll
+        for (int e = 0; e < NV / 2; ++e) o[e] = pack_bf16_rne(v[i][2 * e], v[i][2 * e + 1]);
+        if (DGRAD) {  // bits 2 e and 2 e + 1 of the signs -> 0 / 1 in either half of a pair
+          const uint32_t k = (C == 16 ? keep[i] >> (4 * q) : keep[i]) | all, k2 = k | k << 15;
+#pragma unroll
+          for (int e = 0; e < NV / 2; ++e) o[e] = keep2(o[e], (k2 >> (2 * e)) & 0x00010001u);
+        }
+        const uint32_t mine = at[u] + to_own;
+        const int n = (wm + WM * u) * 16;
+        if (n + 16 <= pixels || n + j < pixels) {
+          if (C == 16) lds_write8(mine, o[0], o[1]);
+          else lds_write16(mine, o[0], o[1], o[NV / 2 - 2], o[NV / 2 - 1]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u) at[u] = opaque(at[u] + to_next);
+    prev_y = (char*)L.y + pix0 * PB;
+    prev_bits = L.bits_out ? (char*)L.bits_out + pix0 * (C / 8) : nullptr;
+    L = next;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b) start[b] = next_start[b];
+    if (C == 16) {
+#pragma unroll
+      for (int t = 0; t < 5; ++t) wreg[t] = next_wreg[t];
+    }
+    // the next layer's first tap row, or (16 channels) its signs: older than this layer's stores and the signs after them
+    if (more && C != 16) wait_vm<2 * FP + SG>();
+    else if (DGRAD && l + 2 < p.n) wait_vm<NS + 1>();
+    else if (DGRAD && more) wait_vm<NS>();
+    wg_barrier();
+  }
+  store_out(p.n & 1 ? (int)g.buf_bytes : 0, prev_y, prev_bits);
+}
+
+inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+int plane_bytes(int H, int W, int imgs) { return ((imgs * (H + 1) + 1) * (W + 1) + 1) * 32; }
+int buffer_bytes(int C, int H, int W, int imgs) { return cdiv(plane_bytes(H, W, imgs) * (C / 16), 1024) * 1024; }
+int sign_bytes(int C, int H, int W, int imgs) {  // of the 16-byte lines that may hold them
+  const int n = imgs * H * W * (C / 8);
+  return cdiv(n % 16 ? n + 15 : n, 1024) * 1024;
+}
+int weight_bytes(int C) { return C == 16 ? 0 : 9 * C / 32 * (C / 16) * 1024; }
+int lds_bytes(int C, int H, int W, int imgs) { return 2 * buffer_bytes(C, H, W, imgs) + weight_bytes(C) + sign_slots(C) * sign_bytes(C, H, W, imgs); }
+int wave_rows(int C) { return C == 64 ? kWaves / 2 : kWaves; }
+int most_runs(int C) { return C == 64 ? 4 : 8; }
+
+template <int C, int RUNS>
+void launch_inst(const ChainParams& p, const ChainGeom& g, int wgs, int smem, hipStream_t s) {
+  static DeviceOnce lds[2];
+  if (p.dgrad) {
+    allow_whole_lds(lds[1], (const void*)conv_chain_kernel<C, RUNS, true>);
+    conv_chain_kernel<C, RUNS, true><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+  } else {
+    allow_whole_lds(lds[0], (const void*)conv_chain_kernel<C, RUNS, false>);
+    conv_chain_kernel<C, RUNS, false><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+  }
+}
+
+}  // namespace
+
+// Images of a workgroup: as few as fill the chip once; more share a copy of the weights.
+static int images_of(int C, int H, int W, int Nimg, int nrep) {
+  if ((C != 16 && C != 32 && C != 64) || H < 1 || W < 1 || Nimg < 1 || nrep < 1 || Nimg % nrep != 0) return 0;
+  if ((long long)H * W > 4096) return 0;  // (far beyond what LDS holds; keeps the products below in range)
+  auto fits = [&](int imgs) {
+    return lds_bytes(C, H, W, imgs) <= 160 * 1024 && cdiv(cdiv(imgs * H * W, 16), wave_rows(C)) <= most_runs(C);
+  };
+  int imgs = 0;
+  for (int i = 1; i <= 8 && fits(i) && (nrep == 1 || Nimg / nrep % i == 0); i *= 2) {
+    imgs = i;
+    if (cdiv(Nimg, i) <= 256) break;
+  }
+  return imgs;
+}
+
+// us per step of a net with two (six) such layers in one module, a launch a layer / here, at the best of several runs: 16 channels at 32 x 32, 64
+// images 75 / 76, 194 images 98 / 90, 776 images 200 / 194; 32 channels at 16 x 16, 64 images 74 / 67, 776 images 138 / 128; 64 channels at 8 x
+// 8, 64 images 78 / 74, 776 images 124 / 112. Where one image takes more than half of a CU's LDS, two layers do not make up for a last
+// round of few workgroups, and other modules' kernels find no room beside them: 64 channels at 14 x 14, 64 images 87 / 92 (137 / 132), 194 images 115 /
+// 105 (214 / 159), 776 images 221 / 228 (458 / 413); 32 channels at 28 x 28, 8 images 69 / 75 (106 / 112), 194 images 114 / 110 (199 / 159), 776
+// images 267 / 273 (527 / 504). Two such layers of 64 channels in either of two modules, 194 images of 14 x 14: 180 / 183.
+int conv_chain_least(int C, int H, int W, int Nimg, int nrep) {
+  const int imgs = images_of(C, H, W, Nimg, nrep);
+  if (imgs == 0) return 0;
+  if (imgs > 1 || lds_bytes(C, H, W, 1) <= 80 * 1024) return 2;
+  return Nimg < 64 && H * W > 640 ? 0 : 4;
+}
+
+void launch_conv_chain(int C, const ChainParams& p, hipStream_t s) {
+  ChainGeom g;
+  g.imgs = images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1);
+  g.buf_bytes = buffer_bytes(C, p.H, p.W, g.imgs);
+  g.plane = plane_bytes(p.H, p.W, g.imgs);
+  g.sign_bytes = sign_bytes(C, p.H, p.W, g.imgs);
+  g.dP = make_divisor1(g.plane / 16);
+  g.dQ = make_divisor1(p.W + 1);
+  g.dH1 = make_divisor1(p.H + 1);
+  g.dW = make_divisor1(p.W);
+  g.dH = make_divisor1(p.H);
+  const int wgs = cdiv(p.Nimg, g.imgs), smem = lds_bytes(C, p.H, p.W, g.imgs);
+  const int runs = cdiv(cdiv(g.imgs * p.H * p.W, 16), wave_rows(C));
+#define DDS_CHAIN_CASE(C, RUNS) \
+  case (C) * 8 + (RUNS) - 1: launch_inst<C, RUNS>(p, g, wgs, smem, s); break;
+  switch (C * 8 + runs - 1) {
+    DDS_CHAIN_CASE(16, 1) DDS_CHAIN_CASE(16, 2) DDS_CHAIN_CASE(16, 3) DDS_CHAIN_CASE(16, 4)
+    DDS_CHAIN_CASE(16, 5) DDS_CHAIN_CASE(16, 6) DDS_CHAIN_CASE(16, 7) DDS_CHAIN_CASE(16, 8)
+    DDS_CHAIN_CASE(32, 1) DDS_CHAIN_CASE(32, 2) DDS_CHAIN_CASE(32, 3) DDS_CHAIN_CASE(32, 4)
+    DDS_CHAIN_CASE(32, 5) DDS_CHAIN_CASE(32, 6) DDS_CHAIN_CASE(32, 7) DDS_CHAIN_CASE(32, 8)
+    DDS_CHAIN_CASE(64, 1) DDS_CHAIN_CASE(64, 2) DDS_CHAIN_CASE(64, 3) DDS_CHAIN_CASE(64, 4)
+  }
+#undef DDS_CHAIN_CASE
+}
+
+}  // namespace dds

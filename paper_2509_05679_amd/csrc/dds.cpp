@@ -99,6 +99,7 @@ struct Node {
   bool dgrad_folded = false;  // shortcut node: no dgrad launch of its own
   int wgroup = -1;            // launch that this layer's weight gradient goes with ...
   bool wgroup_last = false;   // ... and the backward pass has reached its last layer
+  int chain = -1;             // run of layers that share a forward and an input-gradient launch (Module::chains)
 };
 
 struct GradBuf {
@@ -115,6 +116,8 @@ struct Module {
   // weight gradients that wait for the rest of their launch, with their algorithmic FLOPs
   struct WgradQueue { std::vector<WgradParams> layers; std::vector<double> flops; };
   std::vector<WgradQueue> wgroups;
+  struct Chain { int first, last; };  // nodes
+  std::vector<Chain> chains;
   size_t slot_bytes = 0;
   char* ring = nullptr;
   // Recompute policy (modules with d > 0): a ring slot keeps only what other iterations or modules read (the
@@ -558,6 +561,38 @@ int plan_module(const dds_spec& sp, int k0, int K, int N, int dt, const Tensor* 
   return DDS_OK;
 }
 
+// Finds the runs of layers that one launch takes through LDS (chain.hip): neighbouring 3x3 stride-1 nodes of one width and image
+// size. What a node adds must be what the node before it read, in the forward pass (residual) and, the other way round, in the
+// backward pass (gradient of the shortcut); only the first of a launch may add any other tensor.
+void plan_chains(dds_ctx& c, Module& m) {
+  if (c.dt != DT_BF16) return;
+  auto least = [&](const Node& nd) {  // nodes of a run; 0: not such a node
+    if (nd.kind != N_CONV || nd.out_f32 || nd.fold_sc >= 0) return 0;
+    const ParamLayer& L = m.layers[nd.layer];
+    const Tensor& ti = m.tensors[nd.in];
+    const Tensor& to = m.tensors[nd.out];
+    const bool ok = L.R == 3 && L.stride == 1 && L.pad == 1 && L.Cin == L.Cout && L.Cin == L.Cinpad && L.Cout == L.Coutpad && to.kind == T_RING &&
+                    (!nd.relu || to.has_bits) && (!nd.mask_in || ti.has_bits);
+    return ok ? conv_chain_least(L.Cin, to.H, to.W, c.N, c.copies) : 0;
+  };
+  auto follows = [&](const Node& a, const Node& b) {
+    return b.in == a.out && m.layers[a.layer].Cin == m.layers[b.layer].Cin && (b.res < 0 || b.res == a.in) &&
+           (a.addend == G_NONE || a.addend == b.gout) && b.gin == a.gout;
+  };
+  const int n = (int)m.nodes.size();
+  for (int i = 0; i < n; ++i) {
+    const int few = least(m.nodes[i]);
+    if (few == 0) continue;
+    int last = i;
+    while (last + 1 < n && last - i + 1 < kChainMax && least(m.nodes[last + 1]) > 0 && follows(m.nodes[last], m.nodes[last + 1])) ++last;
+    if (last - i + 1 >= few) {
+      for (int k = i; k <= last; ++k) m.nodes[k].chain = (int)m.chains.size();
+      m.chains.push_back({i, last});
+    }
+    i = last;
+  }
+}
+
 // workgroups of the update kernel that a layer takes
 int update_blocks(const dds_ctx& c, const ParamLayer& L) {
   if (!c.gossip) return update_tiles(c.dt, L.nsplit, L.Cout, L.RS, L.Cinpad);
@@ -800,6 +835,7 @@ int build(dds_ctx& c, const dds_spec* sp, int K, int W, const int* delays) {
     const Tensor* in = k0 ? &c.mods[k0 - 1].tensors[c.mods[k0 - 1].out_tensor] : nullptr;
     rc = plan_module(*sp, k0, K, c.N, c.dt, in, m);
     if (rc) return rc;
+    plan_chains(c, m);
   }
   // sizes that index arithmetic in the kernels keeps in 32 bits
   for (Module& m : c.mods)
@@ -939,6 +975,100 @@ BnParams bn_params(dds_ctx& c, Module& m, const Node& nd, int slot, const float*
   return p;
 }
 
+// Forward launch of a convolution or linear node; master, work: the parameters it uses.
+ConvParams conv_forward(dds_ctx& c, Module& m, const Node& nd, int slot, int in_slot, const float* master, const char* work) {
+  const int es = dtype_size(c.dt);
+  const Tensor& ti = m.tensors[nd.in];
+  const Tensor& to = m.tensors[nd.out];
+  const ParamLayer& L = m.layers[nd.layer];
+  ConvParams p{};
+  p.x = tptr(c, m, nd.in, slot, in_slot);
+  p.w = c.dt == DT_BF16 ? (const void*)(work + (size_t)L.off * es) : (const void*)(master + L.off);
+  p.y = tptr(c, m, nd.out, slot, in_slot);
+  p.bias = master + L.off + (long long)L.Cout * L.RS * L.Cinpad;
+  p.res = nd.res >= 0 ? tptr(c, m, nd.res, slot, in_slot) : nullptr;
+  p.mask = nullptr;
+  p.bits_out = nd.relu ? bits_ptr(c, m, nd.out, slot, in_slot) : nullptr;
+  p.zeros = c.zeros;
+  p.Nimg = c.N; p.H = ti.H; p.W = ti.W; p.Cx = ti.Cpad;
+  p.Ho = to.H; p.Wo = to.W;
+  p.M = c.N * to.H * to.W;
+  // general mixing matrix: data-group r's images meet data-group r's weights
+  p.nrep = c.copies;
+  p.w_rep = m.n_master * es;
+  p.bias_rep = m.n_master;
+  p.Nout = L.Cout;
+  p.ldy = to.Cpad;
+  p.R = L.R; p.S = L.R; p.stride = L.stride; p.pad = L.pad;
+  p.Ktot = L.RS * L.Cinpad;
+  p.alpha = nd.alpha;
+  p.relu = nd.relu;
+  p.out_f32 = nd.out_f32;
+  p.dgrad = 0;
+  return p;
+}
+
+// Input-gradient launch of such a node.
+ConvParams conv_dgrad(dds_ctx& c, Module& m, const Node& nd, const Sched& sc) {
+  const int slot = sc.bwd_slot, in_slot = sc.in_bwd_slot;
+  const Tensor& ti = m.tensors[nd.in];
+  const Tensor& to = m.tensors[nd.out];
+  const ParamLayer& L = m.layers[nd.layer];
+  ConvParams p{};
+  p.x = gptr(c, m, nd.gout, sc);
+  p.w = L.stash + (size_t)slot * L.stash_slot_bytes;
+  p.y = gptr(c, m, nd.gin, sc);
+  p.bias = nullptr;
+  p.res = nd.addend != G_NONE ? gptr(c, m, nd.addend, sc) : nullptr;
+  p.nrep = c.copies;  // data-group r back-propagates through its own snapshot
+  p.w_rep = (long long)m.R * L.stash_slot_bytes;
+  if (nd.fold_sc >= 0) {
+    const Node& scn = m.nodes[nd.fold_sc];
+    const ParamLayer& Ls = m.layers[scn.layer];
+    p.x2 = gptr(c, m, scn.gout, sc);
+    p.w2 = Ls.stash + (size_t)slot * Ls.stash_slot_bytes;
+    p.Cx2 = m.tensors[scn.out].Cpad;
+    p.w2_rep = (long long)m.R * Ls.stash_slot_bytes;
+  }
+  p.maskbits = nd.mask_in ? bits_ptr(c, m, nd.in, slot, in_slot) : nullptr;
+  p.mask = nd.mask_in && !p.maskbits ? tptr(c, m, nd.in, slot, in_slot) : nullptr;
+  p.zeros = c.zeros;
+  p.Nimg = c.N; p.H = to.H; p.W = to.W; p.Cx = to.Cpad;
+  p.Ho = ti.H; p.Wo = ti.W;
+  p.M = c.N * ti.H * ti.W;
+  p.Nout = L.Cin;
+  p.ldy = ti.Cpad;
+  p.R = L.R; p.S = L.R; p.stride = L.stride; p.pad = L.pad;
+  p.Ktot = L.RS * L.Coutpad;
+  p.alpha = nd.alpha;
+  p.relu = 0;
+  p.out_f32 = 0;
+  p.dgrad = 1;
+  return p;
+}
+
+// The launches of a chain's layers, in the order in which they are walked, as one.
+void run_chain(dds_ctx& c, const std::vector<ConvParams>& layers, bool timed, hipStream_t s) {
+  const ConvParams& p0 = layers[0];
+  ChainParams p{};
+  p.x = p0.x; p.res = p0.res; p.zeros = p0.zeros;
+  p.Nimg = p0.Nimg; p.H = p0.H; p.W = p0.W;
+  p.n = (int)layers.size();
+  p.dgrad = p0.dgrad;
+  p.nrep = p0.nrep; p.w_rep = p0.w_rep; p.bias_rep = p0.bias_rep;
+  for (int i = 0; i < p.n; ++i) {
+    const ConvParams& q = layers[i];
+    p.layer[i] = ChainLayer{q.w, q.bias, q.y, q.bits_out, q.maskbits, q.alpha, q.relu, q.res != nullptr};
+  }
+  std::vector<dds_ctx::ProfRec> recs;
+  if (c.profiling)
+    for (const ConvParams& q : layers) recs.push_back({q.dgrad ? 4 : 3, 2.0 * q.M * q.Nout * q.Ktot, 1.0 / p.n, nullptr, nullptr, false});
+  ProfScope ps(c, s, 0, 0.0, timed);
+  ps.layers = std::move(recs);
+  launch_conv_chain(p0.Nout, p, s);
+  ++c.launches;
+}
+
 // Forward pass of a mini-batch through the tensors of ring slot `slot`; its input (modules above the first) is in
 // slot `in_slot` of the ring of the module below. snap < 0: with the current parameters (the pass of iteration
 // t = f + k0). snap >= 0: the same pass again with the parameter snapshot of that slot, which rebuilds the tensors
@@ -948,44 +1078,26 @@ void run_forward(dds_ctx& c, Module& m, int slot, int in_slot, hipStream_t s, in
   const size_t snap_off = snap >= 0 ? (size_t)snap * c.copies * m.n_master : 0;
   const float* master = snap >= 0 ? m.snap_master + snap_off : m.master;
   const char* work = snap >= 0 ? (m.snap_work ? m.snap_work + snap_off * es : nullptr) : m.work;
+  std::vector<ConvParams> chain;
   for (const Node& nd : m.nodes) {
     if (nd.kind == N_CE) continue;
     const Tensor& ti = m.tensors[nd.in];
-    const Tensor& to = m.tensors[nd.out];
     char* x = tptr(c, m, nd.in, slot, in_slot);
     char* y = tptr(c, m, nd.out, slot, in_slot);
     switch (nd.kind) {
       case N_CONV: {
-        const ParamLayer& L = m.layers[nd.layer];
-        ConvParams p{};
-        p.x = x;
-        p.w = c.dt == DT_BF16 ? (const void*)(work + (size_t)L.off * es) : (const void*)(master + L.off);
-        p.y = y;
-        p.bias = master + L.off + (long long)L.Cout * L.RS * L.Cinpad;
-        p.res = nd.res >= 0 ? tptr(c, m, nd.res, slot, in_slot) : nullptr;
-        p.mask = nullptr;
-        p.bits_out = nd.relu ? bits_ptr(c, m, nd.out, slot, in_slot) : nullptr;
-        p.zeros = c.zeros;
-        p.Nimg = c.N; p.H = ti.H; p.W = ti.W; p.Cx = ti.Cpad;
-        p.Ho = to.H; p.Wo = to.W;
-        p.M = c.N * to.H * to.W;
-        // general mixing matrix: data-group r's images meet data-group r's weights
-        p.nrep = c.copies;
-        p.w_rep = m.n_master * es;
-        p.bias_rep = m.n_master;
-        p.Nout = L.Cout;
-        p.ldy = to.Cpad;
-        p.R = L.R; p.S = L.R; p.stride = L.stride; p.pad = L.pad;
-        p.Ktot = L.RS * L.Cinpad;
-        p.alpha = nd.alpha;
-        p.relu = nd.relu;
-        p.out_f32 = nd.out_f32;
-        p.dgrad = 0;
-        {
-          // the per-class launch timings cover each launch once: the repeated pass is the same launches again
-          ProfScope ps(c, s, 0, 2.0 * p.M * L.Cout * L.Cin * L.RS, snap < 0);
-          ps.cls += 3 * launch_conv(c.dt, p, s);
+        const ConvParams p = conv_forward(c, m, nd, slot, in_slot, master, work);
+        // the per-class launch timings cover each launch once: the repeated pass is the same launches again
+        if (nd.chain >= 0) {
+          chain.push_back(p);
+          if (&nd != &m.nodes[m.chains[nd.chain].last]) continue;
+          run_chain(c, chain, snap < 0, s);
+          chain.clear();
+          continue;
         }
+        const ParamLayer& L = m.layers[nd.layer];
+        ProfScope ps(c, s, 0, 2.0 * p.M * L.Cout * L.Cin * L.RS, snap < 0);
+        ps.cls += 3 * launch_conv(c.dt, p, s);
         break;
       }
       case N_BN: {
@@ -1019,14 +1131,19 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
     const Node& nd = m.nodes[ni];
     if (nd.kind == N_CE) continue;  // dlogits were produced by the loss kernel
     const Tensor& ti = m.tensors[nd.in];
-    const Tensor& to = m.tensors[nd.out];
     char* x = tptr(c, m, nd.in, slot, in_slot);
     char* gout = gptr(c, m, nd.gout, sc);
     char* gin = gptr(c, m, nd.gin, sc);
     switch (nd.kind) {
       case N_CONV: {
         const ParamLayer& L = m.layers[nd.layer];
-        const int ldg = to.Cpad;
+        // The input gradients of a chain come ahead of its weight gradients, which they feed.
+        if (nd.chain >= 0 && ni == m.chains[nd.chain].last) {
+          std::vector<ConvParams> chain;
+          for (int k = ni; k >= m.chains[nd.chain].first; --k)
+            if (m.nodes[k].gin != G_NONE) chain.push_back(conv_dgrad(c, m, m.nodes[k], sc));
+          run_chain(c, chain, true, s);
+        }
         // The weight gradient reads no weights: one launch serves every data-group. With a mixing matrix (and in fp32) no
         // split mixes two of them, so that data-group r's gradient is the sum of its own nsplit / W splits.
         WgradParams w = wgrad_shape(c, m, nd);
@@ -1056,37 +1173,8 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
           group.layers.clear();
           group.flops.clear();
         }
-        if (nd.gin != G_NONE) {
-          ConvParams p{};
-          p.x = gout;
-          p.w = L.stash + (size_t)slot * L.stash_slot_bytes;
-          p.y = gin;
-          p.bias = nullptr;
-          p.res = nd.addend != G_NONE ? gptr(c, m, nd.addend, sc) : nullptr;
-          p.nrep = c.copies;  // data-group r back-propagates through its own snapshot
-          p.w_rep = (long long)m.R * L.stash_slot_bytes;
-          if (nd.fold_sc >= 0) {
-            const Node& scn = m.nodes[nd.fold_sc];
-            const ParamLayer& Ls = m.layers[scn.layer];
-            p.x2 = gptr(c, m, scn.gout, sc);
-            p.w2 = Ls.stash + (size_t)slot * Ls.stash_slot_bytes;
-            p.Cx2 = m.tensors[scn.out].Cpad;
-            p.w2_rep = (long long)m.R * Ls.stash_slot_bytes;
-          }
-          p.maskbits = nd.mask_in ? bits_ptr(c, m, nd.in, slot, in_slot) : nullptr;
-          p.mask = nd.mask_in && !p.maskbits ? x : nullptr;
-          p.zeros = c.zeros;
-          p.Nimg = c.N; p.H = to.H; p.W = to.W; p.Cx = ldg;
-          p.Ho = ti.H; p.Wo = ti.W;
-          p.M = c.N * ti.H * ti.W;
-          p.Nout = L.Cin;
-          p.ldy = ti.Cpad;
-          p.R = L.R; p.S = L.R; p.stride = L.stride; p.pad = L.pad;
-          p.Ktot = L.RS * L.Coutpad;
-          p.alpha = nd.alpha;
-          p.relu = 0;
-          p.out_f32 = 0;
-          p.dgrad = 1;
+        if (nd.gin != G_NONE && nd.chain < 0) {
+          const ConvParams p = conv_dgrad(c, m, nd, sc);
           {
             ProfScope ps(c, s, 1, 2.0 * w.P * L.Cout * L.Cin * L.RS);
             ps.cls += 3 * launch_conv(c.dt, p, s);

@@ -60,6 +60,28 @@ struct ConvParams {
   long long w_rep, w2_rep, bias_rep;
 };
 
+// A run of 3x3 stride-1 pad-1 layers of C channels in and out, bf16 (chain.hip): layer i + 1 reads what layer i writes. Epilogue of a layer:
+// v = alpha * (acc + bias[n]); v += what the layer before read (layer 0: res), if add; relu; v = maskbits ? v : 0. Weights as in ConvParams.
+constexpr int kChainMax = 16;
+struct ChainLayer {
+  const void* w;
+  const float* bias;     // or null
+  void* y;
+  void* bits_out;        // sign plane of y or null
+  const void* maskbits;  // sign plane or null
+  float alpha;
+  int relu, add;
+};
+struct ChainParams {
+  const void* x;    // input of layer 0
+  const void* res;  // what layer 0 adds, or null
+  const void* zeros;
+  int Nimg, H, W, n, dgrad;
+  int nrep;         // data-groups with weights of their own, as in ConvParams
+  long long w_rep, bias_rep;
+  ChainLayer layer[kChainMax];
+};
+
 // Weight-gradient GEMM with split reduction:
 //   partial[z][m*NK + n] = alpha * sum_{p in split z} dy[p, m] * gather(x; p, n)
 //   partial[z][Mout*NK + m] = alpha * sum_p dy[p, m]                (bias gradient)
@@ -149,6 +171,9 @@ int launch_conv(int dt, const ConvParams& p, hipStream_t s);
 bool launch_linear(int dt, const ConvParams& p, hipStream_t s);
 // bf16 3x3 stride-1 layers with 16-channel rows, stems (narrow.hip); false: not taken, nothing launched
 bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
+// Fewest layers that are faster in one launch than in one each; 0: no number is, or the kernel does not take them.
+int conv_chain_least(int C, int H, int W, int Nimg, int nrep);
+void launch_conv_chain(int C, const ChainParams& p, hipStream_t s);
 // n layers of one key (wgrad_work), or one of any kind. Returns 1 if wgrad_tiles or wgrad_slim took them, whose 3x3 and stride-2
 // layers have a class of their own, 0 if wgrad_gemm or wgrad_f32 did; -1, nothing launched, if their splits fit none of them.
 int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);

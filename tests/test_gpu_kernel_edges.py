@@ -447,3 +447,34 @@ def test_weight_gradients_that_share_no_launch_run_beside_the_input_gradients(mo
     beside = best()
     monkeypatch.setenv("DDS_SERIAL", "1")
     assert beside < 0.95 * best()
+
+
+def _identity_blocks(c, blocks, h, w, W, B, cuts=()):
+    """A stem to c channels and residual blocks of that width; cuts: blocks that a module ends behind."""
+    ops, bounds = [{"op": "conv", "cin": 3, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}], [0]
+    for i in range(blocks):
+        ops += [{"op": "res_begin"}, {"op": "conv", "cin": c, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
+                {"op": "conv", "cin": c, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "res_add", "scale": 0.7, "shortcut": None}, {"op": "relu"}]
+        if i in cuts:
+            bounds.append(len(ops))
+    ops += [{"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
+    bounds.append(len(ops))
+    return Workload(name=f"identity_blocks_{c}", ops=ops, bounds=bounds, K=len(bounds) - 1, W=W, B=B, in_shape=(3, h, w), classes=10,
+                    precision="bf16", lr=0.05, momentum=0.0, steps=2)
+
+
+@pytest.mark.parametrize("c,blocks,h,w,W,B,cuts", [
+    (16, 2, 1, 1, 1, 3, ()), (16, 9, 5, 7, 1, 4, ()), (16, 3, 32, 32, 1, 2, (0,)), (16, 2, 31, 33, 1, 64, ()), (16, 2, 32, 33, 1, 64, ()), (16, 1, 30, 18, 1, 3, ()),
+    (32, 2, 2, 3, 1, 300, ()), (32, 2, 16, 16, 1, 3, (0,)), (32, 2, 31, 31, 1, 64, ()), (32, 1, 9, 9, 1, 257, ()), (32, 2, 32, 31, 1, 64, ()),
+    (64, 2, 8, 8, 1, 1021, ()), (64, 2, 8, 8, 2, 258, (0,)), (64, 2, 14, 14, 1, 2, ()), (64, 2, 16, 16, 1, 1, ()), (64, 1, 3, 5, 1, 2050, ()), (64, 2, 17, 16, 1, 1, ())])
+def test_runs_of_narrow_layers_share_a_launch(c, blocks, h, w, W, B, cuts):
+    # one pixel; more layers than a launch takes; a residual added by the first layer of a module's launch; the largest images of each width and
+    # the first beyond them (32 x 33 of 16 channels, 32 x 31 of 32, 17 x 16 of 64: a launch each); two and more images a workgroup, the last one short of them
+    _compare(_identity_blocks(c, blocks, h, w, W, B, cuts), seed=50, T=2 * len(cuts) + 2)
+
+
+@pytest.mark.parametrize("c,h,w,W,B", [(16, 9, 5, 3, 2), (32, 6, 6, 2, 130), (64, 4, 4, 2, 260), (64, 4, 4, 4, 131)])
+def test_runs_of_narrow_layers_with_weights_per_data_group(c, h, w, W, B):
+    # (64, ..., 131): an odd number of images per data-group, one a workgroup
+    from test_gpu_gossip import _compare as compare_gossip
+    compare_gossip(_identity_blocks(c, 2, h, w, W, B, (0,)), seed=51, T=4, mixing=ring_mixing(W, 0.3))
