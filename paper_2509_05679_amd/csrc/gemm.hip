@@ -1419,43 +1419,36 @@ __device__ __forceinline__ uint2 lds_tr16(const char* p) {
 // Geometry the host passes along with WgradParams.
 struct WgradGeom {
   int cblocks;     // 64-channel blocks of the real input tensor
-  int sub[4];      // S2: sub-pixel (dy * 2 + dx) served by block row / cblocks
-  int rmap[2][2];  // S2: real kernel row for (virtual row R', dy), -1 if none; the same table serves columns
-  // wgrad_dma_body
-  int tiles_h;     // 128-pixel tiles per image (a power of two; 1 when a tile holds whole images)
-  // wgrad_flat_body
+  int sub[4];      // wgrad_flat_body<true>: sub-pixel (dy * 2 + dx) served by block row / cblocks
+  int rmap[2][2];  // wgrad_flat_body<true>: real kernel row for (virtual row R', dy), -1 if none; the same table serves columns
+  // wgrad_dma_body, wgrad_s2_dma_body
+  int tiles_h;     // tiles per image (a power of two; 1 when a tile holds whole images)
+  // wgrad_flat_body, wgrad_s2_flat_body
   int Q;           // position pitch of an image row, Wo + 1
   int imgs_rep;    // images per data-group
-  int rep_tiles;   // 128-position tiles per data-group
-  int patch_rows;  // 128 + 2Q + 2 (S2: 128 + Q + 1) rounded up to 8
+  int rep_tiles;   // tiles per data-group
+  int patch_rows;  // of a tile, whole 8-row fills
   Divisor dQ, dH;  // by Q and by Ho + 1 (wgrad_rows_body: by Wo and by Ho)
 };
 
-// S2 = false: 3x3, stride 1, pad 1 (nine taps, TW x TH tiles of the image itself).
-// S2 = true: a 3x3 stride-2 pad-1 convolution seen as a stride-1 one on the
-// input regrouped into 2x2 sub-pixels: output pixel (oy, ox) and real tap r read input row
-// 2*oy + r - pad, i.e. sub-pixel row dy of super-pixel row oy - 1 or oy. A workgroup takes the
-// 64 channels of ONE sub-pixel (dy, dx); its patch is that sub-grid (gathered at pixel stride
-// 2 by the fills) and only the virtual taps R', S' in {0, 1} that a real tap maps to are
-// accumulated: 1, 2, 2 and 4 of them for the four sub-pixels of a 3x3 kernel, none wasted.
 __device__ __forceinline__ uint2 lds_tr16_at(uint32_t lds_byte_address) {
   s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t DDS_LDS_AS*)(size_t)lds_byte_address);
   return __builtin_bit_cast(uint2, v);
 }
 
-// Waves: four per tap group, each owning a 32(k) x 32(c) quarter of the block. Stride 1 runs
-// three tap groups (one per kernel row, 12 waves, three per SIMD) so that the LDS reads of one wave
+// Waves: four per tap group, each owning a 32(k) x 32(c) quarter of the block; three
+// tap groups (one per kernel row, 12 waves, three per SIMD) so that the LDS reads of one wave
 // hide behind the MFMAs of the others; a group's row shift is folded into its lanes' base addresses.
-template <int TWLOG, int THLOG, bool S2>
+template <int TWLOG, int THLOG>
 __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
   constexpr int TW = 1 << TWLOG, TH = 1 << THLOG, PW = TW + 2, PP = (TH + 2) * PW;
   constexpr int IMGS = 128 / (TW * TH);
   static_assert(IMGS >= 1 && IMGS * TW * TH == 128, "a tile is 128 pixels");
-  constexpr int NWV = S2 ? 4 : 12;                // waves per workgroup
+  constexpr int NWV = 12;                         // waves per workgroup
   constexpr int PROW = (IMGS * PP + 7) / 8 * 8;   // patch rows, whole 8-row fills
   constexpr int FY = (16 + NWV - 1) / NWV;        // dY fills per wave (16 per tile)
   constexpr int PF = (PROW / 8 + NWV - 1) / NWV;  // patch fills per wave
-  constexpr int NT = S2 ? 4 : 3;                  // taps accumulated by one wave
+  constexpr int NT = 3;                           // taps accumulated by one wave
   // Two slots: tiles in flight in LDS (the next one is copied while this one is multiplied) keep a workgroup at 84 KB,
   // so that a conv workgroup of another module fits on the same CU; a third slot (copies two tiles ahead,
   // 126 KB) was 1-2 % slower per training step on every configuration although each launch alone was not.
@@ -1465,11 +1458,9 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wave_m = wave & 1, wave_n = (wave >> 1) & 1;
-  const int tg = wave >> 2;  // tap group: kernel row of this wave's three taps (stride 1)
+  const int tg = wave >> 2;  // tap group: kernel row of this wave's three taps
   const int k0 = bx * 64;
-  const int sub = S2 ? wg.sub[by / wg.cblocks] : 0;
-  const int sdy = sub >> 1, sdx = sub & 1;
-  const int c0 = (S2 ? by % wg.cblocks : by) * 64;
+  const int c0 = by * 64;
   // Split z = (data-group, j): the data-group's tiles are dealt to its q splits as evenly as whole
   // tiles allow (tile counts differ by at most one), so a split never mixes two data-groups.
   const int q = p.nsplit / p.nrep, rep_tiles = (p.P >> 7) / p.nrep;
@@ -1488,7 +1479,7 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
   constexpr int pw_total = PROW >> 3;
   const bool ycol_ok = k0 + (c16 >> 1) < p.ldy;   // this lane's 8 output channels exist
   const bool xcol_ok = c0 + (c16 >> 1) < p.Cx;    // ... and its 8 input channels (tensors narrower than a 64-channel block)
-  const size_t tile_ybytes = 128 * ybytes, tile_xbytes = (S2 ? 4 : 1) * 128 * xbytes;
+  const size_t tile_ybytes = 128 * ybytes, tile_xbytes = 128 * xbytes;
   const char* ysrc0 = (const char*)p.dy + ((size_t)tile0 * 128 + (size_t)(wave * 8 + l8)) * ybytes + (size_t)k0 * 2 + c16;
   const char* xsrc0 = (const char*)p.x + (size_t)tile0 * tile_xbytes + (size_t)c0 * 2 + c16;
   int prel[PF], pflag[PF];  // byte offset from the tile origin; yy | column valid << 8
@@ -1499,8 +1490,7 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
     if (row < IMGS * PP) {
       const int im = row / PP, rem = row - im * PP;
       const int yy = rem / PW, xx = rem - yy * PW;
-      if (S2) rel = (int)((((long long)im * p.H + 2 * (yy - 1) + sdy) * p.W + 2 * (xx - 1) + sdx) * (long long)xbytes);
-      else rel = (int)((((long long)im * p.H + yy - 1) * p.W + (xx - 1)) * (long long)xbytes);
+      rel = (int)((((long long)im * p.H + yy - 1) * p.W + (xx - 1)) * (long long)xbytes);
       flag = yy | (((unsigned)(xx - 1) < (unsigned)p.Wo ? 1 : 0) << 8);
     }
     prel[u] = rel;
@@ -1548,24 +1538,10 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     const int ql = 8 * khalf + rsub + 4 * hh;
-    const int rl = (ql >> TWLOG) * PW + (ql & (TW - 1)) + (S2 ? 0 : tg * PW);
+    const int rl = (ql >> TWLOG) * PW + (ql & (TW - 1)) + tg * PW;
 #pragma unroll
     for (int v = 0; v < 4; ++v) baddr[hh][v] = rl * 128 + ((b_c ^ (((rl + v) & 3) << 1)) << 4) + 8 * (seg & 1);
   }
-  bool live[NT];
-  int tapreal[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (S2) {
-      const int rr = wg.rmap[t >> 1][sdy], ss = wg.rmap[t & 1][sdx];
-      live[t] = rr >= 0 && ss >= 0;
-      tapreal[t] = rr * p.S + ss;
-    } else {
-      live[t] = true;
-      tapreal[t] = tg * 3 + t;
-    }
-  }
-
   f32x16_t acc[NT], accb;
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -1604,10 +1580,9 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
       af[set] = make_uint4(a0.x, a0.y, a1.x, a1.y);
 #pragma unroll
       for (int tap = 0; tap < NT; ++tap) {
-        const int toff = S2 ? (tap >> 1) * PW + (tap & 1) : tap;  // stride 1: the row shift sits in the base
-        const int v = (rc + toff) & 3;
-        const uint2 b0 = lds_tr16_at(bp[0][v] + (rc + toff) * 128);
-        const uint2 b1 = lds_tr16_at(bp[1][v] + (rc + toff) * 128);
+        const int v = (rc + tap) & 3;  // the row shift sits in the base
+        const uint2 b0 = lds_tr16_at(bp[0][v] + (rc + tap) * 128);
+        const uint2 b1 = lds_tr16_at(bp[1][v] + (rc + tap) * 128);
         bf[set][tap] = make_uint4(b0.x, b0.y, b1.x, b1.y);
       }
     };
@@ -1617,9 +1592,8 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
     for (int ks = 0; ks < 8; ++ks) {
       if (ks + 1 < 8) load_frags(ks + 1, (ks + 1) & 1);
 #pragma unroll
-      for (int tap = 0; tap < NT; ++tap)
-        if (!S2 || live[tap]) mfma16B<bf16_t>(af[ks & 1], bf[ks & 1][tap], acc[tap]);
-      if (wave_n == 0 && by == 0 && tg == (S2 ? 0 : 1)) mfma16B<bf16_t>(af[ks & 1], ones, accb);  // bias gradient: column sums of dY
+      for (int tap = 0; tap < NT; ++tap) mfma16B<bf16_t>(af[ks & 1], bf[ks & 1][tap], acc[tap]);
+      if (wave_n == 0 && by == 0 && tg == 1) mfma16B<bf16_t>(af[ks & 1], ones, accb);  // bias gradient: column sums of dY
     }
   }
   wait_vm<0>();
@@ -1633,10 +1607,171 @@ __device__ __forceinline__ void wgrad_dma_body(const WgradParams& p, const Wgrad
     if (cin < p.Cx) {
 #pragma unroll
       for (int tap = 0; tap < NT; ++tap)
-        if (live[tap]) out[(size_t)k * p.NK + tapreal[tap] * p.Cx + cin] = p.alpha * acc[tap][e];
+        out[(size_t)k * p.NK + (tg * 3 + tap) * p.Cx + cin] = p.alpha * acc[tap][e];
     }
-    if (wave_n == 0 && (lane & 31) == 0 && by == 0 && tg == (S2 ? 0 : 1)) out[(size_t)p.Mout * p.NK + k] = p.alpha * accb[e];
+    if (wave_n == 0 && (lane & 31) == 0 && by == 0 && tg == 1) out[(size_t)p.Mout * p.NK + k] = p.alpha * accb[e];
   }
+}
+
+// ------------------------------------------------------------------ 3x3 stride-2 pad-1 weight gradients (bf16)
+// Output pixel (oy, ox) and tap r read input row 2 oy + r - 1: of the input regrouped into 2x2 sub-pixels (dy, dx), tap rows 0 and 2 read dy =
+// 1 of super-rows oy - 1 and oy, tap row 1 dy = 0 of oy; columns likewise. A tile is 64 output pixels, its patch four planes, one per
+// sub-pixel (gathered at pixel stride 2 by the copies), in which consecutive output pixels are consecutive rows; otherwise as at stride
+// 1: 64(k) x 64(c) for all nine taps, twelve waves, a kernel row per four of them, and in the launch of the stride-1 layers.
+// Bound by the copies (46 KB for 144 MFMAs) and the barrier of a tile. Before, a workgroup of four waves took one sub-pixel of 128-pixel tiles
+// with the 1, 2, 2 or 4 taps that meet it, so dY was copied four times and the workgroups' work differed as much. ResNet-18, 512 images, serial
+// time of all weight gradients of a step but the stem's: 810 -> 595 us (the three stride-2 layers with their shortcuts took 265 in launches of their
+// own); steps of 512 images 2.065 -> 2.02 ms, of 64 0.482 -> 0.460, ResNet-20 in one module 0.300 -> 0.291, ResNet-56 1.65 -> 1.60.
+struct S2Acc {
+  f32x16_t tap[3], bias;
+};
+__device__ __forceinline__ void wgrad_s2_store(const WgradParams& p, const S2Acc& acc, int k0, int c0, int z, int wave_m, int wave_n, int tg, int lane, bool bias_wave) {
+  float* out = p.partial + (size_t)z * p.Pl;
+  const int cin = c0 + wave_n * 32 + (lane & 31);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int k = k0 + wave_m * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    if (k >= p.Mout) continue;
+    if (cin < p.Cx) {
+#pragma unroll
+      for (int s = 0; s < 3; ++s) out[(size_t)k * p.NK + (tg * 3 + s) * p.Cx + cin] = p.alpha * acc.tap[s][e];
+    }
+    if (bias_wave && (lane & 31) == 0) out[(size_t)p.Mout * p.NK + k] = p.alpha * acc.bias[e];
+  }
+}
+
+// Input of 2 Ho x 2 Wo with Ho and Wo powers of two, whole 64-pixel tiles of rows of one image or of whole images: every address in the loop is
+// a register plus a constant. ALL: an image's plane has a row above it whether dy needs one or not (tiles of several images, whose
+// distance in a plane is a constant then).
+template <int TWLOG, int THLOG>
+struct S2Tile {
+  static constexpr int TW = 1 << TWLOG, TH = 1 << THLOG, IMGS = 64 / (TW * TH);
+  static constexpr bool ALL = IMGS > 1;
+  static_assert(IMGS >= 1 && IMGS * TW * TH == 64, "a tile is 64 pixels");
+  static constexpr int height(int dy) { return TH + (ALL ? 1 : dy); }
+  static constexpr int rows(int d) { return (IMGS * height(d >> 1) * (TW + (d & 1)) + 7) / 8 * 8; }
+  static constexpr int base(int d) { return d == 0 ? 0 : base(d - 1) + rows(d - 1); }  // of the planes (0,0), (0,1), (1,0), (1,1)
+  static constexpr int patch = base(3) + rows(3);
+};
+template <int TWLOG, int THLOG>
+__device__ __forceinline__ void wgrad_s2_dma_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
+  typedef S2Tile<TWLOG, THLOG> T;
+  constexpr int TW = T::TW, TH = T::TH, NWV = 12;
+  constexpr int PF = (T::patch / 8 + NWV - 1) / NWV;  // patch fills per wave
+  constexpr int SLOT = 8192 + T::patch * 128;
+  const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = (wave >> 1) & 1, tg = wave >> 2;
+  const int k0 = bx * 64, c0 = by * 64;
+  const int q = p.nsplit / p.nrep, rep_tiles = (p.P >> 6) / p.nrep;
+  const int zr = z / q, zj = z - zr * q;
+  const int tile0 = zr * rep_tiles + (int)(((long long)zj * rep_tiles) / q);
+  const int ntiles = zr * rep_tiles + (int)(((long long)(zj + 1) * rep_tiles) / q) - tile0;
+  const size_t ybytes = (size_t)p.ldy * 2, xbytes = (size_t)p.Cx * 2;
+
+  const int l8 = lane >> 3;
+  const int c16 = ((lane & 7) ^ ((l8 & 3) << 1)) * 16;  // global 16-byte column for LDS slot lane&7 of a row with row&3 == l8&3
+  const char* zsrc = (const char*)p.zeros + c16;
+  const bool ycol_ok = k0 + (c16 >> 1) < p.ldy, xcol_ok = c0 + (c16 >> 1) < p.Cx;
+  const size_t tile_ybytes = 64 * ybytes, tile_xbytes = 256 * xbytes;
+  const char* ysrc0 = (const char*)p.dy + ((size_t)tile0 * 64 + (size_t)(wave * 8 + l8)) * ybytes + (size_t)k0 * 2 + c16;
+  const char* xsrc0 = (const char*)p.x + (size_t)tile0 * tile_xbytes + (size_t)c0 * 2 + c16;
+  int prel[PF], pflag[PF];  // byte offset from the tile's first input pixel; super-row from the tile's first, -2 where the column is none
+#pragma unroll
+  for (int u = 0; u < PF; ++u) {
+    const int row = (wave + NWV * u) * 8 + l8;
+    const int d = row < T::base(1) ? 0 : row < T::base(2) ? 1 : row < T::base(3) ? 2 : 3;
+    const int dy = d >> 1, dx = d & 1, pw = TW + dx, ph = T::ALL ? TH + 1 : TH + dy;
+    const int r = row - (d == 0 ? 0 : d == 1 ? T::base(1) : d == 2 ? T::base(2) : T::base(3));
+    const int im = r / (pw * ph), rem = r - im * (pw * ph), yy = rem / pw, xx = rem - yy * pw;
+    const int sy = yy - (T::ALL ? 1 : dy), sx = xx - dx;
+    prel[u] = (int)((((long long)im * p.H + 2 * sy + dy) * p.W + 2 * sx + dx) * (long long)xbytes);
+    pflag[u] = im < T::IMGS && sx >= 0 ? sy : -2;
+  }
+  auto fill_tile = [&](int t, int slot) {
+    if (t >= ntiles) return;
+    const int h0 = ((tile0 + t) & (wg.tiles_h - 1)) << THLOG;
+    const uint32_t base = lds_ring + slot * SLOT;
+    if (wave < 8) dma16(ycol_ok ? ysrc0 + (size_t)t * tile_ybytes : zsrc, base + wave * 1024);
+    const char* xsrc = xsrc0 + (size_t)t * tile_xbytes;
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      const int f = wave + NWV * u;
+      if (f >= T::patch / 8) continue;  // wave-uniform
+      const bool ok = xcol_ok && pflag[u] >= -1 && h0 + pflag[u] >= 0;
+      dma16(ok ? xsrc + prel[u] : zsrc, base + 8192 + f * 1024);
+    }
+  };
+  fill_tile(0, 0);
+
+  const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;  // fragment addressing as in wgrad_dma_body
+  const int rsub = lq >> 2, seg = lq & 3;
+  const int a_c = 4 * wave_m + 2 * grp16 + (seg >> 1), b_c = 4 * wave_n + 2 * grp16 + (seg >> 1);
+  const int a_lane = (8 * khalf + rsub) * 128 + ((a_c ^ (rsub << 1)) << 4) + 8 * (seg & 1);
+  // patch rows: a lane's part for each plane of its kernel row and each value of the constant part mod 4 (the column swizzle depends on it)
+  const int dy = tg == 1 ? 0 : 1, ys = T::ALL ? (tg == 0 ? 0 : 1) : tg == 2 ? 1 : 0;
+  int baddr[2][2][4];
+#pragma unroll
+  for (int dx = 0; dx < 2; ++dx)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int ql = 8 * khalf + rsub + 4 * hh;
+      const int plane = dy ? (dx ? T::base(3) : T::base(2)) : (dx ? T::base(1) : T::base(0));
+      const int rl = plane + ((ql >> TWLOG) + ys) * (TW + dx) + (ql & (TW - 1));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) baddr[dx][hh][v] = 8192 + rl * 128 + ((b_c ^ (((rl + v) & 3) << 1)) << 4) + 8 * (seg & 1);
+    }
+  S2Acc acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc.tap[0][e] = acc.tap[1][e] = acc.tap[2][e] = acc.bias[e] = 0.f;
+  const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+  const bool idle_wave = k0 + wave_m * 32 >= p.Mout || c0 + wave_n * 32 >= p.Cx;
+  const bool bias_wave = wave_n == 0 && by == 0 && tg == 1;
+
+  for (int t = 0; t < ntiles; ++t) {
+    wait_vm<0>();
+    wg_barrier();
+    fill_tile(t + 1, (t + 1) & 1);
+    if (idle_wave) continue;
+    uint32_t base = lds_ring + (t & 1) * SLOT;
+    asm volatile("" : "+s"(base));
+    uint32_t bp[2][2][4];
+#pragma unroll
+    for (int dx = 0; dx < 2; ++dx)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          bp[dx][hh][v] = base + baddr[dx][hh][v];
+          asm volatile("" : "+v"(bp[dx][hh][v]));  // constants ride in the instructions' offsets (see wgrad_dma_body)
+        }
+    uint32_t ybuf = base + a_lane;
+    asm volatile("" : "+v"(ybuf));
+    uint4 af[2], bf[2][3];
+    auto load_frags = [&](int ks, int set) {  // ks is a constant after unrolling
+      const int q0 = ks * 16;
+      const uint2 a0 = lds_tr16_at(ybuf + ks * 2048), a1 = lds_tr16_at(ybuf + ks * 2048 + 512);
+      af[set] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        const int dx = s == 1 ? 0 : 1, pw = TW + dx;
+        const int rc = (q0 >> (TWLOG + THLOG)) * ((TH + 1) * pw) + ((q0 >> TWLOG) & (TH - 1)) * pw + (q0 & (TW - 1)) + (s == 2 ? 1 : 0);
+        const uint2 b0 = lds_tr16_at(bp[dx][0][rc & 3] + rc * 128), b1 = lds_tr16_at(bp[dx][1][rc & 3] + rc * 128);
+        bf[set][s] = make_uint4(b0.x, b0.y, b1.x, b1.y);
+      }
+    };
+    load_frags(0, 0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks + 1 < 4) load_frags(ks + 1, (ks + 1) & 1);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) mfma16B<bf16_t>(af[ks & 1], bf[ks & 1][s], acc.tap[s]);
+      if (bias_wave) mfma16B<bf16_t>(af[ks & 1], ones, acc.bias);  // bias gradient: column sums of dY
+    }
+  }
+  wait_vm<0>();
+  wgrad_s2_store(p, acc, k0, c0, z, wave_m, wave_n, tg, lane, bias_wave);
 }
 
 // ------------------------------------------------------------------ the same weight gradients for any image size (bf16)
@@ -1792,10 +1927,126 @@ __device__ __forceinline__ void wgrad_flat_body(const WgradParams& p, const Wgra
   }
 }
 
-// Linear layers and 1x1 convolutions of stride 1 and 2 (bf16): no taps; tiles of 128 output pixels, the rest as above. Against
+// The same for any image size, on positions as in wgrad_flat_body: a plane of a tile holds the positions from 64 before ... the tile's first, less
+// one row of Q if dy (tap row 0) and less one if dx (tap column 0), on.
+struct S2Flat {
+  int rows[4], base[4], total;  // of the planes (dy, dx) = (0,0), (0,1), (1,0), (1,1)
+};
+__host__ __device__ inline S2Flat s2_flat(int Q) {
+  S2Flat f;
+  f.total = 0;
+  for (int d = 0; d < 4; ++d) {
+    f.rows[d] = (64 + (d >> 1) * Q + (d & 1) + 7) / 8 * 8;
+    f.base[d] = f.total;
+    f.total += f.rows[d];
+  }
+  return f;
+}
+__device__ __forceinline__ void wgrad_s2_flat_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
+  constexpr int NWV = 12;
+  const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const S2Flat pl = s2_flat(wg.Q);
+  const int slot_bytes = 8192 + pl.total * 128;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_m = wave & 1, wave_n = (wave >> 1) & 1, tg = wave >> 2;
+  const int k0 = bx * 64, c0 = by * 64;
+  const int q = p.nsplit / p.nrep;
+  const int zr = z / q, zj = z - zr * q;
+  const int tile0 = (int)(((long long)zj * wg.rep_tiles) / q);
+  const int ntiles = (int)(((long long)(zj + 1) * wg.rep_tiles) / q) - tile0;
+
+  const int l8 = lane >> 3;
+  const int c16 = ((lane & 7) ^ ((l8 & 3) << 1)) * 16;  // global 16-byte column for LDS slot lane&7 of a row with row&3 == l8&3
+  const char* zsrc = (const char*)p.zeros + c16;
+  const bool ycol_ok = k0 + (c16 >> 1) < p.ldy, xcol_ok = c0 + (c16 >> 1) < p.Cx;
+  const char* ybase = (const char*)p.dy + (size_t)k0 * 2 + c16;
+  const char* xbase = (const char*)p.x + (size_t)c0 * 2 + c16;
+  const uint32_t ybytes = (uint32_t)p.ldy * 2, xbytes = (uint32_t)p.Cx * 2;
+  const int img0 = zr * wg.imgs_rep;
+  auto fill_tile = [&](int t, int slot) {
+    if (t >= ntiles) return;
+    const int u0 = (tile0 + t) * 64;
+    const uint32_t base = lds_ring + slot * slot_bytes;
+    for (int f = wave; f < 8 + (pl.total >> 3); f += NWV) {  // eight fills of dY rows, then the planes: eight rows each
+      const int r = (f - 8) * 8;
+      const int d = r < pl.base[1] ? 0 : r < pl.base[2] ? 1 : r < pl.base[3] ? 2 : 3;  // wave-uniform
+      const int dy = f < 8 ? 0 : d >> 1, dx = f < 8 ? 0 : d & 1;
+      const int u = u0 + (f < 8 ? f * 8 : r - (d == 0 ? 0 : d == 1 ? pl.base[1] : d == 2 ? pl.base[2] : pl.base[3]) - dy * wg.Q - dx) + l8;
+      // position in the data-group -> image of the group, row, column of the output grid; none on the extra rows and columns
+      const uint32_t uu = (uint32_t)max(u, 0);
+      const int line = (int)(__umulhi(uu, wg.dQ.mul) >> wg.dQ.shift), w = (int)uu - line * wg.Q;
+      const int im = (int)(__umulhi((uint32_t)line, wg.dH.mul) >> wg.dH.shift), h = line - im * (p.Ho + 1) - 1;
+      bool ok = u >= 0 && w < p.Wo && h >= 0 && im < wg.imgs_rep;
+      const char* src = zsrc;
+      if (f < 8) {
+        if (ok && ycol_ok) src = ybase + (size_t)((uint32_t)(((img0 + im) * p.Ho + h) * p.Wo + w)) * ybytes;
+      } else {
+        const int hi = 2 * h + dy, wi = 2 * w + dx;
+        ok = ok && xcol_ok && hi < p.H && wi < p.W;
+        if (ok) src = xbase + (size_t)((uint32_t)(((img0 + im) * p.H + hi) * p.W + wi)) * xbytes;
+      }
+      dma16(src, base + f * 1024);
+    }
+  };
+  fill_tile(0, 0);
+
+  const int lq = lane & 15, grp16 = (lane >> 4) & 1, khalf = lane >> 5;  // fragment addressing as in wgrad_dma_body
+  const int rsub = lq >> 2, seg = lq & 3;
+  const int a_c = 4 * wave_m + 2 * grp16 + (seg >> 1), b_c = 4 * wave_n + 2 * grp16 + (seg >> 1);
+  const int a_lane = (8 * khalf + rsub) * 128 + ((a_c ^ (rsub << 1)) << 4) + 8 * (seg & 1);
+  int baddr[2][3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int plane = tg == 1 ? (s == 1 ? pl.base[0] : pl.base[1]) : (s == 1 ? pl.base[2] : pl.base[3]);
+      const int row = plane + 8 * khalf + rsub + 4 * hh + (tg == 2 ? wg.Q : 0) + (s == 2 ? 1 : 0);
+      baddr[hh][s] = 8192 + row * 128 + ((b_c ^ ((row & 3) << 1)) << 4) + 8 * (seg & 1);
+    }
+  S2Acc acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc.tap[0][e] = acc.tap[1][e] = acc.tap[2][e] = acc.bias[e] = 0.f;
+  const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+  const bool idle_wave = k0 + wave_m * 32 >= p.Mout || c0 + wave_n * 32 >= p.Cx;
+  const bool bias_wave = wave_n == 0 && by == 0 && tg == 1;
+
+  for (int t = 0; t < ntiles; ++t) {
+    wait_vm<0>();
+    wg_barrier();
+    fill_tile(t + 1, (t + 1) & 1);
+    if (idle_wave) continue;
+    const uint32_t base = lds_ring + (t & 1) * slot_bytes;
+    uint32_t bp[2][3];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) { bp[0][s] = base + baddr[0][s]; bp[1][s] = base + baddr[1][s]; }
+    uint4 af[2], bf[2][3];
+    auto load_frags = [&](int ks, int set) {
+      const uint2 a0 = lds_tr16_at(base + a_lane + ks * 2048), a1 = lds_tr16_at(base + a_lane + ks * 2048 + 512);
+      af[set] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        const uint2 b0 = lds_tr16_at(bp[0][s] + ks * 2048), b1 = lds_tr16_at(bp[1][s] + ks * 2048);
+        bf[set][s] = make_uint4(b0.x, b0.y, b1.x, b1.y);
+      }
+    };
+    load_frags(0, 0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      if (ks + 1 < 4) load_frags(ks + 1, (ks + 1) & 1);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) mfma16B<bf16_t>(af[ks & 1], bf[ks & 1][s], acc.tap[s]);
+      if (bias_wave) mfma16B<bf16_t>(af[ks & 1], ones, acc.bias);  // bias gradient: column sums of dY
+    }
+  }
+  wait_vm<0>();
+  wgrad_s2_store(p, acc, k0, c0, z, wave_m, wave_n, tg, lane, bias_wave);
+}
+
+// Linear layers and 1x1 convolutions of stride 1 and 2 (bf16): no taps; tiles of 128 output pixels, four waves, the rest as above. Against
 // operands transposed in registers (wgrad_gemm_kernel), each launch alone, a net of three linear layers: 512 -> 512 in the middle at
 // 16 / 512 / 4096 rows 32 / 44 / 58 -> 22 / 23 / 33 us, 2048 -> 32 at 16384 rows 120 -> 65 us. A head shares the launch of its module's
-// stride-2 layers, where the old kernel took 11 to 16 us with one to twelve workgroups.
+// shortcuts, where the old kernel took 11 to 16 us with one to twelve workgroups.
 __device__ __forceinline__ void wgrad_rows_body(const WgradParams& p, const WgradGeom& wg, char* smem, int bx, int by, int z) {
   constexpr int SLOT = 32768;
   const uint32_t lds_ring = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
@@ -1874,8 +2125,8 @@ __device__ __forceinline__ void wgrad_rows_body(const WgradParams& p, const Wgra
   }
 }
 
-// One launch takes several layers (3x3 ones of stride 1, or those of stride 2 and 1x1 ones): workgroup -> (layer, k-block, sub-pixel / c-block,
-// split). Every (k, c) block of one split reads the same dY rows and X patches, so they should meet in one L2: workgroups are
+// One launch takes several layers (3x3 ones of either stride, or 1x1 ones and those of stride 2 with long rows): workgroup -> (layer, k-block,
+// sub-pixel / c-block, split). Every (k, c) block of one split reads the same dY rows and X patches, so they should meet in one L2: workgroups are
 // handed to the eight XCDs round-robin in launch order, hence launch index i lands on XCD i % 8 as the (i / 8)-th workgroup
 // of that XCD. Where the split count is a multiple of eight, XCD x takes the splits z = x (mod 8) and runs all blocks of
 // a split back to back, so they are resident together and walk the pixel tiles at the same pace (a layer's workgroups start at a
@@ -1883,7 +2134,7 @@ __device__ __forceinline__ void wgrad_rows_body(const WgradParams& p, const Wgra
 struct WgradLayer {
   WgradParams p;
   WgradGeom g;
-  int tiling;  // 0..3: wgrad_dma_body for rows of 32, 16, 8, 4 pixels; 4: wgrad_flat_body; 5: wgrad_rows_body
+  int tiling;  // 0..3: wgrad_dma_body for rows of 32, 16, 8, 4 pixels; 4: wgrad_flat_body; 5: wgrad_rows_body; 6..9: wgrad_s2_dma_body, 10: wgrad_s2_flat_body
   int first;   // first workgroup
   int gx, gy;  // k-blocks, (sub-pixel, c-block) pairs
 };
@@ -1893,8 +2144,8 @@ struct WgradGroup {
 };
 static_assert(sizeof(WgradGroup) <= 4096, "kernel arguments");
 
-template <bool S2>
-__global__ __launch_bounds__(S2 ? 256 : 768, S2 ? 2 : 1) void wgrad_tiles_kernel(WgradGroup grp) {
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) void wgrad_tiles_kernel(WgradGroup grp) {
   extern __shared__ __align__(16) char smem[];
   int li = 0;
   while (li + 1 < grp.n && (int)blockIdx.x >= grp.layer[li + 1].first) ++li;
@@ -1905,14 +2156,22 @@ __global__ __launch_bounds__(S2 ? 256 : 768, S2 ? 2 : 1) void wgrad_tiles_kernel
   const int j = lin >> xcds;
   const int z = ((j / nblk) << xcds) + (lin & ((1 << xcds) - 1)), blk = j % nblk;
   const int bx = blk % l.gx, by = blk / l.gx;
+  if (WAVES == 4) {
+    if (l.tiling == 4) wgrad_flat_body<true>(l.p, l.g, smem, bx, by, z);
+    else wgrad_rows_body(l.p, l.g, smem, bx, by, z);
+    return;
+  }
   switch (l.tiling) {
-    case 0: wgrad_dma_body<5, 2, S2>(l.p, l.g, smem, bx, by, z); break;
-    case 1: wgrad_dma_body<4, 3, S2>(l.p, l.g, smem, bx, by, z); break;
-    case 2: wgrad_dma_body<3, 3, S2>(l.p, l.g, smem, bx, by, z); break;
-    case 3: wgrad_dma_body<2, 2, S2>(l.p, l.g, smem, bx, by, z); break;
-    case 4: wgrad_flat_body<S2>(l.p, l.g, smem, bx, by, z); break;
-    default:
-      if (S2) wgrad_rows_body(l.p, l.g, smem, bx, by, z);
+    case 0: wgrad_dma_body<5, 2>(l.p, l.g, smem, bx, by, z); break;
+    case 1: wgrad_dma_body<4, 3>(l.p, l.g, smem, bx, by, z); break;
+    case 2: wgrad_dma_body<3, 3>(l.p, l.g, smem, bx, by, z); break;
+    case 3: wgrad_dma_body<2, 2>(l.p, l.g, smem, bx, by, z); break;
+    case 4: wgrad_flat_body<false>(l.p, l.g, smem, bx, by, z); break;
+    case 6: wgrad_s2_dma_body<5, 1>(l.p, l.g, smem, bx, by, z); break;
+    case 7: wgrad_s2_dma_body<4, 2>(l.p, l.g, smem, bx, by, z); break;
+    case 8: wgrad_s2_dma_body<3, 3>(l.p, l.g, smem, bx, by, z); break;
+    case 9: wgrad_s2_dma_body<2, 2>(l.p, l.g, smem, bx, by, z); break;
+    case 10: wgrad_s2_flat_body(l.p, l.g, smem, bx, by, z); break;
   }
 }
 
@@ -2126,23 +2385,25 @@ int launch_conv_one(const ConvParams& p, hipStream_t s) {
   return 0;
 }
 
-// bf16 problems of whole 128-pixel tiles per data-group (nrep of them) go to wgrad_dma_body: 3x3 stride 1 pad 1, and the
-// stride-2 ones on even-sized images. Returns its tiling, -1 if it is none of them.
+// bf16 problems of whole tiles (128 pixels, 64 at stride 2) per data-group (nrep of them) go to wgrad_dma_body (3x3 stride 1 pad 1) and
+// wgrad_s2_dma_body (3x3 stride 2 pad 1 on even-sized images). Returns the tiling, -1 if it is none of them.
 int wgrad_dma_tiling(const WgradParams& p, int nrep, int* tiles_h) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
   const bool s2 = p.R == 3 && p.S == 3 && p.stride == 2 && p.pad == 1 && p.H == 2 * p.Ho && p.W == 2 * p.Wo;
   if (!s1 && !s2) return -1;
-  if (nrep < 1 || p.P % (128 * nrep) != 0) return -1;
+  const int tile_log = s2 ? 6 : 7;
+  if (nrep < 1 || p.P % ((1 << tile_log) * nrep) != 0) return -1;
   if (p.Cx % 8 != 0 || (p.Cx > 64 && p.Cx % 64 != 0) || p.zeros == nullptr) return -1;
   // byte offsets of patch rows relative to the tile origin are 32-bit
   if ((long long)(128 + 2 * p.W + 4) * 4 * p.Cx * 2 >= (1ll << 31) || p.Cx * 2 + 256 > kZeroBytes) return -1;
   const int lw = ilog2_exact(p.Wo), lh = ilog2_exact(p.Ho);
   if (lw < 2 || lh < 0 || p.Wo > 32) return -1;
-  int th_log;
-  if (p.Ho * p.Wo >= 128) { th_log = 7 - lw; *tiles_h = p.Ho >> th_log; if (th_log > lh) return -1; }
+  int th_log;  // rows of a tile
+  if (lw + lh >= tile_log) { th_log = tile_log - lw; *tiles_h = p.Ho >> th_log; }
   else { th_log = lh; *tiles_h = 1; }
-  if (!((lw == 5 && th_log == 2) || (lw == 4 && th_log == 3) || (lw == 3 && th_log == 3) || (lw == 2 && th_log == 2))) return -1;
-  return 5 - lw;
+  const int want = s2 ? (lw == 5 ? 1 : lw == 4 ? 2 : lw == 3 ? 3 : 2) : (lw == 5 ? 2 : lw == 4 ? 3 : lw == 3 ? 3 : 2);
+  if (th_log != want) return -1;
+  return (s2 ? 6 : 0) + 5 - lw;
 }
 
 // Sub-pixels of a 3x3 stride-2 layer in launch order and the real tap of (virtual tap, sub-pixel offset): rows 2oy-1, 2oy, 2oy+1
@@ -2152,22 +2413,30 @@ int wgrad_s2_taps(int (&sub)[4], int (&rmap)[2][2]) {
   return 4;
 }
 
-// 3x3 pad 1, stride 1 and 2, of any image size: wgrad_flat_body. False: not one of them.
-bool wgrad_flat_geometry(const WgradParams& p, int nrep, WgradGeom& wg) {
+// 3x3 pad 1, stride 1 and 2, of any image size: wgrad_flat_body, wgrad_s2_flat_body. Returns the tiling, -1: not one of them.
+int wgrad_flat_geometry(const WgradParams& p, int nrep, WgradGeom& wg, int* slot) {
   const bool s1 = p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.H == p.Ho && p.W == p.Wo;
   const bool s2 = p.R == 3 && p.S == 3 && p.stride == 2 && p.pad == 1 && p.Ho == (p.H + 1) / 2 && p.Wo == (p.W + 1) / 2;
-  if ((!s1 && !s2) || nrep < 1 || p.Nimg % nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return false;
-  if (p.zeros == nullptr) return false;
+  if ((!s1 && !s2) || nrep < 1 || p.Nimg % nrep != 0 || p.Cx % 8 != 0 || p.ldy % 8 != 0) return -1;
+  if (p.zeros == nullptr) return -1;
   wg.Q = p.Wo + 1;
   wg.imgs_rep = p.Nimg / nrep;
   const long long positions = (long long)wg.imgs_rep * (p.Ho + 1) * wg.Q;
-  if (positions + 128 + 2 * wg.Q >= (1ll << 31) || (long long)p.Nimg * p.H * p.W >= (1ll << 31)) return false;
-  wg.rep_tiles = (int)((positions + 127) / 128);
-  wg.patch_rows = (128 + (s2 ? wg.Q + 1 : 2 * wg.Q + 2) + 7) / 8 * 8;
-  if (2 * (16384 + wg.patch_rows * 128) > 160 * 1024) return false;  // rows of at most 190 (stride 2: 382) output pixels
+  if (positions + 128 + 2 * wg.Q >= (1ll << 31) || (long long)p.Nimg * p.H * p.W >= (1ll << 31)) return -1;
   wg.dQ = make_divisor(wg.Q);
   wg.dH = make_divisor(p.Ho + 1);
-  return true;
+  // Four planes of a tile in two slots: rows of at most 151 output pixels at stride 2. Longer ones are taken a sub-pixel at a time, where dY is copied
+  // for each but a tile's rows above the image row are a quarter.
+  if (s2 && 2 * (8192 + s2_flat(wg.Q).total * 128) <= 160 * 1024) {
+    wg.patch_rows = s2_flat(wg.Q).total;
+    wg.rep_tiles = (int)((positions + 63) / 64);
+    *slot = 8192 + wg.patch_rows * 128;
+    return 10;
+  }
+  wg.rep_tiles = (int)((positions + 127) / 128);
+  wg.patch_rows = (128 + (s2 ? wg.Q + 1 : 2 * wg.Q + 2) + 7) / 8 * 8;
+  *slot = 16384 + wg.patch_rows * 128;
+  return 2 * *slot <= 160 * 1024 ? 4 : -1;  // rows of at most 190 (stride 2: 382) output pixels
 }
 
 // The layer's part of a launch of wgrad_tiles_kernel but for its place in it (p.nrep is looked at, p.nsplit and the pointers but
@@ -2188,24 +2457,30 @@ bool wgrad_layer(const WgradParams& p, WgradLayer& l, int* rep_tiles, int* smem)
     return true;
   }
   l.tiling = wgrad_dma_tiling(p, p.nrep, &l.g.tiles_h);
-  int rows;
-  if (l.tiling >= 0) {
-    const int tw = p.Wo, th = p.Ho * p.Wo >= 128 ? 128 / tw : p.Ho;
-    rows = ((128 / (tw * th)) * (th + 2) * (tw + 2) + 7) / 8 * 8;
-    *rep_tiles = p.P / (128 * p.nrep);
-  } else {
-    l.tiling = 4;
-    if (!wgrad_flat_geometry(p, p.nrep, l.g)) return false;
-    rows = l.g.patch_rows;
-    *rep_tiles = l.g.rep_tiles;
+  int slot;
+  switch (l.tiling) {
+    case 6: slot = 8192 + S2Tile<5, 1>::patch * 128; break;
+    case 7: slot = 8192 + S2Tile<4, 2>::patch * 128; break;
+    case 8: slot = 8192 + S2Tile<3, 3>::patch * 128; break;
+    case 9: slot = 8192 + S2Tile<2, 2>::patch * 128; break;
+    case -1:
+      l.tiling = wgrad_flat_geometry(p, p.nrep, l.g, &slot);
+      if (l.tiling < 0) return false;
+      break;
+    default: {
+      const int tw = p.Wo, th = p.Ho * p.Wo >= 128 ? 128 / tw : p.Ho;
+      slot = 16384 + ((128 / (tw * th)) * (th + 2) * (tw + 2) + 7) / 8 * 8 * 128;
+    }
   }
-  *smem = 2 * (16384 + rows * 128);  // two slots
-  if (p.stride == 2) l.gy *= wgrad_s2_taps(l.g.sub, l.g.rmap);
+  if (l.tiling == 4 || l.tiling == 10) *rep_tiles = l.g.rep_tiles;
+  else *rep_tiles = p.P / ((l.tiling < 4 ? 128 : 64) * p.nrep);
+  *smem = 2 * slot;
+  if (l.tiling == 4 && p.stride == 2) l.gy *= wgrad_s2_taps(l.g.sub, l.g.rmap);
   return true;
 }
 
 // Waves of a workgroup: which of the two kernels takes the layer.
-inline int wgrad_waves(const WgradParams& p) { return p.stride == 2 || p.R == 1 ? 4 : 12; }
+inline int wgrad_waves(const WgradParams& p, const WgradLayer& l) { return l.tiling == 5 || (l.tiling == 4 && p.stride == 2) ? 4 : 12; }
 
 // False: not taken, nothing launched.
 bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
@@ -2215,7 +2490,7 @@ bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) {
     WgradLayer& l = g.layer[i];
     int tiles = 0, need = 0;
-    if (p[i].nrep < 1 || p[i].nsplit % p[i].nrep != 0 || wgrad_waves(p[i]) != wgrad_waves(p[0]) || !wgrad_layer(p[i], l, &tiles, &need)) return false;
+    if (p[i].nrep < 1 || p[i].nsplit % p[i].nrep != 0 || !wgrad_layer(p[i], l, &tiles, &need) || wgrad_waves(p[i], l) != wgrad_waves(p[0], g.layer[0])) return false;
     const int q = p[i].nsplit / p[i].nrep;
     if (q < 1 || q > tiles) return false;  // no empty split
     l.first = wgs;
@@ -2224,12 +2499,12 @@ bool launch_wgrad_tiles(const WgradParams* p, int n, hipStream_t s) {
   }
   g.n = n;
   static DeviceOnce lds[2];
-  if (wgrad_waves(p[0]) == 4) {
-    allow_whole_lds(lds[1], (const void*)wgrad_tiles_kernel<true>);
-    wgrad_tiles_kernel<true><<<wgs, 256, smem, s>>>(g);
+  if (wgrad_waves(p[0], g.layer[0]) == 4) {
+    allow_whole_lds(lds[1], (const void*)wgrad_tiles_kernel<4>);
+    wgrad_tiles_kernel<4><<<wgs, 256, smem, s>>>(g);
   } else {
-    allow_whole_lds(lds[0], (const void*)wgrad_tiles_kernel<false>);
-    wgrad_tiles_kernel<false><<<wgs, 768, smem, s>>>(g);
+    allow_whole_lds(lds[0], (const void*)wgrad_tiles_kernel<12>);
+    wgrad_tiles_kernel<12><<<wgs, 768, smem, s>>>(g);
   }
   return true;
 }
@@ -2292,7 +2567,7 @@ WgradWork wgrad_work(int dt, const WgradParams& shape) {
     w.key += 4;
   } else if (wgrad_layer(shape, l, &w.tiles, &smem)) {
     w.blocks = l.gx * l.gy;
-    w.key = wgrad_waves(shape) == 4 ? 2 : 1;
+    w.key = wgrad_waves(shape, l) == 4 ? 2 : 1;
   }
   return w;
 }
@@ -2337,8 +2612,8 @@ void wgrad_choose_splits(int dt, const WgradParams* shapes, int n, bool one_modu
   // Workgroups of the launch. The partial sums cost HBM traffic in proportion to the split counts (written here, read by the
   // update), and a workgroup of the wide kernel keeps others of its kind off the CU: half of the chip, three quarters where each
   // has 32 tiles all the same. ms per 8 steps with 128 / 192 / 256: ResNet-18 in four modules 17.3 / 17.0 / 17.4, 64 images of it 4.3 /
-  // 4.4 / 4.6; ResNet-20 in one module 3.50 / 3.58 / 3.59. A stride-2 workgroup has four waves where a stride-1 one has twelve, and the
-  // four sub-pixels of a 3x3 kernel carry 4 : 2 : 2 : 1 taps: twice as many, or two rounds where rows are so long that one takes
+  // 4.4 / 4.6; ResNet-20 in one module 3.50 / 3.58 / 3.59. A workgroup of 1x1 layers has four waves where one of 3x3 layers has twelve, and of
+  // stride-2 layers of long rows the four sub-pixels carry 4 : 2 : 2 : 1 taps: twice as many, or two rounds where rows are so long that one takes
   // more than half of a CU's LDS and 384 would be one and a half (128 -> 128 channels from 512 x 512 pixels, two images, 453 -> 270 us). A stride-1 layer that
   // shares its launch with no other has no launch to save its partial sums for: the chip (3 -> 256 channels at 32 x 32, 62
   // images, 128 / 256: 30.7 / 19.0 us), but not where other modules want it too (a net of 32 and 64 channels in two modules, us per 8

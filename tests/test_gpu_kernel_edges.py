@@ -261,6 +261,15 @@ def test_stride2_weight_gradients_longest_rows(w):
     _compare(_stride2_net(16, 16, 3, 2, w, 1, 2), seed=35, T=2)
 
 
+@pytest.mark.parametrize("c1,c2,h,w,W,B", [
+    (64, 64, 64, 64, 1, 1), (16, 32, 32, 32, 1, 3), (64, 128, 16, 16, 2, 3), (128, 200, 8, 8, 1, 4), (24, 72, 32, 16, 3, 1), (64, 64, 16, 64, 1, 2),
+    (40, 64, 4, 302, 1, 2), (40, 64, 4, 303, 1, 2)])
+def test_stride2_weight_gradients_by_tile(c1, c2, h, w, W, B):
+    # tiles of two rows of 32, four of 16, an image of 8 x 8, four of 4 x 4; data-groups of a single tile; one tile after another down an image; the
+    # longest rows whose four planes fit twice and the first that are taken a sub-pixel at a time
+    _compare(_stride2_net(c1, c2, 3, h, w, W, B), seed=52, T=2)
+
+
 def test_shared_reductions_with_weights_per_data_group():
     # four data-groups of 256 or more pixels in one launch of few tiles: both kernels whose 64 x 64 tiles two halves of a workgroup
     # share, forward and input gradients (3x3 at 8 x 8 and 4 x 4, stride 2 with the folded shortcut)
