@@ -1,4 +1,4 @@
-// Runs of consecutive 3x3 stride-1 layers of equal width (16, 32 or 64 channels), bf16, in one launch: forward or input gradient.
+// Runs of consecutive 3x3 stride-1 layers of equal width (16 to 128 channels), bf16, in one launch: forward or input gradient.
 //
 // An image of these layers fits in LDS (32 KB at 32 x 32 x 16, 16 x 16 x 32 takes 16 KB, 8 x 8 x 64 takes 8 KB), and nothing but the
 // weights ties one image to another: a workgroup reads whole images once, takes them through every layer of the run and only
@@ -391,6 +391,223 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
   store_out(p.n & 1 ? (int)g.buf_bytes : 0, prev_y, prev_bits);
 }
 
+// Wider layers, whose image fits in LDS once: 64 channels at up to 1024 pixels, 128 at up to 256. The outputs of a layer wait in the accumulators
+// until every wave has read its last operand, then take the input's place. A wave owns 64 output channels of RUNS runs of 16 pixels; a stage is half
+// of a tap's input channels (18 a layer, 32 MFMAs of a wave at full size). Its weights travel in a ring of four slots, four stages ahead;
+// the fragments of the next stage are read into registers during this one, so that between a stage's barrier and its first product lies
+// nothing. What a residual layer adds is read from memory again, where this lane (or the launch before) wrote it. Lanes whose run ends past the
+// last pixel repeat it: they compute and write the same values.
+// us a layer and pass, a launch a layer / here: 64 channels at 32 x 32, 256 images 28 / 24, 512 images 52 / 45; 128 channels at 16 x 16, 256 images
+// 32 / 19, 512 images 45 / 38, of which the matrix unit is busy for 8 an image. The rest goes to 18 barriers and an epilogue that waits for its
+// residual and signs and for room among the stores. Stores spread over the next layer's stages, with the residual asked for in the last ones, took
+// registers that 64 channels do not have (32 us at 256 images) and gave nothing at 128 channels.
+struct WideGeom {
+  int imgs;
+  uint32_t plane, buf_bytes;
+  Divisor dP, dQ, dH1, dW, dH;
+};
+
+template <int C, int RUNS, bool DGRAD>
+__global__ __launch_bounds__(64 * kWaves, 2) void conv_wide_chain_kernel(ChainParams p, WideGeom g) {
+  constexpr int PB = 2 * C, NBLK = C / 16, WN = C / 64, WM = kWaves / WN;
+  constexpr int KPS = C / 64;                       // 32-channel steps of a stage
+  constexpr int SLOT = KPS * NBLK * 1024;           // fragments of a stage
+  constexpr int FILLS = C == 64 ? 1 : 2;            // copies of a wave: every other stage (C == 64), or two a stage
+  constexpr int YOUNGER = C == 64 ? 1 : 2 * FILLS;  // copies of a wave behind the ones that a stage waits for
+  extern __shared__ __align__(16) char smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int HW = p.H * p.W, Q = p.W + 1;
+  const int img0 = blockIdx.x * g.imgs, imgs = min(g.imgs, p.Nimg - img0);
+  const int pixels = imgs * HW;
+  const size_t pix0 = (size_t)img0 * HW;  // the workgroup's images are consecutive pixels of every tensor
+  const int wrep = p.nrep > 1 ? img0 / (p.Nimg / p.nrep) : 0;
+  const size_t wrep_off = (size_t)wrep * p.w_rep;
+  const int plane = (int)g.plane, row = Q * 32;
+  const uint32_t ring = lds0 + g.buf_bytes;
+
+  auto opaque = [](int v) { asm volatile("" : "+v"(v)); return v; };
+  auto chan_of = [](int b, int r) { return 32 * (b >> 1) + 8 * (r >> 2) + 4 * (b & 1) + (r & 3); };  // as in conv_chain_kernel
+  const int wblock = chan_of(C == 64 ? wave & 3 : wave, 0) * 9 * PB;
+  auto fill_stage = [&](const void* w, int t, int slot) {  // stage t of a layer
+    const int tap = DGRAD ? 8 - (t >> 1) : t >> 1;
+    const int l = opaque(lane);  // (formed here: kept, it would go to scratch memory, and a read of that waits for every copy)
+    const uint32_t wlane = (uint32_t)(chan_of(0, l & 15) * 9 * PB + (l >> 4) * 16);
+    const uint64_t from = (uint64_t)w + wrep_off + (uint32_t)(wblock + tap * PB + (t & 1) * C);  // (uniform, which the compiler loses track of)
+    const char* base = (const char*)((uint64_t)__builtin_amdgcn_readfirstlane((int)(from >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)from));
+    if (C == 64) {
+      if (wave >> 2 == (t & 1)) dma16s(base, wlane, ring + slot * SLOT + (wave & 3) * 1024);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KPS; ++k) dma16s(base + k * 64, wlane, ring + slot * SLOT + (k * NBLK + wave) * 1024);
+    }
+  };
+  {
+    const char* base = (const char*)p.x + pix0 * PB;
+    for (int f = wave; f < (int)(g.buf_bytes >> 10); f += kWaves) {
+      const uint32_t piece = f * 64 + lane, pl = divide(piece, g.dP), in_plane = piece - pl * (uint32_t)(plane >> 4);
+      const uint32_t u = in_plane >> 1, line = divide(u, g.dQ), im = divide(line, g.dH1);
+      const int w = (int)(u - line * Q) - 1, h = (int)(line - im * (p.H + 1)) - 1;
+      const bool in = w >= 0 && h >= 0 && (int)im < imgs && pl < NBLK;
+      const char* at = base + (uint32_t)((im * HW + h * p.W + w) * PB + pl * 32 + (in_plane & 1) * 16);
+      dma16(in ? at : (const char*)p.zeros, lds0 + f * 1024);
+    }
+  }
+  ChainLayer L = p.layer[0];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) fill_stage(L.w, t, t);
+
+  int at[RUNS];  // as in conv_chain_kernel; the tap row moves it
+#pragma unroll
+  for (int u = 0; u < RUNS; ++u) {
+    const uint32_t n = (uint32_t)min((wm + WM * u) * 16 + j, pixels - 1);
+    const uint32_t line = divide(n, g.dW), im = divide(line, g.dH);
+    at[u] = (int)(lds0 + ((line + im + 1) * Q + (n - line * p.W) + 1) * 32) - row - 32 + (q & 1) * 16 + (q >> 1) * plane;
+  }
+  const int own = row + 32 + wn * 4 * plane;
+  auto load_bias = [&](const ChainLayer& l, f32x4_t (&b)[4]) {
+    const float* from = l.bias ? l.bias + (size_t)wrep * p.bias_rep : (const float*)p.zeros;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i] = *(const f32x4_t*)(from + chan_of(wn * 4 + i, 4 * q));
+  };
+  f32x4_t start[4] = {};
+  if (!DGRAD) load_bias(L, start);
+  wait_vm<0>();
+  wg_barrier();
+
+  constexpr int G = RUNS < 2 ? 1 : 2, NG = (RUNS + G - 1) / G, ITEMS = KPS * NG;  // items of a stage: steps, within them groups of runs
+  uint4 x[2][G], w[2][KPS][4];
+  auto read_weights = [&](int slot, uint4 (&v)[KPS][4]) {
+#pragma unroll
+    for (int k = 0; k < KPS; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[k][i] = lds_read16(ring + slot * SLOT + (k * NBLK + wn * 4 + i) * 1024 + lane * 16);
+  };
+  read_weights(0, w[0]);
+  int slot = 0;
+  const void *before = p.res, *input = p.x;  // what the layer before read, what this one does
+  for (int l = 0; l < p.n; ++l) {
+    const bool more = l + 1 < p.n;
+    const ChainLayer next = p.layer[more ? l + 1 : l];
+    f32x4_t acc[RUNS][4];
+    auto request = [&](int i, int item, uint4 (&v)[G]) {  // stage 6 a + i: tap column i / 2, half i % 2 of the channels
+      const int ks = (i & 1) * KPS + item / NG;
+#pragma unroll
+      for (int k = 0; k < G; ++k) {
+        const int u = item % NG * G + k;
+        if (u < RUNS) v[k] = lds_read16((ks == 0 ? at[u] : opaque(at[u]) + ks * 2 * plane) + 32 * (i >> 1));
+      }
+    };
+    request(0, 0, x[0]);
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u)
+#pragma unroll
+      for (int n = 0; n < 4; ++n) acc[u][n] = start[n];
+#pragma unroll 1
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        // Everyone has read this stage's weights, and the next stage's are there: copied four stages ahead. (In order: behind them this wave's copies
+        // of two more stages and, at a layer's first three, the stores of the layer before.)
+        if (a == 0 && i < 3 && l > 0) wait_vm<YOUNGER + 2 * RUNS>();
+        else if (i >= 3 && a == 2 && !more) wait_vm<0>();  // (nothing is copied any more)
+        else wait_vm<YOUNGER>();
+        wg_barrier();
+        const int t = a * 6 + i + 4;
+        if (t < 18) fill_stage(L.w, t, slot);
+        else if (more) fill_stage(next.w, t - 18, slot);
+        slot = (slot + 1) & 3;
+        read_weights(slot, w[(i + 1) & 1]);
+#pragma unroll
+        for (int item = 0; item < ITEMS; ++item) {
+          const int cur = i * ITEMS + item;
+          if (item + 1 < ITEMS) request(i, item + 1, x[(cur + 1) & 1]);
+          else if (i < 5) request(i + 1, 0, x[(cur + 1) & 1]);
+          else {
+#pragma unroll
+            for (int u = 0; u < RUNS; ++u) at[u] = opaque(at[u] + row);
+            if (a < 2) request(0, 0, x[(cur + 1) & 1]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < G; ++k) {
+            const int u = item % NG * G + k;
+            if (u >= RUNS) continue;
+#pragma unroll
+            for (int n = 0; n < 4; ++n) acc[u][n] = mfma16(w[i & 1][item / NG][n], x[cur & 1][k], acc[u][n]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u) at[u] = opaque(at[u] - 3 * row);
+
+    // epilogue: a run at a time, what it needs from memory asked for a run ahead
+    const float lower = !DGRAD && L.relu ? 0.f : -__builtin_inff();
+    const char* res = (const char*)before + pix0 * PB;
+    const char* mask = DGRAD ? (const char*)L.maskbits + pix0 * (C / 8) : nullptr;
+    const int n0 = opaque(wm * 16 + j);
+    auto pixel = [&](int u) { return min(opaque(n0) + WM * 16 * u, pixels - 1); };
+    uint4 r[2][2];
+    uint32_t keep[2][2];
+    auto ask = [&](int u, int set) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        if (L.add) r[set][b] = *(const uint4*)(res + (uint32_t)(pixel(u) * PB + wn * 128 + b * 64 + q * 16));
+        if (DGRAD) keep[set][b] = L.maskbits ? *(const uint8_t*)(mask + (uint32_t)(pixel(u) * (C / 8) + wn * 8 + b * 4 + q)) : 0xffu;
+      }
+    };
+    ask(0, 0);
+    wg_barrier();  // every wave has read its last operand
+    char* y = (char*)L.y + pix0 * PB;
+    char* bits = !DGRAD && L.bits_out ? (char*)L.bits_out + pix0 * (C / 8) : nullptr;
+#pragma unroll
+    for (int u = 0; u < RUNS; ++u) {
+      const int set = u & 1;
+      if (u + 1 < RUNS) ask(u + 1, set ^ 1);
+      else if (!DGRAD) load_bias(next, start);  // (the last layer: its own again)
+      {
+        const int n = pixel(u);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = L.alpha * acc[u][2 * b + (e >> 2)][e & 3];
+          if (L.add) {
+            const uint32_t rr[4] = {r[set][b].x, r[set][b].y, r[set][b].z, r[set][b].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += __uint_as_float(e & 1 ? rr[e >> 1] & 0xffff0000u : rr[e >> 1] << 16);
+          }
+          if (!DGRAD)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = __builtin_amdgcn_fmed3f(v[e], lower, __builtin_inff());  // one instruction; NaN -> lower
+          uint32_t o[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = pack_bf16_rne(v[2 * e], v[2 * e + 1]);
+          if (DGRAD) {  // bits 2 e and 2 e + 1 of the signs -> 0 / 1 in either half of a pair
+            const uint32_t k2 = keep[set][b] | keep[set][b] << 15;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = keep2(o[e], (k2 >> (2 * e)) & 0x00010001u);
+          }
+          lds_write16(at[u] + own + b * 2 * plane, o[0], o[1], o[2], o[3]);
+          *(uint4*)(y + (uint32_t)(n * PB + wn * 128 + b * 64 + q * 16)) = make_uint4(o[0], o[1], o[2], o[3]);
+          if (!DGRAD && bits) {  // pair e's low half belongs to bit 2 e, its high half (bit 16) to bit 2 e + 1; behind a ReLU nothing is negative
+            const uint32_t t = nonzero2(o[0]) | nonzero2(o[1]) << 2 | nonzero2(o[2]) << 4 | nonzero2(o[3]) << 6;
+            *(uint8_t*)(bits + (uint32_t)(n * (C / 8) + wn * 8 + b * 4 + q)) = (uint8_t)(t | t >> 15);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    before = input;
+    input = L.y;
+    L = next;
+    wg_barrier();
+  }
+}
+
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 int plane_bytes(int H, int W, int imgs) { return ((imgs * (H + 1) + 1) * (W + 1) + 1) * 32; }
@@ -416,6 +633,19 @@ void launch_inst(const ChainParams& p, const ChainGeom& g, int wgs, int smem, hi
   }
 }
 
+int wide_lds_bytes(int C, int H, int W, int imgs) { return buffer_bytes(C, H, W, imgs) + 4 * (C / 64) * (C / 16) * 1024; }
+template <int C, int RUNS>
+void launch_wide_inst(const ChainParams& p, const WideGeom& g, int wgs, int smem, hipStream_t s) {
+  static DeviceOnce lds[2];
+  if (p.dgrad) {
+    allow_whole_lds(lds[1], (const void*)conv_wide_chain_kernel<C, RUNS, true>);
+    conv_wide_chain_kernel<C, RUNS, true><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+  } else {
+    allow_whole_lds(lds[0], (const void*)conv_wide_chain_kernel<C, RUNS, false>);
+    conv_wide_chain_kernel<C, RUNS, false><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+  }
+}
+
 }  // namespace
 
 // Images of a workgroup: as few as fill the chip once; more share a copy of the weights.
@@ -433,6 +663,37 @@ static int images_of(int C, int H, int W, int Nimg, int nrep) {
   return imgs;
 }
 
+// The same of the wide kernel.
+static int wide_images_of(int C, int H, int W, int Nimg, int nrep) {
+  if ((C != 64 && C != 128) || H < 1 || W < 1 || Nimg < 1 || nrep < 1 || Nimg % nrep != 0 || (long long)H * W > 4096) return 0;
+  auto fits = [&](int imgs) {
+    return wide_lds_bytes(C, H, W, imgs) <= 160 * 1024 && cdiv(cdiv(imgs * H * W, 16), kWaves * 64 / C) <= (C == 64 ? 8 : 4);
+  };
+  int imgs = 0;
+  for (int i = 1; i <= 8 && fits(i) && (nrep == 1 || Nimg / nrep % i == 0); i *= 2) {
+    imgs = i;
+    if (cdiv(Nimg, i) <= 256) break;
+  }
+  return imgs;
+}
+static int wide_runs(int C, int H, int W, int imgs) { return cdiv(cdiv(imgs * H * W, 16), kWaves * 64 / C); }
+
+// Fewest layers of a wide run worth a shared launch. An image keeps its CU for the whole run, so the images have to fill the chip once (192 of 256
+// CUs and more) or twice (460 of 512). us per step of a net with two (four) such layers, a launch a layer / here: 64 channels at 32 x 32, 128 images 174
+// / 192 (273 / 291), 194 images 243 / 223 (397 / 359), 256 images 296 / 280 (455 / 401), 384 images 376 / 406 (612 / 627), 460 images 436 / 443
+// (719 / 679), 700 images 598 / 623 (974 / 1036); at 24 x 24, 256 images 214 / 182 (345 / 269), 384 images 287 / 295 (440 / 423), 512 images 348 /
+// 331 (540 / 471); 128 channels at 16 x 16, 128 images 160 / 160 (249 / 244), 256 images 261 / 227 (388 / 312), 512 images 380 / 343 (647 / 562), 1024 images 652
+// / 629 (1108 / 1050); at 12 x 12, 160 images 148 / 149 (228 / 218), 194 images 159 / 155 (256 / 238), 256 images 201 / 170 (325 / 253), 384 images 267 /
+// 278 (395 / 399), 512 images 317 / 286 (513 / 439), 700 images 359 / 371 (599 / 601); at 8 x 8, 128 images 92 / 107 (127 / 150), 194 images 120 / 113 (184 /
+// 159), 512 images 161 / 143 (253 / 205).
+static int wide_least(int C, int H, int W, int Nimg, int nrep) {
+  const int imgs = wide_images_of(C, H, W, Nimg, nrep);
+  if (imgs == 0) return 0;
+  const int wgs = cdiv(Nimg, imgs);
+  if (wgs < 192 || (wgs > 256 && wgs < 460) || wgs > 512) return 0;
+  return wgs > 256 && wide_runs(C, H, W, imgs) == 8 ? 4 : 2;
+}
+
 // us per step of a net with two (six) such layers in one module, a launch a layer / here, at the best of several runs: 16 channels at 32 x 32, 64
 // images 75 / 76, 194 images 98 / 90, 776 images 200 / 194; 32 channels at 16 x 16, 64 images 74 / 67, 776 images 138 / 128; 64 channels at 8 x
 // 8, 64 images 78 / 74, 776 images 124 / 112. Where one image takes more than half of a CU's LDS, two layers do not make up for a last
@@ -441,12 +702,35 @@ static int images_of(int C, int H, int W, int Nimg, int nrep) {
 // images 267 / 273 (527 / 504). Two such layers of 64 channels in either of two modules, 194 images of 14 x 14: 180 / 183.
 int conv_chain_least(int C, int H, int W, int Nimg, int nrep) {
   const int imgs = images_of(C, H, W, Nimg, nrep);
-  if (imgs == 0) return 0;
+  if (imgs == 0) return wide_least(C, H, W, Nimg, nrep);
   if (imgs > 1 || lds_bytes(C, H, W, 1) <= 80 * 1024) return 2;
   return Nimg < 64 && H * W > 640 ? 0 : 4;
 }
 
+static void launch_wide_chain(int C, const ChainParams& p, hipStream_t s) {
+  WideGeom g;
+  g.imgs = wide_images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1);
+  g.plane = plane_bytes(p.H, p.W, g.imgs);
+  g.buf_bytes = buffer_bytes(C, p.H, p.W, g.imgs);
+  g.dP = make_divisor1(g.plane / 16);
+  g.dQ = make_divisor1(p.W + 1);
+  g.dH1 = make_divisor1(p.H + 1);
+  g.dW = make_divisor1(p.W);
+  g.dH = make_divisor1(p.H);
+  const int wgs = cdiv(p.Nimg, g.imgs), smem = wide_lds_bytes(C, p.H, p.W, g.imgs);
+  const int runs = wide_runs(C, p.H, p.W, g.imgs);
+#define DDS_WIDE_CASE(C, RUNS) \
+  case (C) * 8 + (RUNS) - 1: launch_wide_inst<C, RUNS>(p, g, wgs, smem, s); break;
+  switch (C * 8 + runs - 1) {
+    DDS_WIDE_CASE(64, 2) DDS_WIDE_CASE(64, 3) DDS_WIDE_CASE(64, 4)
+    DDS_WIDE_CASE(64, 5) DDS_WIDE_CASE(64, 6) DDS_WIDE_CASE(64, 7) DDS_WIDE_CASE(64, 8)
+    DDS_WIDE_CASE(128, 1) DDS_WIDE_CASE(128, 2) DDS_WIDE_CASE(128, 3) DDS_WIDE_CASE(128, 4)
+  }
+#undef DDS_WIDE_CASE
+}
+
 void launch_conv_chain(int C, const ChainParams& p, hipStream_t s) {
+  if (images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1) == 0) return launch_wide_chain(C, p, s);
   ChainGeom g;
   g.imgs = images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1);
   g.buf_bytes = buffer_bytes(C, p.H, p.W, g.imgs);

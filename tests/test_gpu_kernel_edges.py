@@ -459,11 +459,12 @@ def test_weight_gradients_that_share_no_launch_run_beside_the_input_gradients(mo
 
 
 def _identity_blocks(c, blocks, h, w, W, B, cuts=()):
-    """A stem to c channels and residual blocks of that width; cuts: blocks that a module ends behind."""
+    """A stem to c channels and residual blocks of that width; cuts: blocks that a module ends behind. (Nine blocks added at 0.7 each end the first
+    step at a loss of 1e9, with every library.)"""
     ops, bounds = [{"op": "conv", "cin": 3, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"}], [0]
     for i in range(blocks):
         ops += [{"op": "res_begin"}, {"op": "conv", "cin": c, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
-                {"op": "conv", "cin": c, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "res_add", "scale": 0.7, "shortcut": None}, {"op": "relu"}]
+                {"op": "conv", "cin": c, "cout": c, "k": 3, "stride": 1, "pad": 1}, {"op": "res_add", "scale": 0.7 / blocks, "shortcut": None}, {"op": "relu"}]
         if i in cuts:
             bounds.append(len(ops))
     ops += [{"op": "gap"}, {"op": "linear", "cin": c, "cout": 10}, {"op": "softmax_ce"}]
@@ -482,7 +483,18 @@ def test_runs_of_narrow_layers_share_a_launch(c, blocks, h, w, W, B, cuts):
     _compare(_identity_blocks(c, blocks, h, w, W, B, cuts), seed=50, T=2 * len(cuts) + 2)
 
 
-@pytest.mark.parametrize("c,h,w,W,B", [(16, 9, 5, 3, 2), (32, 6, 6, 2, 130), (64, 4, 4, 2, 260), (64, 4, 4, 4, 131)])
+@pytest.mark.parametrize("c,blocks,h,w,W,B,cuts", [
+    (64, 2, 32, 32, 1, 192, ()), (64, 2, 31, 33, 1, 194, (0,)), (64, 1, 32, 32, 1, 461, ()), (64, 3, 17, 16, 1, 256, ()), (64, 1, 20, 21, 2, 100, ()), (64, 2, 1, 250, 1, 193, ()),
+    (64, 2, 32, 33, 1, 192, ()), (128, 2, 16, 16, 1, 200, (0,)), (128, 9, 5, 3, 1, 192, ()), (128, 2, 14, 14, 1, 460, ()), (128, 2, 8, 8, 1, 1021, ()), (128, 2, 4, 4, 3, 516, ()),
+    (128, 2, 12, 12, 1, 257, ()), (128, 2, 17, 16, 1, 194, ())])
+def test_runs_of_wider_layers_share_a_launch(c, blocks, h, w, W, B, cuts):
+    # one to eight runs of 16 pixels a wave; more layers than a launch takes; a module's first layer adding a residual; several images a workgroup, the
+    # last one short of them; the largest images and the first beyond them (32 x 33 of 64 channels, 17 x 16 of 128); fewest images, two rounds, and
+    # counts (257) and lengths (two layers of 461 images) that keep a launch a layer
+    _compare(_identity_blocks(c, blocks, h, w, W, B, cuts), seed=53, T=2 * len(cuts) + 2)
+
+
+@pytest.mark.parametrize("c,h,w,W,B", [(16, 9, 5, 3, 2), (32, 6, 6, 2, 130), (64, 4, 4, 2, 260), (64, 4, 4, 4, 131), (64, 17, 17, 2, 100), (128, 8, 8, 2, 100)])
 def test_runs_of_narrow_layers_with_weights_per_data_group(c, h, w, W, B):
     # (64, ..., 131): an odd number of images per data-group, one a workgroup
     from test_gpu_gossip import _compare as compare_gossip
