@@ -7,6 +7,7 @@
 #include "device_once.h"
 #include "kernels.h"
 #include "lds_copy.h"
+#include "norm_fold.h"
 
 namespace dds {
 namespace {
@@ -58,6 +59,7 @@ struct ChainGeom {
   uint32_t plane;      // bytes of LDS of 16 channels of one layer's images, by positions
   uint32_t buf_bytes;  // of all channels, whole 1 KiB fills
   uint32_t sign_bytes; // input gradient: of the images' signs, whole fills
+  uint32_t fold_at;    // NORM: where the normalisation's factors are made, behind everything else
   Divisor dP;          // by the plane's 16-byte pieces
   Divisor dQ, dH1;     // by W + 1 and H + 1 (positions)
   Divisor dW, dH;      // by W and H (pixels)
@@ -88,8 +90,14 @@ struct Shape {
 // images 2.6 against 7.2 to 8, 1024 images 7.4 forward and 9.0 backward (33 MB written, 4.5 TB/s) against 22; 32 at 16 x 16 1.9 against 5.6 and 5.5 against 14;
 // 64 at 8 x 8 2.8 and 2.4 against 5.8, 5.1 against 12. (With operands read where they are used, each product waited for its LDS read: 3.9 us at 16
 // channels and 194 images; with one set of weights in registers and signs read by the epilogue, backward 10.2 us at 1024.)
-template <int C, int RUNS, bool DGRAD>
-__global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 : 2) void conv_chain_kernel(ChainParams p, ChainGeom g) {
+// NORM: a single layer whose input is made here, by a normalisation: the image arrives as the convolution before left it (forward; what the normalisation adds
+// in the second buffer) or as the gradient behind the normalisation (input gradient; its own input in the second buffer), is streamed in place
+// and to memory, and multiplied. Saves a launch and a read of the tensor in either direction. Bound by memory for many images: 16 channels at 32 x 32, 776
+// images, forward 24.5 us for 75 to 100 MB (streaming and convolution apart: 15.3 + 17.8), input gradient 28.2 us for 100 to 125 MB (14.1 + 16.6); 32
+// channels at 16 x 16 17.1 (11.4 + 12.5) and 20.0 (8.6 + 12.5), where a workgroup's phases follow one another. Normalised
+// ResNet-20 in two modules, us per 8 steps: 4 groups of 194 10030 / 9694, of 16 4436 / 3805, one of 194 4949 / 4574, 4 of 200 recomputing 13436 / 12335.
+template <int C, int RUNS, bool DGRAD, bool NORM>
+__global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 : 2) void conv_chain_kernel(ChainParams p, ChainGeom g, BnParams norm) {
   typedef Shape<C> S;
   constexpr int PB = S::PB, CPP = S::CPP, NBLK = S::NBLK, NBW = S::NBW, WM = S::WM;
   extern __shared__ __align__(16) char smem[];
@@ -146,15 +154,19 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
     }
   };
   ChainLayer L = p.layer[0];
-  fill_images(p.x, 0);
+  SplitFold<DGRAD, 64 * kWaves, C> fold;
+  const int nrep0 = NORM ? img0 / (p.Nimg / norm.W) : 0;  // data-group of the normalisation
+  if (NORM) fold.request(norm, nrep0);
+  fill_images(NORM && DGRAD ? norm.dy : NORM ? norm.x : p.x, 0);
   load_weights(L.w, wreg);
   if (C != 16) {
 #pragma unroll
     for (int a = 0; a < 3; ++a) fill_weights(L.w, a);
   }
-  if (p.res) {
-    fill_images(p.res, g.buf_bytes);
-  } else {
+  const void* second = NORM ? DGRAD ? norm.x : norm.res : p.res;  // what the second buffer holds at first
+  if (second) {
+    fill_images(second, g.buf_bytes);
+  } else if (!NORM) {
     for (uint32_t a = tid * 16; a < g.buf_bytes; a += 1024 * kWaves) lds_write16(lds0 + g.buf_bytes + a, 0u, 0u, 0u, 0u);
   }
 
@@ -216,21 +228,68 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
   f32x4_t start[NBW] = {}, next_start[NBW] = {};
   if (!DGRAD) load_bias(L, start);
   if (DGRAD) fill_signs(L, 0);
-  if (DGRAD && C == 16 && p.n > 1) fill_signs(p.layer[1], 1);
+  if (DGRAD && C == 16 && !NORM && p.n > 1) fill_signs(p.layer[1], 1);
+  float* cf = (float*)(smem + g.fold_at + 8 * fold.kDoubles);
+  if (NORM) fold.finish(norm, nrep0, img0 % (p.Nimg / norm.W) == 0, (double*)(smem + g.fold_at), cf);
   wait_vm<0>();
   wg_barrier();
+  if (NORM) {  // what is normalised -> the layer's input, in place and to memory (the expressions are those of bn_fwd_apply_kernel and bn_bwd_apply_kernel)
+    const int c0 = tid % CPP * 8;
+    float k[DGRAD ? 5 : 2][8];
+#pragma unroll
+    for (int i = 0; i < (DGRAD ? 5 : 2); ++i) {
+      const float4 lo = *(const float4*)(cf + i * C + c0), hi = *(const float4*)(cf + i * C + c0 + 4);
+      k[i][0] = lo.x; k[i][1] = lo.y; k[i][2] = lo.z; k[i][3] = lo.w; k[i][4] = hi.x; k[i][5] = hi.y; k[i][6] = hi.z; k[i][7] = hi.w;
+    }
+    char* out = (char*)(DGRAD ? norm.dx : norm.y) + pix0 * PB;
+    char* out_bits = !DGRAD && norm.bits_out ? (char*)norm.bits_out + pix0 * (C / 8) : nullptr;
+    auto halves = [](const uint4& v, float (&f)[8]) {
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = __uint_as_float(e & 1 ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+    };
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      if (tid + 64 * kWaves * i >= pixels * CPP) break;
+      const int mine = opaque(piece_at[i]);
+      float f[8], h[8] = {};
+      halves(lds_read16(mine), f);
+      if (second) halves(lds_read16(mine + (int)g.buf_bytes), h);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (DGRAD) {
+          const float xh = (h[e] - k[0][e]) * k[DGRAD ? 1 : 0][e];
+          f[e] = k[DGRAD ? 2 : 0][e] * f[e] - k[DGRAD ? 3 : 0][e] - xh * k[DGRAD ? 4 : 0][e];
+        } else {
+          float v = fmaf(f[e], k[0][e], k[1][e]);
+          if (second) v += h[e];
+          if (norm.relu) v = v > 0.f ? v : 0.f;
+          f[e] = v;
+        }
+      }
+      const uint4 o = make_uint4(pack_bf16_rne(f[0], f[1]), pack_bf16_rne(f[2], f[3]), pack_bf16_rne(f[4], f[5]), pack_bf16_rne(f[6], f[7]));
+      lds_write16(mine, o.x, o.y, o.z, o.w);
+      *(uint4*)(out + ((uint32_t)opaque(piece[i]) << 4)) = o;
+      if (out_bits) {
+        const uint32_t t = nonzero2(o.x) | nonzero2(o.y) << 2 | nonzero2(o.z) << 4 | nonzero2(o.w) << 6;
+        *(uint8_t*)(out_bits + (uint32_t)opaque(piece[i])) = (uint8_t)(t | t >> 15);
+      }
+    }
+    wg_barrier();
+    if (DGRAD && p.res) fill_images(p.res, g.buf_bytes);
+  }
 
   // A wave's loads, copies and stores retire in the order of their issue; copies are waited for by the number of younger operations, so
   // that neither the stores nor the copies of later pieces are.
   char *prev_y = nullptr, *prev_bits = nullptr;
-  for (int l = 0; l < p.n; ++l) {
+  for (int l = 0; l < (NORM ? 1 : p.n); ++l) {
     const int src = l & 1 ? (int)g.buf_bytes : 0, dst = (int)g.buf_bytes - src;
-    const bool more = l + 1 < p.n;
-    const ChainLayer next = p.layer[more ? l + 1 : l];
-    if (!DGRAD) load_bias(next, next_start);  // (the last layer: its own again)
-    load_weights(next.w, next_wreg);
-    if (l > 0) store_out(src, prev_y, prev_bits);
-    if (DGRAD && C == 16 && l + 2 < p.n) fill_signs(p.layer[l + 2], (l + 2) % SLOTS);
+    const bool more = !NORM && l + 1 < p.n;
+    const ChainLayer next = NORM ? L : p.layer[more ? l + 1 : l];
+    if (!DGRAD && !NORM) load_bias(next, next_start);  // (the last layer: its own again)
+    if (!NORM) load_weights(next.w, next_wreg);
+    if (!NORM && l > 0) store_out(src, prev_y, prev_bits);
+    if (DGRAD && C == 16 && !NORM && l + 2 < p.n) fill_signs(p.layer[l + 2], (l + 2) % SLOTS);
 
     // Operands of one item (a step and G of the runs) are requested while the item before is multiplied; left to itself the compiler
     // reads each one just ahead of its product and waits for it.
@@ -295,6 +354,7 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
         // this layer's signs). Younger than they: the copies behind them, this layer's stores, the next layer's weights so far.
         constexpr int OPS = NS, OPSB = DGRAD ? NS : 2 * NS;  // without and with the signs of the layer before (the bias is not counted on)
         const bool with_bits = !DGRAD && prev_bits;
+        if (NORM) continue;
         if (a == 0) {
           if (with_bits) wait_vm<FP + SG + OPSB>();
           else wait_vm<FP + SG + OPS>();
@@ -312,6 +372,10 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
       }
     }
 
+    if (NORM && L.add) {  // what the layer adds, asked for ahead of the products
+      wait_vm<0>();
+      wg_barrier();
+    }
     // epilogue, a few runs at a time: what they add, arithmetic, stores
     const int to_own = own + dst - src, to_next = dst - src;
     constexpr int NV = 4 * NBW, GRP = C == 16 ? 4 : 2;
@@ -383,12 +447,13 @@ __global__ __launch_bounds__(64 * kWaves, C == 16 || (C == 32 && RUNS <= 4) ? 4 
       for (int t = 0; t < 5; ++t) wreg[t] = next_wreg[t];
     }
     // the next layer's first tap row, or (16 channels) its signs: older than this layer's stores and the signs after them
-    if (more && C != 16) wait_vm<2 * FP + SG>();
+    if (NORM) {}
+    else if (more && C != 16) wait_vm<2 * FP + SG>();
     else if (DGRAD && l + 2 < p.n) wait_vm<NS + 1>();
     else if (DGRAD && more) wait_vm<NS>();
     wg_barrier();
   }
-  store_out(p.n & 1 ? (int)g.buf_bytes : 0, prev_y, prev_bits);
+  store_out(NORM || (p.n & 1) ? (int)g.buf_bytes : 0, prev_y, prev_bits);
 }
 
 // Wider layers, whose image fits in LDS once: 64 channels at up to 1024 pixels, 128 at up to 256. The outputs of a layer wait in the accumulators
@@ -618,18 +683,21 @@ int sign_bytes(int C, int H, int W, int imgs) {  // of the 16-byte lines that ma
 }
 int weight_bytes(int C) { return C == 16 ? 0 : 9 * C / 32 * (C / 16) * 1024; }
 int lds_bytes(int C, int H, int W, int imgs) { return 2 * buffer_bytes(C, H, W, imgs) + weight_bytes(C) + sign_slots(C) * sign_bytes(C, H, W, imgs); }
+// with a normalisation: one slot of signs, and where its factors are made (SplitFold::kDoubles and kBnCoefRows rows)
+int norm_fold_at(int C, int H, int W, int imgs) { return 2 * buffer_bytes(C, H, W, imgs) + weight_bytes(C) + sign_bytes(C, H, W, imgs); }
+int norm_lds_bytes(int C, int H, int W, int imgs) { return norm_fold_at(C, H, W, imgs) + 8 * 2 * kWaves * C + 4 * kBnCoefRows * C; }
 int wave_rows(int C) { return C == 64 ? kWaves / 2 : kWaves; }
 int most_runs(int C) { return C == 64 ? 4 : 8; }
 
-template <int C, int RUNS>
-void launch_inst(const ChainParams& p, const ChainGeom& g, int wgs, int smem, hipStream_t s) {
+template <int C, int RUNS, bool NORM>
+void launch_inst(const ChainParams& p, const ChainGeom& g, const BnParams& n, int wgs, int smem, hipStream_t s) {
   static DeviceOnce lds[2];
   if (p.dgrad) {
-    allow_whole_lds(lds[1], (const void*)conv_chain_kernel<C, RUNS, true>);
-    conv_chain_kernel<C, RUNS, true><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+    allow_whole_lds(lds[1], (const void*)conv_chain_kernel<C, RUNS, true, NORM>);
+    conv_chain_kernel<C, RUNS, true, NORM><<<wgs, 64 * kWaves, smem, s>>>(p, g, n);
   } else {
-    allow_whole_lds(lds[0], (const void*)conv_chain_kernel<C, RUNS, false>);
-    conv_chain_kernel<C, RUNS, false><<<wgs, 64 * kWaves, smem, s>>>(p, g);
+    allow_whole_lds(lds[0], (const void*)conv_chain_kernel<C, RUNS, false, NORM>);
+    conv_chain_kernel<C, RUNS, false, NORM><<<wgs, 64 * kWaves, smem, s>>>(p, g, n);
   }
 }
 
@@ -729,22 +797,23 @@ static void launch_wide_chain(int C, const ChainParams& p, hipStream_t s) {
 #undef DDS_WIDE_CASE
 }
 
-void launch_conv_chain(int C, const ChainParams& p, hipStream_t s) {
-  if (images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1) == 0) return launch_wide_chain(C, p, s);
+template <bool NORM>
+static void launch_narrow(int C, int imgs, const ChainParams& p, const BnParams& n, hipStream_t s) {
   ChainGeom g;
-  g.imgs = images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1);
-  g.buf_bytes = buffer_bytes(C, p.H, p.W, g.imgs);
-  g.plane = plane_bytes(p.H, p.W, g.imgs);
-  g.sign_bytes = sign_bytes(C, p.H, p.W, g.imgs);
+  g.imgs = imgs;
+  g.buf_bytes = buffer_bytes(C, p.H, p.W, imgs);
+  g.plane = plane_bytes(p.H, p.W, imgs);
+  g.sign_bytes = sign_bytes(C, p.H, p.W, imgs);
+  g.fold_at = norm_fold_at(C, p.H, p.W, imgs);
   g.dP = make_divisor1(g.plane / 16);
   g.dQ = make_divisor1(p.W + 1);
   g.dH1 = make_divisor1(p.H + 1);
   g.dW = make_divisor1(p.W);
   g.dH = make_divisor1(p.H);
-  const int wgs = cdiv(p.Nimg, g.imgs), smem = lds_bytes(C, p.H, p.W, g.imgs);
-  const int runs = cdiv(cdiv(g.imgs * p.H * p.W, 16), wave_rows(C));
+  const int wgs = cdiv(p.Nimg, imgs), smem = NORM ? norm_lds_bytes(C, p.H, p.W, imgs) : lds_bytes(C, p.H, p.W, imgs);
+  const int runs = cdiv(cdiv(imgs * p.H * p.W, 16), wave_rows(C));
 #define DDS_CHAIN_CASE(C, RUNS) \
-  case (C) * 8 + (RUNS) - 1: launch_inst<C, RUNS>(p, g, wgs, smem, s); break;
+  case (C) * 8 + (RUNS) - 1: launch_inst<C, RUNS, NORM>(p, g, n, wgs, smem, s); break;
   switch (C * 8 + runs - 1) {
     DDS_CHAIN_CASE(16, 1) DDS_CHAIN_CASE(16, 2) DDS_CHAIN_CASE(16, 3) DDS_CHAIN_CASE(16, 4)
     DDS_CHAIN_CASE(16, 5) DDS_CHAIN_CASE(16, 6) DDS_CHAIN_CASE(16, 7) DDS_CHAIN_CASE(16, 8)
@@ -753,6 +822,35 @@ void launch_conv_chain(int C, const ChainParams& p, hipStream_t s) {
     DDS_CHAIN_CASE(64, 1) DDS_CHAIN_CASE(64, 2) DDS_CHAIN_CASE(64, 3) DDS_CHAIN_CASE(64, 4)
   }
 #undef DDS_CHAIN_CASE
+}
+
+void launch_conv_chain(int C, const ChainParams& p, hipStream_t s) {
+  const int imgs = images_of(C, p.H, p.W, p.Nimg, p.nrep > 1 ? p.nrep : 1);
+  if (imgs == 0) launch_wide_chain(C, p, s);
+  else launch_narrow<false>(C, imgs, p, BnParams{}, s);
+}
+
+// Images of a workgroup that normalises, all of one data-group; 0: a launch each. Where two workgroups share a CU, one's copies run beside the
+// other's products. Larger ones have to be done in one round, and to fill it unless an image is small. us per step of a net of five normalised layers of 2
+// groups of 97 (4 of 194), streamed apart / here: 16 channels at 32 x 32 243 / 219 (529 / 498), at 16 x 16 206 / 166 (260 / 231), 32 channels at 16 x 16
+// 227 / 197 (355 / 329), 64 channels at 8 x 8 223 / 196 (304 / 306), at 4 x 4 215 / 179 (225 / 238: 388 workgroups; 4 groups of 256, 256 of them:
+// 214 / 194). One workgroup a CU, 4 groups of 16, 64 and 194: 32 channels at 28 x 28 222 / 237, 357 / 318, 748 / 833; 64 channels at 14 x 14 226 / 230, 301 / 276, -.
+static int norm_images_of(int C, int H, int W, int Nimg, int W_groups) {
+  if ((C != 16 && C != 32 && C != 64) || H < 1 || W < 1 || Nimg < 1 || W_groups < 1 || Nimg % W_groups != 0 || (long long)H * W > 4096) return 0;
+  auto runs = [&](int imgs) { return cdiv(cdiv(imgs * H * W, 16), wave_rows(C)); };
+  auto fits = [&](int imgs, int room) { return norm_lds_bytes(C, H, W, imgs) <= room && runs(imgs) <= most_runs(C) && Nimg / W_groups % imgs == 0; };
+  const bool two = fits(1, 80 * 1024);
+  const int room = two ? 80 * 1024 : 160 * 1024, enough = two ? 512 : 256;
+  if (!fits(1, room)) return 0;
+  int imgs = 1;
+  while (cdiv(Nimg, imgs) > enough && imgs < 8 && fits(2 * imgs, room)) imgs *= 2;
+  const int wgs = cdiv(Nimg, imgs);
+  if (!two && (wgs > 256 || (runs(1) > 2 && wgs < 192))) return 0;
+  return imgs;
+}
+bool norm_conv_fits(int C, int H, int W, int Nimg, int W_groups) { return norm_images_of(C, H, W, Nimg, W_groups) > 0; }
+void launch_norm_conv(int C, const ChainParams& p, const BnParams& n, hipStream_t s) {
+  launch_narrow<true>(C, norm_images_of(C, p.H, p.W, p.Nimg, n.W), p, n, s);
 }
 
 }  // namespace dds

@@ -100,6 +100,8 @@ struct Node {
   int wgroup = -1;            // launch that this layer's weight gradient goes with ...
   bool wgroup_last = false;   // ... and the backward pass has reached its last layer
   int chain = -1;             // run of layers that share a forward and an input-gradient launch (Module::chains)
+  int norm_fwd = -1, norm_bwd = -1;  // convolution: normalisation that its forward / its input gradient reads from and streams in the same launch
+  bool streamed_fwd = false, streamed_bwd = false;  // ... and that node: streamed so
 };
 
 struct GradBuf {
@@ -593,6 +595,30 @@ void plan_chains(dds_ctx& c, Module& m) {
   }
 }
 
+// Finds the normalisations that the launch of the convolution behind them streams: forward the next node, input gradient the node before.
+void plan_norms(dds_ctx& c, Module& m) {
+  if (c.dt != DT_BF16) return;
+  auto rides = [&](const Node& bn, const Node& nd) {
+    if (bn.kind != N_BN || nd.kind != N_CONV || nd.chain >= 0 || nd.out_f32 || nd.fold_sc >= 0) return false;
+    const ParamLayer& L = m.layers[nd.layer];
+    const Tensor& ti = m.tensors[nd.in];
+    const Tensor& to = m.tensors[nd.out];
+    return L.R == 3 && L.stride == 1 && L.pad == 1 && L.Cin == L.Cout && L.Cin == L.Cinpad && L.Cout == L.Coutpad && (!nd.relu || to.has_bits) &&
+           (!nd.mask_in || ti.has_bits) && bn_plan(c.W, (long long)c.B * to.H * to.W, to.Cpad, 2).fold && norm_conv_fits(L.Cin, to.H, to.W, c.N, c.W);
+  };
+  for (int i = 0; i + 1 < (int)m.nodes.size(); ++i) {
+    Node &a = m.nodes[i], &b = m.nodes[i + 1];
+    if (rides(a, b) && b.in == a.out && b.res < 0 && (!a.relu || m.tensors[a.out].has_bits)) {
+      b.norm_fwd = i;
+      a.streamed_fwd = true;
+    }
+    if (rides(b, a) && b.in == a.out && a.gin != G_NONE && a.gout >= 0 && a.gout == b.gin) {
+      a.norm_bwd = i + 1;
+      b.streamed_bwd = true;
+    }
+  }
+}
+
 // workgroups of the update kernel that a layer takes
 int update_blocks(const dds_ctx& c, const ParamLayer& L) {
   if (!c.gossip) return update_tiles(c.dt, L.nsplit, L.Cout, L.RS, L.Cinpad);
@@ -836,6 +862,7 @@ int build(dds_ctx& c, const dds_spec* sp, int K, int W, const int* delays) {
     rc = plan_module(*sp, k0, K, c.N, c.dt, in, m);
     if (rc) return rc;
     plan_chains(c, m);
+    plan_norms(c, m);
   }
   // sizes that index arithmetic in the kernels keeps in 32 bits
   for (Module& m : c.mods)
@@ -975,6 +1002,25 @@ BnParams bn_params(dds_ctx& c, Module& m, const Node& nd, int slot, const float*
   return p;
 }
 
+BnParams bn_forward(dds_ctx& c, Module& m, const Node& nd, int slot, int in_slot, const float* master) {
+  BnParams p = bn_params(c, m, nd, slot, master);
+  p.x = tptr(c, m, nd.in, slot, in_slot);
+  p.y = tptr(c, m, nd.out, slot, in_slot);
+  p.res = nd.res >= 0 ? tptr(c, m, nd.res, slot, in_slot) : nullptr;
+  p.bits_out = nd.relu ? bits_ptr(c, m, nd.out, slot, in_slot) : nullptr;
+  p.streamed_later = nd.streamed_fwd;
+  return p;
+}
+
+BnParams bn_backward(dds_ctx& c, Module& m, const Node& nd, const Sched& sc) {
+  BnParams p = bn_params(c, m, nd, sc.bwd_slot, m.master);
+  p.x = tptr(c, m, nd.in, sc.bwd_slot, sc.in_bwd_slot);
+  p.dy = gptr(c, m, nd.gout, sc);
+  p.dx = gptr(c, m, nd.gin, sc);
+  p.streamed_later = nd.streamed_bwd;
+  return p;
+}
+
 // Forward launch of a convolution or linear node; master, work: the parameters it uses.
 ConvParams conv_forward(dds_ctx& c, Module& m, const Node& nd, int slot, int in_slot, const float* master, const char* work) {
   const int es = dtype_size(c.dt);
@@ -1047,8 +1093,8 @@ ConvParams conv_dgrad(dds_ctx& c, Module& m, const Node& nd, const Sched& sc) {
   return p;
 }
 
-// The launches of a chain's layers, in the order in which they are walked, as one.
-void run_chain(dds_ctx& c, const std::vector<ConvParams>& layers, bool timed, hipStream_t s) {
+// The launches of a chain's layers, in the order in which they are walked, as one; norm: or of one layer and of the streaming of a normalisation.
+void run_chain(dds_ctx& c, const std::vector<ConvParams>& layers, bool timed, hipStream_t s, const BnParams* norm = nullptr) {
   const ConvParams& p0 = layers[0];
   ChainParams p{};
   p.x = p0.x; p.res = p0.res; p.zeros = p0.zeros;
@@ -1065,7 +1111,8 @@ void run_chain(dds_ctx& c, const std::vector<ConvParams>& layers, bool timed, hi
     for (const ConvParams& q : layers) recs.push_back({q.dgrad ? 4 : 3, 2.0 * q.M * q.Nout * q.Ktot, 1.0 / p.n, nullptr, nullptr, false});
   ProfScope ps(c, s, 0, 0.0, timed);
   ps.layers = std::move(recs);
-  launch_conv_chain(p0.Nout, p, s);
+  if (norm) launch_norm_conv(p0.Nout, p, *norm, s);
+  else launch_conv_chain(p0.Nout, p, s);
   ++c.launches;
 }
 
@@ -1095,19 +1142,20 @@ void run_forward(dds_ctx& c, Module& m, int slot, int in_slot, hipStream_t s, in
           chain.clear();
           continue;
         }
+        if (nd.norm_fwd >= 0) {
+          const BnParams n = bn_forward(c, m, m.nodes[nd.norm_fwd], slot, in_slot, master);
+          run_chain(c, {p}, snap < 0, s, &n);
+          continue;
+        }
         const ParamLayer& L = m.layers[nd.layer];
         ProfScope ps(c, s, 0, 2.0 * p.M * L.Cout * L.Cin * L.RS, snap < 0);
         ps.cls += 3 * launch_conv(c.dt, p, s);
         break;
       }
       case N_BN: {
-        BnParams p = bn_params(c, m, nd, slot, master);
-        p.x = x;
-        p.y = y;
-        p.res = nd.res >= 0 ? tptr(c, m, nd.res, slot, in_slot) : nullptr;
-        p.bits_out = nd.relu ? bits_ptr(c, m, nd.out, slot, in_slot) : nullptr;
+        const BnParams p = bn_forward(c, m, nd, slot, in_slot, master);
         launch_bn_forward(c.dt, p, s);
-        c.launches += p.fold ? 1 : 2;
+        c.launches += p.streamed_later ? 0 : p.fold ? 1 : 2;
         break;
       }
       case N_MAXPOOL:
@@ -1144,6 +1192,10 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
             if (m.nodes[k].gin != G_NONE) chain.push_back(conv_dgrad(c, m, m.nodes[k], sc));
           run_chain(c, chain, true, s);
         }
+        if (nd.norm_bwd >= 0) {  // (makes gout, too)
+          const BnParams n = bn_backward(c, m, m.nodes[nd.norm_bwd], sc);
+          run_chain(c, {conv_dgrad(c, m, nd, sc)}, true, s, &n);
+        }
         // The weight gradient reads no weights: one launch serves every data-group. With a mixing matrix (and in fp32) no
         // split mixes two of them, so that data-group r's gradient is the sum of its own nsplit / W splits.
         WgradParams w = wgrad_shape(c, m, nd);
@@ -1173,7 +1225,7 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
           group.layers.clear();
           group.flops.clear();
         }
-        if (nd.gin != G_NONE && nd.chain < 0) {
+        if (nd.gin != G_NONE && nd.chain < 0 && nd.norm_bwd < 0) {
           const ConvParams p = conv_dgrad(c, m, nd, sc);
           {
             ProfScope ps(c, s, 1, 2.0 * w.P * L.Cout * L.Cin * L.RS);
@@ -1184,12 +1236,9 @@ int run_backward(dds_ctx& c, Module& m, const Sched& sc, hipStream_t s, hipStrea
         break;
       }
       case N_BN: {
-        BnParams p = bn_params(c, m, nd, slot, m.master);
-        p.x = x;
-        p.dy = gout;
-        p.dx = gin;
+        const BnParams p = bn_backward(c, m, nd, sc);
         launch_bn_backward(c.dt, p, s);
-        c.launches += p.fold ? 2 : 3;
+        c.launches += p.streamed_later ? 1 : p.fold ? 2 : 3;
         break;
       }
       case N_MAXPOOL:

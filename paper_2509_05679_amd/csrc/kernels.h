@@ -138,6 +138,7 @@ struct BnParams {
   int nsums, nsplit;  // row splits of a data-group: of the kernels that sum, of those that stream
   long long rows_per_rep, rows_per_sum, rows_per_split;
   bool fold;          // the streaming kernels join the splits' sums themselves
+  bool streamed_later;  // only the sums are launched: the streaming rides in the convolution that follows (launch_norm_conv)
   float eps, alpha;
   int relu;
 };
@@ -174,6 +175,10 @@ bool launch_conv_narrow(const ConvParams& p, hipStream_t s);
 // Fewest layers that are faster in one launch than in one each; 0: no number is, or the kernel does not take them.
 int conv_chain_least(int C, int H, int W, int Nimg, int nrep);
 void launch_conv_chain(int C, const ChainParams& p, hipStream_t s);
+// A batch normalisation whose sums are there (n.fold) and a single such layer that reads what it makes, in one launch; forward: n.x, n.res -> n.y
+// -> layer; input gradient: n.dy, n.x -> n.dx -> layer (p.res: what the layer adds). norm_conv_fits: is there such a kernel
+bool norm_conv_fits(int C, int H, int W, int Nimg, int W_groups);
+void launch_norm_conv(int C, const ChainParams& p, const BnParams& n, hipStream_t s);
 // n layers of one key (wgrad_work), or one of any kind. Returns 1 if wgrad_tiles or wgrad_slim took them, whose 3x3 and stride-2
 // layers have a class of their own, 0 if wgrad_gemm or wgrad_f32 did; -1, nothing launched, if their splits fit none of them.
 int launch_wgrad(int dt, const WgradParams* p, int n, hipStream_t s);

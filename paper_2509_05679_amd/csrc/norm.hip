@@ -8,7 +8,7 @@
 //   backward: g = alpha * dy;  dbeta = sum g;  dgamma = sum g * xhat;
 //             dx = gamma * rstd * (g - dbeta / m - xhat * dgamma / m),  m = rows per group
 // The backward uses the mean, rstd and gamma that the forward of the same mini-batch stored.
-#include "kernels.h"
+#include "norm_fold.h"
 
 namespace dds {
 namespace {
@@ -163,63 +163,6 @@ __global__ __launch_bounds__(256) void bn_fwd_stats_kernel(BnParams p) {
   fold_rows(red, cg, l.rpp, p.ld, 1.0, p.scratch + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * p.ld * 2);
 }
 
-// The sums a, b of channel c of data-group `rep` -> the factors of the streaming kernel, coef[row * stride]; `leave`: and what
-// outlives it. Forward (sum x, sum x^2): mean, rstd (and the gamma in use) into `stats`; coef rows: scale, shift. Backward (sum g,
-// sum g*xhat): dbeta, dgamma in fp32 into row `rep` of the parameter-gradient partials (dgamma[c] at c * gstride,
-// dbeta[c] at C * gstride + c: the layout of a 1x1 "convolution" with one input channel, so that the update kernels
-// treat gamma / beta like any other layer with one split per data-group); coef rows: mean, rstd, and k0, k1, k2 of
-// dx = k0 * dy - k1 - xhat * k2. Channels past C (row padding) get zeros.
-// What they need beside the sums is asked for (channel_inputs) before those are there.
-struct ChannelInputs { float mean, rstd, gamma, beta; };
-template <bool BWD>
-__device__ __forceinline__ ChannelInputs channel_inputs(const BnParams& p, int rep, int c) {
-  ChannelInputs in{};
-  if (BWD) {
-    const float* st = p.stats + (size_t)rep * 3 * p.ld + c;
-    in.mean = st[0];
-    in.rstd = st[p.ld];
-    in.gamma = st[2 * p.ld];
-  } else {
-    const int k = c < p.C ? c : p.C - 1;
-    in.gamma = p.gamma[(size_t)rep * p.rep_stride + (size_t)k * p.gstride];
-    in.beta = p.beta[(size_t)rep * p.rep_stride + k];
-  }
-  return in;
-}
-template <bool BWD>
-__device__ __forceinline__ void channel_factors(const BnParams& p, const ChannelInputs& in, int rep, int c, double a, double b, bool leave, float* coef, int stride) {
-  const double m = (double)p.rows_per_rep;
-  const bool real = c < p.C;
-  if (BWD) {
-    const float gr = in.gamma * in.rstd;
-    if (real && leave) {
-      float* row = p.partial + (size_t)rep * p.pstride;
-      row[(size_t)c * p.gstride] = (float)b;
-      row[(size_t)p.C * p.gstride + c] = (float)a;
-    }
-    // dx = gr * (alpha*dy - db/m - xhat*dg/m), db and dg already carry alpha
-    coef[0] = real ? in.mean : 0.f;
-    coef[stride] = real ? in.rstd : 0.f;
-    coef[2 * stride] = real ? gr * p.alpha : 0.f;
-    coef[3 * stride] = real ? gr * (float)(a / m) : 0.f;
-    coef[4 * stride] = real ? gr * (float)(b / m) : 0.f;
-  } else {
-    const double mean = a / m;
-    double var = b / m - mean * mean;
-    var = var > 0.0 ? var : 0.0;
-    const float meanf = (float)mean, rstd = (float)(1.0 / sqrt(var + (double)p.eps));
-    const float g = real ? in.gamma : 0.f, beta = real ? in.beta : 0.f;
-    if (leave) {
-      float* st = p.stats + (size_t)rep * 3 * p.ld;
-      st[c] = meanf;
-      st[p.ld + c] = rstd;
-      st[2 * p.ld + c] = g;
-    }
-    coef[0] = p.alpha * g * rstd;
-    coef[stride] = p.alpha * (beta - meanf * g * rstd);
-  }
-}
-
 // grid (ld / 4, W), 256 threads = 64 split lanes x 4 channels (ld is a multiple of four): folds the nsums partial sums of a
 // channel (lane j takes splits j, j+64, ...; a tree over the sixteen lanes of a wave, then the four waves in order) once per
 // data-group and leaves the per-channel factors of the streaming kernel in coef[rep][.][ld], so that each of its
@@ -253,51 +196,6 @@ __global__ __launch_bounds__(256) void bn_finalize_kernel(BnParams p) {
   channel_factors<BWD>(p, in, rep, c, a, b, true, p.coef + (size_t)rep * kBnCoefRows * p.ld + c, p.ld);
 }
 
-// The same by every workgroup of the streaming kernel, for rows of at most kBnFoldLd channels (bn_plan): 256 threads = 256 / C'
-// split lanes x C' channels, C' = ld rounded up to a power of two; a lane has at most kBnFoldSums / 256 * C' = eight splits
-// to add. request() asks for everything that comes from memory, ahead of the first rows (loads return in order); finish()
-// leaves the factors at cf[row * kBnFoldLd + c] in LDS, and the first workgroup of a data-group what outlives the kernel.
-template <bool BWD>
-struct SplitFold {
-  int c, clog;
-  double2 v[8];
-  ChannelInputs in;
-  __device__ __forceinline__ void request(const BnParams& p) {
-    clog = p.ld > 32 ? 6 : p.ld > 16 ? 5 : p.ld > 8 ? 4 : 3;
-    c = threadIdx.x & ((1 << clog) - 1);
-    const int rep = blockIdx.y, j = threadIdx.x >> clog, cc = min(c, p.ld - 1);
-    const double* row = p.scratch + ((size_t)rep * p.nsums * p.ld + cc) * 2;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *(const double2*)(row + (size_t)min(j + u * (256 >> clog), p.nsums - 1) * p.ld * 2);
-    in = channel_inputs<BWD>(p, rep, min((int)threadIdx.x, p.ld - 1));
-  }
-  __device__ __forceinline__ void finish(const BnParams& p, float* cf) {
-    __shared__ double red[2][4][kBnFoldLd];
-    double a = 0.0, b = 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool ok = (int)(threadIdx.x >> clog) + u * (256 >> clog) < p.nsums;
-      a += ok ? v[u].x : 0.0;
-      b += ok ? v[u].y : 0.0;
-    }
-    for (int d = 1 << clog; d < 64; d <<= 1) {
-      a += __shfl_xor(a, d, 64);
-      b += __shfl_xor(b, d, 64);
-    }
-    if ((int)(threadIdx.x & 63) < 1 << clog) {
-      red[0][threadIdx.x >> 6][c] = a;
-      red[1][threadIdx.x >> 6][c] = b;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < p.ld) {
-      a = b = 0.0;
-      for (int j = 0; j < 4; ++j) { a += red[0][j][threadIdx.x]; b += red[1][j][threadIdx.x]; }
-      channel_factors<BWD>(p, in, blockIdx.y, threadIdx.x, a, b, blockIdx.x == 0, cf + threadIdx.x, kBnFoldLd);
-    }
-    __syncthreads();
-  }
-};
-
 // grid (nsplit, W): streams its rows; FOLD: the factors are made here, from the splits' sums. HBM-bound (reads x and the residual,
 // writes y and 1/16 of it in sign bits); the rows of a trip are requested before anything is computed, the first ones
 // before the per-channel factors, and stores and sign bits are packed conversions. Average over the ResNet-18 shapes at
@@ -326,10 +224,11 @@ __global__ __launch_bounds__(256) void bn_fwd_apply_kernel(BnParams p) {
   };
   float f[4][8], q[4][8];
   long long r = l.row_lo + l.tr;
-  SplitFold<false> fold;
-  if (FOLD) fold.request(p);
+  SplitFold<false, 256> fold;
+  __shared__ double red[FOLD ? SplitFold<false, 256>::kDoubles : 1];
+  if (FOLD) fold.request(p, blockIdx.y);
   load_rows(r, f, q);
-  if (FOLD) fold.finish(p, cf);
+  if (FOLD) fold.finish(p, blockIdx.y, blockIdx.x == 0, red, cf);
   if (!active) return;
   load_coef(coef, l, scale);
   load_coef(coef + stride, l, shift);
@@ -433,10 +332,11 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(BnParams p) {
   };
   float f[4][8], g[4][8];
   long long r = l.row_lo + l.tr;
-  SplitFold<true> fold;
-  if (FOLD) fold.request(p);
+  SplitFold<true, 256> fold;
+  __shared__ double red[FOLD ? SplitFold<true, 256>::kDoubles : 1];
+  if (FOLD) fold.request(p, blockIdx.y);
   load_rows(r, f, g);
-  if (FOLD) fold.finish(p, cf);
+  if (FOLD) fold.finish(p, blockIdx.y, blockIdx.x == 0, red, cf);
   if (!active) return;
   load_coef(coef, l, mean);
   load_coef(coef + stride, l, rstd);
@@ -502,12 +402,14 @@ BnPlan bn_plan(int W, long long rows_per_rep, int ld, int es) {
 
 void launch_bn_forward(int dt, const BnParams& p, hipStream_t s) {
   DDS_BN_DISPATCH(dt, bn_fwd_stats_kernel, <<<dim3(p.nsums, p.W), 256, 0, s>>>(p));
+  if (p.streamed_later) return;
   if (!p.fold) bn_finalize_kernel<false><<<dim3(p.ld / 4, p.W), 256, 0, s>>>(p);
   DDS_BN_DISPATCH_FOLD(dt, p.fold, bn_fwd_apply_kernel, <<<dim3(p.nsplit, p.W), 256, 0, s>>>(p));
 }
 
 void launch_bn_backward(int dt, const BnParams& p, hipStream_t s) {
   DDS_BN_DISPATCH(dt, bn_bwd_stats_kernel, <<<dim3(p.nsums, p.W), 256, 0, s>>>(p));
+  if (p.streamed_later) return;
   if (!p.fold) bn_finalize_kernel<true><<<dim3(p.ld / 4, p.W), 256, 0, s>>>(p);
   DDS_BN_DISPATCH_FOLD(dt, p.fold, bn_bwd_apply_kernel, <<<dim3(p.nsplit, p.W), 256, 0, s>>>(p));
 }
