@@ -7,14 +7,16 @@
 // (Plain products of few rows: linear.hip. 16-channel layers: narrow.hip.)
 //
 // Operand tiles are K-contiguous in LDS ([row][k]; wgrad_dma_body, wgrad_flat_body and wgrad_f32_kernel keep [pixel][channel])
-// and feed v_mfma_f32_32x32x16_bf16 (bf16) or v_mfma_f32_32x32x2_f32 (fp32) with one 16-byte LDS read per operand fragment.
+// and feed v_mfma_f32_32x32x16_bf16 (bf16) or v_mfma_f32_32x32x2_f32 (fp32) with one 16-byte LDS read per operand fragment. The fp32 kernels
+// of 3x3 stride-1 layers and of weight gradients multiply bf16 parts instead (split3): six of those products cost 3/8 of one on the fp32 unit.
 // Lanes 0-31 read the first 16 bytes of a 32-byte k-step and lanes 32-63 the second, for A and B alike, so the
 // pairing of k indices inside an instruction is consistent by construction.
 //
-// fp32 sums keep one order per problem, whichever kernel or tile its size selects: a program's fp32 results change by single
-// ReLU decisions when the last bits of a sum do. That is why here and in linear.hip and misc.hip (update, pooling) some rules
-// name the type; see launch_dma, wgrad_generic_split, linear_kernel, gap_fwd_kernel and update_elems. (The mixing update of
-// misc.hip is not held to it: its sum runs over the row-lanes that the split count selects.)
+// The fp32 sums of linear, 1x1 and strided layers keep one order per problem, whichever kernel or tile its size selects: a program's fp32
+// results change by single ReLU decisions when the last bits of a sum do. That is why here and in linear.hip and misc.hip (update, pooling)
+// some rules name the type; see wgrad_generic_split, linear_kernel, gap_fwd_kernel and update_elems. (The mixing update of misc.hip is not held
+// to it: its sum runs over the row-lanes that the split count selects.) 3x3 stride-1 layers keep the order of their tile's kernel: a chunk of sixteen
+// channels, its taps, resident weights apart from the rest.
 #include <cstdlib>
 
 #include "device_once.h"
@@ -38,6 +40,74 @@ template <> __device__ __forceinline__ void mfma16B<float>(const uint4& a, const
   c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+}
+
+// Eight fp32 values as sums of three bf16 values each: every step rounds to nearest, the remainders are exact and the third part holds what is
+// left (8 bits a step of 24). Of the nine products of parts the three smallest are below 2^-24 of the whole and left out. Relative 2-norm error
+// against fp64, medians of 6 seeds, fp32 unit / parts: outputs of a layer of 64 channels 2.9e-7 / 1.6e-7, of 512 8.1e-7 / 2.0e-7; input gradients 3.1e-7
+// / 1.9e-7 and 8.2e-7 / 2.6e-7; weights after 4 to 10 steps of the fp32 CNN at 1 x 8 6.7e-8 / 6.0e-8, 2 x 16 8.3e-7 / 1.6e-7, of ResNet-20 at 16 5.03e-8 / 5.03e-8,
+// of the odd net at 12 x 12 5.29e-8 / 5.29e-8; worst layer of the normalised ResNet-18 in fp32 at 4 x 3 3.1e-5 / 1.7e-5. (The unit
+// truncates where it adds, so the long sums are formed by the vector unit out of short ones: with six additions to the long sum for every
+// sixteen terms a layer's errors were 1.15 times the fp32 unit's.)
+// (value - part by v_dot2c_f32_bf16, one instruction for two: 99 -> 113 us a launch, it is slower than the two.)
+struct Parts { uint4 part[3]; };
+__device__ __forceinline__ uint32_t split_pair(float& lo, float& hi) {  // leaves the remainders
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  const uint32_t pair = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{lo, hi}), bf16x2_t));
+  lo -= __uint_as_float(pair << 16);
+  hi -= __uint_as_float(pair & 0xffff0000u);
+  return pair;
+}
+__device__ __forceinline__ Parts split3(const float (&v)[8]) {
+  Parts r;
+  uint32_t w[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float lo = v[2 * e], hi = v[2 * e + 1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k][e] = split_pair(lo, hi);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) r.part[k] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+  return r;
+}
+__device__ __forceinline__ Parts split3(const uint4& x, const uint4& y) {
+  return split3({__uint_as_float(x.x), __uint_as_float(x.y), __uint_as_float(x.z), __uint_as_float(x.w), __uint_as_float(y.x), __uint_as_float(y.y),
+                 __uint_as_float(y.z), __uint_as_float(y.w)});
+}
+// c[] += b[] a over sixteen k: the six products of parts that reach 2^-24 of a term, smallest first, summed apart so that the
+// long sum is rounded once in sixteen k.
+constexpr int kPartA[6] = {0, 2, 1, 0, 1, 0}, kPartB[6] = {2, 0, 1, 1, 0, 0};
+template <int N>
+__device__ __forceinline__ void mfma_split(const Parts& a, const Parts (&b)[N], f32x16_t* const (&c)[N]) {
+  f32x16_t t[N] = {};
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int n = 0; n < N; ++n) mfma16B<bf16_t>(b[n].part[kPartA[k]], a.part[kPartB[k]], t[n]);
+#pragma unroll
+  for (int n = 0; n < N; ++n) *c[n] += t[n];
+}
+template <int N>
+__device__ __forceinline__ bool any_nan(const f32x16_t (&acc)[N]) {
+  bool r = false;
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r |= acc[n][e] != acc[n][e];
+  return r;
+}
+// Is `mine` set in any lane of the workgroup? (words: of LDS, one per wave, that nobody reads or copies to any more when all waves are here)
+__device__ __forceinline__ bool workgroup_any(bool mine, char* words, int wave, int nwaves) {
+  __syncthreads();
+  const bool w = __ballot(mine) != 0;
+  volatile int* at = (volatile int*)words;
+  at[wave] = w;
+  __syncthreads();
+  int r = 0;
+  for (int i = 0; i < nwaves; ++i) r |= at[i];
+  return r != 0;
 }
 
 __device__ __forceinline__ uint4 keep_if(bool ok, const uint4& v) {
@@ -671,6 +741,8 @@ __device__ __forceinline__ void add_halves(f32x16_t (&acc)[NJ][NI], char* smem, 
       if (khalf == 0) acc[j][i] += buf[(j * NI + i) * 64];
 }
 
+constexpr int kPartsRow = 96;  // bytes of a pixel's sixteen channels, split: three rows of 32 bytes
+
 struct DmaGeom {
   int patch_rows;   // BM + 2W + 2 rounded up to whole wave fills
   int out_bytes;    // bytes of LDS the epilogue may stage tiles in (everything below the dump block)
@@ -678,11 +750,17 @@ struct DmaGeom {
   Divisor dW, dH;
 };
 
+// fp32 (but RES): a workgroup splits the patch once a chunk (split3), into rows of three 32-byte parts that all nine taps read, and every wave
+// the weights of its own 32 channels as it reads them. Eight waves; a vector instruction in three of four MFMA cycles is hidden, more add up, so waves
+// are 128 pixels tall (24 MFMAs for one fragment of weights) wherever the launch still fills the chip: 256 x 128 tiles of the fp32 CNN's layers against
+// 128 x 128 ones of 64 x 32 a wave 10840 -> 9100 us per 8 steps. us a launch, fp32 unit / here, 19.3 GFLOP each: 155 / 111 (256 tiles
+// of 128 x 128), 157 / 100, 166 / 117 (256 x 128, 256 and 512 tiles), 150 / 98 (512 x 64), 285 / 190 (128 tiles). The patch split by each wave as it read
+// it: 128 us where this takes 111. Bound by matrix and vector unit, which take turns (766 and 720 cycles of 1400 a stage of 128 x 128).
 // RES (one channel chunk only): the weights of all nine taps are resident beside the patch, so everything is requested
 // at once and the taps run without a barrier between them.
 // KS = 2: eight waves, each four of which have operand buffers of their own and walk half of the channel chunks.
 template <typename T, int BM, int BN, int WM, int WN, int PS, int KB, bool RES = false, int KS = 1>
-__global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
+__global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), sizeof(T) == 4 && WM < 128 ? 4 : 2) void conv3x3_dma_kernel(ConvParams p_, DmaGeom g) {
   ConvParams p = p_;
   constexpr int ES = sizeof(T);
   constexpr int NW = (BM / WM) * (BN / WN);  // waves per workgroup (each owns a WM x WN sub-tile)
@@ -693,13 +771,15 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   constexpr int NKS = KB / 32;         // MFMA k-steps per stage
   constexpr int RPL = KB == 128 ? 1 : 2;  // log2(rows per 256 bytes of LDS)
   static_assert(KB == 64 || KB == 128, "row depth");
-  static_assert(RES ? PS == 0 && (RG >= NW || (RG % 2 == 0 && NW % RG == 0)) : RG >= NW, "fills of a weight tile per wave");
+  static_assert(RES ? PS == 0 && (RG >= NW || (RG % 2 == 0 && NW % RG == 0)) : RG >= NW || NW == 2 * RG, "fills of a weight tile per wave");
   constexpr int NI = WM / 32, NJ = WN / 32;
-  static_assert(NW == 4 && (KS == 1 || (KS == 2 && !RES)), "four waves per tile");
+  static_assert(NW == (ES == 4 && !RES ? 8 : 4) && (KS == 1 || (KS == 2 && !RES)), "waves per tile");
+  constexpr bool PLANES = ES == 4 && !RES;  // the patch is split once a chunk, into rows of three 32-byte parts behind it
+  static_assert(!PLANES || (KB == 64 && KS == 1), "sixteen channels a chunk");
   extern __shared__ __align__(16) char smem[];
   const int prow = g.patch_rows;
   const int pbuf_bytes = prow * KB;
-  const int wring_off = (PS > 0 ? 2 : 1) * pbuf_bytes;
+  const int wring_off = PLANES ? prow * (KB + kPartsRow) : (PS > 0 ? 2 : 1) * pbuf_bytes;
   const uint32_t lds0 = (uint32_t)(size_t)(DDS_LDS_AS char*)smem;
   const uint32_t lds_dump = lds0 + g.out_bytes;   // 1 KiB that absorbs surplus fills
   const int zero_off = g.out_bytes + 1024;        // 256 bytes of zeros
@@ -719,7 +799,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   const int nchunks = (p.Cx * ES) / KB / KS;  // channel chunks of this half
   const size_t pixbytes = (size_t)p.Cx * ES;
   const size_t chunk0 = (size_t)khalf * nchunks * KB;
-  if (tid < 16) *(uint4*)(smem + zero_off + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+  if (tid < (PLANES ? 32 : 16)) *(uint4*)(smem + zero_off + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
 
   const int l8 = lane / CPR;  // row inside a fill
   const int pcol = lane % CPR;
@@ -739,7 +819,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   }
   auto patch_dst = [&](int j, int buf) {
     const int wl = wave + NW * j;
-    return wl < pw_total ? lds_pbuf + buf * pbuf_bytes + wl * 1024 : lds_dump;
+    return wl < pw_total ? lds_pbuf + (PLANES ? 0 : buf * pbuf_bytes) + wl * 1024 : lds_dump;
   };
   // weight rows: byte offset of this lane's 16 bytes inside the weight tensor at tap 0, chunk 0.
   // Rows past Nout repeat the last one: their output columns lie past ldy == Nout and are never stored.
@@ -752,7 +832,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   auto fill_w = [&](int chunk, int tap, int slot) {
     const char* base = (const char*)p.w + (size_t)tap * pixbytes + chunk0 + (size_t)chunk * KB;  // wave-uniform
 #pragma unroll
-    for (int u = 0; u < WL; ++u) dma16s(base, wvo[u], lds_wring + slot * (BN * KB) + (wave + NW * u) * 1024);
+    for (int u = 0; u < WL; ++u) dma16s(base, wvo[u], lds_wring + slot * (BN * KB) + (wave % RG + NW * u) * 1024);  // (twice the same where two waves share a fill)
   };
 
   // pixel of the 32-pixel fragment held by this lane: quads {0,3,5,6} -> pixels 0..15, {1,2,4,7} -> 16..31
@@ -798,7 +878,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int m = wave_m * WM + i * 32 + lpix;
-    rowb[i] = (m + p.W + 1) * KB + half * 16;
+    rowb[i] = PLANES ? m + p.W + 1 : (m + p.W + 1) * KB + half * 16;
     const uint32_t pix = (uint32_t)(m0 + m);
     const int line = (int)(__umulhi(pix, g.dW.mul) >> g.dW.shift), w = (int)pix - line * p.W;
     const int h = line - (int)(__umulhi((uint32_t)line, g.dH.mul) >> g.dH.shift) * p.H;
@@ -808,13 +888,14 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
     ok_s0[i] = g.dgrad ? right : left;
     ok_s2[i] = g.dgrad ? left : right;
   }
-  const int tap_w = (g.dgrad ? -p.W : p.W) * KB, tap_1 = g.dgrad ? -KB : KB;
+  constexpr int ROW = PLANES ? 1 : KB;  // unit of rowb
+  const int tap_w = (g.dgrad ? -p.W : p.W) * ROW, tap_1 = g.dgrad ? -ROW : ROW;
   int boff[NJ][NKS];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int n = wave_n * WN + j * 32 + (lane & 31);
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) boff[j][ks] = n * KB + (((2 * ks + half) ^ ((n >> RPL) & (CPR - 1))) << 4);
+    for (int ks = 0; ks < NKS; ++ks) boff[j][ks] = n * KB + (((PLANES ? 2 * half + ks : 2 * ks + half) ^ ((n >> RPL) & (CPR - 1))) << 4);
   }
   f32x16_t acc[NJ][NI];
 #pragma unroll
@@ -835,7 +916,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
       int rb = rowb[i];
       asm volatile("" : "+v"(rb));  // keeps the nine taps' addresses from being precomputed (and spilled)
       const int t = rb + tapoff;    // row * KB + half * 16; f(row) = bits 8.. of it
-      const int a = (t ^ ((t >> 4) & ((CPR - 1) << 4))) + pbuf;
+      const int a = PLANES ? (int)__umul24(t, kPartsRow) + pbuf_bytes + (((t >> 3 ^ half) & 1) << 4) : (t ^ ((t >> 4) & ((CPR - 1) << 4))) + pbuf;
       if (tap_r == 1 && tap_s == 1) {
         a0[i] = a;
       } else {
@@ -846,8 +927,73 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
       asm volatile("" : "+v"(a0[i]));
     }
   };
+  // fp32: sums of a chunk, which join the long ones behind its last tap
+  f32x16_t inner[PLANES ? NJ : 1][PLANES ? NI : 1] = {};
+  auto fold = [&]() {
+    if constexpr (PLANES)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          acc[j][i] += inner[j][i];
+          inner[j][i] = f32x16_t{};
+        }
+  };
   auto compute = [&](int slot) {
     const char* wb = wring + slot * (BN * KB);
+    if constexpr (PLANES) {
+      uint4 b[NJ][2];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) b[j][k] = *(const uint4*)(wb + boff[j][k]);
+      constexpr int G = NI < 2 ? NI : 2;  // blocks of pixels at a time
+      Parts a[G];
+      auto read_a = [&](int i0) {
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) a[i].part[k] = *(const uint4*)(smem + a0[i0 + i] + 32 * k);
+      };
+      Parts w[NJ];
+      read_a(0);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) w[j] = split3(b[j][0], b[j][1]);
+#pragma unroll
+      for (int i0 = 0; i0 < NI; i0 += G) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < G; ++i) mfma16B<bf16_t>(w[j].part[kPartA[k]], a[i].part[kPartB[k]], inner[j][i0 + i]);
+        if (i0 + G < NI) read_a(i0 + G);
+      }
+      return;
+    } else if constexpr (ES == 4) {
+#pragma unroll
+      for (int k2 = 0; k2 < NKS; k2 += 2) {
+        uint4 a[NI][2], b[NJ][2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i) a[i][k] = *(const uint4*)(smem + (a0[i] ^ ((k2 + k) << 5)));
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) b[j][k] = *(const uint4*)(wb + boff[j][k2 + k]);
+        }
+        Parts w[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) w[j] = split3(b[j][0], b[j][1]);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          f32x16_t* sums[NJ];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) sums[j] = &acc[j][i];
+          mfma_split<NJ>(split3(a[i][0], a[i][1]), w, sums);
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       uint4 a[NI], b[NJ];
@@ -862,6 +1008,18 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
     }
   };
 
+  auto split_patch = [&]() {
+    for (int u = tid; u < 2 * prow; u += 64 * NW) {
+      const int r = u >> 1, h = u & 1;
+      const char* from = smem + r * KB;
+      const int f = (r >> RPL) & (CPR - 1);
+      const Parts t = split3(*(const uint4*)(from + (((2 * h) ^ f) << 4)), *(const uint4*)(from + (((2 * h + 1) ^ f) << 4)));
+#pragma unroll
+      for (int k = 0; k < 3; ++k) *(uint4*)(smem + pbuf_bytes + r * kPartsRow + 32 * k + (((r >> 3 ^ h) & 1) << 4)) = t.part[k];
+    }
+    wg_barrier();
+  };
+
 // One stage = one tap of one channel chunk. VM = fills per lane issued after the weight
 // tile this stage consumes: one weight tile plus the patch slices of the two previous stages.
 #define DDS_STAGE(TAP)                                                                              \
@@ -869,6 +1027,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
     constexpr int VM = WL + PS * (((TAP) >= 2 && (TAP) <= 8 ? 1 : 0) + ((TAP) >= 1 && (TAP) <= 7 ? 1 : 0)); \
     wait_vm<VM>();                                                                                  \
     wg_barrier();                                                                                   \
+    if constexpr (PLANES && (TAP) == 0) split_patch();                                              \
     {                                                                                               \
       int ct = chunk + ((TAP) + 2 >= 9 ? 1 : 0), tt = ((TAP) + 2) % 9;                             \
       if (ct >= nchunks) { ct = nchunks - 1; tt = 8; }                                              \
@@ -896,9 +1055,54 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), 2) void conv3x3_dm
   } else
   for (int chunk = 0; chunk < nchunks; ++chunk) {
     DDS_STAGE(0) DDS_STAGE(1) DDS_STAGE(2) DDS_STAGE(3) DDS_STAGE(4) DDS_STAGE(5) DDS_STAGE(6) DDS_STAGE(7) DDS_STAGE(8)
+    fold();
   }
 #undef DDS_STAGE
   wait_vm<0>();
+
+  if constexpr (ES == 4) {
+    // No part of an infinity, or of what rounds to one, is a remainder: every sum that meets one is NaN here. A workgroup that finds a NaN
+    // forms its sums again on the fp32 matrix unit, from the operands as they are.
+    bool nan = false;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) nan |= any_nan(acc[j]);
+    if (workgroup_any(nan, smem + g.out_bytes, wave_wg, NW)) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
+#pragma unroll 1
+      for (int t = 0; t < 9 * nchunks; ++t) {
+        const int chunk = t / 9, tap = t - 9 * chunk, r = tap / 3, c = tap - 3 * r;
+        if (!RES) {
+          wg_barrier();
+          if (tap == 0)
+#pragma unroll
+            for (int j = 0; j < NPRO; ++j)
+              if (wave + NW * j < pw_total) dma16s(pbase + (size_t)chunk * KB, poff[j], lds_pbuf + (wave + NW * j) * 1024);
+          fill_w(chunk, tap, 0);
+          wait_vm<0>();
+          wg_barrier();
+        }
+        const char* wb = wring + (RES ? tap * (BN * KB) : 0);
+        const int shift = (r - 1) * tap_w / ROW + (c - 1) * tap_1 / ROW;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const int row = wave_m * WM + i * 32 + lpix + p.W + 1 + shift;
+          const bool in = (r == 0 ? ok_r0[i] : r == 2 ? ok_r2[i] : true) && (c == 0 ? ok_s0[i] : c == 2 ? ok_s2[i] : true);
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks) {
+            const int col = PLANES ? 2 * half + ks : 2 * ks + half;  // as boff
+            const uint4 a = *(const uint4*)(smem + (in ? row * KB + ((col ^ ((row >> RPL) & (CPR - 1))) << 4) : zero_off));
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) mfma16B<float>(*(const uint4*)(wb + boff[j][ks]), a, acc[j][i]);
+          }
+        }
+      }
+    }
+  }
 
   if (KS > 1) add_halves<NI, NJ>(acc, smem, khalf, wave, lane);
   const auto pixel = [&](int row) { return m0 + row < p.M ? m0 + row : -1; };
@@ -926,11 +1130,12 @@ bool launch_dma_inst(const ConvParams& p, hipStream_t s) {
   const int fills_per_wave = (g.patch_rows / FROWS + NW - 1) / NW;
   if (fills_per_wave > ((KB == 128 && PS == 0) ? 11 : 7)) return false;  // patch offsets kept per lane
   if (PS == 0 ? nchunks != 1 : (nchunks * KS < 2 || 7 * PS < fills_per_wave)) return false;
-  int operands = KS * ((PS > 0 ? 2 : 1) * g.patch_rows * KB + (RES ? 9 : 3) * BN * KB);
+  constexpr bool PLANES = sizeof(T) == 4 && !RES;
+  int operands = KS * (PLANES ? g.patch_rows * (KB + kPartsRow) : (PS > 0 ? 2 : 1) * g.patch_rows * KB) + KS * (RES ? 9 : 3) * BN * KB;
   constexpr int tile = BM * BN * (int)sizeof(T);  // the output tile is staged where the operands were, if two workgroups still fit a CU
   if (operands < tile && tile <= 72 * 1024) operands = tile;
   g.out_bytes = operands;
-  const int smem = operands + 1024 + 256;
+  const int smem = operands + 1024 + (PLANES ? 512 : 256);
   if (smem > 160 * 1024) return false;
   static DeviceOnce lds;
   allow_whole_lds(lds, (const void*)conv3x3_dma_kernel<T, BM, BN, WM, WN, PS, KB, RES, KS>);
@@ -965,35 +1170,44 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
   // 8 x 8, 194 images: 11.2 -> 5.5 us; with 776 workgroups 16.4 us against 10.5 us for the 256-pixel tiles).
   if (rowbytes == 128 && p.ldy <= 64) {
     if (p.M <= 64 * 256 && launch_dma_inst<T, 64, 64, 32, 32, 0, 128, true>(p, s)) return true;
-    if (launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, s)) return true;
+    if constexpr (sizeof(T) == 2)
+      if (launch_dma_inst<T, 256, 64, 64, 64, 0, 128>(p, s)) return true;
   }
   if (nchunks == 1) {
-    if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
-    return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
+    if constexpr (sizeof(T) == 4) {
+      if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 32, 0, KB>(p, s);
+      return launch_dma_inst<T, 128, 128, 64, 32, 0, KB>(p, s);
+    } else {
+      if (p.ldy <= 64) return launch_dma_inst<T, 256, 64, 64, 64, 0, KB>(p, s);
+      return launch_dma_inst<T, 256, 128, 128, 64, 0, KB>(p, s);
+    }
   }
-  // fp32 sums of several chunks: channels outermost where the sides are powers of two up to 32, else taps outermost
-  // (conv_gather_kernel, as conv_gemm_kernel before it). This kernel would take such sides, too. Forward launches of a step, 7 x 7
-  // to 56 x 56: 128 and more channels 5-12 % faster (28 x 28, 128 channels, 32 images 117 -> 106 us), 64 channels slower below
-  // 100000 pixels (14 x 14, 194 images 74 -> 103 us). The order is kept.
-  if (sizeof(T) == 4 && (ilog2_exact(p.H) < 0 || ilog2_exact(p.W) < 0 || p.W > 32 || p.H * p.W < 16)) return false;
   // small images: 128-pixel tiles give more workgroups. 256-pixel tiles from 256 workgroups up (one per CU: half the
   // weight copies per FLOP; with the other modules' kernels sharing the chip this beat two 128-pixel workgroups per
-  // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step). In fp32, where a launch is long enough for its own, 128 columns
-  // wide they wait for a second one per CU: 256 tiles of 512 channels at 4 x 4 2.26 -> 2.00 ms per step (launch 611 -> 588 us),
-  // of 96 channels 0.62 -> 0.52 ms, 384 of 128 channels at 8 x 8 1.05 -> 0.99 ms (329 -> 265 us); 512 tiles the other way, 2.29 against
-  // 2.40 ms at 256 channels. (64 columns wide a 128 x 128 tile would multiply half padding: 285 against 392 us per step.)
+  // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step).
+  // fp32, us per 8 steps on either side of the lines: fp32 CNN, 4 groups of 128, 128 x 128 tiles / 256 x 128 and 512 x 64 ones 10840 / 9100. Images
+  // of any sides (conv_gather_kernel before, whose stages re-read every pixel for each tap): 28 x 28, 2 groups of 97 4240 / 3375, 30 x 30, 3 of 150 7794 /
+  // 6685, 36 x 36, 4 of 200 16989 / 14513, 9 x 9, one of 16 1700 / 1732.
   const long long tiles256 = (long long)((p.M + 255) / 256) * ((p.ldy + 127) / 128);
-  if (tiles256 >= (sizeof(T) == 4 && p.ldy > 64 ? 512 : 256)) {
-    if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, s)) return true;
-    if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
+  if constexpr (sizeof(T) == 4) {
+    if (p.ldy <= 64) {
+      // (data-groups with weights of their own begin at multiples of 256 pixels)
+      if (p.M >= 512 * 256 && (p.nrep <= 1 || p.M / p.nrep % 512 == 0) && launch_dma_inst<T, 512, 64, 128, 32, 1, KB>(p, s)) return true;
+      return launch_dma_inst<T, 256, 64, 64, 32, 1, KB>(p, s);
+    }
+    if (tiles256 >= 256 && launch_dma_inst<T, 256, 128, 128, 32, 1, KB>(p, s)) return true;
+    return launch_dma_inst<T, 128, 128, 64, 32, 1, KB>(p, s);
+  } else {
+    if (tiles256 >= 256) {
+      if (p.ldy <= 64 && launch_dma_inst<T, 256, 64, 64, 64, 1, KB>(p, s)) return true;
+      if (launch_dma_inst<T, 256, 128, 128, 64, 1, KB>(p, s)) return true;
+    }
+    // Launches that would leave half of the CUs without a 128 x 128 tile: 64 x 64 tiles whose channel chunks two halves of
+    // eight waves share, a quarter of the stages (and of whole cache lines). 64 images, alone: 512 channels at 4 x 4 47.6 ->
+    // 19.2 us, 256 at 8 x 8 26.6 -> 12.0 us; 128 at 16 x 16 (128 tiles) 17.2 against 16.3 us and no faster in the step.
+    if ((long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128) < 128 && launch_dma_inst<T, 64, 64, 32, 32, 1, 128, false, 2>(p, s)) return true;
+    return launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, s);
   }
-  // Launches that would leave half of the CUs without a 128 x 128 tile: 64 x 64 tiles whose channel chunks two halves of
-  // eight waves share, a quarter of the stages (and of whole cache lines). 64 images, alone: 512 channels at 4 x 4 47.6 ->
-  // 19.2 us, 256 at 8 x 8 26.6 -> 12.0 us; 128 at 16 x 16 (128 tiles) 17.2 against 16.3 us and no faster in the step.
-  // (fp32 stages are long enough as they are.)
-  if (sizeof(T) == 2 && (long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128) < 128 &&
-      launch_dma_inst<T, 64, 64, 32, 32, 1, 128, false, 2>(p, s)) return true;
-  return launch_dma_inst<T, 128, 128, 64, 64, 1, KB>(p, s);
 }
 
 // ------------------------------------------------------------------ any other convolution with whole 64-byte channel chunks
@@ -2176,18 +2390,15 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 2 : 1) void wgrad_tiles_ke
 }
 
 // ------------------------------------------------------------------ wgrad, fp32
-// partial[z][m][n] = alpha * sum over the pixels of split z of dY[p][m] * X(p; n), n = (tap, c). v_mfma_f32_32x32x2_f32
-// takes one value of one pixel per lane, so both operands are used as they lie in memory: panels of 32 pixels x 32
-// channels, [pixel][128 bytes], copied global -> LDS (two slots), of which 32 consecutive lanes read 32 consecutive channels of a
-// pixel with no conflict and a constant offset per step. Lane l of wave w always copies pixel 8 w + l / 8 of a tile,
+// partial[z][m][n] = alpha * sum over the pixels of split z of dY[p][m] * X(p; n), n = (tap, c). Both operands are used as they lie
+// in memory: panels of 32 pixels x 32 channels, [pixel][128 bytes], copied global -> LDS (two slots), of which 32 consecutive lanes read 32
+// consecutive channels of a pixel with no conflict and a constant offset per step; a lane reads eight pixels of one channel, splits them
+// into bf16 parts (split3) and has a fragment of v_mfma_f32_32x32x16_bf16. Lane l of wave w always copies pixel 8 w + l / 8 of a tile,
 // 16 bytes of one tap per panel: one image position per lane and tile, stepped without a division. Any kernel size,
 // stride, image size and batch; linear layers are the 1x1 case. The bias gradient is the product with a column of ones,
-// in the first column of workgroups: each of its waves adds one 32-row block of it to its four (two) products. (With
-// both blocks on one wave that wave issued six instructions for four, and the workgroup waited for it: 349 / 306 / 231 us
-// for the wide layers of the fp32 CNN, 512 images.) Pixels are summed in the order of wgrad_gemm_kernel (pairs four apart).
-// Bound by the matrix unit (64 cycles per 4 kFLOP; 126 us for 19.3 GFLOP). Against operands transposed in registers, alone:
-// 281 / 280 / 232 -> 252 / 239 / 198 us for those layers, 157 -> 85 us for the 3-channel stem; the fp32 CNN takes 14.6 instead of
-// 15.9 ms per 8 iterations.
+// in the first column of workgroups: each of its waves adds one 32-row block of it to its four (two) products. The sums of two tiles join the long
+// ones together, on the vector unit. Bound by the split (176 vector instructions of a wave for 24 MFMAs of 64 x 64). The wide layers of the fp32 CNN,
+// 512 images, alone, v_mfma_f32_32x32x2_f32 (64 cycles per 4 kFLOP) / parts: 256 / 174, 246 / 168, 206 / 137 us, the 3-channel stem 86 / 71.
 struct Wgrad32Geom {
   int sw, sh, si;         // 32 pixels = si images + sh rows + sw columns of the output grid
 };
@@ -2207,9 +2418,16 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
   const int ntiles = (p.pix_per_split + 31) / 32;
 
   const int l8 = lane >> 3, c4 = (lane & 7) * 4;  // pixel of a fill, first channel of this lane's 16 bytes
-  int pix = first + wave * 8 + l8;
-  int line = pix / p.Wo, ow = pix - line * p.Wo;
-  int img = line / p.Ho, oh = line - img * p.Ho;
+  int pix, ow, oh, img, filled;
+  auto start = [&]() {
+    pix = first + wave * 8 + l8;
+    const int line = pix / p.Wo;
+    ow = pix - line * p.Wo;
+    img = line / p.Ho;
+    oh = line - img * p.Ho;
+    filled = 0;
+  };
+  start();
   bool n_ok[BP];
   int n_r[BP], n_s[BP], n_off[BP];  // tap and element offset of this lane's columns in every panel
 #pragma unroll
@@ -2222,7 +2440,6 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
     n_off[b] = (n_r[b] * p.W + n_s[b]) * p.Cx + c;
   }
   const float* zsrc = (const float*)p.zeros + c4;
-  int filled = 0;
   auto fill = [&](int slot) {  // the next tile
     if (filled++ >= ntiles) return;
     const uint32_t base = lds0 + slot * SLOT + wave * 1024;
@@ -2249,36 +2466,90 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradParams p, Wgrad3
   const int l32 = (lane >> 5) * 512 + (lane & 31) * 4;  // steps pair pixels 8 i + j and 8 i + 4 + j; channel lane % 32
   const int bias_block = NI > 1 ? wave_n : 0;  // the 32-row block whose bias gradient this wave sums
   const bool bias_wave = blockIdx.y == 0 && wave_n < NI;
-  f32x16_t acc[NI][NJ], accb;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    accb[e] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j][e] = 0.f;
-  }
+  f32x16_t acc[NI][NJ] = {}, inner[NI][NJ] = {}, accb = {};
   for (int t = 0; t < ntiles; ++t) {
     wait_vm<0>();
     wg_barrier();
     fill((t + 1) & 1);
     const char* sa = smem + (t & 1) * SLOT + wave_m * NI * 4096 + l32;
     const char* sb = smem + (t & 1) * SLOT + (AP + wave_n * NJ) * 4096 + l32;
-#pragma unroll 4
-    for (int ks = 0; ks < 16; ++ks) {
-      float a[NI], b[NJ];
 #pragma unroll
-      for (int i = 0; i < NI; ++i) a[i] = *(const float*)(sa + i * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
+    for (int g = 0; g < 2; ++g) {  // sixteen pixels
+      float a[NI][8], b[NJ][8];
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
+      for (int k = 0; k < 8; ++k) {
+        const int at = (2 * g + (k >> 2)) * 1024 + (k & 3) * 128;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) a[i][k] = *(const float*)(sa + i * 4096 + at);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) b[j][k] = *(const float*)(sb + j * 4096 + at);
+      }
+      Parts x[NJ], y[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) y[i] = split3(a[i]);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) x[j] = split3(b[j]);
+      // (Ahead of the products, not behind them: the compiler counts no wait from a product to an addition of its sums across the end of this branch.)
+      if (bias_wave) {
+        const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+#pragma unroll
+        for (int k = 2; k >= 0; --k) {
+          if (bias_block == 0) mfma16B<bf16_t>(y[0].part[k], ones, accb);
+          else mfma16B<bf16_t>(y[NI - 1].part[k], ones, accb);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) mfma16B<bf16_t>(y[i].part[kPartA[k]], x[j].part[kPartB[k]], inner[i][j]);
+      __builtin_amdgcn_sched_barrier(0);  // (the fragments of both groups at once would not fit the registers)
+    }
+    if ((t & 1) || t + 1 == ntiles) {
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-      if (bias_wave) accb = __builtin_amdgcn_mfma_f32_32x32x2f32(bias_block == 0 ? a[0] : a[NI - 1], 1.f, accb, 0, 0, 0);
+        for (int j = 0; j < NJ; ++j) {
+          acc[i][j] += inner[i][j];
+          inner[i][j] = f32x16_t{};
+        }
     }
   }
   wait_vm<0>();
+
+  bool nan = any_nan(acc[0]) | any_nan(acc[NI - 1]);
+  if (bias_wave) nan |= any_nan<1>({accb});
+  if (workgroup_any(nan, smem, wave, 4)) {  // (as in conv3x3_dma_kernel)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x16_t{};
+    accb = f32x16_t{};
+    start();
+#pragma unroll 1
+    for (int t = 0; t < ntiles; ++t) {
+      wg_barrier();
+      fill(0);
+      wait_vm<0>();
+      wg_barrier();
+      const char* sa = smem + wave_m * NI * 4096 + l32;
+      const char* sb = smem + (AP + wave_n * NJ) * 4096 + l32;
+#pragma unroll 4
+      for (int ks = 0; ks < 16; ++ks) {
+        float a[NI], b[NJ];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) a[i] = *(const float*)(sa + i * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) b[j] = *(const float*)(sb + j * 4096 + (ks >> 2) * 1024 + (ks & 3) * 128);
+        if (bias_wave) accb = __builtin_amdgcn_mfma_f32_32x32x2f32(bias_block == 0 ? a[0] : a[NI - 1], 1.f, accb, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
 
   float* out = p.partial + (size_t)z * p.Pl;
 #pragma unroll

@@ -107,6 +107,72 @@ def test_fp32_conv3x3_tiles_by_pixel_count(B):
     _compare(_conv_chain("f32", (32, 96), 4, 4, 1, B), seed=32, T=2, every_step=True, tiny=True)
 
 
+@pytest.mark.parametrize("widths,h,w,W,B", [
+    ((32, 64), 4, 4, 1, 8193),    # 512 x 64 tiles, the last one ragged
+    ((64, 192), 8, 8, 1, 513),    # 256 x 128 tiles, ragged columns
+    ((64, 80), 8, 8, 3, 11),      # 128 x 128 tiles
+    ((16, 48), 5, 7, 2, 9),       # one chunk, 256 x 64 tiles
+    ((16, 136), 6, 5, 1, 9),      # ... and 128 x 128 ones
+    ((64, 64), 3, 319, 1, 1),     # 256 x 64 tiles, the longest rows
+    ((64, 64), 3, 320, 1, 1),     # one more: conv_gather_kernel
+    ((48, 96), 3, 359, 1, 1),     # 128 x 128 tiles, the longest rows
+    ((48, 96), 3, 360, 1, 1)])    # one more: conv_gather_kernel
+def test_fp32_conv3x3_of_split_operands_by_tile(widths, h, w, W, B):
+    _compare(_conv_chain("f32", widths, h, w, W, B), seed=61, T=2, every_step=True, tiny=True)
+
+
+def test_fp32_conv3x3_tiles_stay_within_a_data_group():
+    # 65792 pixels a data-group, of 256 x 64 but not of 512 x 64 tiles
+    from test_gpu_gossip import _compare as compare_gossip
+    compare_gossip(_conv_chain("f32", (32, 64), 4, 4, 2, 4112), seed=62, T=2, mixing=ring_mixing(2, 0.3))
+
+
+@pytest.mark.parametrize("cin,cout,h,B", [(16, 16, 8, 3), (32, 64, 8, 3), (64, 64, 8, 5), (64, 128, 8, 5), (64, 192, 8, 520), (32, 64, 16, 513)])
+def test_fp32_conv3x3_of_values_whose_parts_are_not_finite(cin, cout, h, B):
+    # Infinities and values that round to one in bf16: forward sums as fp64 has them (a NaN leaves the epilogue as -infinity), and
+    # the weight gradient of a value near the largest. Bound: each of 9 cin terms may add a rounding error of 2^-24 to the sum.
+    import paper_2509_05679_amd as P
+    import torch.nn.functional as F
+    ops = [{"op": "conv", "cin": cin, "cout": cout, "k": 3, "stride": 1, "pad": 1}, {"op": "gap"},
+           {"op": "linear", "cin": cout, "cout": 10}, {"op": "softmax_ce"}]
+    gen = torch.Generator().manual_seed(63)
+    weights = torch.randn((cout, cin, 3, 3), generator=gen) * (2.0 / (9 * cin)) ** 0.5
+    head = torch.randn((10, cout), generator=gen) * 0.1
+    clean = torch.randn((B, cin, h, h), generator=gen)
+    y = torch.randint(10, (B,), generator=gen, dtype=torch.int32)
+    for values in ((float("inf"),), (float("-inf"), float("inf")), (3.4e38, 1e-39)):
+        x = clean.clone()
+        for i, v in enumerate(values):
+            x[i, (5 * i) % cin, 3 * i, 1 + i] = v
+        wl = Workload(name="not_finite", ops=ops, bounds=[0, 1, len(ops)], K=2, W=1, B=B, in_shape=(cin, h, h), classes=10, precision="f32",
+                      lr=1e-37, momentum=0.0, steps=4)
+        tr = P.Trainer(P.Spec.from_workload(wl), 1)
+        first = np.concatenate([weights.numpy().ravel(), np.zeros(cout, np.float32)])
+        tr.dds_set_params(0, first)
+        tr.dds_set_params(1, np.concatenate([head.numpy().ravel(), np.zeros(10, np.float32)]))
+        for _ in range(3):  # the third updates module 0, with the gradient of the first
+            tr.dds_step([x.cuda()], [y.cuda()])
+        torch.cuda.synchronize()
+        got = torch.from_numpy(tr.dds_debug_read(P.DDS_DBG_OUTPUT, 0, 0).view(np.float32).copy()).reshape(B, h, h, cout).permute(0, 3, 1, 2)
+        updated = torch.from_numpy(tr.dds_get_params(0)).double()[:weights.numel()].reshape(weights.shape)
+        tr.close()
+        wd = weights.double().requires_grad_()
+        out = F.conv2d(x.double(), wd, padding=1)
+        want = out.detach().float()
+        want = torch.where(want.isnan(), torch.full_like(want, float("-inf")), want)
+        finite = want.isfinite()
+        assert torch.equal(got.isfinite(), finite) and torch.equal(got[~finite], want[~finite])
+        small = finite & (want.abs() < 1e3)
+        bound = 9 * cin * 2.0 ** -24
+        assert (got[small] - want[small]).norm() <= bound * want[small].norm()
+        if values[0] == 3.4e38:
+            assert (got[finite].double() - out.detach()[finite]).norm() <= bound * out.detach()[finite].norm()
+            F.cross_entropy(out.mean((2, 3)) @ head.double().T, y.long()).backward()
+            change = wl.lr * wd.grad
+            assert change.norm() > 0
+            assert ((weights.double() - updated) - change).norm() <= 1e-5 * change.norm() + 2.0 ** -24 * weights.double().norm()
+
+
 def _stride2_net(c1, c2, k, h, w, W, B, precision="bf16"):
     ops = [{"op": "conv", "cin": 3, "cout": c1, "k": 3, "stride": 1, "pad": 1}, {"op": "relu"},
            {"op": "conv", "cin": c1, "cout": c2, "k": k, "stride": 2, "pad": k // 2}, {"op": "relu"},
