@@ -773,7 +773,7 @@ __global__ __launch_bounds__(64 * KS * (BM / WM) * (BN / WN), sizeof(T) == 4 && 
   static_assert(KB == 64 || KB == 128, "row depth");
   static_assert(RES ? PS == 0 && (RG >= NW || (RG % 2 == 0 && NW % RG == 0)) : RG >= NW || NW == 2 * RG, "fills of a weight tile per wave");
   constexpr int NI = WM / 32, NJ = WN / 32;
-  static_assert(NW == (ES == 4 && !RES ? 8 : 4) && (KS == 1 || (KS == 2 && !RES)), "waves per tile");
+  static_assert((NW == 4 || (NW == 8 && ES == 4 && !RES)) && (KS == 1 || (KS == 2 && !RES)), "waves per tile");
   constexpr bool PLANES = ES == 4 && !RES;  // the patch is split once a chunk, into rows of three 32-byte parts behind it
   static_assert(!PLANES || (KB == 64 && KS == 1), "sixteen channels a chunk");
   extern __shared__ __align__(16) char smem[];
@@ -1187,15 +1187,20 @@ bool launch_dma(const ConvParams& p, hipStream_t s) {
   // CU at 256 channels, 2.27 vs 2.31 ms per ResNet-18 step).
   // fp32, us per 8 steps on either side of the lines: fp32 CNN, 4 groups of 128, 128 x 128 tiles / 256 x 128 and 512 x 64 ones 10840 / 9100. Images
   // of any sides (conv_gather_kernel before, whose stages re-read every pixel for each tap): 28 x 28, 2 groups of 97 4240 / 3375, 30 x 30, 3 of 150 7794 /
-  // 6685, 36 x 36, 4 of 200 16989 / 14513, 9 x 9, one of 16 1700 / 1732.
+  // 6685, 36 x 36, 4 of 200 16989 / 14513, 9 x 9, one of 16 1700 / 1732. Launches that leave three of four CUs without a 128 x 128 or 256 x 64 tile:
+  // 64 x 64 ones, four waves: fp32 CNN, one group of 8 3050 / 1900, of 32 3215 / 2065, of 80 3630 / 2735, 2 of 64 3990 / 3360, ResNet-20 at 16 6470 / 5290,
+  // at 194 11650 / 10590, 9 x 9, one of 16 1725 / 1250, 20 x 20, 2 of 97 2780 / 2354; up to 32768 pixels of 64 channels ResNet-20 at 500 and 512
+  // 20630 / 21130 and 20830 / 21510, up to 128 tiles of 128 x 128 the fp32 CNN at 4 x 128 8910 / 9130.
   const long long tiles256 = (long long)((p.M + 255) / 256) * ((p.ldy + 127) / 128);
   if constexpr (sizeof(T) == 4) {
     if (p.ldy <= 64) {
       // (data-groups with weights of their own begin at multiples of 256 pixels)
       if (p.M >= 512 * 256 && (p.nrep <= 1 || p.M / p.nrep % 512 == 0) && launch_dma_inst<T, 512, 64, 128, 32, 1, KB>(p, s)) return true;
+      if (p.M <= 64 * 256 && launch_dma_inst<T, 64, 64, 32, 32, 1, KB>(p, s)) return true;
       return launch_dma_inst<T, 256, 64, 64, 32, 1, KB>(p, s);
     }
     if (tiles256 >= 256 && launch_dma_inst<T, 256, 128, 128, 32, 1, KB>(p, s)) return true;
+    if ((long long)((p.M + 127) / 128) * ((p.ldy + 127) / 128) <= 64 && launch_dma_inst<T, 64, 64, 32, 32, 1, KB>(p, s)) return true;
     return launch_dma_inst<T, 128, 128, 64, 32, 1, KB>(p, s);
   } else {
     if (tiles256 >= 256) {

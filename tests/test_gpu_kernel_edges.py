@@ -110,10 +110,13 @@ def test_fp32_conv3x3_tiles_by_pixel_count(B):
 @pytest.mark.parametrize("widths,h,w,W,B", [
     ((32, 64), 4, 4, 1, 8193),    # 512 x 64 tiles, the last one ragged
     ((64, 192), 8, 8, 1, 513),    # 256 x 128 tiles, ragged columns
-    ((64, 80), 8, 8, 3, 11),      # 128 x 128 tiles
+    ((64, 80), 8, 8, 1, 133),     # 128 x 128 tiles
+    ((64, 80), 8, 8, 3, 11),      # 64 x 64 tiles, ragged columns
+    ((64, 64), 3, 191, 1, 1),     # ... the longest rows
+    ((64, 64), 3, 192, 1, 1),     # one more: 256 x 64 tiles
     ((16, 48), 5, 7, 2, 9),       # one chunk, 256 x 64 tiles
     ((16, 136), 6, 5, 1, 9),      # ... and 128 x 128 ones
-    ((64, 64), 3, 319, 1, 1),     # 256 x 64 tiles, the longest rows
+    ((64, 64), 3, 319, 1, 1),     # ... the longest rows
     ((64, 64), 3, 320, 1, 1),     # one more: conv_gather_kernel
     ((48, 96), 3, 359, 1, 1),     # 128 x 128 tiles, the longest rows
     ((48, 96), 3, 360, 1, 1)])    # one more: conv_gather_kernel
